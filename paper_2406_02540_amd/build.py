@@ -1,4 +1,4 @@
-"""Builds libvidiq.so (the C-ABI library with the gfx950 kernels) in-tree with hipcc.
+"""Builds libvidiq.so (the C-ABI library with the gfx950 kernels) in-tree with hipcc, and the torch extension.
 
 Usage: python -m paper_2406_02540_amd.build
 """
@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
@@ -14,6 +15,8 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libvidiq.so")
 CEILINGS_PATH = os.path.join(PKG_DIR, "vq_ceilings")  # stand-alone program, see csrc/vq_ceilings.hip
 SOURCES = ["vq_api.hip", "vq_quantize.hip", "vq_fused.hip", "vq_fused_gelu.hip", "vq_gemm.hip", "vq_gemm_192.hip", "vq_gemm_small.hip"]
+
+EXT_PATH = os.path.join(PKG_DIR, "_vq_torch.so")  # the torch side (csrc/vq_torch.cpp): host code only
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -36,10 +39,27 @@ def hipcc() -> str:
     return "hipcc"
 
 
+def ext_command(out: str) -> list:
+    """The compiler call for the torch extension (plain C++ against torch's headers)."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I", os.path.join(ROOT, "include"), "-I", os.path.join(root, "include"),
+            "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-I", "/opt/rocm/include",
+            "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "vq_torch.cpp"),
+            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", out]
+
+
 def build(verbose: bool = True) -> str:
-    """Compiles every source for gfx950 and links the shared library. Always recompiles."""
+    """Compiles every source for gfx950 and links the shared library, then the torch extension. Always recompiles."""
     objs = []
     procs = []
+    ext_tmp = EXT_PATH + ".tmp.%d" % os.getpid()
+    cmd = ext_command(ext_tmp)
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    ext = subprocess.Popen(cmd)
     for src in SOURCES:
         obj = os.path.join(CSRC, src.replace(".hip", ".o"))
         cmd = [hipcc(), *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
@@ -57,6 +77,9 @@ def build(verbose: bool = True) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, LIB_PATH)
+    if ext.wait() != 0:
+        raise RuntimeError("g++ failed on vq_torch.cpp")
+    os.replace(ext_tmp, EXT_PATH)
     # the ceilings probe (register-only MFMA loop, copy kernel): its own small executable
     tmp = CEILINGS_PATH + ".tmp.%d" % os.getpid()
     cmd = [hipcc(), *[f for f in HIPCC_FLAGS if f != "-fPIC"], os.path.join(CSRC, "vq_ceilings.hip"), "-o", tmp]
