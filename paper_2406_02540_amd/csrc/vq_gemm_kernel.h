@@ -160,8 +160,8 @@ __device__ __forceinline__ v16f mfma_block(v4i w, v4i x, v16f c) {
 }
 
 // K_TAIL:  K is a multiple of 16 but not of 128 (the last stage is partly past K).
-// GENERIC: any N and an optional copy of the integer sums; stores go out element by
-//          element.  The fast variant needs N % 8 == 0 and writes whole lines.
+// GENERIC: any N and an optional copy of the integer sums; rows of Y start at any even address.
+//          The other variant needs N % 8 == 0 and writes whole, aligned lines.
 template <class S, int W_BITS, bool K_TAIL, bool GENERIC>
 __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant(const GemmArgs a) {
     constexpr int TB = S::TB;
@@ -584,47 +584,64 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                             out[g][e / 2] = (int)dequant_pair((float)acc[b][tb][r0 + e], sp[e], (float)acc[b][tb][r0 + e + 1],
                                                               sp[e + 1], (unsigned)bias2[g][e / 2]);
                     }
-                    if (GENERIC && tl < cur.rows_x) {
-                        const long tok = cur.tok0 + tl;
+                    if (GENERIC && a.acc_out && tl < cur.rows_x) {
+                        int32_t* const arow = a.acc_out + (cur.tok0 + tl) * a.N;
                         const long c0 = chw + 32 * h + 8 * g;
-                        const half8 oh = (half8)out[g];  // (reinterprets the bits)
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
                             if (c0 + e < a.N) {
-                                a.y[tok * a.N + c0 + e] = oh[e];
-                                if (a.acc_out) {
-                                    const int v = (int)acc[b][tb][r0 + e];
-                                    a.acc_out[tok * a.N + c0 + e] = (W_BITS == 4) ? (v >> 4) : v;
-                                }
+                                const int v = (int)acc[b][tb][r0 + e];
+                                arow[c0 + e] = (W_BITS == 4) ? (v >> 4) : v;
                             }
                         }
                     }
                 }
-                if (!GENERIC) {
-                    // The block goes out in two halves of 16 token rows: the lanes that hold them
-                    // stage their 64 bytes each, then the wave writes the 16 rows x 128 B out, a
-                    // full line per 8 lanes.  Only this wave touches its staging area and the LDS
-                    // operations of a wave execute in order; the fences only keep the compiler
-                    // from reordering them.
+                // The block goes out in two halves of 16 token rows: the lanes that hold them
+                // stage their 64 bytes each, then the wave writes the 16 rows x 128 B out, a
+                // full line per 8 lanes.  Only this wave touches its staging area and the LDS
+                // operations of a wave execute in order; the fences only keep the compiler
+                // from reordering them.
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        if (((el >> 4) & 1) == p) {
+                for (int p = 0; p < 2; ++p) {
+                    if (((el >> 4) & 1) == p) {
 #pragma unroll
-                            for (int g = 0; g < 4; ++g) *(v4i*)(lds + (st_wr ^ (g << 4))) = out[g];
-                        }
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        v4i rows[2];
+                        for (int g = 0; g < 4; ++g) *(v4i*)(lds + (st_wr ^ (g << 4))) = out[g];
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    v4i rows[2];
 #pragma unroll
-                        for (int i = 0; i < 2; ++i) rows[i] = *(const v4i*)(lds + (st_rd ^ (i << 6)) + i * 1024);
+                    for (int i = 0; i < 2; ++i) rows[i] = *(const v4i*)(lds + (st_rd ^ (i << 6)) + i * 1024);
 #pragma unroll
-                        for (int i = 0; i < 2; ++i)
+                    for (int i = 0; i < 2; ++i) {
+                        if (!GENERIC) {
                             __builtin_amdgcn_raw_buffer_store_b128(
                                 rows[i], rsrc_y, y_off0 + (unsigned)((tb * 32 + p * 16 + i * 8) * a.N * 2), 0,
                                 2 /* nontemporal */);
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
+                            continue;
+                        }
+                        // Rows of Y that start at any even address: the same 16 bytes per lane,
+                        // unaligned; a lane whose eight channels straddle N writes those that exist.
+                        // Through the caches, not past them: neighbouring waves share the lines that
+                        // a row's ends fall into.  2891 x 1168 -> 2820: 64 us when every lane wrote its
+                        // elements one by one, 26 with these stores past the caches, 23 as it is.
+                        const int row = wave_t * 32 * TB + tb * 32 + p * 16 + i * 8 + (el >> 3);
+                        const int left = a.N - cl;
+                        if (row < cur.rows_x && left > 0) {
+                            typedef v4i v4i_any __attribute__((aligned(2)));
+                            _Float16* const dst = a.y + (cur.tok0 + row) * a.N + cl;
+                            if (left >= 8) {
+                                *(v4i_any*)dst = rows[i];
+                            } else {
+                                const half8 o = (half8)rows[i];
+#pragma unroll
+                                for (int e = 0; e < 7; ++e)
+                                    if (e < left) dst[e] = o[e];
+                            }
+                        }
                     }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
                 }
             }
         }

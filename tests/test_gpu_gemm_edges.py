@@ -1,0 +1,50 @@
+"""GEMM kernels at the edges of their tiles and of rows that end inside a vector store: every
+output against the exact integer sums, and nothing written outside the output."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def vq():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2406_02540_amd as pkg
+    from paper_2406_02540_amd import binding
+    binding.lib()
+    return pkg
+
+
+def check_gemm(vq, bits, M, N, K, seed=3):
+    """Integer sums from float64 products (exact: |sum| <= K * 127^2 < 2^53), outputs from them in
+    float64 rounded once: the dequantization is one rounding of an exact multiply-add."""
+    print(f"w{bits}a8 M={M} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    qmax = 127 if bits == 8 else 7
+    xq = torch.randint(-127, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    wq = torch.randint(-qmax, qmax + 1, (N, K), generator=g, device="cuda", dtype=torch.int8)
+    w = wq if bits == 8 else ((wq[:, ::2] & 15) | ((wq[:, 1::2] & 15) << 4)).view(torch.uint8).contiguous()
+    # power-of-two scales: their product and its product with the sum are exact in fp32
+    xs = torch.exp2(torch.randint(-12, -8, (M,), generator=g, device="cuda").float())
+    ws = torch.exp2(torch.randint(-8, -4, (N,), generator=g, device="cuda").float())
+    b = torch.randn(N, generator=g, device="cuda").half()
+    acc = xq.double() @ wq.double().t()
+    want = (acc * xs.double()[:, None] * ws.double()[None] + b.double()).half()
+    gemm = vq.vq_gemm_w8a8 if bits == 8 else vq.vq_gemm_w4a8
+    guard = 64
+    buf = torch.full((M * N + guard,), 7.0, dtype=torch.float16, device="cuda")
+    y = buf[:M * N].view(M, N)
+    gemm(xq, xs, w, ws, b, y=y)
+    assert torch.equal(y, want), (y != want).sum().item()
+    assert (buf[M * N:] == 7.0).all()
+    y2, acc2 = gemm(xq, xs, w, ws, b, return_acc=True)
+    assert torch.equal(y2, want) and torch.equal(acc2.double(), acc)
+
+
+# tiles of 256 tokens (both widths), rows of Y at odd addresses: N % 8 = 1, 3, 7, 4
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N,K", [(2891, 2817, 160), (2900, 3075, 128), (5003, 1151, 96), (2305, 4612, 288)])
+def test_unaligned_output_rows(vq, bits, M, N, K):
+    check_gemm(vq, bits, M, N, K)
