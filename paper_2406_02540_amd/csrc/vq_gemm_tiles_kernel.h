@@ -1,0 +1,362 @@
+// int8 x int8 -> int32 MFMA GEMM with the dequantization epilogue for problems whose tiles of
+// 256 tokens would not fill the chip (same arithmetic as vq_gemm_kernel.h; ViDiT-Q appendix
+// "Hardware implementation of quantized linear layers").
+//
+// Such a launch is one or two tiles per CU long, so what counts is what happens once: the start,
+// the first stage's memory latency (the caches of an XCD start cold), the way out.  Hence one
+// workgroup per tile, not persistent, with a short epilogue, and small tiles (chosen by
+// launch_gemm's cost table) so that every CU has one.  A tile is WT x WC wavefronts of (32 BT)
+// tokens x (32 BC) channels, times KW groups of such wavefronts: the groups share the tile and
+// divide the K steps of every stage among themselves (their sums meet in LDS at the end), which is
+// what puts two to four wavefronts on a SIMD where the tile alone has work for one.  K is walked in
+// stages of 128 bytes (one cache line per row) through a ring of RING LDS buffers, RING - 1 stages
+// of direct-to-LDS loads in flight: a CU takes at most about 54 bytes per cycle on this path
+// (0.26 us for the 32 KiB of a 128 x 128 stage out of L2, against 0.21 us for its products), and
+// only as many bytes as the ring holds per memory latency (about 0.9 us beyond L2).
+//
+// Measured against the 64 x 64 tile this kernel replaces (four wavefronts, every K step on its own
+// LDS latency, one workgroup per CU), GEMM alone in a captured graph, us:
+//   tokens x K -> channels   before   now        tokens x K -> channels   before   now
+//   1 x 1152 -> 1152           5.5    4.4        1001 x 1152 -> 4608       24.9   13.1
+//   64 x 4608 -> 1152         12.9    7.8        2048 x 1152 -> 1152       16.2    9.6
+//   256 x 1152 -> 1152         5.7    5.1        4096 x 1152 -> 1152       25.5   13.3
+//   240 x 4096 -> 2304        12.7    9.9        4096 x 4608 -> 1152       62     30 (now 256 x 192)
+#pragma once
+#include <type_traits>
+
+#include "vq_gemm_common.h"
+#include "vq_internal.h"
+
+namespace vq {
+
+struct TileArgs {
+    const int8_t* xq;
+    const float* x_scale;
+    const void* w;
+    const float* w_scale;
+    const _Float16* bias;
+    _Float16* y;
+    int32_t* acc_out;
+    int M, N, K;
+    int tiles_t, tiles_c, tiles, tiles_per_xcd;
+};
+
+namespace {
+
+constexpr int kStageK = 128;      // K bytes per stage
+constexpr int kTileXcds = 8;
+constexpr int kTileBand = 8;     // token tiles per band in the tile order
+
+template <int WT_, int WC_, int BT_, int BC_, int KW_, int RING_, int WGS_>
+struct OneTile {
+    static constexpr int WT = WT_, WC = WC_, BT = BT_, BC = BC_, KW = KW_, RING = RING_;
+    static constexpr int kSpatial = WT * WC;              // wavefronts of one K group
+    static constexpr int kWaves = kSpatial * KW;
+    static constexpr int kThreads = 64 * kWaves;
+    static constexpr int kWavesPerSimd = (kWaves * WGS_ + 3) / 4;  // WGS_ workgroups share a CU
+    static constexpr int kT = WT * BT * 32;               // tokens of the tile
+    static constexpr int kC = WC * BC * 32;               // channels of the tile
+    static constexpr int kXS = kT * kStageK, kWS = kC * kStageK;
+    static constexpr int kRingBytes = RING * (kXS + kWS);
+    static constexpr int kSums = KW * kT * kC * 4;        // every K group's int32 tile, once the stages are done
+    static constexpr int kBody = kRingBytes > kSums ? kRingBytes : kSums;
+    static constexpr int kScales = kC * 4 + kT * 4 + kC * 2;
+    static constexpr int kLds = kBody + kScales;
+    static_assert(kLds * WGS_ <= 160 * 1024, "LDS of one CU");
+    static_assert((4 / KW) * KW == 4, "K groups");
+};
+
+// Stage loads younger than the one needed: LEFT stages of PER loads.
+template <int PER, int MAX_LEFT>
+__device__ __forceinline__ void wait_stages(int left) {
+    if constexpr (MAX_LEFT == 0) {
+        wait_loads_before_and_barrier<0>();
+    } else {
+        if (left >= MAX_LEFT) wait_loads_before_and_barrier<PER * MAX_LEFT>();
+        else wait_stages<PER, MAX_LEFT - 1>(left);
+    }
+}
+
+template <class S, int W_BITS, bool K_TAIL>
+__global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant_tile(const TileArgs a) {
+    constexpr int BT = S::BT, BC = S::BC, KW = S::KW, RING = S::RING;
+    __shared__ __attribute__((aligned(1024))) int8_t lds[S::kLds];
+    int8_t* const lds_x = lds;
+    int8_t* const lds_w = lds + RING * S::kXS;
+    int8_t* const lds_sc = lds + S::kBody;   // w_scale[kC] | x_scale[kT] | bias[kC]
+    const unsigned lds_x_addr = (unsigned)(uintptr_t)(lds_ptr)lds_x;
+    const unsigned lds_w_addr = (unsigned)(uintptr_t)(lds_ptr)lds_w;
+
+    // Workgroup ids are dealt round-robin to the XCDs: each gets a contiguous run of tiles, in
+    // bands of token tiles, column by column within a band, so that its L2 sees few panels.
+    const int logical = (blockIdx.x % kTileXcds) * a.tiles_per_xcd + blockIdx.x / kTileXcds;
+    if ((int)(blockIdx.x / kTileXcds) >= a.tiles_per_xcd || logical >= a.tiles) return;
+    const int band_tiles = kTileBand * a.tiles_c;
+    const int band = logical / band_tiles, in_band = logical - band * band_tiles;
+    const int band_rows = min(a.tiles_t - band * kTileBand, kTileBand);
+    const int col = in_band / band_rows;
+    const long tok0 = (long)(band * kTileBand + in_band - col * band_rows) * S::kT;
+    const long ch0 = (long)col * S::kC;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = wave / S::kSpatial, sp = wave % S::kSpatial;
+    const int wave_t = sp % S::WT, wave_c = sp / S::WT;
+    const int K = a.K;
+    constexpr int kWDiv = (W_BITS == 8) ? 1 : 2;
+    const int rows_x = (int)min((long)S::kT, a.M - tok0);
+    const int rows_w = (int)min((long)S::kC, a.N - ch0);
+    const int nk = (K + kStageK - 1) / kStageK;
+
+    // Scales and bias, one channel and token per thread; parked in LDS behind the mainloop.
+    constexpr int kPre = (S::kC > S::kT ? S::kC : S::kT) > S::kThreads ? 2 : 1;
+    static_assert(kPre * S::kThreads >= S::kC && kPre * S::kThreads >= S::kT, "scales");
+    float pre_ws[kPre], pre_xs[kPre];
+    _Float16 pre_b[kPre];
+#pragma unroll
+    for (int p = 0; p < kPre; ++p) {
+        const int i = tid + p * S::kThreads;
+        pre_ws[p] = a.w_scale[min(ch0 + i, (long)a.N - 1)];
+        pre_xs[p] = a.x_scale[min(tok0 + i, (long)a.M - 1)];
+        pre_b[p] = a.bias ? a.bias[min(ch0 + i, (long)a.N - 1)] : (_Float16)0.0f;
+    }
+
+    // ---- global -> LDS ---------------------------------------------------------------------
+    // One load fills 1 KiB: 8 rows x 128 B (lane l: row l/8, physical chunk l%8 holding logical
+    // chunk (l%8) ^ ((row/2)%8)) or, for packed nibbles, 16 rows x 64 B (row l/4, chunk (l%4) ^
+    // ((row/4)%4)).  Row groups 0 .. kXG-1 are activations, the rest weights; wavefront w takes
+    // groups w, w + kWaves, ...
+    constexpr int kXG = S::kT / 8, kWG = (W_BITS == 8) ? S::kC / 8 : S::kC / 16;
+    constexpr int kGroups = kXG + kWG;
+    constexpr int kPer = (kGroups + S::kWaves - 1) / S::kWaves;     // loads of a wavefront per stage
+    constexpr int kFull = kGroups - (kPer - 1) * S::kWaves;          // wavefronts that have that many
+    const v4i rsrc_x = make_rsrc(a.xq + tok0 * K, clamp_u32((a.M - tok0) * (long)K));
+    const v4i rsrc_w = make_rsrc((const int8_t*)a.w + ch0 * (K / kWDiv), clamp_u32((a.N - ch0) * (long)(K / kWDiv)));
+    int voff[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int g = wave + S::kWaves * j;
+        if (g < kXG) {
+            const int r = g * 8 + (lane >> 3);
+            voff[j] = __mul24(min(r, rows_x - 1), K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+        } else if (W_BITS == 8) {
+            const int r = (g - kXG) * 8 + (lane >> 3);
+            voff[j] = __mul24(min(r, rows_w - 1), K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+        } else {
+            const int r = (g - kXG) * 16 + (lane >> 2);
+            voff[j] = __mul24(min(r, rows_w - 1), K / 2) + (((lane & 3) ^ ((r >> 2) & 3)) << 4);
+        }
+    }
+    auto issue_one = [&](int slot, int k0, int j) {
+        const int g = wave + S::kWaves * j;   // (wave-uniform)
+        if (j == kPer - 1 && kFull < S::kWaves && wave >= kFull) return;
+        if (g < kXG)
+            load_stage_to_lds_16<K_TAIL>(rsrc_x, lds_x_addr + slot * S::kXS + g * 1024, voff[j], k0);
+        else
+            load_stage_to_lds_16<K_TAIL>(rsrc_w, lds_w_addr + slot * S::kWS + (g - kXG) * 1024, voff[j], k0 / kWDiv);
+    };
+    auto issue_stage = [&](int slot, int k0) {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) issue_one(slot, k0, j);
+    };
+    // Waits until stage `it` has landed for every wavefront (up to RING - 2 younger ones stay in flight).
+    auto wait_stage = [&](int it) {
+        const int left = nk - 1 - it;
+        if (kFull < S::kWaves && wave >= kFull)
+            wait_stages<kPer - 1, RING - 2>(left);
+        else
+            wait_stages<kPer, RING - 2>(left);
+    };
+
+    // ---- LDS -> MFMA operands ---------------------------------------------------------------
+    const int fr_row = lane & 31;
+    const int x_off0 = (wave_t * 32 * BT + fr_row) * kStageK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4);
+    const int w_off0 = (W_BITS == 8)
+                           ? (wave_c * 32 * BC + fr_row) * kStageK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4)
+                           : (wave_c * 32 * BC + fr_row) * (kStageK / 2) + (((fr_row >> 2) & 3) << 4) + (lane >> 5) * 8;
+
+    v16i acc[BC][BT];
+#pragma unroll
+    for (int cb = 0; cb < BC; ++cb)
+#pragma unroll
+        for (int tb = 0; tb < BT; ++tb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[cb][tb][r] = 0;
+    // Operand registers are double buffered: the products of a K step are issued behind the LDS
+    // reads of the step after it, across the stage barrier too.
+    v4i xf[2][BT], wf[2][BC];
+#pragma unroll
+    for (int tb = 0; tb < BT; ++tb) xf[1][tb] = v4i{0, 0, 0, 0};
+#pragma unroll
+    for (int cb = 0; cb < BC; ++cb) wf[1][cb] = v4i{0, 0, 0, 0};
+
+#pragma unroll 1
+    for (int s = 0; s < RING - 1 && s < nk; ++s) issue_stage(s, s * kStageK);
+
+    constexpr int kSteps = 4 / KW;   // K steps of a stage that are this group's
+    auto stage = [&](int it, int slot, auto parity_tag) __attribute__((always_inline)) {
+        constexpr int P = decltype(parity_tag)::value;
+        wait_stage(it);
+        const bool fetch = it + RING - 1 < nk;
+        const int f_slot = slot == 0 ? RING - 1 : slot - 1, f_k0 = (it + RING - 1) * kStageK;
+        const int8_t* xs = lds_x + slot * S::kXS;
+        const int8_t* ws = lds_w + slot * S::kWS;
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) {
+            const int cur = (s + P) & 1;
+            const int ks = kg * kSteps + s;
+#pragma unroll
+            for (int cb = 0; cb < BC; ++cb) {
+                if (W_BITS == 8)
+                    wf[cur][cb] = *(const v4i*)(ws + (w_off0 ^ (ks << 5)) + cb * 32 * kStageK);
+                else
+                    wf[cur][cb] = widen_nibbles(*(const v2i*)(ws + (w_off0 ^ (ks << 4)) + cb * 32 * (kStageK / 2)));
+                // chunks past K hold bytes of the next row (or nothing): a zero weight removes them
+                if (K_TAIL && it == nk - 1 && it * kStageK + (2 * ks + (lane >> 5)) * 16 >= K) wf[cur][cb] = v4i{0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int tb = 0; tb < BT; ++tb) xf[cur][tb] = *(const v4i*)(xs + (x_off0 ^ (ks << 5)) + tb * 32 * kStageK);
+            __builtin_amdgcn_sched_barrier(0);
+            // The stage's loads are spread over its products (the CU's load path takes 64 bytes per
+            // cycle: a burst of loads keeps the wavefront from its products).
+#pragma unroll
+            for (int m = 0; m < BC * BT; ++m) {
+                constexpr int kProducts = kSteps * BC * BT;
+                const int at = s * BC * BT + m;
+#pragma unroll
+                for (int j = 0; j < kPer; ++j)
+                    if (j * kProducts / kPer == at && fetch) issue_one(f_slot, f_k0, j);
+                const int cb = m / BT, tb = m % BT;
+                acc[cb][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[cur ^ 1][cb], xf[cur ^ 1][tb], acc[cb][tb], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    auto last_products = [&](auto parity_tag) __attribute__((always_inline)) {
+        constexpr int P = decltype(parity_tag)::value;
+#pragma unroll
+        for (int cb = 0; cb < BC; ++cb)
+#pragma unroll
+            for (int tb = 0; tb < BT; ++tb)
+                acc[cb][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[P][cb], xf[P][tb], acc[cb][tb], 0, 0, 0);
+    };
+    typedef std::integral_constant<int, 0> P0;
+    typedef std::integral_constant<int, 1> P1;
+    int slot = 0;
+    auto next_slot = [&] { slot = (slot == RING - 1) ? 0 : slot + 1; };
+    if constexpr (kSteps % 2 == 0) {
+#pragma unroll 1
+        for (int it = 0; it < nk; ++it) {
+            stage(it, slot, P0{});
+            next_slot();
+        }
+        last_products(P1{});
+    } else {  // one step per stage: the operand buffers alternate from stage to stage
+        int it = 0;
+#pragma unroll 1
+        for (; it + 1 < nk; it += 2) {
+            stage(it, slot, P0{});
+            next_slot();
+            stage(it + 1, slot, P1{});
+            next_slot();
+        }
+        if (it < nk) {
+            stage(it, slot, P0{});
+            last_products(P0{});
+        } else {
+            last_products(P1{});
+        }
+    }
+
+    // ---- the sums, through LDS, to rows of the output ------------------------------------------------
+    // Every group leaves its sums as a row-major int32 tile, 16-byte chunks (four channels) XOR-ed by
+    // the row; then a thread takes eight consecutive channels of a row at a time, adds the groups'
+    // sums, dequantizes and writes 16 bytes, consecutive threads along the row.  A thread's channels
+    // are the same in every row it takes, so their scales and biases stay in registers.  (The code is
+    // short on purpose: it runs once per workgroup, and instructions not seen before come from L2.)
+#pragma unroll
+    for (int p = 0; p < kPre; ++p) {
+        const int i = tid + p * S::kThreads;
+        if (i < S::kC) *(float*)(lds_sc + i * 4) = pre_ws[p];
+        if (i < S::kT) *(float*)(lds_sc + S::kC * 4 + i * 4) = pre_xs[p];
+        if (i < S::kC) *(_Float16*)(lds_sc + S::kC * 4 + S::kT * 4 + i * 2) = pre_b[p];
+    }
+    wait_lds_and_barrier();   // nobody reads the stage buffers any more
+    constexpr int kXor = (S::kC / 4) % 16 == 0 ? 15 : 7;
+    constexpr int kRow = S::kC * 4;
+    {
+        const int t = wave_t * 32 * BT + (lane & 31);
+        int8_t* const mine = lds + kg * (S::kT * kRow) + t * kRow;
+#pragma unroll
+        for (int cb = 0; cb < BC; ++cb)
+#pragma unroll
+            for (int tb = 0; tb < BT; ++tb)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {   // register 4j + i is channel 8j + 4 (lane/32) + i of the block
+                    const int chunk = (wave_c * BC + cb) * 8 + 2 * j + (lane >> 5);
+                    *(v4i*)(mine + tb * 32 * kRow + ((chunk ^ (t & kXor)) << 4)) =
+                        v4i{acc[cb][tb][4 * j], acc[cb][tb][4 * j + 1], acc[cb][tb][4 * j + 2], acc[cb][tb][4 * j + 3]};
+                }
+    }
+    wait_lds_and_barrier();
+    constexpr int kPerRow = S::kC / 8;                       // threads of a row
+    constexpr int kRowStep = S::kThreads / kPerRow;          // rows taken at a time
+    if (kRowStep * kPerRow < S::kThreads && tid >= kRowStep * kPerRow) return;
+    const int c0 = (tid % kPerRow) * 8;
+    if (c0 >= rows_w) return;
+    const v4f s0 = *(const v4f*)(lds_sc + c0 * 4), s1 = *(const v4f*)(lds_sc + c0 * 4 + 16);
+    const v4i bias8 = *(const v4i*)(lds_sc + S::kC * 4 + S::kT * 4 + c0 * 2);
+    _Float16* const ytile = a.y + tok0 * a.N + ch0;
+    const bool whole = c0 + 8 <= rows_w;
+    typedef v4i v4i_any __attribute__((aligned(2)));   // (rows of Y start at any even address)
+#pragma unroll 1
+    for (int t = tid / kPerRow; t < rows_x; t += kRowStep) {
+        v4i v0 = {0, 0, 0, 0}, v1 = v0;
+#pragma unroll
+        for (int g = 0; g < KW; ++g) {
+            const int8_t* row = lds + g * (S::kT * kRow) + t * kRow;
+            v0 += *(const v4i*)(row + (((c0 >> 2) ^ (t & kXor)) << 4));
+            v1 += *(const v4i*)(row + ((((c0 >> 2) + 1) ^ (t & kXor)) << 4));
+        }
+        const float xsc = *(const float*)(lds_sc + S::kC * 4 + t * 4) * ((W_BITS == 4) ? 0.0625f : 1.0f);
+        v4i out;
+        out[0] = (int)dequant_pair((float)v0[0], xsc * s0[0], (float)v0[1], xsc * s0[1], (unsigned)bias8[0]);
+        out[1] = (int)dequant_pair((float)v0[2], xsc * s0[2], (float)v0[3], xsc * s0[3], (unsigned)bias8[1]);
+        out[2] = (int)dequant_pair((float)v1[0], xsc * s1[0], (float)v1[1], xsc * s1[1], (unsigned)bias8[2]);
+        out[3] = (int)dequant_pair((float)v1[2], xsc * s1[2], (float)v1[3], xsc * s1[3], (unsigned)bias8[3]);
+        _Float16* const yrow = ytile + (long)t * a.N + c0;
+        if (whole) {
+            *(v4i_any*)yrow = out;
+        } else {
+            const half8 o = (half8)out;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (c0 + e < rows_w) yrow[e] = o[e];
+        }
+        if (a.acc_out) {
+            int32_t* const arow = a.acc_out + (tok0 + t) * a.N + ch0 + c0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (c0 + e < rows_w) arow[e] = (e < 4 ? v0[e & 3] : v1[e & 3]) >> ((W_BITS == 4) ? 4 : 0);
+        }
+    }
+}
+
+template <class S, int W_BITS>
+hipError_t launch_tile_shape(TileArgs a, hipStream_t stream) {
+    a.tiles_t = (a.M + S::kT - 1) / S::kT;
+    a.tiles_c = (a.N + S::kC - 1) / S::kC;
+    const long tiles = (long)a.tiles_t * a.tiles_c;
+    if (tiles > 0x7FFFFF00l) return hipErrorInvalidValue;
+    a.tiles = (int)tiles;
+    a.tiles_per_xcd = (a.tiles + kTileXcds - 1) / kTileXcds;
+    const dim3 grid((unsigned)(a.tiles_per_xcd * kTileXcds)), block(S::kThreads);
+    if (a.K % kStageK)
+        hipLaunchKernelGGL((gemm_i8_dequant_tile<S, W_BITS, true>), grid, block, 0, stream, a);
+    else
+        hipLaunchKernelGGL((gemm_i8_dequant_tile<S, W_BITS, false>), grid, block, 0, stream, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace vq

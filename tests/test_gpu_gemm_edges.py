@@ -48,3 +48,15 @@ def check_gemm(vq, bits, M, N, K, seed=3):
 @pytest.mark.parametrize("M,N,K", [(2891, 2817, 160), (2900, 3075, 128), (5003, 1151, 96), (2305, 4612, 288)])
 def test_unaligned_output_rows(vq, bits, M, N, K):
     check_gemm(vq, bits, M, N, K)
+
+
+# one tile per workgroup, each size the launcher can choose: 32 x 32, 64 x 64, 128 x 64, 128 x 128,
+# 128 x 256, with ragged last tiles, K of one stage, of a ring's length more or less, and a tail
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 32), (1, 1, 32), (31, 33, 64), (33, 31, 4608), (65, 129, 1152), (32, 32, 1024),
+                                   (63, 4607, 96), (300, 2000, 1152), (256, 4608, 512),
+                                   (1001, 1160, 1152), (1001, 1157, 416),
+                                   (1100, 2050, 320), (1500, 2000, 1152), (2000, 1999, 4608),
+                                   (1001, 4609, 1152), (1030, 4600, 128), (1025, 4097, 96)])
+def test_one_tile_per_workgroup(vq, bits, M, N, K):
+    check_gemm(vq, bits, M, N, K)
