@@ -166,6 +166,25 @@ def test_channel_absmax_bit_exact(vq, oracle, R, K):
     assert np.array_equal(host(got), oracle.channel_absmax(np.concatenate([x, x2])))
 
 
+# one slab and the first size past it, a row group's edges, partly filled column blocks, many slabs
+@pytest.mark.parametrize("R,K", [(1, 8), (31, 4), (32, 120), (33, 136), (256, 128), (257, 128), (129, 1144), (40000, 72)])
+def test_channel_absmax_chunks(vq, R, K):
+    say(f"channel_absmax chunks R={R} K={K}")
+    g = np.random.default_rng(720 + R + K)
+    for dtype in (np.float16, np.float32):
+        x = (g.standard_normal((R, K)) * np.exp(g.uniform(-3, 3, (1, K)))).astype(dtype)
+        x[R - 1, K - 1] = -np.inf
+        x[R // 2, 0] = np.nan                      # a maximum passes over NaN ...
+        if R > 1:
+            x[0, 0] = 3.0
+        want = np.fmax.reduce(np.abs(x), axis=0, initial=0).astype(np.float32)   # (... and is 0 over nothing else)
+        got = vq.vq_channel_absmax(dev(x))
+        again = vq.vq_channel_absmax(dev(x), dev(want * np.float32(2)), accumulate=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(host(got), want)
+        assert np.array_equal(host(again), want * np.float32(2))
+
+
 @pytest.mark.parametrize("alpha", [0.0, 0.3, 0.5, 1.0])
 def test_balance_mask(vq, oracle, alpha):
     g = np.random.default_rng(800)
