@@ -63,15 +63,35 @@ __device__ __forceinline__ float gelu_tanh(float x) {
 }
 
 // The value of the lane whose index differs in one bit (1, 2, 4 or 8), as data movement
-// inside a row of 16 lanes: DPP quad permutes for 1 and 2, ds_swizzle (bit mode) for 4 and 8.
+// inside a row of 16 lanes: DPP quad permutes for 1 and 2, a DPP rotation by half the row for 8,
+// ds_swizzle (bit mode) for 4.
 template <int MASK>
 __device__ __forceinline__ float from_lane_xor(float v) {
     const int iv = __builtin_bit_cast(int, v);
     int r;
     if (MASK == 1) r = __builtin_amdgcn_mov_dpp(iv, 0xB1, 0xF, 0xF, true);       // quad_perm [1,0,3,2]
     else if (MASK == 2) r = __builtin_amdgcn_mov_dpp(iv, 0x4E, 0xF, 0xF, true);  // quad_perm [2,3,0,1]
+    else if (MASK == 8) r = __builtin_amdgcn_mov_dpp(iv, 0x128, 0xF, 0xF, true);  // row_ror:8
     else r = __builtin_amdgcn_ds_swizzle(iv, (MASK << 10) | 0x1F);               // and 0x1F, or 0, xor MASK
     return __builtin_bit_cast(float, r);
+}
+
+constexpr float kHadamardScale = 0.08838834764831845f;  // 1 / sqrt(128)
+
+// Stages of the Walsh-Hadamard transform inside a lane's chunks of 8 values: index bits FROM .. TO - 1.
+template <int FROM, int TO, int NCH>
+__device__ __forceinline__ void hadamard_register_stages(float (&t)[NCH][8]) {
+#pragma unroll
+    for (int i = 0; i < NCH; ++i)
+#pragma unroll
+        for (int bit = 1 << FROM; bit < 1 << TO; bit <<= 1)
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (!(j & bit)) {
+                    const float lo = t[i][j], hi = t[i][j | bit];
+                    t[i][j] = lo + hi;
+                    t[i][j | bit] = lo - hi;
+                }
 }
 
 // One stage of the Walsh-Hadamard transform across lanes: index bit MASK of the lane.
@@ -186,18 +206,7 @@ __global__ __launch_bounds__(kQuantThreads) void produce_quantize_tokens(const F
                 chunk_done(t[i]);
             }
         }
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-#pragma unroll
-            for (int bit = 1; bit < 8; bit <<= 1)
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (!(j & bit)) {
-                        const float lo = t[i][j], hi = t[i][j | bit];
-                        t[i][j] = lo + hi;
-                        t[i][j | bit] = lo - hi;
-                    }
-        }
+        hadamard_register_stages<0, 3>(t);
         hadamard_lane_stage<1>(t, sub);
         hadamard_lane_stage<2>(t, sub);
         hadamard_lane_stage<4>(t, sub);
@@ -205,7 +214,7 @@ __global__ __launch_bounds__(kQuantThreads) void produce_quantize_tokens(const F
 #pragma unroll
         for (int i = 0; i < NCH; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) t[i][j] = t[i][j] * 0.08838834764831845f;  // 1 / sqrt(128)
+            for (int j = 0; j < 8; ++j) t[i][j] = t[i][j] * kHadamardScale;
     }
 
     if (PRODUCER == kGeluErf || PRODUCER == kGeluTanh) {

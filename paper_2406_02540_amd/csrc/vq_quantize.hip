@@ -292,7 +292,65 @@ __global__ __launch_bounds__(kQuantThreads) void balance_mask_elems(const float*
     chan_mul[k] = 1.0f / s;
 }
 
-// Offline weight quantizer: one workgroup per output channel, fp32 input.
+// Offline weight quantizer, rows of whole 16-byte chunks that a wavefront holds in registers: one
+// output channel per wavefront, a lane the chunks lane, lane + 64, ... of four values (every load
+// covers 1 KiB), read once and asked for all at once.  Memory-bound, 4 bytes per element in.  The row
+// and chan_s are range-checked buffers: chunks past K read as zero and are not written.
+// BITS == 4 writes two nibbles per byte (k even in bits 0..3, k odd in 4..7).
+// 4608 x 1152 to 4 bits: 4.8-5.7 us (a workgroup per channel, two passes of 4-byte loads: 9.9 us).
+template <int BITS, int NCH>
+__global__ __launch_bounds__(kQuantThreads) void quantize_weight_wave(const float* __restrict__ w,
+                                                                      const float* __restrict__ chan_s,
+                                                                      void* __restrict__ wq_out,
+                                                                      float* __restrict__ w_scale, int N, int K) {
+    constexpr float qmax = (BITS == 8) ? 127.0f : 7.0f;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long n = (long)blockIdx.x * kRowsPerBlock + wave;
+    if (n >= N) return;  // (uniform per wavefront)
+    const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void*)(w + n * K), 0, K * 4, 0x00020000);
+    float4v t[NCH];
+#pragma unroll
+    for (int i = 0; i < NCH; ++i)
+        t[i] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs_w, (i * kWave + lane) * 16, 0, 0));
+    if (chan_s) {
+        const __amdgpu_buffer_rsrc_t rs_s = __builtin_amdgcn_make_buffer_rsrc((void*)chan_s, 0, K * 4, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+            const float4v s = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs_s, (i * kWave + lane) * 16, 0, 0));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) t[i][j] = t[i][j] * s[j];
+        }
+    }
+    float amax = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) amax = fmaxf(amax, fabsf(t[i][j]));
+    amax = group_max<kWave>(amax);
+    float scale = 0.0f, inv = 0.0f;
+    if (amax != 0.0f) {
+        scale = amax / qmax;
+        inv = qmax / amax;
+    }
+    if (lane == 0) w_scale[n] = scale;
+    const __amdgpu_buffer_rsrc_t rs_q = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((int8_t*)wq_out + n * (BITS == 8 ? K : K / 2)), 0, BITS == 8 ? K : K / 2, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        int q[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q[j] = quantize_one(t[i][j], inv, qmax);
+        if (BITS == 8)
+            __builtin_amdgcn_raw_buffer_store_b32(pack4(q[0], q[1], q[2], q[3]), rs_q, (i * kWave + lane) * 4, 0, 0);
+        else
+            __builtin_amdgcn_raw_buffer_store_b16(
+                (short)((q[0] & 0xF) | ((q[1] & 0xF) << 4) | ((q[2] & 0xF) << 8) | ((q[3] & 0xF) << 12)), rs_q,
+                (i * kWave + lane) * 2, 0, 0);
+    }
+}
+
+// The same for any row: one workgroup per output channel, two passes (the second one hits in cache).
 // BITS == 4 writes two nibbles per byte (k even in bits 0..3, k odd in 4..7).
 template <int BITS, bool HAS_S>
 __global__ __launch_bounds__(kQuantThreads) void quantize_weight_rows(
@@ -494,8 +552,28 @@ hipError_t launch_quantize_static(const void* x_f16, const float* chan_mul, floa
     return hipGetLastError();
 }
 
+// The smallest instantiated chunk count that holds the row.
+template <int BITS, int NCH = 1>
+hipError_t launch_weight_wave(int nch, const float* w, const float* chan_s, void* wq_out, float* w_scale, int N, int K,
+                              hipStream_t stream) {
+    if constexpr (NCH > 32) {
+        return hipErrorInvalidValue;
+    } else {
+        if (nch > NCH)  // (every count up to 8, then steps of an eighth or more)
+            return launch_weight_wave<BITS, NCH + (NCH < 8 ? 1 : NCH < 20 ? 2 : 4)>(nch, w, chan_s, wq_out, w_scale, N, K, stream);
+        hipLaunchKernelGGL((quantize_weight_wave<BITS, NCH>), dim3((unsigned)((N + (long)kRowsPerBlock - 1) / kRowsPerBlock)),
+                           dim3(kQuantThreads), 0, stream, w, chan_s, wq_out, w_scale, N, K);
+        return hipGetLastError();
+    }
+}
+
 hipError_t launch_quantize_weight(const float* w, const float* chan_s, int w_bits, void* wq_out,
                                   float* w_scale, int N, int K, hipStream_t stream) {
+    if (K % 4 == 0 && K <= 4 * kWave * 32) {
+        const int nch = (K / 4 + kWave - 1) / kWave;
+        return w_bits == 8 ? launch_weight_wave<8>(nch, w, chan_s, wq_out, w_scale, N, K, stream)
+                           : launch_weight_wave<4>(nch, w, chan_s, wq_out, w_scale, N, K, stream);
+    }
     const dim3 grid((unsigned)N), block(kQuantThreads);
 #define VQ_LAUNCH_W(BITS, HAS)                                                                  \
     hipLaunchKernelGGL((quantize_weight_rows<BITS, HAS>), grid, block, 0, stream, w, chan_s, \

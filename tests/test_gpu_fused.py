@@ -211,6 +211,24 @@ def test_hadamard_quantize(vq, oracle, M, K, with_mul):
     check_valid(host(q), host(s), t, None, q_ref, s_ref)
 
 
+@pytest.mark.parametrize("N,K", [(1, 128), (33, 128), (7, 1152), (3, 8192), (57, 1152)])
+def test_rotate_weight_sizes(vq, N, K):
+    # fewer chunks than a workgroup takes, exactly one group of 16 lanes past it, rows that straddle workgroups:
+    # fp32 butterflies in order of the channel's bits, the same in numpy
+    say(f"rotate_weight N={N} K={K}")
+    g = np.random.default_rng(4600 + N + K)
+    w = (g.standard_normal((N, K)) * 0.02).astype(np.float32)
+    s = np.exp(g.uniform(np.log(0.5), np.log(2), K)).astype(np.float32)
+    for chan_s in (None, s):
+        t = (w if chan_s is None else w * s[None]).reshape(N, K // 128, 128)
+        for bit in range(7):
+            p = t.reshape(N, K // 128, 64 >> bit, 2, 1 << bit)
+            t = np.stack([p[..., 0, :] + p[..., 1, :], p[..., 0, :] - p[..., 1, :]], axis=-2).reshape(N, K // 128, 128)
+        got = vq.vq_rotate_weight(dev(w), None if chan_s is None else dev(chan_s))
+        torch.cuda.synchronize()
+        assert np.array_equal(host(got), (t * np.float32(0.08838834764831845)).reshape(N, K))
+
+
 def test_rotate_weight_and_rotated_layer(vq, oracle):
     g = np.random.default_rng(4545)
     M, N, K = 300, 264, 1152

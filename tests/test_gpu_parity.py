@@ -101,6 +101,23 @@ def test_quantize_weight_bit_exact(vq, oracle):
         assert np.array_equal(host(wq), wq_ref)
 
 
+# edges of the register-resident rows: one chunk of four, a full wavefront of them and one past it, the
+# step from 8 to 10 chunks, the largest row and the first that does not fit; partly filled workgroups
+@pytest.mark.parametrize("N,K", [(1, 4), (5, 252), (3, 256), (6, 260), (2, 2048), (7, 2052), (4, 8192), (2, 8196)])
+@pytest.mark.parametrize("bits", [8, 4])
+def test_quantize_weight_rows_in_registers(vq, oracle, N, K, bits):
+    say(f"quantize_weight rows N={N} K={K} bits={bits}")
+    g = np.random.default_rng(N * 37 + K + bits)
+    w = g.normal(0, 0.02, (N, K)).astype(np.float32)
+    w[0, K - 1] = -3.0      # the extreme value in the last channel
+    s = np.exp(g.uniform(np.log(0.25), np.log(4.0), K)).astype(np.float32)
+    for chan_s in (None, s):
+        wq_ref, ws_ref = oracle.quantize_weight(w, chan_s, bits)
+        wq, ws = vq.vq_quantize_weight(dev(w), None if chan_s is None else dev(chan_s), bits)
+        assert np.array_equal(host(ws).view(np.uint32), ws_ref.view(np.uint32))
+        assert np.array_equal(host(wq), oracle.pack_int4(wq_ref) if bits == 4 else wq_ref)
+
+
 # ---- GEMM + epilogue ---------------------------------------------------------------------
 
 def _gemm_case(vq, oracle, M, N, K, bits, seed, bias=True, full_range=True):
