@@ -141,6 +141,7 @@ struct TilePos {
 struct TileLoads {
     v4i rsrc_x, rsrc_w;
     int voff_x[4], voff_w[6];
+    int k_end_x, k_end_w;   // (used with a K tail only: see load_stage_to_lds_16)
 };
 
 // One 32 x 32 block: int8 operands (32 values of K per lane pair) into int32 sums, or,
@@ -237,9 +238,10 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         t.ch0 = (long)col * S::kTileC;
         t.rows_x = (int)min((long)S::kTileT, a.M - t.tok0);
         t.rows_w = (int)min((long)S::kTileC, a.N - t.ch0);
-        ld.rsrc_x = make_rsrc(a.xq + t.tok0 * K, clamp_u32((a.M - t.tok0) * (long)K));
+        // (with a K tail the buffers end with the tile's last row: see load_stage_to_lds_16)
+        ld.rsrc_x = make_rsrc(a.xq + t.tok0 * K, K_TAIL ? (unsigned)(t.rows_x * K) : clamp_u32((a.M - t.tok0) * (long)K));
         ld.rsrc_w = make_rsrc((const int8_t*)a.w + t.ch0 * (K / kWDiv),
-                              clamp_u32((a.N - t.ch0) * (long)(K / kWDiv)));
+                              K_TAIL ? (unsigned)(t.rows_w * (K / kWDiv)) : clamp_u32((a.N - t.ch0) * (long)(K / kWDiv)));
         // The per-lane offsets are relative to the tile and clamp rows past the matrix: between
         // two full tiles they do not change.  (Rows < 256 and row lengths < 2^24: 24-bit products.)
         const bool full = t.rows_x == S::kTileT && t.rows_w == S::kTileC;
@@ -248,6 +250,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         const int l = opaque(lane);
         if (loads_x) {
             const int ld_chunk16 = ((l & 7) ^ ((4 * (wave & 1) + (l >> 4)) & 7)) << 4;
+            ld.k_end_x = K - ld_chunk16;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = (wave + 8 * j) * 8 + (l >> 3);
@@ -257,6 +260,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         if (loads_w) {
             const int ld_chunk16 = ((l & 7) ^ ((4 * (w_loader & 1) + (l >> 4)) & 7)) << 4;
             const int ld_chunk16_w4 = ((l & 3) ^ (l >> 4)) << 4;
+            ld.k_end_w = W_BITS != 4 ? K - ld_chunk16 : K / 2 - ld_chunk16_w4;
 #pragma unroll
             for (int j = 0; j < kWPer; ++j) {
                 const int g = w_loader + S::kWLoaders * j;   // row group of this load
@@ -274,11 +278,12 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // One load of a wave's share of a stage.  A wave with both kinds alternates them (X, W, X,
     // W, ...) as long as it has W loads left.
     auto issue_x = [&](const TileLoads& ld, int buf, int k0, int j) {
-        load_stage_to_lds_16<K_TAIL>(ld.rsrc_x, lds_x_addr + buf * kXStage + (wave + 8 * j) * 1024, ld.voff_x[j], k0);
+        load_stage_to_lds_16<K_TAIL>(ld.rsrc_x, lds_x_addr + buf * kXStage + (wave + 8 * j) * 1024, ld.voff_x[j], k0,
+                                     ld.k_end_x);
     };
     auto issue_w = [&](const TileLoads& ld, int buf, int k0, int j) {
         load_stage_to_lds_16<K_TAIL>(ld.rsrc_w, lds_w_addr + buf * kWStage + (w_loader + S::kWLoaders * j) * 1024,
-                                     ld.voff_w[j], W_BITS != 4 ? k0 : k0 / 2);
+                                     ld.voff_w[j], W_BITS != 4 ? k0 : k0 / 2, ld.k_end_w);
     };
     auto issue_single = [&](const TileLoads& ld, int buf, int k0, int s) {
         if (S::kSplitRoles) {
@@ -417,16 +422,12 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             constexpr int kReads = TB + 2;
             constexpr int kReadsPerPiece = (kReads + TB - 2) / (TB - 1);   // spread over all pieces but the last
             auto read_one = [&](int ks, int r, v4i(&xo)[TB], v4i(&wo)[2]) __attribute__((always_inline)) {
-                const bool past_k = K_TAIL && it == nk - 1 && it * kTileK + (2 * ks + (lane >> 5)) * 16 >= K;
                 if (r == 0 || r == kReads - 1) {
                     const int cb = (r == 0) ? 0 : 1;
                     if (W_BITS != 4)
                         wo[cb] = *(const v4i*)(ws + w_off(ks) + cb * 32 * kTileK);
                     else
                         wo[cb] = widen_nibbles(*(const v2i*)(ws + w_off(ks) + cb * 32 * (kTileK / 2)));
-                    // K is a multiple of 16 but not of 128: chunks past K hold bytes of the next
-                    // row (or nothing); a zero weight operand removes them.
-                    if (past_k) wo[cb] = v4i{0, 0, 0, 0};
                 } else {
                     const int tb = r - 1;
                     xo[tb] = *(const v4i*)(xs + x_off(ks) + tb * 32 * kTileK);

@@ -130,30 +130,39 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     constexpr int kGroups = kXG + kWG;
     constexpr int kPer = (kGroups + S::kWaves - 1) / S::kWaves;     // loads of a wavefront per stage
     constexpr int kFull = kGroups - (kPer - 1) * S::kWaves;          // wavefronts that have that many
-    const v4i rsrc_x = make_rsrc(a.xq + tok0 * K, clamp_u32((a.M - tok0) * (long)K));
-    const v4i rsrc_w = make_rsrc((const int8_t*)a.w + ch0 * (K / kWDiv), clamp_u32((a.N - ch0) * (long)(K / kWDiv)));
-    int voff[kPer];
+    // (with a K tail the buffers end with the tile's last row: see load_stage_to_lds_16)
+    const v4i rsrc_x = make_rsrc(a.xq + tok0 * K, K_TAIL ? (unsigned)(rows_x * K) : clamp_u32((a.M - tok0) * (long)K));
+    const v4i rsrc_w = make_rsrc((const int8_t*)a.w + ch0 * (K / kWDiv),
+                                 K_TAIL ? (unsigned)(rows_w * (K / kWDiv)) : clamp_u32((a.N - ch0) * (long)(K / kWDiv)));
+    int voff[kPer], k_end[kPer];   // (k_end: used with a K tail only)
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
         const int g = wave + S::kWaves * j;
         if (g < kXG) {
             const int r = g * 8 + (lane >> 3);
-            voff[j] = __mul24(min(r, rows_x - 1), K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+            const int at = ((lane & 7) ^ ((r >> 1) & 7)) << 4;
+            voff[j] = __mul24(min(r, rows_x - 1), K) + at;
+            k_end[j] = K - at;
         } else if (W_BITS == 8) {
             const int r = (g - kXG) * 8 + (lane >> 3);
-            voff[j] = __mul24(min(r, rows_w - 1), K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+            const int at = ((lane & 7) ^ ((r >> 1) & 7)) << 4;
+            voff[j] = __mul24(min(r, rows_w - 1), K) + at;
+            k_end[j] = K - at;
         } else {
             const int r = (g - kXG) * 16 + (lane >> 2);
-            voff[j] = __mul24(min(r, rows_w - 1), K / 2) + (((lane & 3) ^ ((r >> 2) & 3)) << 4);
+            const int at = ((lane & 3) ^ ((r >> 2) & 3)) << 4;
+            voff[j] = __mul24(min(r, rows_w - 1), K / 2) + at;
+            k_end[j] = K / 2 - at;
         }
     }
     auto issue_one = [&](int slot, int k0, int j) {
         const int g = wave + S::kWaves * j;   // (wave-uniform)
         if (j == kPer - 1 && kFull < S::kWaves && wave >= kFull) return;
         if (g < kXG)
-            load_stage_to_lds_16<K_TAIL>(rsrc_x, lds_x_addr + slot * S::kXS + g * 1024, voff[j], k0);
+            load_stage_to_lds_16<K_TAIL>(rsrc_x, lds_x_addr + slot * S::kXS + g * 1024, voff[j], k0, k_end[j]);
         else
-            load_stage_to_lds_16<K_TAIL>(rsrc_w, lds_w_addr + slot * S::kWS + (g - kXG) * 1024, voff[j], k0 / kWDiv);
+            load_stage_to_lds_16<K_TAIL>(rsrc_w, lds_w_addr + slot * S::kWS + (g - kXG) * 1024, voff[j], k0 / kWDiv,
+                                         k_end[j]);
     };
     auto issue_stage = [&](int slot, int k0) {
 #pragma unroll
@@ -211,8 +220,6 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                     wf[cur][cb] = *(const v4i*)(ws + (w_off0 ^ (ks << 5)) + cb * 32 * kStageK);
                 else
                     wf[cur][cb] = widen_nibbles(*(const v2i*)(ws + (w_off0 ^ (ks << 4)) + cb * 32 * (kStageK / 2)));
-                // chunks past K hold bytes of the next row (or nothing): a zero weight removes them
-                if (K_TAIL && it == nk - 1 && it * kStageK + (2 * ks + (lane >> 5)) * 16 >= K) wf[cur][cb] = v4i{0, 0, 0, 0};
             }
 #pragma unroll
             for (int tb = 0; tb < BT; ++tb) xf[cur][tb] = *(const v4i*)(xs + (x_off0 ^ (ks << 5)) + tb * 32 * kStageK);
