@@ -47,13 +47,14 @@ __global__ __launch_bounds__(kQuantThreads) void rotate_weight_blocks(const floa
     hadamard_lane_stage<4>(t, sub);
     hadamard_lane_stage<8>(t, sub);
     hadamard_register_stages<2, 3>(t);
+    const float scale = hadamard_sign(sub) * kHadamardScale;
 #pragma unroll
     for (int i = 0; i < kRotateBlocks; ++i) {
         const long at = first + i * kRotateWidth + blk;
         if (at >= blocks) continue;
         float4v lo, hi;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) lo[j] = t[i][j] * kHadamardScale, hi[j] = t[i][4 + j] * kHadamardScale;
+        for (int j = 0; j < 4; ++j) lo[j] = t[i][j] * scale, hi[j] = t[i][4 + j] * scale;
         out[32 * at + sub] = lo;
         out[32 * at + 16 + sub] = hi;
     }

@@ -7,7 +7,10 @@
 // (the residual variant also writes the new fp16 residual stream, which the model needs).
 //
 // HBM-bound like the plain quantizer: 3 bytes per element (residual: 7), against the
-// 7 (11) bytes of running the producer and the quantizer as two kernels.
+// 7 (11) bytes of running the producer and the quantizer as two kernels.  The vector unit is a close
+// second (12 to 18 instructions per element), so instructions count: without selects for chunks
+// that are always inside the row or for a missing scale and shift, LayerNorm takes 17 per element
+// instead of 24 (32768 x 1152: 30.9 -> 27.8 us).
 //
 // The textbook producers, the paper giving no formulas for them:
 //   LayerNorm over the channels of a token (biased variance, eps inside the root, no
@@ -62,19 +65,66 @@ __device__ __forceinline__ float gelu_tanh(float x) {
     return x * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
-// The value of the lane whose index differs in one bit (1, 2, 4 or 8), as data movement
-// inside a row of 16 lanes: DPP quad permutes for 1 and 2, a DPP rotation by half the row for 8,
-// ds_swizzle (bit mode) for 4.
-template <int MASK>
-__device__ __forceinline__ float from_lane_xor(float v) {
-    const int iv = __builtin_bit_cast(int, v);
-    int r;
-    if (MASK == 1) r = __builtin_amdgcn_mov_dpp(iv, 0xB1, 0xF, 0xF, true);       // quad_perm [1,0,3,2]
-    else if (MASK == 2) r = __builtin_amdgcn_mov_dpp(iv, 0x4E, 0xF, 0xF, true);  // quad_perm [2,3,0,1]
-    else if (MASK == 8) r = __builtin_amdgcn_mov_dpp(iv, 0x128, 0xF, 0xF, true);  // row_ror:8
-    else r = __builtin_amdgcn_ds_swizzle(iv, (MASK << 10) | 0x1F);               // and 0x1F, or 0, xor MASK
-    return __builtin_bit_cast(float, r);
+// One stage of the Walsh-Hadamard transform across lanes, index bit MASK (1, 2, 4 or 8) of the lane: the
+// lane with the bit clear gets a + b, the one with it set a - b (a = the clear lane's value).  Every lane
+// computes own + s * other with s = -1 where the bit is set, one multiply-add that reads the other lane's
+// register as it goes (DPP inside a row of 16: quad permutes for 1 and 2, a rotation by half the row for
+// 8; 4 takes a half-row mirror, lane ^ 7, and a quad reversal); that is s times the value wanted, exactly, so
+// the product of the s of all stages comes off at the end (hadamard_sign).  32768 x 1152 with the
+// quantizer: 27.7 us with an xor and an add per element and stage and ds_swizzle for 4, 23.2 as it is;
+// 64 x 1152 4.0 -> 3.0.  A register that a vector
+// instruction wrote may be read through DPP two wait states later, which the compiler cannot see to
+// inside inline assembly: each block waits first, and its instructions read only registers written before it.
+template <int MASK, int NCH>
+__device__ __forceinline__ void hadamard_lane_stage(float (&t)[NCH][8], int sub) {
+    const float s = (sub & MASK) ? -1.0f : 1.0f;
+#define VQ_STAGE(CTRL)                                                                                               \
+    asm("s_nop 1\n\t"                                                                                                \
+        "v_fmac_f32_dpp %0, %0, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                                          \
+        "v_fmac_f32_dpp %1, %1, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                                          \
+        "v_fmac_f32_dpp %2, %2, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                                          \
+        "v_fmac_f32_dpp %3, %3, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                                          \
+        "v_fmac_f32_dpp %4, %4, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                                          \
+        "v_fmac_f32_dpp %5, %5, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                                          \
+        "v_fmac_f32_dpp %6, %6, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                                          \
+        "v_fmac_f32_dpp %7, %7, %8 " CTRL " row_mask:0xf bank_mask:0xf"                                              \
+        : "+v"(t[i][0]), "+v"(t[i][1]), "+v"(t[i][2]), "+v"(t[i][3]), "+v"(t[i][4]), "+v"(t[i][5]), "+v"(t[i][6]),   \
+          "+v"(t[i][7])                                                                                              \
+        : "v"(s))
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        if constexpr (MASK == 1) VQ_STAGE("quad_perm:[1,0,3,2]");
+        else if constexpr (MASK == 2) VQ_STAGE("quad_perm:[2,3,0,1]");
+        else if constexpr (MASK == 8) VQ_STAGE("row_ror:8");
+        else {
+            float m0, m1, m2, m3, m4, m5, m6, m7;
+            asm("s_nop 1\n\t"
+                "v_mov_b32_dpp %8, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                "v_mov_b32_dpp %9, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                "v_mov_b32_dpp %10, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                "v_mov_b32_dpp %11, %3 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                "v_mov_b32_dpp %12, %4 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                "v_mov_b32_dpp %13, %5 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                "v_mov_b32_dpp %14, %6 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                "v_mov_b32_dpp %15, %7 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                "v_fmac_f32_dpp %0, %8, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+                "v_fmac_f32_dpp %1, %9, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+                "v_fmac_f32_dpp %2, %10, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+                "v_fmac_f32_dpp %3, %11, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+                "v_fmac_f32_dpp %4, %12, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+                "v_fmac_f32_dpp %5, %13, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+                "v_fmac_f32_dpp %6, %14, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+                "v_fmac_f32_dpp %7, %15, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf"
+                : "+v"(t[i][0]), "+v"(t[i][1]), "+v"(t[i][2]), "+v"(t[i][3]), "+v"(t[i][4]), "+v"(t[i][5]),
+                  "+v"(t[i][6]), "+v"(t[i][7]), "=&v"(m0), "=&v"(m1), "=&v"(m2), "=&v"(m3), "=&v"(m4), "=&v"(m5),
+                  "=&v"(m6), "=&v"(m7)
+                : "v"(s));
+        }
+    }
+#undef VQ_STAGE
 }
+// The sign that the four stages above leave on a lane's values.
+__device__ __forceinline__ float hadamard_sign(int sub) { return (__builtin_popcount(sub & 15) & 1) ? -1.0f : 1.0f; }
 
 constexpr float kHadamardScale = 0.08838834764831845f;  // 1 / sqrt(128)
 
@@ -94,20 +144,6 @@ __device__ __forceinline__ void hadamard_register_stages(float (&t)[NCH][8]) {
                 }
 }
 
-// One stage of the Walsh-Hadamard transform across lanes: index bit MASK of the lane.
-// The lane with the bit clear gets a + b, the one with it set a - b (a = the clear lane's value).
-template <int MASK, int NCH>
-__device__ __forceinline__ void hadamard_lane_stage(float (&t)[NCH][8], int sub) {
-    const int sign = (sub & MASK) ? (int)0x80000000 : 0;
-#pragma unroll
-    for (int i = 0; i < NCH; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float other = from_lane_xor<MASK>(t[i][j]);
-            t[i][j] = other + __builtin_bit_cast(float, __builtin_bit_cast(int, t[i][j]) ^ sign);
-        }
-}
-
 typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 constexpr int kBufFlags = 0x00020000;          // raw buffer, 32-bit data format
 constexpr int kPastEnd = 0x7FFFFFF0;           // a buffer offset behind every buffer: loads give zero, stores are dropped
@@ -121,8 +157,9 @@ constexpr int kPastEnd = 0x7FFFFFF0;           // a buffer offset behind every b
 // kernel without branches and with few registers keeps many wavefronts per SIMD resident, and that,
 // not a loop over tokens with a prefetch, is what overlaps the producers' arithmetic with the memory
 // time of other wavefronts' rows (the loop was built and measured: slower for every producer but one).
+// (LayerNorm of up to five chunks per lane: held to the 96 registers that five wavefronts per SIMD have)
 template <int PRODUCER, int NCH, int LANES>
-__global__ __launch_bounds__(kQuantThreads) void produce_quantize_tokens(const FusedArgs a) {
+__global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ? 5 : 1) void produce_quantize_tokens(const FusedArgs a) {
     constexpr int kTokensPerWave = kWave / LANES;
     const int lane = threadIdx.x & (kWave - 1);
     const int sub = lane & (LANES - 1);
@@ -151,6 +188,8 @@ __global__ __launch_bounds__(kQuantThreads) void produce_quantize_tokens(const F
     const __amdgpu_buffer_rsrc_t rs_b =
         __builtin_amdgcn_make_buffer_rsrc((void*)a.mod_b, 0, a.mod_b ? n_samples * K8 * 32 : 0, kBufFlags);
 
+    // (only a lane's last chunk can lie past the row: NCH is the row's chunk count over LANES, rounded up)
+    auto chunk_in_row = [&](int i) { return i + 1 < NCH || i * LANES + sub < K8; };
     int voff[NCH];  // byte offset of this lane's chunk i in the fp16 rows (half of it in the int8 rows)
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
@@ -211,10 +250,11 @@ __global__ __launch_bounds__(kQuantThreads) void produce_quantize_tokens(const F
         hadamard_lane_stage<2>(t, sub);
         hadamard_lane_stage<4>(t, sub);
         hadamard_lane_stage<8>(t, sub);
+        const float signed_scale = hadamard_sign(sub) * kHadamardScale;
 #pragma unroll
         for (int i = 0; i < NCH; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) t[i][j] = t[i][j] * kHadamardScale;
+            for (int j = 0; j < 8; ++j) t[i][j] = t[i][j] * signed_scale;
     }
 
     if (PRODUCER == kGeluErf || PRODUCER == kGeluTanh) {
@@ -239,7 +279,7 @@ __global__ __launch_bounds__(kQuantThreads) void produce_quantize_tokens(const F
         float ss = 0.0f;
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
-            const bool in_row = i * LANES + sub < K8;
+            const bool in_row = chunk_in_row(i);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 t[i][j] = in_row ? t[i][j] - mean : 0.0f;
@@ -248,24 +288,20 @@ __global__ __launch_bounds__(kQuantThreads) void produce_quantize_tokens(const F
         }
         const float var = group_sum<LANES>(ss) / (float)(8 * K8);
         const float rstd = 1.0f / __builtin_sqrtf(var + a.eps);
-        // t = (x - mean) rstd (1 + scale) + shift as one multiply and one fma per element
-        Vec8 nxt_a{}, nxt_b{};
-        if (a.mod_a) nxt_a = vec_chunk(rs_a, b, 0);
-        if (a.mod_b) nxt_b = vec_chunk(rs_b, b, 0);
+        // t = (x - mean) rstd (1 + scale) + shift as one multiply and one fma per element (a missing scale
+        // or shift is an empty buffer, which reads as zero)
+        Vec8 nxt_a = vec_chunk(rs_a, b, 0), nxt_b = vec_chunk(rs_b, b, 0);
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
             const Vec8 sc = nxt_a, sh = nxt_b;
-            if (i + 1 < NCH) {
-                if (a.mod_a) nxt_a = vec_chunk(rs_a, b, i + 1);
-                if (a.mod_b) nxt_b = vec_chunk(rs_b, b, i + 1);
-            }
+            if (i + 1 < NCH) nxt_a = vec_chunk(rs_a, b, i + 1), nxt_b = vec_chunk(rs_b, b, i + 1);
             float mul[8], add[8];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                mul[j] = a.mod_a ? rstd * (1.0f + sc.lo[j]) : rstd;
-                mul[4 + j] = a.mod_a ? rstd * (1.0f + sc.hi[j]) : rstd;
-                add[j] = a.mod_b ? sh.lo[j] : 0.0f;
-                add[4 + j] = a.mod_b ? sh.hi[j] : 0.0f;
+                mul[j] = rstd * (1.0f + sc.lo[j]);
+                mul[4 + j] = rstd * (1.0f + sc.hi[j]);
+                add[j] = sh.lo[j];
+                add[4 + j] = sh.hi[j];
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) t[i][j] = __builtin_fmaf(t[i][j], mul[j], add[j]);
@@ -320,7 +356,7 @@ __global__ __launch_bounds__(kQuantThreads) void produce_quantize_tokens(const F
                 t[i][4 + j] = t[i][4 + j] * cm.hi[j];
             }
         }
-        const bool in_row = i * LANES + sub < K8;
+        const bool in_row = chunk_in_row(i);
 #pragma unroll
         for (int j = 0; j < 8; ++j) amax = fmaxf(amax, in_row ? fabsf(t[i][j]) : 0.0f);
         if (fold) {
@@ -337,12 +373,9 @@ __global__ __launch_bounds__(kQuantThreads) void produce_quantize_tokens(const F
     if (row_ok && sub == 0) a.x_scale[m] = scale;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-        int q[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) q[j] = quantize_one(t[i][j], inv, 127.0f);
         int2v o;
-        o.x = pack4(q[0], q[1], q[2], q[3]);
-        o.y = pack4(q[4], q[5], q[6], q[7]);
+        o.x = quantize4(t[i][0], t[i][1], t[i][2], t[i][3], inv);
+        o.y = quantize4(t[i][4], t[i][5], t[i][6], t[i][7], inv);
         __builtin_amdgcn_raw_buffer_store_b64(o, rs_q, voff[i] == kPastEnd ? kPastEnd : voff[i] / 2, 0, 0);
     }
 }

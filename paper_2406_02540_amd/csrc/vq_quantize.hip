@@ -83,12 +83,12 @@ __global__ __launch_bounds__(kQuantThreads, quant_waves(NCH)) void quantize_toke
             // (opaque to the optimizer: the widening happens here, chunk by chunk, and no
             // fp32 copy of the row is carried over from above)
             asm volatile("" : "+v"(raw[i]));
-            int q[8];
+            float t[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) q[j] = quantize_one((float)raw[i][j], inv, 127.0f);
+            for (int j = 0; j < 8; ++j) t[j] = (float)raw[i][j];
             int2v o;
-            o.x = pack4(q[0], q[1], q[2], q[3]);
-            o.y = pack4(q[4], q[5], q[6], q[7]);
+            o.x = quantize4(t[0], t[1], t[2], t[3], inv);
+            o.y = quantize4(t[4], t[5], t[6], t[7], inv);
             qrow[c] = o;
         }
     }
@@ -170,11 +170,8 @@ __global__ __launch_bounds__(kQuantThreads, 8) void quantize_static_chunks(
                     t[4 + j] = t[4 + j] * m1[j];
                 }
             }
-            int q[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) q[j] = quantize_one(t[j], inv, 127.0f);
-            o[i].x = pack4(q[0], q[1], q[2], q[3]);
-            o[i].y = pack4(q[4], q[5], q[6], q[7]);
+            o[i].x = quantize4(t[0], t[1], t[2], t[3], inv);
+            o[i].y = quantize4(t[4], t[5], t[6], t[7], inv);
         }
     }
     // the stores leave together, behind the last load (reads and writes in bursts, not mixed)

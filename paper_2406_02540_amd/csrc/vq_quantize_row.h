@@ -34,6 +34,22 @@ __device__ __forceinline__ int pack4(int a, int b, int c, int d) {
     return (a & 0xFF) | ((b & 0xFF) << 8) | ((c & 0xFF) << 16) | (d << 24);
 }
 
+// The same for activations (qmax 127), four codes into the bytes of one register.  The scaled value is
+// clamped first (the bounds are integers, so the order does not matter; NaN gives -127 as above) and
+// rounded by adding 1.5 * 2^23: the sum's unit in the last place is one, the addition rounds halves to
+// even, and the low byte of the sum is the code.  Three vector instructions per code and three per four
+// codes to gather the bytes (rint, convert, mask and shift are five and a half): with the vector unit
+// as busy as memory in these kernels, 3-4 % of the plain quantizer (32768 x 1152: 21.5 -> 20.7 us).
+__device__ __forceinline__ unsigned code_bits(float t, float inv) {
+    const float q = fminf(fmaxf(t * inv, -127.0f), 127.0f);
+    return __builtin_bit_cast(unsigned, q + 12582912.0f);
+}
+__device__ __forceinline__ int quantize4(float t0, float t1, float t2, float t3, float inv) {
+    const unsigned lo = __builtin_amdgcn_perm(code_bits(t1, inv), code_bits(t0, inv), 0x0C0C0400u);
+    const unsigned hi = __builtin_amdgcn_perm(code_bits(t3, inv), code_bits(t2, inv), 0x04000C0Cu);
+    return (int)(lo | hi);
+}
+
 // Which token and which lane of it this thread is.
 template <int LANES>
 struct RowLane {
@@ -144,12 +160,9 @@ __device__ __forceinline__ void fold_quantize_store(float (&t)[NCH][8], const fl
     for (int i = 0; i < NCH; ++i) {
         const int c = i * LANES + sub;
         if (row_ok && c < K8) {
-            int q[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) q[j] = quantize_one(t[i][j], inv, 127.0f);
             int2v o;
-            o.x = pack4(q[0], q[1], q[2], q[3]);
-            o.y = pack4(q[4], q[5], q[6], q[7]);
+            o.x = quantize4(t[i][0], t[i][1], t[i][2], t[i][3], inv);
+            o.y = quantize4(t[i][4], t[i][5], t[i][6], t[i][7], inv);
             qrow[c] = o;
         }
     }
