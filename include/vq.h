@@ -215,7 +215,8 @@ int vq_gemm_w4a8(const int8_t* xq, const float* x_scale, const uint8_t* wq4, con
  *
  *   workspace  device scratch of at least vq_linear_workspace_bytes(M,N,K,w_bits)
  *              bytes, 16-byte aligned; holds xq and x_scale between the two
- *              kernels; contents are unspecified afterwards.
+ *              kernels (a layer of few tokens is one kernel and leaves it alone);
+ *              contents are unspecified afterwards.
  */
 int vq_linear(const void* x_f16, const float* chan_mul, const void* w, int w_bits,
               const float* w_scale, const void* bias_f16, void* y_f16,

@@ -119,21 +119,68 @@ int validate_fused(const void* x, const void* chan_mul, const void* xq, const vo
     return VQ_OK;
 }
 
+vq::ProducerArgs producer_args(int producer, const void* x, const float* chan_mul) {
+    vq::ProducerArgs p{};
+    p.producer = producer;
+    p.x = x;
+    p.chan_mul = chan_mul;
+    p.tokens_per_sample = 1;
+    return p;
+}
+vq::ProducerArgs layernorm_args(const void* x, const float* mod_scale, const float* mod_shift, int tokens_per_sample,
+                                float eps, const float* chan_mul) {
+    vq::ProducerArgs p = producer_args(vq::kLayerNorm, x, chan_mul);
+    p.mod_a = mod_scale;
+    p.mod_b = mod_shift;
+    p.tokens_per_sample = tokens_per_sample;
+    p.eps = eps;
+    return p;
+}
+vq::ProducerArgs residual_args(const void* x, const void* y, const float* gate, int tokens_per_sample, void* r,
+                               const float* chan_mul) {
+    vq::ProducerArgs p = producer_args(vq::kResidual, x, chan_mul);
+    p.y = y;
+    p.r = r;
+    p.mod_a = gate;
+    p.tokens_per_sample = tokens_per_sample;
+    return p;
+}
+
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// Whether `out`, of `out_bytes`, shares memory with the layer's activations (or the residual's branch).
+bool overlaps(const void* out, size_t out_bytes, const void* in, size_t in_bytes) {
+    const uintptr_t o = (uintptr_t)out, i = (uintptr_t)in;
+    return in && o < i + in_bytes && i < o + out_bytes;
+}
+
+// The layer behind its producer, operands validated: in one launch where that is the faster way, otherwise
+// the quantizer into xq and x_scale and the GEMM behind it.  (The one launch reads a token several times,
+// so nothing that it writes may be a part of what it reads.)
+int enqueue_layer(const vq::ProducerArgs& p, const void* w, int w_bits, const float* w_scale, const void* bias_f16,
+                  void* y_f16, int8_t* xq, float* x_scale, int M, int N, int K, int num_cus, hipStream_t stream) {
+    if (vq::small_layer(p.producer, M, N, K, w_bits, num_cus)) {
+        const size_t in = 2 * (size_t)M * K, out = 2 * (size_t)M * N;
+        if (!overlaps(y_f16, out, p.x, in) && !overlaps(y_f16, out, p.y, in) && !overlaps(y_f16, out, p.r, in) &&
+            !overlaps(p.x, in, p.r, in) && !overlaps(p.y, in, p.r, in))
+            return launch_status(vq::launch_linear_small(p, w, w_bits, w_scale, bias_f16, y_f16, M, N, K, stream));
+    }
+    const int v = launch_status(vq::launch_producer_quantize(p, xq, x_scale, M, K, stream));
+    if (v != VQ_OK) return v;
+    return launch_status(vq::launch_gemm(xq, x_scale, w, w_bits, w_scale, bias_f16, y_f16, nullptr, M, N, K, num_cus,
+                                         stream));
+}
+
 // Shared by the layer entry points that take a workspace: validates the layer, splits the
-// workspace into xq and x_scale, lets `quantize` enqueue the (plain or fused) quantizer into
-// them and enqueues the GEMM behind it.  `fused`: the quantizer is one of the fused ones, which
-// hold a token in registers (K % 8 == 0, K <= VQ_MAX_FUSED_K).
-template <class Quantize>
-int linear_through_workspace(const void* x_f16, const float* chan_mul, const void* w, int w_bits,
-                             const float* w_scale, const void* bias_f16, void* y_f16, void* workspace,
-                             size_t workspace_bytes, int M, int N, int K, void* hip_stream, bool fused,
-                             Quantize quantize) {
+// workspace into xq and x_scale and enqueues the layer.  The fused quantizers hold a token in
+// registers (K % 8 == 0, K <= VQ_MAX_FUSED_K).
+int linear_through_workspace(const vq::ProducerArgs& p, const void* w, int w_bits, const float* w_scale,
+                             const void* bias_f16, void* y_f16, void* workspace, size_t workspace_bytes, int M, int N,
+                             int K, void* hip_stream) {
     if (w_bits != 8 && w_bits != 4) return VQ_ERR_BITS;
     if (M < 0 || N < 0 || K <= 0 || K > VQ_MAX_K) return VQ_ERR_SHAPE;
     if (K % (w_bits == 8 ? 16 : 32) != 0) return VQ_ERR_SHAPE;
-    if (fused && K > VQ_MAX_FUSED_K) return VQ_ERR_SHAPE;
+    if (p.producer != vq::kPlain && K > VQ_MAX_FUSED_K) return VQ_ERR_SHAPE;
     if (M == 0 || N == 0) return VQ_OK;
     if (!workspace) return VQ_ERR_NULL;
     if (misaligned(workspace)) return VQ_ERR_ALIGN;
@@ -141,18 +188,14 @@ int linear_through_workspace(const void* x_f16, const float* chan_mul, const voi
     int8_t* xq = (int8_t*)workspace;
     float* x_scale = (float*)((char*)workspace + round_up((size_t)M * (size_t)K, kAlign));
     // validate both halves before anything is enqueued
-    int v = validate_quantize(x_f16, chan_mul, xq, x_scale, M, K);
+    int v = validate_quantize(p.x, p.chan_mul, xq, x_scale, M, K);
     if (v != VQ_OK) return v;
     v = validate_gemm(xq, x_scale, w, w_scale, bias_f16, y_f16, nullptr, w_bits, M, N, K);
     if (v != VQ_OK) return v;
     int num_cus = 0;
     const int arch = check_arch(&num_cus);
     if (arch != VQ_OK) return arch;
-    hipStream_t stream = (hipStream_t)hip_stream;
-    v = launch_status(quantize(xq, x_scale, stream));
-    if (v != VQ_OK) return v;
-    return launch_status(vq::launch_gemm(xq, x_scale, w, w_bits, w_scale, bias_f16, y_f16, nullptr,
-                                         M, N, K, num_cus, stream));
+    return enqueue_layer(p, w, w_bits, w_scale, bias_f16, y_f16, xq, x_scale, M, N, K, num_cus, (hipStream_t)hip_stream);
 }
 
 }  // namespace
@@ -178,8 +221,8 @@ int vq_gelu_quantize(const void* h_f16, int approximate, const float* chan_mul, 
     if (M == 0) return VQ_OK;
     const int arch = check_arch();
     if (arch != VQ_OK) return arch;
-    return launch_status(vq::launch_gelu_quantize(h_f16, approximate, chan_mul, xq, x_scale, M, K,
-                                                  (hipStream_t)hip_stream));
+    return launch_status(vq::launch_producer_quantize(
+        producer_args(approximate ? vq::kGeluTanh : vq::kGeluErf, h_f16, chan_mul), xq, x_scale, M, K, (hipStream_t)hip_stream));
 }
 
 int vq_hadamard_quantize(const void* x_f16, const float* chan_mul, int8_t* xq, float* x_scale, int M, int K,
@@ -190,7 +233,7 @@ int vq_hadamard_quantize(const void* x_f16, const float* chan_mul, int8_t* xq, f
     if (M == 0) return VQ_OK;
     const int arch = check_arch();
     if (arch != VQ_OK) return arch;
-    return launch_status(vq::launch_hadamard_quantize(x_f16, chan_mul, xq, x_scale, M, K,
+    return launch_status(vq::launch_producer_quantize(producer_args(vq::kHadamard, x_f16, chan_mul), xq, x_scale, M, K,
                                                       (hipStream_t)hip_stream));
 }
 
@@ -214,9 +257,9 @@ int vq_layernorm_quantize(const void* x_f16, const float* mod_scale, const float
     if ((mod_scale && misaligned(mod_scale)) || (mod_shift && misaligned(mod_shift))) return VQ_ERR_ALIGN;
     const int arch = check_arch();
     if (arch != VQ_OK) return arch;
-    return launch_status(vq::launch_layernorm_quantize(x_f16, mod_scale, mod_shift, tokens_per_sample, eps,
-                                                       chan_mul, xq, x_scale, M, K,
-                                                       (hipStream_t)hip_stream));
+    return launch_status(vq::launch_producer_quantize(
+        layernorm_args(x_f16, mod_scale, mod_shift, tokens_per_sample, eps, chan_mul), xq, x_scale, M, K,
+        (hipStream_t)hip_stream));
 }
 
 int vq_residual_quantize(const void* x_f16, const void* y_f16, const float* gate, int tokens_per_sample,
@@ -230,7 +273,7 @@ int vq_residual_quantize(const void* x_f16, const void* y_f16, const float* gate
     if (misaligned(y_f16) || misaligned(r_f16) || (gate && misaligned(gate))) return VQ_ERR_ALIGN;
     const int arch = check_arch();
     if (arch != VQ_OK) return arch;
-    return launch_status(vq::launch_residual_quantize(x_f16, y_f16, gate, tokens_per_sample, r_f16, chan_mul,
+    return launch_status(vq::launch_producer_quantize(residual_args(x_f16, y_f16, gate, tokens_per_sample, r_f16, chan_mul),
                                                       xq, x_scale, M, K, (hipStream_t)hip_stream));
 }
 
@@ -301,10 +344,8 @@ size_t vq_linear_workspace_bytes(int M, int N, int K, int w_bits) {
 int vq_linear(const void* x_f16, const float* chan_mul, const void* w, int w_bits,
               const float* w_scale, const void* bias_f16, void* y_f16, void* workspace,
               size_t workspace_bytes, int M, int N, int K, void* hip_stream) {
-    return linear_through_workspace(x_f16, chan_mul, w, w_bits, w_scale, bias_f16, y_f16, workspace, workspace_bytes,
-                                    M, N, K, hip_stream, false, [&](int8_t* xq, float* x_scale, hipStream_t stream) {
-                                        return vq::launch_quantize_per_token(x_f16, chan_mul, xq, x_scale, M, K, stream);
-                                    });
+    return linear_through_workspace(producer_args(vq::kPlain, x_f16, chan_mul), w, w_bits, w_scale, bias_f16, y_f16,
+                                    workspace, workspace_bytes, M, N, K, hip_stream);
 }
 
 int vq_layernorm_linear(const void* x_f16, const float* mod_scale, const float* mod_shift,
@@ -313,22 +354,16 @@ int vq_layernorm_linear(const void* x_f16, const float* mod_scale, const float* 
                         size_t workspace_bytes, int M, int N, int K, void* hip_stream) {
     if (tokens_per_sample <= 0 || !(eps >= 0.0f)) return VQ_ERR_SHAPE;
     if ((mod_scale && misaligned(mod_scale)) || (mod_shift && misaligned(mod_shift))) return VQ_ERR_ALIGN;
-    return linear_through_workspace(x_f16, chan_mul, w, w_bits, w_scale, bias_f16, y_f16, workspace, workspace_bytes,
-                                    M, N, K, hip_stream, true, [&](int8_t* xq, float* x_scale, hipStream_t stream) {
-                                        return vq::launch_layernorm_quantize(x_f16, mod_scale, mod_shift, tokens_per_sample,
-                                                                             eps, chan_mul, xq, x_scale, M, K, stream);
-                                    });
+    return linear_through_workspace(layernorm_args(x_f16, mod_scale, mod_shift, tokens_per_sample, eps, chan_mul), w, w_bits, w_scale, bias_f16, y_f16,
+                                    workspace, workspace_bytes, M, N, K, hip_stream);
 }
 
 int vq_gelu_linear(const void* h_f16, int approximate, const float* chan_mul, const void* w, int w_bits,
                    const float* w_scale, const void* bias_f16, void* y_f16, void* workspace,
                    size_t workspace_bytes, int M, int N, int K, void* hip_stream) {
     if (approximate != 0 && approximate != 1) return VQ_ERR_SHAPE;
-    return linear_through_workspace(h_f16, chan_mul, w, w_bits, w_scale, bias_f16, y_f16, workspace, workspace_bytes,
-                                    M, N, K, hip_stream, true, [&](int8_t* xq, float* x_scale, hipStream_t stream) {
-                                        return vq::launch_gelu_quantize(h_f16, approximate, chan_mul, xq, x_scale, M, K,
-                                                                        stream);
-                                    });
+    return linear_through_workspace(producer_args(approximate ? vq::kGeluTanh : vq::kGeluErf, h_f16, chan_mul), w, w_bits, w_scale, bias_f16, y_f16,
+                                    workspace, workspace_bytes, M, N, K, hip_stream);
 }
 
 int vq_residual_linear(const void* x_f16, const void* y_in_f16, const float* gate, int tokens_per_sample,
@@ -340,21 +375,16 @@ int vq_residual_linear(const void* x_f16, const void* y_in_f16, const float* gat
         if (!y_in_f16 || !r_f16) return VQ_ERR_NULL;
         if (misaligned(y_in_f16) || misaligned(r_f16) || (gate && misaligned(gate))) return VQ_ERR_ALIGN;
     }
-    return linear_through_workspace(x_f16, chan_mul, w, w_bits, w_scale, bias_f16, y_f16, workspace, workspace_bytes,
-                                    M, N, K, hip_stream, true, [&](int8_t* xq, float* x_scale, hipStream_t stream) {
-                                        return vq::launch_residual_quantize(x_f16, y_in_f16, gate, tokens_per_sample,
-                                                                            r_f16, chan_mul, xq, x_scale, M, K, stream);
-                                    });
+    return linear_through_workspace(residual_args(x_f16, y_in_f16, gate, tokens_per_sample, r_f16, chan_mul), w, w_bits, w_scale, bias_f16, y_f16,
+                                    workspace, workspace_bytes, M, N, K, hip_stream);
 }
 
 int vq_hadamard_linear(const void* x_f16, const float* chan_mul, const void* w, int w_bits,
                        const float* w_scale, const void* bias_f16, void* y_f16, void* workspace,
                        size_t workspace_bytes, int M, int N, int K, void* hip_stream) {
     if (K > 0 && K % VQ_HADAMARD_BLOCK != 0) return VQ_ERR_SHAPE;
-    return linear_through_workspace(x_f16, chan_mul, w, w_bits, w_scale, bias_f16, y_f16, workspace, workspace_bytes,
-                                    M, N, K, hip_stream, true, [&](int8_t* xq, float* x_scale, hipStream_t stream) {
-                                        return vq::launch_hadamard_quantize(x_f16, chan_mul, xq, x_scale, M, K, stream);
-                                    });
+    return linear_through_workspace(producer_args(vq::kHadamard, x_f16, chan_mul), w, w_bits, w_scale, bias_f16, y_f16,
+                                    workspace, workspace_bytes, M, N, K, hip_stream);
 }
 
 int vq_linear_static(const void* x_f16, const float* chan_mul, const void* w, int w_bits,
@@ -377,11 +407,8 @@ int vq_linear_static(const void* x_f16, const float* chan_mul, const void* w, in
     if (v != VQ_OK) return v;
     v = validate_gemm(xq, x_scale, w, w_scale, bias_f16, y_f16, nullptr, w_bits, M, N, K);
     if (v != VQ_OK) return v;
-    hipStream_t stream = (hipStream_t)hip_stream;
-    v = launch_status(vq::launch_quantize_per_token(x_f16, chan_mul, xq, x_scale, M, K, stream));
-    if (v != VQ_OK) return v;
-    return launch_status(vq::launch_gemm(xq, x_scale, w, w_bits, w_scale, bias_f16, y_f16, nullptr,
-                                         M, N, K, num_cus, stream));
+    return enqueue_layer(producer_args(vq::kPlain, x_f16, chan_mul), w, w_bits, w_scale, bias_f16, y_f16, xq, x_scale, M, N,
+                         K, num_cus, (hipStream_t)hip_stream);
 }
 
 int vq_quantize_weight(const float* w_f32, const float* chan_s, int w_bits, void* wq_out,

@@ -70,30 +70,11 @@ hipError_t launch_producer_other(int producer, const FusedArgs& a, hipStream_t s
     }
 }
 
-hipError_t launch_gelu_quantize(const void* h_f16, int approximate, const float* chan_mul, int8_t* xq,
-                                float* x_scale, int M, int K, hipStream_t stream) {
-    FusedArgs a{};
-    a.x = (const half8*)h_f16;
-    a.chan_mul = (const float4v*)chan_mul;
-    a.xq = (int2v*)xq;
-    a.x_scale = x_scale;
-    a.M = M;
-    a.K8 = K / 8;
-    a.tokens_per_sample = 1;
-    return launch_producer_gelu(approximate ? kGeluTanh : kGeluErf, a, stream);
-}
-
-hipError_t launch_hadamard_quantize(const void* x_f16, const float* chan_mul, int8_t* xq, float* x_scale,
-                                    int M, int K, hipStream_t stream) {
-    FusedArgs a{};
-    a.x = (const half8*)x_f16;
-    a.chan_mul = (const float4v*)chan_mul;
-    a.xq = (int2v*)xq;
-    a.x_scale = x_scale;
-    a.M = M;
-    a.K8 = K / 8;
-    a.tokens_per_sample = 1;
-    return launch_producer_other(kHadamard, a, stream);
+hipError_t launch_producer_quantize(const ProducerArgs& p, int8_t* xq, float* x_scale, int M, int K, hipStream_t stream) {
+    if (p.producer == kPlain) return launch_quantize_per_token(p.x, p.chan_mul, xq, x_scale, M, K, stream);
+    const FusedArgs a = fused_args(p, xq, x_scale, M, K);
+    if (p.producer == kGeluErf || p.producer == kGeluTanh) return launch_producer_gelu(p.producer, a, stream);
+    return launch_producer_other(p.producer, a, stream);
 }
 
 hipError_t launch_rotate_weight(const float* w, const float* chan_s, float* w_rot, int N, int K,
@@ -102,40 +83,6 @@ hipError_t launch_rotate_weight(const float* w, const float* chan_s, float* w_ro
     hipLaunchKernelGGL(rotate_weight_blocks, dim3((unsigned)((blocks + per_wg - 1) / per_wg)), dim3(kQuantThreads), 0,
                        stream, (const float4v*)w, (const float4v*)chan_s, (float4v*)w_rot, blocks, K / 128);
     return hipGetLastError();
-}
-
-hipError_t launch_layernorm_quantize(const void* x_f16, const float* mod_scale, const float* mod_shift,
-                                     int tokens_per_sample, float eps, const float* chan_mul, int8_t* xq,
-                                     float* x_scale, int M, int K, hipStream_t stream) {
-    FusedArgs a{};
-    a.x = (const half8*)x_f16;
-    a.mod_a = (const float4v*)mod_scale;
-    a.mod_b = (const float4v*)mod_shift;
-    a.chan_mul = (const float4v*)chan_mul;
-    a.xq = (int2v*)xq;
-    a.x_scale = x_scale;
-    a.M = M;
-    a.K8 = K / 8;
-    a.tokens_per_sample = tokens_per_sample;
-    a.eps = eps;
-    return launch_producer_other(kLayerNorm, a, stream);
-}
-
-hipError_t launch_residual_quantize(const void* x_f16, const void* y_f16, const float* gate,
-                                    int tokens_per_sample, void* r_f16, const float* chan_mul, int8_t* xq,
-                                    float* x_scale, int M, int K, hipStream_t stream) {
-    FusedArgs a{};
-    a.x = (const half8*)x_f16;
-    a.y = (const half8*)y_f16;
-    a.r_out = (half8*)r_f16;
-    a.mod_a = (const float4v*)gate;
-    a.chan_mul = (const float4v*)chan_mul;
-    a.xq = (int2v*)xq;
-    a.x_scale = x_scale;
-    a.M = M;
-    a.K8 = K / 8;
-    a.tokens_per_sample = tokens_per_sample;
-    return launch_producer_other(kResidual, a, stream);
 }
 
 }  // namespace vq

@@ -25,7 +25,6 @@
 
 namespace vq {
 
-enum Producer { kGeluErf = 0, kGeluTanh = 1, kLayerNorm = 2, kResidual = 3, kHadamard = 4 };
 
 struct FusedArgs {
     const half8* x;          // [M,K8] the producer's input
@@ -40,6 +39,23 @@ struct FusedArgs {
     int tokens_per_sample;
     float eps;
 };
+
+inline FusedArgs fused_args(const ProducerArgs& p, int8_t* xq, float* x_scale, int M, int K) {
+    FusedArgs a{};
+    a.x = (const half8*)p.x;
+    a.y = (const half8*)p.y;
+    a.r_out = (half8*)p.r;
+    a.mod_a = (const float4v*)p.mod_a;
+    a.mod_b = (const float4v*)p.mod_b;
+    a.chan_mul = (const float4v*)p.chan_mul;
+    a.xq = (int2v*)xq;
+    a.x_scale = x_scale;
+    a.M = M;
+    a.K8 = K / 8;
+    a.tokens_per_sample = p.tokens_per_sample;
+    a.eps = p.eps;
+    return a;
+}
 
 // The producers are compiled in two translation units (each (producer, chunks, lanes) combination
 // is a kernel of its own, 48 per producer).
@@ -76,7 +92,7 @@ __device__ __forceinline__ float gelu_tanh(float x) {
 // instruction wrote may be read through DPP two wait states later, which the compiler cannot see to
 // inside inline assembly: each block waits first, and its instructions read only registers written before it.
 template <int MASK, int NCH>
-__device__ __forceinline__ void hadamard_lane_stage(float (&t)[NCH][8], int sub) {
+__device__ __forceinline__ void hadamard_lane_stage(float (&t)[NCH][8], int sub, int used = NCH) {
     const float s = (sub & MASK) ? -1.0f : 1.0f;
 #define VQ_STAGE(CTRL)                                                                                               \
     asm("s_nop 1\n\t"                                                                                                \
@@ -93,6 +109,7 @@ __device__ __forceinline__ void hadamard_lane_stage(float (&t)[NCH][8], int sub)
         : "v"(s))
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
+        if (i >= used) continue;   // (uniform; a constant where every chunk is used)
         if constexpr (MASK == 1) VQ_STAGE("quad_perm:[1,0,3,2]");
         else if constexpr (MASK == 2) VQ_STAGE("quad_perm:[2,3,0,1]");
         else if constexpr (MASK == 8) VQ_STAGE("row_ror:8");
@@ -130,9 +147,10 @@ constexpr float kHadamardScale = 0.08838834764831845f;  // 1 / sqrt(128)
 
 // Stages of the Walsh-Hadamard transform inside a lane's chunks of 8 values: index bits FROM .. TO - 1.
 template <int FROM, int TO, int NCH>
-__device__ __forceinline__ void hadamard_register_stages(float (&t)[NCH][8]) {
+__device__ __forceinline__ void hadamard_register_stages(float (&t)[NCH][8], int used = NCH) {
 #pragma unroll
-    for (int i = 0; i < NCH; ++i)
+    for (int i = 0; i < NCH; ++i) {
+        if (i >= used) continue;
 #pragma unroll
         for (int bit = 1 << FROM; bit < 1 << TO; bit <<= 1)
 #pragma unroll
@@ -142,6 +160,7 @@ __device__ __forceinline__ void hadamard_register_stages(float (&t)[NCH][8]) {
                     t[i][j] = lo + hi;
                     t[i][j | bit] = lo - hi;
                 }
+    }
 }
 
 typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
@@ -157,29 +176,29 @@ constexpr int kPastEnd = 0x7FFFFFF0;           // a buffer offset behind every b
 // kernel without branches and with few registers keeps many wavefronts per SIMD resident, and that,
 // not a loop over tokens with a prefetch, is what overlaps the producers' arithmetic with the memory
 // time of other wavefronts' rows (the loop was built and measured: slower for every producer but one).
-// (LayerNorm of up to five chunks per lane: held to the 96 registers that five wavefronts per SIMD have)
-template <int PRODUCER, int NCH, int LANES>
-__global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ? 5 : 1) void produce_quantize_tokens(const FusedArgs a) {
+//
+// Where the codes and scales go is `out`'s business: out.scale(token of the wavefront, value) by one lane
+// per existing token, out.codes(token of the wavefront, chunk of the row, whether it exists, 8 codes).
+// EXACT: NCH is the row's chunk count over LANES, rounded up; otherwise it is an upper bound, and chunk
+// groups past the row are skipped (a wave-uniform branch each).  writes_r: this wavefront writes the
+// residual sum (where several compute it, one does).
+template <int PRODUCER, int NCH, int LANES, bool EXACT, class Out>
+__device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_first, int lane, bool writes_r,
+                                                     const Out& out) {
     constexpr int kTokensPerWave = kWave / LANES;
-    const int lane = threadIdx.x & (kWave - 1);
     const int sub = lane & (LANES - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (uniform: the buffer descriptors below are scalar)
     const int K8 = a.K8;
-    const long w_first = ((long)blockIdx.x * kRowsPerBlock + wave) * kTokensPerWave;  // first token of this wavefront
-    if (w_first >= a.M) return;  // (uniform per wavefront)
     const long m = w_first + lane / LANES;
     const bool row_ok = m < a.M;
 
     const int ntok = (int)(a.M - w_first < kTokensPerWave ? a.M - w_first : kTokensPerWave);
     const __amdgpu_buffer_rsrc_t rs_x =
         __builtin_amdgcn_make_buffer_rsrc((void*)(a.x + w_first * K8), 0, ntok * K8 * 16, kBufFlags);
-    const __amdgpu_buffer_rsrc_t rs_q =
-        __builtin_amdgcn_make_buffer_rsrc((void*)(a.xq + w_first * K8), 0, ntok * K8 * 8, kBufFlags);
     const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(PRODUCER == kResidual ? a.y + w_first * K8 : a.x), 0, PRODUCER == kResidual ? ntok * K8 * 16 : 0, kBufFlags);
     const __amdgpu_buffer_rsrc_t rs_r = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(PRODUCER == kResidual ? a.r_out + w_first * K8 : (half8*)a.x), 0, PRODUCER == kResidual ? ntok * K8 * 16 : 0,
-        kBufFlags);
+        (void*)(PRODUCER == kResidual ? a.r_out + w_first * K8 : (half8*)a.x), 0,
+        PRODUCER == kResidual && writes_r ? ntok * K8 * 16 : 0, kBufFlags);
     const int n_samples = (int)((a.M + (long)a.tokens_per_sample - 1) / a.tokens_per_sample);
     const __amdgpu_buffer_rsrc_t rs_cm =
         __builtin_amdgcn_make_buffer_rsrc((void*)a.chan_mul, 0, a.chan_mul ? K8 * 32 : 0, kBufFlags);
@@ -188,8 +207,9 @@ __global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ?
     const __amdgpu_buffer_rsrc_t rs_b =
         __builtin_amdgcn_make_buffer_rsrc((void*)a.mod_b, 0, a.mod_b ? n_samples * K8 * 32 : 0, kBufFlags);
 
-    // (only a lane's last chunk can lie past the row: NCH is the row's chunk count over LANES, rounded up)
-    auto chunk_in_row = [&](int i) { return i + 1 < NCH || i * LANES + sub < K8; };
+    // (with EXACT only a lane's last chunk can lie past the row)
+    auto chunk_in_row = [&](int i) { return (EXACT && i + 1 < NCH) || i * LANES + sub < K8; };
+    const int used = EXACT ? NCH : (K8 + LANES - 1) / LANES;   // chunk groups of the row
     int voff[NCH];  // byte offset of this lane's chunk i in the fp16 rows (half of it in the int8 rows)
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
@@ -221,6 +241,7 @@ __global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ?
     float t[NCH][8];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
+        if (i >= used) continue;
         const half8 raw = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rs_x, voff[i], 0, 2 /* nontemporal */));
 #pragma unroll
         for (int j = 0; j < 8; ++j) t[i][j] = (float)raw[j];
@@ -235,6 +256,7 @@ __global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ?
             Vec8 nxt = vec_chunk(rs_cm, 0, 0);
 #pragma unroll
             for (int i = 0; i < NCH; ++i) {
+                if (i >= used) continue;
                 const Vec8 cm = nxt;
                 if (i + 1 < NCH) nxt = vec_chunk(rs_cm, 0, i + 1);
 #pragma unroll
@@ -245,21 +267,24 @@ __global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ?
                 chunk_done(t[i]);
             }
         }
-        hadamard_register_stages<0, 3>(t);
-        hadamard_lane_stage<1>(t, sub);
-        hadamard_lane_stage<2>(t, sub);
-        hadamard_lane_stage<4>(t, sub);
-        hadamard_lane_stage<8>(t, sub);
+        hadamard_register_stages<0, 3>(t, used);
+        hadamard_lane_stage<1>(t, sub, used);
+        hadamard_lane_stage<2>(t, sub, used);
+        hadamard_lane_stage<4>(t, sub, used);
+        hadamard_lane_stage<8>(t, sub, used);
         const float signed_scale = hadamard_sign(sub) * kHadamardScale;
 #pragma unroll
-        for (int i = 0; i < NCH; ++i)
+        for (int i = 0; i < NCH; ++i) {
+            if (i >= used) continue;
 #pragma unroll
             for (int j = 0; j < 8; ++j) t[i][j] = t[i][j] * signed_scale;
+        }
     }
 
     if (PRODUCER == kGeluErf || PRODUCER == kGeluTanh) {
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
+            if (i >= used) continue;
 #pragma unroll
             for (int j = 0; j < 8; ++j) t[i][j] = (PRODUCER == kGeluErf) ? gelu_erf(t[i][j]) : gelu_tanh(t[i][j]);
             // one chunk at a time: interleaving all of them would need a register per
@@ -272,13 +297,16 @@ __global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ?
         // two passes over the registers: the mean, then the variance about it
         float s = 0.0f;
 #pragma unroll
-        for (int i = 0; i < NCH; ++i)
+        for (int i = 0; i < NCH; ++i) {
+            if (i >= used) continue;
 #pragma unroll
             for (int j = 0; j < 8; ++j) s = s + t[i][j];  // (chunks past the row hold zeros)
+        }
         const float mean = group_sum<LANES>(s) / (float)(8 * K8);
         float ss = 0.0f;
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
+            if (i >= used) continue;
             const bool in_row = chunk_in_row(i);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -293,6 +321,7 @@ __global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ?
         Vec8 nxt_a = vec_chunk(rs_a, b, 0), nxt_b = vec_chunk(rs_b, b, 0);
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
+            if (i >= used) continue;
             const Vec8 sc = nxt_a, sh = nxt_b;
             if (i + 1 < NCH) nxt_a = vec_chunk(rs_a, b, i + 1), nxt_b = vec_chunk(rs_b, b, i + 1);
             float mul[8], add[8];
@@ -314,6 +343,7 @@ __global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ?
         if (a.mod_a) nxt = vec_chunk(rs_a, b, 0);
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
+            if (i >= used) continue;
             const Vec8 gate = nxt;
             if (a.mod_a && i + 1 < NCH) nxt = vec_chunk(rs_a, b, i + 1);
             const half8 yv = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rs_y, voff[i], 0, 2 /* nontemporal */));
@@ -347,6 +377,7 @@ __global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ?
     if (fold) nxt_cm = vec_chunk(rs_cm, 0, 0);
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
+        if (i >= used) continue;
         if (fold) {
             const Vec8 cm = nxt_cm;
             if (i + 1 < NCH) nxt_cm = vec_chunk(rs_cm, 0, i + 1);
@@ -370,14 +401,39 @@ __global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ?
         scale = amax / 127.0f;
         inv = 127.0f / amax;
     }
-    if (row_ok && sub == 0) a.x_scale[m] = scale;
+    if (row_ok && sub == 0) out.scale(lane / LANES, scale);
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
+        if (i >= used) continue;
         int2v o;
         o.x = quantize4(t[i][0], t[i][1], t[i][2], t[i][3], inv);
         o.y = quantize4(t[i][4], t[i][5], t[i][6], t[i][7], inv);
-        __builtin_amdgcn_raw_buffer_store_b64(o, rs_q, voff[i] == kPastEnd ? kPastEnd : voff[i] / 2, 0, 0);
+        out.codes(lane / LANES, i * LANES + sub, voff[i] != kPastEnd, o);
     }
+}
+
+// The stand-alone kernels: codes and scales go to memory.
+struct RowsInMemory {
+    __amdgpu_buffer_rsrc_t rs_q;   // the wavefront's rows of codes
+    float* x_scale;                // and its first token's scale
+    int K8;
+    __device__ __forceinline__ void scale(int token, float s) const { x_scale[token] = s; }
+    __device__ __forceinline__ void codes(int token, int chunk, bool exists, int2v o) const {
+        __builtin_amdgcn_raw_buffer_store_b64(o, rs_q, exists ? (token * K8 + chunk) * 8 : kPastEnd, 0, 0);
+    }
+};
+
+// (LayerNorm of up to five chunks per lane: held to the 96 registers that five wavefronts per SIMD have)
+template <int PRODUCER, int NCH, int LANES>
+__global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ? 5 : 1) void produce_quantize_tokens(const FusedArgs a) {
+    constexpr int kTokensPerWave = kWave / LANES;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (uniform: the buffer descriptors are scalar)
+    const long w_first = ((long)blockIdx.x * kRowsPerBlock + wave) * kTokensPerWave;  // first token of this wavefront
+    if (w_first >= a.M) return;  // (uniform per wavefront)
+    const int ntok = (int)(a.M - w_first < kTokensPerWave ? a.M - w_first : kTokensPerWave);
+    const RowsInMemory out{__builtin_amdgcn_make_buffer_rsrc((void*)(a.xq + w_first * a.K8), 0, ntok * a.K8 * 8, kBufFlags),
+                           a.x_scale + w_first, a.K8};
+    produce_and_quantize<PRODUCER, NCH, LANES, true>(a, w_first, threadIdx.x & (kWave - 1), true, out);
 }
 
 template <int PRODUCER, int NCH, int LANES>

@@ -57,13 +57,20 @@ struct OneTile {
     static constexpr int kT = WT * BT * 32;               // tokens of the tile
     static constexpr int kC = WC * BC * 32;               // channels of the tile
     static constexpr int kXS = kT * kStageK, kWS = kC * kStageK;
-    static constexpr int kRingBytes = RING * (kXS + kWS);
     static constexpr int kSums = KW * kT * kC * 4;        // every K group's int32 tile, once the stages are done
-    static constexpr int kBody = kRingBytes > kSums ? kRingBytes : kSums;
     static constexpr int kScales = kC * 4 + kT * 4 + kC * 2;
-    static constexpr int kLds = kBody + kScales;
-    static_assert(kLds * WGS_ <= 160 * 1024, "LDS of one CU");
+    static constexpr int kWgs = WGS_;
     static_assert((4 / KW) * KW == 4, "K groups");
+};
+
+// Where the activations come from: rows of codes in memory, which go through the ring like the weights
+// (here), or the producer's input, quantized by the workgroup itself (vq_linear_small.h).
+struct RowsOfCodes {
+    struct Args {};
+    static constexpr bool kQuantizes = false;
+    static constexpr int kRows = 0, kXBytes = 0;   // (tokens of a tile and LDS bytes where they are not the tile's and the ring's)
+    template <int KT>
+    static __device__ __forceinline__ void quantize(const Args&, long, int, bool, int8_t*, float*) {}
 };
 
 // Stage loads younger than the one needed: LEFT stages of PER loads.
@@ -77,13 +84,20 @@ __device__ __forceinline__ void wait_stages(int left) {
     }
 }
 
-template <class S, int W_BITS, bool K_TAIL>
-__global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant_tile(const TileArgs a) {
+template <class S, class Q, int W_BITS, bool K_TAIL>
+__global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant_tile(const TileArgs a,
+                                                                                     const typename Q::Args qa) {
     constexpr int BT = S::BT, BC = S::BC, KW = S::KW, RING = S::RING;
-    __shared__ __attribute__((aligned(1024))) int8_t lds[S::kLds];
+    constexpr int kRows = Q::kQuantizes ? Q::kRows : S::kT;               // tokens of the tile (a power of two)
+    constexpr int kXBlock = kRows * kStageK;                              // a stage's activations in LDS
+    constexpr int kXArea = Q::kQuantizes ? Q::kXBytes : RING * kXBlock;   // the whole of K, or the ring's
+    constexpr int kStaged = kXArea + RING * S::kWS;
+    constexpr int kBody = kStaged > S::kSums ? kStaged : S::kSums;
+    static_assert((kBody + S::kScales) * S::kWgs <= 160 * 1024, "LDS of one CU");
+    __shared__ __attribute__((aligned(1024))) int8_t lds[kBody + S::kScales];
     int8_t* const lds_x = lds;
-    int8_t* const lds_w = lds + RING * S::kXS;
-    int8_t* const lds_sc = lds + S::kBody;   // w_scale[kC] | x_scale[kT] | bias[kC]
+    int8_t* const lds_w = lds + kXArea;
+    int8_t* const lds_sc = lds + kBody;   // w_scale[kC] | x_scale[kT] | bias[kC]
     const unsigned lds_x_addr = (unsigned)(uintptr_t)(lds_ptr)lds_x;
     const unsigned lds_w_addr = (unsigned)(uintptr_t)(lds_ptr)lds_w;
 
@@ -95,7 +109,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     const int band = logical / band_tiles, in_band = logical - band * band_tiles;
     const int band_rows = min(a.tiles_t - band * kTileBand, kTileBand);
     const int col = in_band / band_rows;
-    const long tok0 = (long)(band * kTileBand + in_band - col * band_rows) * S::kT;
+    const long tok0 = (long)(band * kTileBand + in_band - col * band_rows) * kRows;
     const long ch0 = (long)col * S::kC;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -104,7 +118,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     const int wave_t = sp % S::WT, wave_c = sp / S::WT;
     const int K = a.K;
     constexpr int kWDiv = (W_BITS == 8) ? 1 : 2;
-    const int rows_x = (int)min((long)S::kT, a.M - tok0);
+    const int rows_x = (int)min((long)kRows, a.M - tok0);
     const int rows_w = (int)min((long)S::kC, a.N - ch0);
     const int nk = (K + kStageK - 1) / kStageK;
 
@@ -117,7 +131,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     for (int p = 0; p < kPre; ++p) {
         const int i = tid + p * S::kThreads;
         pre_ws[p] = a.w_scale[min(ch0 + i, (long)a.N - 1)];
-        pre_xs[p] = a.x_scale[min(tok0 + i, (long)a.M - 1)];
+        if (!Q::kQuantizes) pre_xs[p] = a.x_scale[min(tok0 + i, (long)a.M - 1)];
         pre_b[p] = a.bias ? a.bias[min(ch0 + i, (long)a.N - 1)] : (_Float16)0.0f;
     }
 
@@ -126,7 +140,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // chunk (l%8) ^ ((row/2)%8)) or, for packed nibbles, 16 rows x 64 B (row l/4, chunk (l%4) ^
     // ((row/4)%4)).  Row groups 0 .. kXG-1 are activations, the rest weights; wavefront w takes
     // groups w, w + kWaves, ...
-    constexpr int kXG = S::kT / 8, kWG = (W_BITS == 8) ? S::kC / 8 : S::kC / 16;
+    constexpr int kXG = Q::kQuantizes ? 0 : S::kT / 8, kWG = (W_BITS == 8) ? S::kC / 8 : S::kC / 16;
     constexpr int kGroups = kXG + kWG;
     constexpr int kPer = (kGroups + S::kWaves - 1) / S::kWaves;     // loads of a wavefront per stage
     constexpr int kFull = kGroups - (kPer - 1) * S::kWaves;          // wavefronts that have that many
@@ -159,7 +173,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         const int g = wave + S::kWaves * j;   // (wave-uniform)
         if (j == kPer - 1 && kFull < S::kWaves && wave >= kFull) return;
         if (g < kXG)
-            load_stage_to_lds_16<K_TAIL>(rsrc_x, lds_x_addr + slot * S::kXS + g * 1024, voff[j], k0, k_end[j]);
+            load_stage_to_lds_16<K_TAIL>(rsrc_x, lds_x_addr + slot * kXBlock + g * 1024, voff[j], k0, k_end[j]);
         else
             load_stage_to_lds_16<K_TAIL>(rsrc_w, lds_w_addr + slot * S::kWS + (g - kXG) * 1024, voff[j], k0 / kWDiv,
                                          k_end[j]);
@@ -179,7 +193,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 
     // ---- LDS -> MFMA operands ---------------------------------------------------------------
     const int fr_row = lane & 31;
-    const int x_off0 = (wave_t * 32 * BT + fr_row) * kStageK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4);
+    // (a tile of fewer tokens than a block has rows: the rows behind them repeat, and are not written)
+    const int x_row = (wave_t * 32 * BT + fr_row) & (kRows - 1);
+    const int x_off0 = x_row * kStageK + (((lane >> 5) ^ ((x_row >> 1) & 7)) << 4);
     const int w_off0 = (W_BITS == 8)
                            ? (wave_c * 32 * BC + fr_row) * kStageK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4)
                            : (wave_c * 32 * BC + fr_row) * (kStageK / 2) + (((fr_row >> 2) & 3) << 4) + (lane >> 5) * 8;
@@ -201,6 +217,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 
 #pragma unroll 1
     for (int s = 0; s < RING - 1 && s < nk; ++s) issue_stage(s, s * kStageK);
+    // (the weights are on their way; the first stage's barrier is also this one's)
+    if constexpr (Q::kQuantizes)
+        Q::template quantize<kStageK>(qa, tok0, wave, col == 0, lds_x, (float*)(lds_sc + S::kC * 4));
 
     constexpr int kSteps = 4 / KW;   // K steps of a stage that are this group's
     auto stage = [&](int it, int slot, auto parity_tag) __attribute__((always_inline)) {
@@ -208,7 +227,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         wait_stage(it);
         const bool fetch = it + RING - 1 < nk;
         const int f_slot = slot == 0 ? RING - 1 : slot - 1, f_k0 = (it + RING - 1) * kStageK;
-        const int8_t* xs = lds_x + slot * S::kXS;
+        const int8_t* xs = lds_x + (Q::kQuantizes ? it : slot) * kXBlock;
         const int8_t* ws = lds_w + slot * S::kWS;
 #pragma unroll
         for (int s = 0; s < kSteps; ++s) {
@@ -285,7 +304,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     for (int p = 0; p < kPre; ++p) {
         const int i = tid + p * S::kThreads;
         if (i < S::kC) *(float*)(lds_sc + i * 4) = pre_ws[p];
-        if (i < S::kT) *(float*)(lds_sc + S::kC * 4 + i * 4) = pre_xs[p];
+        if (!Q::kQuantizes && i < S::kT) *(float*)(lds_sc + S::kC * 4 + i * 4) = pre_xs[p];
         if (i < S::kC) *(_Float16*)(lds_sc + S::kC * 4 + S::kT * 4 + i * 2) = pre_b[p];
     }
     wait_lds_and_barrier();   // nobody reads the stage buffers any more
@@ -349,19 +368,22 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     }
 }
 
-template <class S, int W_BITS>
-hipError_t launch_tile_shape(TileArgs a, hipStream_t stream) {
-    a.tiles_t = (a.M + S::kT - 1) / S::kT;
+template <class S, class Q, int W_BITS>
+hipError_t launch_tile_shape(TileArgs a, const typename Q::Args& qa, hipStream_t stream) {
+    constexpr int rows = Q::kQuantizes ? Q::kRows : S::kT;
+    a.tiles_t = (a.M + rows - 1) / rows;
     a.tiles_c = (a.N + S::kC - 1) / S::kC;
     const long tiles = (long)a.tiles_t * a.tiles_c;
     if (tiles > 0x7FFFFF00l) return hipErrorInvalidValue;
     a.tiles = (int)tiles;
     a.tiles_per_xcd = (a.tiles + kTileXcds - 1) / kTileXcds;
     const dim3 grid((unsigned)(a.tiles_per_xcd * kTileXcds)), block(S::kThreads);
-    if (a.K % kStageK)
-        hipLaunchKernelGGL((gemm_i8_dequant_tile<S, W_BITS, true>), grid, block, 0, stream, a);
-    else
-        hipLaunchKernelGGL((gemm_i8_dequant_tile<S, W_BITS, false>), grid, block, 0, stream, a);
+    // (a workgroup that quantizes is not slowed by the tail's two instructions per load: one kernel for both)
+    if (Q::kQuantizes || a.K % kStageK) {
+        hipLaunchKernelGGL((gemm_i8_dequant_tile<S, Q, W_BITS, true>), grid, block, 0, stream, a, qa);
+    } else if constexpr (!Q::kQuantizes) {
+        hipLaunchKernelGGL((gemm_i8_dequant_tile<S, Q, W_BITS, false>), grid, block, 0, stream, a, qa);
+    }
     return hipGetLastError();
 }
 

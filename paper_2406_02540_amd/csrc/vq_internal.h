@@ -10,19 +10,25 @@ namespace vq {
 hipError_t launch_quantize_per_token(const void* x_f16, const float* chan_mul, int8_t* xq,
                                      float* x_scale, int M, int K, hipStream_t stream);
 
-// The quantizer fused behind its producer (vq_fused.hip): K % 8 == 0, K <= 8192.
-hipError_t launch_gelu_quantize(const void* h_f16, int approximate, const float* chan_mul, int8_t* xq,
-                                float* x_scale, int M, int K, hipStream_t stream);
-hipError_t launch_hadamard_quantize(const void* x_f16, const float* chan_mul, int8_t* xq, float* x_scale,
-                                    int M, int K, hipStream_t stream);  // K % 128 == 0
+// What runs in front of the quantizer, and its operands (those that it does not have stay null).
+enum Producer { kGeluErf = 0, kGeluTanh = 1, kLayerNorm = 2, kResidual = 3, kHadamard = 4, kPlain = 5 };
+struct ProducerArgs {
+    int producer;
+    const void* x;            // fp16 [M,K]
+    const float* chan_mul;    // Eq. 3's factor [K], or null
+    const void* y;            // residual: the branch output, fp16 [M,K]
+    void* r;                  // residual: the sum, fp16 [M,K]
+    const float* mod_a;       // LayerNorm: scale [B,K]; residual: gate [B,K]; or null
+    const float* mod_b;       // LayerNorm: shift [B,K]; or null
+    int tokens_per_sample;    // >= 1
+    float eps;
+};
+
+// The quantizer behind its producer (vq_fused.hip; kPlain goes to launch_quantize_per_token):
+// K % 8 == 0, K <= 8192 (Hadamard: K % 128 == 0).
+hipError_t launch_producer_quantize(const ProducerArgs& p, int8_t* xq, float* x_scale, int M, int K, hipStream_t stream);
 hipError_t launch_rotate_weight(const float* w, const float* chan_s, float* w_rot, int N, int K,
                                 hipStream_t stream);                  // K % 128 == 0, K <= 8192
-hipError_t launch_layernorm_quantize(const void* x_f16, const float* mod_scale, const float* mod_shift,
-                                     int tokens_per_sample, float eps, const float* chan_mul, int8_t* xq,
-                                     float* x_scale, int M, int K, hipStream_t stream);
-hipError_t launch_residual_quantize(const void* x_f16, const void* y_f16, const float* gate,
-                                    int tokens_per_sample, void* r_f16, const float* chan_mul, int8_t* xq,
-                                    float* x_scale, int M, int K, hipStream_t stream);
 
 // Calibration of Eq. 3's mask: column absmax of fp16 (is_f32 = 0) or fp32 rows, and the mask itself.
 hipError_t launch_channel_absmax(const void* a, int is_f32, float* amax, int R, int K, int accumulate,
@@ -48,5 +54,11 @@ hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, in
 hipError_t launch_gemm_tiles(int tile_t, int tile_c, const int8_t* xq, const float* x_scale, const void* w, int w_bits,
                              const float* w_scale, const void* bias_f16, void* y_f16, int32_t* acc_out,
                              int M, int N, int K, hipStream_t stream);
+
+// A layer of few tokens in one launch (vq_linear_small.hip): quantizer, with its producer, and GEMM.
+// small_layer: whether it is the faster way for these sizes.
+bool small_layer(int producer, int M, int N, int K, int w_bits, int num_cus);
+hipError_t launch_linear_small(const ProducerArgs& p, const void* w, int w_bits, const float* w_scale, const void* bias_f16,
+                               void* y_f16, int M, int N, int K, hipStream_t stream);
 
 }  // namespace vq
