@@ -250,7 +250,7 @@ def run_sweep(args, vq, wl, ceilings):
         "roofline": dict(kernel="gemm_i8_dequant", bound="mfma", achieved=round(g_ach, 1), peak=round(INT8_MFMA_PEAK_TOPS, 1),
                          unit="TOP/s", frac=round(g_ach / INT8_MFMA_PEAK_TOPS, 4), traffic=None,
                          launches="the %d GEMM launches with M >= 1024 of one step, HIP-event durations" % len(big)),
-        "roofline_quantizer": dict(kernel="quantize_tokens_wave", bound="hbm", achieved=round(q_ach, 1), peak=HBM_PEAK_GBS,
+        "roofline_quantizer": dict(kernel="produce_quantize_tokens", bound="hbm", achieved=round(q_ach, 1), peak=HBM_PEAK_GBS,
                                    unit="GB/s", frac=round(q_ach / HBM_PEAK_GBS, 4), traffic=None),
         "device_state": device_state,
         "csrc_sha256": csrc_hash(),
@@ -477,7 +477,7 @@ def main():
     # back to back between one pair of events (no GEMMs in between: a long run of memory-bound launches), and the
     # kernel's own durations in the committed rocprofv3 trace of this command (added below).
     q_achieved = q_bytes / q_time_in_step / 1e9
-    roofline_q = dict(kernel="quantize_tokens_wave", bound="hbm", achieved=round(q_achieved, 1),
+    roofline_q = dict(kernel="produce_quantize_tokens", bound="hbm", achieved=round(q_achieved, 1),
                       peak=HBM_PEAK_GBS, unit="GB/s", frac=round(q_achieved / HBM_PEAK_GBS, 4), traffic=None,
                       launches="the %d quantizer launches with M >= 1024 inside the step, each between its own pair of HIP "
                                "events; bytes = 3MK + 4M (+4K) each" % len(big),

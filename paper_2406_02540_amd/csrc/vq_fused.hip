@@ -1,5 +1,5 @@
 // The quantizers fused behind their producers (kernel template and its description:
-// vq_fused_kernel.h): the entry points, the LayerNorm, residual and Hadamard kernels (the GELU
+// vq_fused_kernel.h): the entry points, the plain, LayerNorm, residual and Hadamard kernels (the GELU
 // ones are compiled in vq_fused_gelu.hip), and the offline weight rotation.
 #include "vq_fused_kernel.h"
 
@@ -66,6 +66,7 @@ hipError_t launch_producer_other(int producer, const FusedArgs& a, hipStream_t s
     switch (producer) {
         case kLayerNorm: return launch_producer<kLayerNorm>(a, stream);
         case kResidual: return launch_producer<kResidual>(a, stream);
+        case kPlain: return launch_producer<kPlain>(a, stream);
         default: return launch_producer<kHadamard>(a, stream);
     }
 }
@@ -75,6 +76,16 @@ hipError_t launch_producer_quantize(const ProducerArgs& p, int8_t* xq, float* x_
     const FusedArgs a = fused_args(p, xq, x_scale, M, K);
     if (p.producer == kGeluErf || p.producer == kGeluTanh) return launch_producer_gelu(p.producer, a, stream);
     return launch_producer_other(p.producer, a, stream);
+}
+
+hipError_t launch_plain_quantize(const void* x_f16, const float* chan_mul, int8_t* xq, float* x_scale, int M, int K,
+                                 hipStream_t stream) {
+    ProducerArgs p{};
+    p.producer = kPlain;
+    p.x = x_f16;
+    p.chan_mul = chan_mul;
+    p.tokens_per_sample = 1;
+    return launch_producer_other(kPlain, fused_args(p, xq, x_scale, M, K), stream);
 }
 
 hipError_t launch_rotate_weight(const float* w, const float* chan_s, float* w_rot, int N, int K,

@@ -6,7 +6,8 @@
 // read once, transformed in registers as fp32, and its int8 codes and scale are written
 // (the residual variant also writes the new fp16 residual stream, which the model needs).
 //
-// HBM-bound like the plain quantizer: 3 bytes per element (residual: 7), against the
+// HBM-bound: 3 bytes per element (residual: 7; kPlain is the quantizer with nothing in front, 32768 x
+// 1152 in 19.6 us, 5.8 TB/s), against the
 // 7 (11) bytes of running the producer and the quantizer as two kernels.  The vector unit is a close
 // second (12 to 18 instructions per element), so instructions count: without selects for chunks
 // that are always inside the row or for a missing scale and shift, LayerNorm takes 17 per element
@@ -36,7 +37,7 @@ struct FusedArgs {
     int2v* xq;
     float* x_scale;
     int M, K8;
-    int tokens_per_sample;
+    int tokens_per_sample, n_samples;
     float eps;
 };
 
@@ -53,6 +54,7 @@ inline FusedArgs fused_args(const ProducerArgs& p, int8_t* xq, float* x_scale, i
     a.M = M;
     a.K8 = K / 8;
     a.tokens_per_sample = p.tokens_per_sample;
+    a.n_samples = (int)((M + (long)p.tokens_per_sample - 1) / p.tokens_per_sample);
     a.eps = p.eps;
     return a;
 }
@@ -167,6 +169,74 @@ typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 constexpr int kBufFlags = 0x00020000;          // raw buffer, 32-bit data format
 constexpr int kPastEnd = 0x7FFFFFF0;           // a buffer offset behind every buffer: loads give zero, stores are dropped
 
+// The per-channel vectors: the balancing factor, and LayerNorm's scale and shift or the residual's gate.
+enum VectorSlot { kVecMul = 0, kVecA = 1, kVecB = 2 };
+constexpr int vector_count(int producer) { return producer == kLayerNorm ? 3 : producer == kResidual ? 2 : 1; }
+struct Vec8 { float4v lo, hi; };   // one chunk of a vector
+
+// Read from memory, every lane its chunks: four bytes per element and vector through the load path, for
+// each token again.
+// BY_CHUNK: so is the residual's branch, in fewer registers, instead of up front with the token.
+template <bool BY_CHUNK = false>
+struct VectorsFromMemory {
+    static constexpr bool kByChunk = BY_CHUNK;
+    __device__ __forceinline__ bool staged(int) const { return false; }
+    __device__ __forceinline__ Vec8 chunk(int, int) const { return {}; }
+    template <class Rs>
+    __device__ __forceinline__ void ask(const Rs&, const Rs&, const Rs&, int) {}
+    __device__ __forceinline__ void park(int) {}
+};
+
+// Read once per workgroup into LDS (the rows of one sample; a workgroup whose tokens belong to several
+// takes scale, shift and gate from memory): asked for ahead of the tokens, so that one latency covers
+// both, and a quarter to an eighth of the bytes through the load path, which at 4 to 12 bytes of
+// vectors for 3 of data was as busy as memory.  Chunks are split in halves: 16 bytes per lane, no bank conflict.
+// 32768 tokens with all their vectors, us, from memory / as it is: 1152 channels LayerNorm 35.1 / 26.7,
+// Hadamard 29.6 / 24.3, balanced 22.2 / 20.0; 4608 channels LayerNorm 123.6 / 84.9, GELU 97.0 / 82.2,
+// Hadamard 103.4 / 81.5, balanced 85.4 / 76.0.  1001 x 1152: balanced 4.5 / 3.1, LayerNorm 4.8 / 4.2.
+template <int PRODUCER, int CHUNKS, int THREADS>
+struct VectorsInLds {
+    static constexpr bool kByChunk = false;
+    static constexpr int kVecs = vector_count(PRODUCER), kFloat4 = 2 * CHUNKS;
+    static constexpr int kPer = (kFloat4 + THREADS - 1) / THREADS;
+    float4v* lds;        // [kVecs][2][CHUNKS]
+    bool used[3];        // (uniform) the vector exists and is staged
+    int row;             // the sample whose rows are staged
+    float4v v[kVecs][kPer];
+    __device__ __forceinline__ bool staged(int which) const { return which < kVecs && used[which]; }
+    __device__ __forceinline__ Vec8 chunk(int which, int c) const {
+        const float4v* p = lds + which * kFloat4 + c;
+        return Vec8{p[0], p[CHUNKS]};
+    }
+    template <class Rs>
+    __device__ __forceinline__ void ask(const Rs& rs_cm, const Rs& rs_a, const Rs& rs_b, int K8) {
+#pragma unroll
+        for (int w = 0; w < kVecs; ++w)
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                const int e = i * THREADS + (int)threadIdx.x;   // which 16 bytes of the row
+                if (used[w])
+                    v[w][i] = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(
+                        w == kVecMul ? rs_cm : w == kVecA ? rs_a : rs_b, e < 2 * K8 ? ((w == kVecMul ? 0 : row * K8 * 2) + e) * 16 : kPastEnd,
+                        0, 0));
+            }
+    }
+    __device__ __forceinline__ void park(int K8) {
+        bool any = false;
+#pragma unroll
+        for (int w = 0; w < kVecs; ++w) {
+            any = any || used[w];
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                const int e = i * THREADS + (int)threadIdx.x;
+                if (used[w] && e < kFloat4) lds[w * kFloat4 + (e & 1) * CHUNKS + (e >> 1)] = v[w][i];
+            }
+        }
+        if (any) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
+        __builtin_amdgcn_sched_barrier(0);   // (the tokens are not waited for ahead of the barrier)
+    }
+};
+
 // A wavefront takes 64 / LANES tokens.  Everything it reads or writes goes through range-checked
 // buffers: the rows through buffers that start at the wavefront's first token and end behind its
 // last one, so that tokens past M and chunks past K (whose offset is pushed behind the buffer) read
@@ -182,16 +252,16 @@ constexpr int kPastEnd = 0x7FFFFFF0;           // a buffer offset behind every b
 // EXACT: NCH is the row's chunk count over LANES, rounded up; otherwise it is an upper bound, and chunk
 // groups past the row are skipped (a wave-uniform branch each).  writes_r: this wavefront writes the
 // residual sum (where several compute it, one does).
-template <int PRODUCER, int NCH, int LANES, bool EXACT, class Out>
+template <int PRODUCER, int NCH, int LANES, bool EXACT, class Vectors, class Out>
 __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_first, int lane, bool writes_r,
-                                                     const Out& out) {
+                                                     Vectors vectors, const Out& out) {
     constexpr int kTokensPerWave = kWave / LANES;
     const int sub = lane & (LANES - 1);
     const int K8 = a.K8;
     const long m = w_first + lane / LANES;
     const bool row_ok = m < a.M;
 
-    const int ntok = (int)(a.M - w_first < kTokensPerWave ? a.M - w_first : kTokensPerWave);
+    const int ntok = (int)max(0l, min((long)kTokensPerWave, a.M - w_first));
     const __amdgpu_buffer_rsrc_t rs_x =
         __builtin_amdgcn_make_buffer_rsrc((void*)(a.x + w_first * K8), 0, ntok * K8 * 16, kBufFlags);
     const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
@@ -199,13 +269,12 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
     const __amdgpu_buffer_rsrc_t rs_r = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(PRODUCER == kResidual ? a.r_out + w_first * K8 : (half8*)a.x), 0,
         PRODUCER == kResidual && writes_r ? ntok * K8 * 16 : 0, kBufFlags);
-    const int n_samples = (int)((a.M + (long)a.tokens_per_sample - 1) / a.tokens_per_sample);
     const __amdgpu_buffer_rsrc_t rs_cm =
         __builtin_amdgcn_make_buffer_rsrc((void*)a.chan_mul, 0, a.chan_mul ? K8 * 32 : 0, kBufFlags);
     const __amdgpu_buffer_rsrc_t rs_a =
-        __builtin_amdgcn_make_buffer_rsrc((void*)a.mod_a, 0, a.mod_a ? n_samples * K8 * 32 : 0, kBufFlags);
+        __builtin_amdgcn_make_buffer_rsrc((void*)a.mod_a, 0, a.mod_a ? a.n_samples * K8 * 32 : 0, kBufFlags);
     const __amdgpu_buffer_rsrc_t rs_b =
-        __builtin_amdgcn_make_buffer_rsrc((void*)a.mod_b, 0, a.mod_b ? n_samples * K8 * 32 : 0, kBufFlags);
+        __builtin_amdgcn_make_buffer_rsrc((void*)a.mod_b, 0, a.mod_b ? a.n_samples * K8 * 32 : 0, kBufFlags);
 
     // (with EXACT only a lane's last chunk can lie past the row)
     auto chunk_in_row = [&](int i) { return (EXACT && i + 1 < NCH) || i * LANES + sub < K8; };
@@ -218,9 +287,11 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
     }
     // The 8 floats of a per-channel vector that belong to chunk i of this lane, row `row` of a
     // [rows][K] array (chunks past K take the last chunk's: finite values that meet only zeros).
-    struct Vec8 { float4v lo, hi; };
-    auto vec_chunk = [&](const __amdgpu_buffer_rsrc_t& rs, int row, int i) {
-        const int off = (row * K8 + min(i * LANES + sub, K8 - 1)) * 32;
+    auto vec_chunk = [&](int which, int row, int i) {
+        const int c = min(i * LANES + sub, K8 - 1);
+        if (vectors.staged(which)) return vectors.chunk(which, c);
+        const __amdgpu_buffer_rsrc_t& rs = which == kVecMul ? rs_cm : which == kVecA ? rs_a : rs_b;
+        const int off = (row * K8 + c) * 32;
         Vec8 v;
         v.lo = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
         v.hi = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0));
@@ -238,13 +309,29 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
     // which sample's modulation this token takes
     const int b = (int)((unsigned)(row_ok ? m : a.M - 1) / (unsigned)a.tokens_per_sample);
 
+    vectors.ask(rs_cm, rs_a, rs_b, K8);
+    half8 raw[NCH];
+#pragma unroll
+    for (int i = 0; i < NCH; ++i)
+        if (i < used) raw[i] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rs_x, voff[i], 0, 2 /* nontemporal */));
+    constexpr bool kBranchFirst = PRODUCER == kResidual && !Vectors::kByChunk;   // the residual's branch with them
+    auto branch_chunk = [&](int i) {
+        return __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rs_y, voff[i], 0, 2 /* nontemporal */));
+    };
+    half8 branch[kBranchFirst ? NCH : 1];
+    if constexpr (kBranchFirst) {
+#pragma unroll
+        for (int i = 0; i < NCH; ++i)
+            if (i < used) branch[i] = branch_chunk(i);
+    }
+    vectors.park(K8);   // (a workgroup barrier where the vectors are staged: every wavefront gets here)
+    if (ntok == 0) return;
     float t[NCH][8];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
         if (i >= used) continue;
-        const half8 raw = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rs_x, voff[i], 0, 2 /* nontemporal */));
 #pragma unroll
-        for (int j = 0; j < 8; ++j) t[i][j] = (float)raw[j];
+        for (int j = 0; j < 8; ++j) t[i][j] = (float)raw[i][j];
     }
 
     if (PRODUCER == kHadamard) {
@@ -253,12 +340,12 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
         // token with one chunk index i, so element 8 (sub%16) + j of the block sits in lane
         // sub, register t[i][j]: three butterfly stages inside the registers, four across lanes.
         if (a.chan_mul) {
-            Vec8 nxt = vec_chunk(rs_cm, 0, 0);
+            Vec8 nxt = vec_chunk(kVecMul, 0, 0);
 #pragma unroll
             for (int i = 0; i < NCH; ++i) {
                 if (i >= used) continue;
                 const Vec8 cm = nxt;
-                if (i + 1 < NCH) nxt = vec_chunk(rs_cm, 0, i + 1);
+                if (i + 1 < NCH) nxt = vec_chunk(kVecMul, 0, i + 1);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     t[i][j] = t[i][j] * cm.lo[j];
@@ -318,12 +405,12 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
         const float rstd = 1.0f / __builtin_sqrtf(var + a.eps);
         // t = (x - mean) rstd (1 + scale) + shift as one multiply and one fma per element (a missing scale
         // or shift is an empty buffer, which reads as zero)
-        Vec8 nxt_a = vec_chunk(rs_a, b, 0), nxt_b = vec_chunk(rs_b, b, 0);
+        Vec8 nxt_a = vec_chunk(kVecA, b, 0), nxt_b = vec_chunk(kVecB, b, 0);
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
             if (i >= used) continue;
             const Vec8 sc = nxt_a, sh = nxt_b;
-            if (i + 1 < NCH) nxt_a = vec_chunk(rs_a, b, i + 1), nxt_b = vec_chunk(rs_b, b, i + 1);
+            if (i + 1 < NCH) nxt_a = vec_chunk(kVecA, b, i + 1), nxt_b = vec_chunk(kVecB, b, i + 1);
             float mul[8], add[8];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -340,13 +427,15 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
 
     if constexpr (PRODUCER == kResidual) {
         Vec8 nxt{};
-        if (a.mod_a) nxt = vec_chunk(rs_a, b, 0);
+        if (a.mod_a) nxt = vec_chunk(kVecA, b, 0);
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
             if (i >= used) continue;
             const Vec8 gate = nxt;
-            if (a.mod_a && i + 1 < NCH) nxt = vec_chunk(rs_a, b, i + 1);
-            const half8 yv = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rs_y, voff[i], 0, 2 /* nontemporal */));
+            if (a.mod_a && i + 1 < NCH) nxt = vec_chunk(kVecA, b, i + 1);
+            half8 yv;
+            if constexpr (kBranchFirst) yv = branch[i];
+            else yv = branch_chunk(i);
             float p[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) p[j] = (float)yv[j];
@@ -374,13 +463,13 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
     float amax = 0.0f;
     const bool fold = PRODUCER != kHadamard && a.chan_mul;  // (the rotation has the scaling before itself)
     Vec8 nxt_cm{};
-    if (fold) nxt_cm = vec_chunk(rs_cm, 0, 0);
+    if (fold) nxt_cm = vec_chunk(kVecMul, 0, 0);
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
         if (i >= used) continue;
         if (fold) {
             const Vec8 cm = nxt_cm;
-            if (i + 1 < NCH) nxt_cm = vec_chunk(rs_cm, 0, i + 1);
+            if (i + 1 < NCH) nxt_cm = vec_chunk(kVecMul, 0, i + 1);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 t[i][j] = t[i][j] * cm.lo[j];
@@ -423,25 +512,70 @@ struct RowsInMemory {
     }
 };
 
+// Which kernels stage their vectors, and with how many threads: workgroups of four wavefronts share up to
+// 20 KiB (eight of them fit a CU's LDS); LayerNorm's up to 56 KiB are shared by eight (two workgroups, four
+// wavefronts per SIMD), and only from kManyTokens on: with fewer there is nothing to wait for but the staging
+// itself.  LayerNorm of short rows, and longer rows of all, read them from memory.  The residual's long rows
+// (two fp16 tokens of more than 5 chunks per lane) take the branch chunk by chunk from kManyTokens on, where
+// the registers of asking first cost a wavefront per SIMD (32768 x 4608: 191 us, 197 asked first; 1000 x
+// 4608 11.8 and 9.1).
+constexpr int kFewVectorBytes = 20 * 1024, kManyVectorBytes = 56 * 1024, kManyTokens = 4096;
+constexpr int vector_bytes(int producer, int nch, int lanes) { return vector_count(producer) * nch * lanes * 32; }
+enum Staging { kNotStaged, kStaged, kStagedWide, kByChunk };
+constexpr Staging staging(int producer, int nch, int lanes) {   // (from kManyTokens on; below, the last two are kNotStaged)
+    const int bytes = vector_bytes(producer, nch, lanes);
+    if (producer == kLayerNorm && nch <= 2) return kNotStaged;
+    if (bytes <= kFewVectorBytes) return kStaged;
+    if (producer == kResidual) return kByChunk;
+    return producer == kLayerNorm && bytes <= kManyVectorBytes ? kStagedWide : kNotStaged;
+}
+constexpr int fused_threads(Staging s) { return s == kStagedWide ? 512 : kQuantThreads; }
+
 // (LayerNorm of up to five chunks per lane: held to the 96 registers that five wavefronts per SIMD have)
-template <int PRODUCER, int NCH, int LANES>
-__global__ __launch_bounds__(kQuantThreads, PRODUCER == kLayerNorm && NCH <= 5 ? 5 : 1) void produce_quantize_tokens(const FusedArgs a) {
+template <int PRODUCER, int NCH, int LANES, Staging STAGING>
+__global__ __launch_bounds__(fused_threads(STAGING), PRODUCER == kLayerNorm && NCH <= 5 ? 5 : 1) void produce_quantize_tokens(
+    const FusedArgs a) {
     constexpr int kTokensPerWave = kWave / LANES;
+    constexpr int kThreads = fused_threads(STAGING), kRows = kThreads / kWave * kTokensPerWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (uniform: the buffer descriptors are scalar)
-    const long w_first = ((long)blockIdx.x * kRowsPerBlock + wave) * kTokensPerWave;  // first token of this wavefront
-    if (w_first >= a.M) return;  // (uniform per wavefront)
-    const int ntok = (int)(a.M - w_first < kTokensPerWave ? a.M - w_first : kTokensPerWave);
+    const long first = (long)blockIdx.x * kRows;
+    const long w_first = first + wave * kTokensPerWave;  // first token of this wavefront
+    const int ntok = (int)max(0l, min((long)kTokensPerWave, a.M - w_first));
     const RowsInMemory out{__builtin_amdgcn_make_buffer_rsrc((void*)(a.xq + w_first * a.K8), 0, ntok * a.K8 * 8, kBufFlags),
                            a.x_scale + w_first, a.K8};
-    produce_and_quantize<PRODUCER, NCH, LANES, true>(a, w_first, threadIdx.x & (kWave - 1), true, out);
+    const int lane = threadIdx.x & (kWave - 1);
+    if constexpr (STAGING == kStaged || STAGING == kStagedWide) {
+        typedef VectorsInLds<PRODUCER, NCH * LANES, kThreads> Staged;
+        __shared__ float4v lds[Staged::kVecs * Staged::kFloat4];
+        Staged vectors;
+        vectors.lds = lds;
+        const int s_first = (int)((unsigned)first / (unsigned)a.tokens_per_sample);
+        const int s_last = (int)((unsigned)min(first + kRows - 1, (long)a.M - 1) / (unsigned)a.tokens_per_sample);
+        vectors.row = s_first;
+        // (the residual's gate alone is not worth a barrier; LayerNorm reads a missing scale or shift as zeros,
+        // from LDS or memory alike)
+        const bool sample = s_first == s_last && (PRODUCER == kLayerNorm || (a.chan_mul && a.mod_a));
+        vectors.used[kVecMul] = a.chan_mul != nullptr;
+        vectors.used[kVecA] = vectors.used[kVecB] = sample;
+        produce_and_quantize<PRODUCER, NCH, LANES, true>(a, w_first, lane, true, vectors, out);
+    } else {
+        produce_and_quantize<PRODUCER, NCH, LANES, true>(a, w_first, lane, true, VectorsFromMemory<STAGING == kByChunk>{}, out);
+    }
 }
 
+template <int PRODUCER, int NCH, int LANES, Staging STAGING>
+hipError_t launch_fused_staging(const FusedArgs& a, hipStream_t stream) {
+    constexpr int threads = fused_threads(STAGING), rows_per_block = threads / LANES;
+    const dim3 grid((unsigned)((a.M + (long)rows_per_block - 1) / rows_per_block)), block(threads);
+    hipLaunchKernelGGL((produce_quantize_tokens<PRODUCER, NCH, LANES, STAGING>), grid, block, 0, stream, a);
+    return hipGetLastError();
+}
 template <int PRODUCER, int NCH, int LANES>
 hipError_t launch_fused(const FusedArgs& a, hipStream_t stream) {
-    constexpr int rows_per_block = kRowsPerBlock * (kWave / LANES);
-    const dim3 grid((unsigned)((a.M + rows_per_block - 1) / rows_per_block)), block(kQuantThreads);
-    hipLaunchKernelGGL((produce_quantize_tokens<PRODUCER, NCH, LANES>), grid, block, 0, stream, a);
-    return hipGetLastError();
+    constexpr Staging kind = staging(PRODUCER, NCH, LANES);
+    if constexpr (kind == kStagedWide || kind == kByChunk)
+        if (a.M < kManyTokens) return launch_fused_staging<PRODUCER, NCH, LANES, kNotStaged>(a, stream);
+    return launch_fused_staging<PRODUCER, NCH, LANES, kind>(a, stream);
 }
 
 // NCH is a template parameter: pick the instantiation for the run-time chunk count.
@@ -458,7 +592,8 @@ hipError_t launch_fused_nch(int nch, const FusedArgs& a, hipStream_t stream) {
 template <int PRODUCER>
 hipError_t launch_producer(const FusedArgs& a, hipStream_t stream) {
     const int k8 = a.K8;
-    switch (lanes_for_row(k8)) {
+    // (many short plain rows: four tokens to a wavefront, 32768 x 512 11.8 -> 10.0 us; few: 1001 x 512 2.1, 2.25 so)
+    switch (PRODUCER == kPlain && k8 <= 64 && a.M >= kManyTokens ? 16 : lanes_for_row(k8)) {
         case 16: return launch_fused_nch<PRODUCER, 16>((k8 + 15) / 16, a, stream);
         case 32: return launch_fused_nch<PRODUCER, 32>((k8 + 31) / 32, a, stream);
         default: return launch_fused_nch<PRODUCER, 64>((k8 + 63) / 64, a, stream);

@@ -10,6 +10,10 @@ namespace vq {
 hipError_t launch_quantize_per_token(const void* x_f16, const float* chan_mul, int8_t* xq,
                                      float* x_scale, int M, int K, hipStream_t stream);
 
+// Its part for rows of whole chunks (vq_fused.hip): K % 8 == 0, K <= 8192, 16-byte aligned.
+hipError_t launch_plain_quantize(const void* x_f16, const float* chan_mul, int8_t* xq, float* x_scale, int M, int K,
+                                 hipStream_t stream);
+
 // What runs in front of the quantizer, and its operands (those that it does not have stay null).
 enum Producer { kGeluErf = 0, kGeluTanh = 1, kLayerNorm = 2, kResidual = 3, kHadamard = 4, kPlain = 5 };
 struct ProducerArgs {

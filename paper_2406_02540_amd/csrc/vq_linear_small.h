@@ -54,7 +54,7 @@ struct Quantizes {
         const int row0 = wave * (kWave / LANES);
         if (tok0 + row0 >= a.M) return;   // (uniform)
         const RowsInLds<kRows> out{lds_x, lds_scale, row0};
-        produce_and_quantize<PRODUCER, NCH, LANES, false>(a, tok0 + row0, threadIdx.x & (kWave - 1), writes_r, out);
+        produce_and_quantize<PRODUCER, NCH, LANES, false>(a, tok0 + row0, threadIdx.x & (kWave - 1), writes_r, VectorsFromMemory<>{}, out);
     }
 };
 

@@ -2,10 +2,8 @@
 //
 // 1. Dynamic per-token activation quantizer (ViDiT-Q Sec. 4.1; Eq. 2 of Sec. 3.1
 //    in symmetric form; activation side of the channel balancing, Eq. 3 of
-//    Sec. 4.2).  HBM-bound: a token is read once (2 B/element), kept in
-//    registers across the absmax reduction (as the fp16 it arrived as, or as
-//    fp32 products where a balancing factor is folded in), and written once
-//    (1 B/element + one fp32 scale).
+//    Sec. 4.2) for rows of any length and alignment; rows of whole 16-byte chunks go to the
+//    kernel that holds them in registers (vq_fused_kernel.h with nothing in front).
 // 2. Offline per-output-channel weight quantizer (same recipe, qmax 127 or 7,
 //    weight side of Eq. 3), with the 4-bit packer fused.
 //
@@ -22,76 +20,6 @@ __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
     return v;
-}
-
-// The token row held in registers (layout and steps: vq_quantize_row.h).  This kernel folds
-// the balancing factor in as the row arrives and keeps the products in fp32: 8 registers per
-// chunk, so the launcher prefers few chunks per lane (K = 1152: 32 lanes x 5 chunks).
-template <int NCH, int LANES>
-__global__ __launch_bounds__(kQuantThreads) void quantize_tokens_wave_mul(
-    const half8* __restrict__ x, const float4v* __restrict__ chan_mul, int2v* __restrict__ xq,
-    float* __restrict__ x_scale, int M, int K8) {
-    const RowLane<LANES> rl(M);
-    float t[NCH][8];
-    load_row<NCH, LANES, true>(x + (rl.row_ok ? rl.m : 0) * K8, rl.row_ok, rl.sub, K8, t, chan_mul);
-    fold_quantize_store<NCH, LANES, false>(t, nullptr, rl.row_ok, rl.sub, K8, rl.m, xq, x_scale);
-}
-
-// Wavefronts per SIMD the register allocation below is held to (4 registers per chunk of the row,
-// 512 registers per SIMD lane).
-constexpr int quant_waves(int nch) { return nch <= 10 ? 8 : nch == 11 ? 7 : nch == 12 ? 6 : nch <= 15 ? 5 : 4; }
-
-// No balancing factor: LANES is chosen so that K / 8 = NCH * LANES exactly where possible
-// (K = 1152: 16 lanes x 9 chunks), which keeps every lane busy on every instruction, and
-// the row stays in registers as the fp16 it arrived as (half the
-// registers of an fp32 copy, so that twice as many wavefronts are resident and every
-// workgroup of the video-sized problem is in flight at once).  The absolute maximum is
-// taken on the fp16 values (exact: fp16 -> fp32 is monotonic and exact), each value is
-// widened once more where it is scaled and rounded.
-template <int NCH, int LANES>
-__global__ __launch_bounds__(kQuantThreads, quant_waves(NCH)) void quantize_tokens_wave(
-    const half8* __restrict__ x, int2v* __restrict__ xq, float* __restrict__ x_scale, int M, int K8) {
-    const RowLane<LANES> rl(M);
-    const half8* row = x + (rl.row_ok ? rl.m : 0) * K8;
-    half8 raw[NCH];
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-        const int c = i * LANES + rl.sub;
-        if (rl.row_ok && c < K8) raw[i] = __builtin_nontemporal_load(row + c);
-        else raw[i] = (half8){0, 0, 0, 0, 0, 0, 0, 0};
-    }
-    half8 hmax = __builtin_elementwise_abs(raw[0]);
-#pragma unroll
-    for (int i = 1; i < NCH; ++i) hmax = __builtin_elementwise_max(hmax, __builtin_elementwise_abs(raw[i]));
-    float amax = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) amax = fmaxf(amax, (float)hmax[j]);
-    amax = group_max<LANES>(amax);
-
-    float scale = 0.0f, inv = 0.0f;
-    if (amax != 0.0f) {
-        scale = amax / 127.0f;
-        inv = 127.0f / amax;
-    }
-    if (rl.row_ok && rl.sub == 0) x_scale[rl.m] = scale;
-
-    int2v* qrow = xq + (rl.row_ok ? rl.m : 0) * K8;
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-        const int c = i * LANES + rl.sub;
-        if (rl.row_ok && c < K8) {
-            // (opaque to the optimizer: the widening happens here, chunk by chunk, and no
-            // fp32 copy of the row is carried over from above)
-            asm volatile("" : "+v"(raw[i]));
-            float t[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) t[j] = (float)raw[i][j];
-            int2v o;
-            o.x = quantize4(t[0], t[1], t[2], t[3], inv);
-            o.y = quantize4(t[4], t[5], t[6], t[7], inv);
-            qrow[c] = o;
-        }
-    }
 }
 
 __device__ __forceinline__ float block_max(float v, float* red) {
@@ -391,57 +319,15 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_weight_rows(
     }
 }
 
-template <int NCH, int LANES>
-hipError_t launch_wave(const void* x, const float* chan_mul, int8_t* xq, float* x_scale, int M,
-                       int K, hipStream_t stream) {
-    constexpr int rows_per_block = kRowsPerBlock * (kWave / LANES);
-    const dim3 grid((unsigned)((M + rows_per_block - 1) / rows_per_block)), block(kQuantThreads);
-    if (chan_mul)
-        hipLaunchKernelGGL((quantize_tokens_wave_mul<NCH, LANES>), grid, block, 0, stream,
-                           (const half8*)x, (const float4v*)chan_mul, (int2v*)xq, x_scale, M, K / 8);
-    else
-        hipLaunchKernelGGL((quantize_tokens_wave<NCH, LANES>), grid, block, 0, stream,
-                           (const half8*)x, (int2v*)xq, x_scale, M, K / 8);
-    return hipGetLastError();
-}
-
-// NCH is a template parameter: pick the instantiation for the run-time chunk count.
-template <int LANES, int NCH = 1>
-hipError_t launch_wave_nch(int nch, const void* x, const float* chan_mul, int8_t* xq, float* x_scale,
-                           int M, int K, hipStream_t stream) {
-    if constexpr (NCH > 16) {
-        return hipErrorInvalidValue;
-    } else {
-        if (nch == NCH) return launch_wave<NCH, LANES>(x, chan_mul, xq, x_scale, M, K, stream);
-        return launch_wave_nch<LANES, NCH + 1>(nch, x, chan_mul, xq, x_scale, M, K, stream);
-    }
-}
-
 }  // namespace
 
 hipError_t launch_quantize_per_token(const void* x_f16, const float* chan_mul, int8_t* xq,
                                      float* x_scale, int M, int K, hipStream_t stream) {
-    // Register-resident path: rows of 16-byte chunks, at most 16 chunks per lane.
+    // Rows of whole 16-byte chunks, at most 16 per lane: held in registers.
     const bool vec = (K % 8 == 0) && (K <= 8 * kWave * 16) &&
                      (((uintptr_t)x_f16 | (uintptr_t)xq) % 16 == 0) &&
                      (chan_mul == nullptr || (uintptr_t)chan_mul % 16 == 0);
-    if (vec) {
-        const int k8 = K / 8;
-        if (chan_mul) {  // the row is held as fp32 products: few chunks per lane first
-            switch (lanes_for_row(k8)) {
-                case 16: return launch_wave_nch<16>((k8 + 15) / 16, x_f16, chan_mul, xq, x_scale, M, K, stream);
-                case 32: return launch_wave_nch<32>((k8 + 31) / 32, x_f16, chan_mul, xq, x_scale, M, K, stream);
-                default: return launch_wave_nch<64>((k8 + 63) / 64, x_f16, chan_mul, xq, x_scale, M, K, stream);
-            }
-        }
-        // held as fp16: the widest lane group that divides the row exactly; a whole wavefront otherwise
-        if (k8 % 64 == 0) return launch_wave_nch<64>(k8 / 64, x_f16, chan_mul, xq, x_scale, M, K, stream);
-        if (k8 % 32 == 0 && k8 / 32 <= 16)
-            return launch_wave_nch<32>(k8 / 32, x_f16, chan_mul, xq, x_scale, M, K, stream);
-        if (k8 % 16 == 0 && k8 / 16 <= 16)
-            return launch_wave_nch<16>(k8 / 16, x_f16, chan_mul, xq, x_scale, M, K, stream);
-        return launch_wave_nch<64>((k8 + 63) / 64, x_f16, chan_mul, xq, x_scale, M, K, stream);
-    }
+    if (vec) return launch_plain_quantize(x_f16, chan_mul, xq, x_scale, M, K, stream);
     const dim3 grid((unsigned)M), block(kQuantThreads);
     if (chan_mul)
         hipLaunchKernelGGL((quantize_tokens_generic<true>), grid, block, 0, stream,

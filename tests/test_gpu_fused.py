@@ -364,3 +364,43 @@ def test_producer_linear_rejected_or_empty(vq):
     assert vq.vq_layernorm_linear(empty, w, 8, ws).shape == (0, 8)
     r, y = vq.vq_residual_linear(empty, empty, w, 8, ws)
     assert r.shape == (0, 192) and y.shape == (0, 8)
+
+
+# The rows of a large call, whose workgroups share the per-channel vectors (and whose lanes or order of loads
+# differ from a small call's), against the same tokens in calls of a few: samples that end inside a workgroup,
+# one sample for all, short rows, the longest staged ones and longer ones, a last workgroup that is partly empty.
+@pytest.mark.parametrize("K,T", [(1152, 1), (1152, 3), (1152, 4099), (256, 7), (504, 4099), (1536, 64), (4608, 5),
+                                 (4608, 2050), (5632, 100)])
+@pytest.mark.parametrize("producer", ["plain", "balanced", "layernorm", "layernorm_bare", "gelu", "residual", "residual_gate"])
+def test_large_calls_match_small_ones(vq, producer, K, T):
+    say(f"large against small {producer} K={K} T={T}")
+    M = 4099
+    g = torch.Generator(device="cuda").manual_seed(8000 + K + T)
+
+    def n(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+
+    x, y_in = (n(M, K) * 3).half(), n(M, K).half()
+    B = (M + T - 1) // T
+    cm, sc, sh = torch.exp(n(K) * 0.3), n(B, K) * 0.2, n(B, K) * 0.5
+
+    def call(lo, hi, t, a, b):
+        xs = x[lo:hi]
+        if producer in ("plain", "balanced"):
+            return vq.vq_quantize_per_token(xs, cm if producer == "balanced" else None)
+        if producer == "layernorm":
+            return vq.vq_layernorm_quantize(xs, a, b, t, 1e-6, cm)
+        if producer == "layernorm_bare":
+            return vq.vq_layernorm_quantize(xs, None, None, None, 1e-6, None)
+        if producer == "gelu":
+            return vq.vq_gelu_quantize(xs, True, cm)
+        return vq.vq_residual_quantize(xs, y_in[lo:hi], a, t, None, cm if producer == "residual" else None)
+
+    whole = call(0, M, T, sc, sh)
+    for lo in (0, 1, 7, 2049, M - 3):
+        i = lo // T                                    # the sample of token lo, up to its end or three tokens on
+        hi = min(lo + 3, (i + 1) * T, M)
+        part = call(lo, hi, hi - lo, sc[i:i + 1].contiguous(), sh[i:i + 1].contiguous())
+        torch.cuda.synchronize()
+        for w, p in zip(whole, part):
+            assert torch.equal(w[lo:hi], p)
