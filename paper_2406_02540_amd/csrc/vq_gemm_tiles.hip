@@ -35,6 +35,7 @@ hipError_t launch_gemm_tiles(int tile_t, int tile_c, const int8_t* xq, const flo
     a.N = N;
     a.K = K;
     a.tiles_t = a.tiles_c = a.tiles = a.tiles_per_xcd = 0;  // (set for the chosen tile)
+    a.div_band = a.div_last = 0;
     if (tile_t == 32 && tile_c == 32) return launch_bits<Tile32x32>(a, w_bits, stream);
     if (tile_t == 64 && tile_c == 64) return launch_bits<Tile64x64>(a, w_bits, stream);
     if (tile_t == 128 && tile_c == 64) return launch_bits<Tile128x64>(a, w_bits, stream);

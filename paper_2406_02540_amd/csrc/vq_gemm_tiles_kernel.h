@@ -17,10 +17,13 @@
 // Measured against the 64 x 64 tile this kernel replaces (four wavefronts, every K step on its own
 // LDS latency, one workgroup per CU), GEMM alone in a captured graph, us:
 //   tokens x K -> channels   before   now        tokens x K -> channels   before   now
-//   1 x 1152 -> 1152           5.5    4.4        1001 x 1152 -> 4608       24.9   13.1
-//   64 x 4608 -> 1152         12.9    7.8        2048 x 1152 -> 1152       16.2    9.6
-//   256 x 1152 -> 1152         5.7    5.1        4096 x 1152 -> 1152       25.5   13.3
+//   1 x 1152 -> 1152           5.5    3.9        1001 x 1152 -> 4608       24.9   13.2
+//   64 x 4608 -> 1152         12.9    7.0        2048 x 1152 -> 1152       16.2    9.4
+//   256 x 1152 -> 1152         5.7    4.6        4096 x 1152 -> 1152       25.5   13.1
 //   240 x 4096 -> 2304        12.7    9.9        4096 x 4608 -> 1152       62     30 (now 256 x 192)
+// The last 0.3 us of the small ones are the way to the first load: reciprocals instead of two divisions,
+// 32-bit instead of 64-bit tile arithmetic, and scales asked for behind the first stages instead of ahead
+// of them.
 #pragma once
 #include <type_traits>
 
@@ -39,7 +42,13 @@ struct TileArgs {
     int32_t* acc_out;
     int M, N, K;
     int tiles_t, tiles_c, tiles, tiles_per_xcd;
+    unsigned div_band, div_last;   // reciprocals of a band's tiles and of the last band's rows (reciprocal_of), or 0
 };
+
+// ceil(2^32 / d): the high half of n times this is n / d for 2 <= d and n * d < 2^32 (the product exceeds
+// n / d by less than n / 2^32 < 1 / d).  The kernel begins with two divisions, and a division by a number
+// that is not known is 25 dependent instructions.
+inline unsigned reciprocal_of(unsigned d) { return 0xFFFFFFFFu / d + 1u; }
 
 namespace {
 
@@ -106,11 +115,15 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     const int logical = (blockIdx.x % kTileXcds) * a.tiles_per_xcd + blockIdx.x / kTileXcds;
     if ((int)(blockIdx.x / kTileXcds) >= a.tiles_per_xcd || logical >= a.tiles) return;
     const int band_tiles = kTileBand * a.tiles_c;
-    const int band = logical / band_tiles, in_band = logical - band * band_tiles;
+    const int band = a.div_band ? (int)__umulhi((unsigned)logical, a.div_band) : logical / band_tiles;
+    const int in_band = logical - band * band_tiles;
     const int band_rows = min(a.tiles_t - band * kTileBand, kTileBand);
-    const int col = in_band / band_rows;
-    const long tok0 = (long)(band * kTileBand + in_band - col * band_rows) * kRows;
-    const long ch0 = (long)col * S::kC;
+    int col;
+    if (band_rows == kTileBand) col = in_band / kTileBand;
+    else if (a.div_last) col = (int)__umulhi((unsigned)in_band, a.div_last);
+    else col = in_band / band_rows;
+    const int tok0 = (band * kTileBand + in_band - col * band_rows) * kRows;   // (< M)
+    const int ch0 = col * S::kC;                                               // (< N)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -118,22 +131,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     const int wave_t = sp % S::WT, wave_c = sp / S::WT;
     const int K = a.K;
     constexpr int kWDiv = (W_BITS == 8) ? 1 : 2;
-    const int rows_x = (int)min((long)kRows, a.M - tok0);
-    const int rows_w = (int)min((long)S::kC, a.N - ch0);
+    const int rows_x = min(kRows, a.M - tok0);
+    const int rows_w = min(S::kC, a.N - ch0);
     const int nk = (K + kStageK - 1) / kStageK;
-
-    // Scales and bias, one channel and token per thread; parked in LDS behind the mainloop.
-    constexpr int kPre = (S::kC > S::kT ? S::kC : S::kT) > S::kThreads ? 2 : 1;
-    static_assert(kPre * S::kThreads >= S::kC && kPre * S::kThreads >= S::kT, "scales");
-    float pre_ws[kPre], pre_xs[kPre];
-    _Float16 pre_b[kPre];
-#pragma unroll
-    for (int p = 0; p < kPre; ++p) {
-        const int i = tid + p * S::kThreads;
-        pre_ws[p] = a.w_scale[min(ch0 + i, (long)a.N - 1)];
-        if (!Q::kQuantizes) pre_xs[p] = a.x_scale[min(tok0 + i, (long)a.M - 1)];
-        pre_b[p] = a.bias ? a.bias[min(ch0 + i, (long)a.N - 1)] : (_Float16)0.0f;
-    }
 
     // ---- global -> LDS ---------------------------------------------------------------------
     // One load fills 1 KiB: 8 rows x 128 B (lane l: row l/8, physical chunk l%8 holding logical
@@ -144,10 +144,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     constexpr int kGroups = kXG + kWG;
     constexpr int kPer = (kGroups + S::kWaves - 1) / S::kWaves;     // loads of a wavefront per stage
     constexpr int kFull = kGroups - (kPer - 1) * S::kWaves;          // wavefronts that have that many
-    // (with a K tail the buffers end with the tile's last row: see load_stage_to_lds_16)
-    const v4i rsrc_x = make_rsrc(a.xq + tok0 * K, K_TAIL ? (unsigned)(rows_x * K) : clamp_u32((a.M - tok0) * (long)K));
-    const v4i rsrc_w = make_rsrc((const int8_t*)a.w + ch0 * (K / kWDiv),
-                                 K_TAIL ? (unsigned)(rows_w * (K / kWDiv)) : clamp_u32((a.N - ch0) * (long)(K / kWDiv)));
+    // (the buffers end with the tile's last row: see load_stage_to_lds_16)
+    const v4i rsrc_x = make_rsrc(a.xq + (long)tok0 * K, (unsigned)(rows_x * K));
+    const v4i rsrc_w = make_rsrc((const int8_t*)a.w + (long)ch0 * (K / kWDiv), (unsigned)(rows_w * (K / kWDiv)));
     int voff[kPer], k_end[kPer];   // (k_end: used with a K tail only)
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
@@ -191,6 +190,23 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             wait_stages<kPer, RING - 2>(left);
     };
 
+#pragma unroll
+    for (int s = 0; s < RING - 1; ++s)
+        if (s < nk) issue_stage(s, s * kStageK);
+
+    // Scales and bias, one channel and token per thread, behind the first stages; parked in LDS behind the mainloop.
+    constexpr int kPre = (S::kC > S::kT ? S::kC : S::kT) > S::kThreads ? 2 : 1;
+    static_assert(kPre * S::kThreads >= S::kC && kPre * S::kThreads >= S::kT, "scales");
+    float pre_ws[kPre], pre_xs[kPre];
+    _Float16 pre_b[kPre];
+#pragma unroll
+    for (int p = 0; p < kPre; ++p) {
+        const int i = tid + p * S::kThreads;
+        pre_ws[p] = a.w_scale[ch0 + min(i, rows_w - 1)];
+        if (!Q::kQuantizes) pre_xs[p] = a.x_scale[tok0 + min(i, rows_x - 1)];
+        pre_b[p] = a.bias ? a.bias[ch0 + min(i, rows_w - 1)] : (_Float16)0.0f;
+    }
+
     // ---- LDS -> MFMA operands ---------------------------------------------------------------
     const int fr_row = lane & 31;
     // (a tile of fewer tokens than a block has rows: the rows behind them repeat, and are not written)
@@ -215,8 +231,6 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 #pragma unroll
     for (int cb = 0; cb < BC; ++cb) wf[1][cb] = v4i{0, 0, 0, 0};
 
-#pragma unroll 1
-    for (int s = 0; s < RING - 1 && s < nk; ++s) issue_stage(s, s * kStageK);
     // (the weights are on their way; the first stage's barrier is also this one's)
     if constexpr (Q::kQuantizes)
         Q::template quantize<kStageK>(qa, tok0, wave, col == 0, lds_x, (float*)(lds_sc + S::kC * 4));
@@ -332,7 +346,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     if (c0 >= rows_w) return;
     const v4f s0 = *(const v4f*)(lds_sc + c0 * 4), s1 = *(const v4f*)(lds_sc + c0 * 4 + 16);
     const v4i bias8 = *(const v4i*)(lds_sc + S::kC * 4 + S::kT * 4 + c0 * 2);
-    _Float16* const ytile = a.y + tok0 * a.N + ch0;
+    _Float16* const ytile = a.y + (long)tok0 * a.N + ch0;
     const bool whole = c0 + 8 <= rows_w;
     typedef v4i v4i_any __attribute__((aligned(2)));   // (rows of Y start at any even address)
 #pragma unroll 1
@@ -360,7 +374,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 if (c0 + e < rows_w) yrow[e] = o[e];
         }
         if (a.acc_out) {
-            int32_t* const arow = a.acc_out + (tok0 + t) * a.N + ch0 + c0;
+            int32_t* const arow = a.acc_out + (long)(tok0 + t) * a.N + ch0 + c0;
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 if (c0 + e < rows_w) arow[e] = (e < 4 ? v0[e & 3] : v1[e & 3]) >> ((W_BITS == 4) ? 4 : 0);
@@ -377,6 +391,10 @@ hipError_t launch_tile_shape(TileArgs a, const typename Q::Args& qa, hipStream_t
     if (tiles > 0x7FFFFF00l) return hipErrorInvalidValue;
     a.tiles = (int)tiles;
     a.tiles_per_xcd = (a.tiles + kTileXcds - 1) / kTileXcds;
+    const int last = a.tiles_t % kTileBand;
+    const bool small = a.tiles < 65536 && kTileBand * (long)a.tiles_c < 65536;
+    a.div_band = small ? reciprocal_of((unsigned)(kTileBand * a.tiles_c)) : 0;
+    a.div_last = small && last > 1 ? reciprocal_of((unsigned)last) : 0;
     const dim3 grid((unsigned)(a.tiles_per_xcd * kTileXcds)), block(S::kThreads);
     // (a workgroup that quantizes is not slowed by the tail's two instructions per load: one kernel for both)
     if (Q::kQuantizes || a.K % kStageK) {
