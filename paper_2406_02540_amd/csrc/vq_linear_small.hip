@@ -4,17 +4,18 @@
 namespace vq {
 
 // The one launch costs what every workgroup's quantizer and the weights that are read again by every
-// eight tokens add up to, so the line is drawn at tiles x K.  Over 1000 problems of 1 to 256 tokens, K 256
-// to 1152 and 128 to 4608 channels, in captured graphs, one launch is faster by (mean; at the line; worst)
-//   plain     21 %; 15 %; +2 %   with tiles x K up to 128 x 1152,
-//   GELU      15 %; 12 %; -0.3 %   and
-//   Hadamard  12 %;  9 %; -5 %    up to 64 x 1152,
-//   residual  12 %; 10 %; -4 %    up to 32 x 1152 (it also reads the branch and writes the sum),
-// and beside that one launch less is 2 us less of the host's time.
+// eight tokens add up to, so the line is drawn at tiles x K.  Over 1100 problems of 1 to 256 tokens, K 256
+// to 1152 and 128 to 4608 channels, in captured graphs, one launch is faster by (mean; above half of the
+// line; worst)
+//   plain     23 %; 11 %; -2 %   with tiles x K up to 256 x 1152,
+//   GELU      18 %; 10 %; -2 %   and
+//   Hadamard  13 %;  8 %; -3 %    up to 160 x 1152,
+//   residual  16 %; 11 %; -6 %    up to 96 x 1152 (it also reads the branch and writes the sum),
+// and beside that one launch less is 2 us less of the host's time.  Beyond num_cus workgroups some wait.
 bool small_layer(int producer, int M, int N, int K, int w_bits, int num_cus) {
     if (producer == kLayerNorm || K > kSmallNch * kSmallLanes * 8) return false;
     const long tiles = (long)((M + kSmallWaves - 1) / kSmallWaves) * ((N + SmallTile::kC - 1) / SmallTile::kC);
-    const int line = producer == kPlain ? 128 : producer == kResidual ? 32 : 64;
+    const int line = producer == kPlain ? 256 : producer == kResidual ? 96 : 160;
     return tiles <= num_cus && tiles * K <= (long)line * 1152;
 }
 
