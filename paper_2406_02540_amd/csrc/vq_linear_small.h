@@ -3,15 +3,15 @@
 // layout.  ViDiT-Q Sec. 5.1 integrates the quantizer into the operation in front of it; this
 // integrates both into the GEMM.
 //
-// Two launches of such a layer are two latencies (3 us for the quantizer, 4.5 for the GEMM) around
+// Two launches of such a layer are two latencies (2.4 us for the quantizer, 3.9 for the GEMM) around
 // less than a microsecond of work each.  In one launch every workgroup of the same tokens quantizes
 // them again while its first seven stages of weights are on their way: eight tokens, one per
 // wavefront, so that this takes a wavefront 300 to 450 vector instructions (with 32 tokens per
-// workgroup, 16 lanes each, it took longer than the launch that it saves: 32 x 1152 -> 1152 9.6 us
-// against 7.5 in two launches and 6.5 as it is).  The matrix cores work on blocks a quarter full.
-// One launch against two in a captured graph, us: 1 x 1152 -> 1152 5.5 / 7.4 (4-bit weights 6.1 / 7.9),
-// 8 x 1152 -> 4608 5.9 / 7.4, 32 x 1152 -> 1152 6.5 / 7.5, 60 x 384 -> 320 4.5 / 5.6, GELU 5.8 / 7.1 and
-// Hadamard 6.3 / 7.4 at one token.
+// workgroup, 16 lanes each, it took longer than the launch that it saves: 32 x 1152 -> 1152 9.6 us when
+// two launches were 7.5).  The matrix cores work on blocks a quarter full.
+// One launch against two in a captured graph, us: 1 x 1152 -> 1152 5.1 / 6.3 (4-bit weights 5.8 / 6.9),
+// 8 x 1152 -> 4608 6.3 / 6.7, 32 x 1152 -> 1152 5.5 / 6.7, 64 x 512 -> 320 4.3 / 5.2; at one token GELU
+// 5.6 / 6.9, Hadamard 5.9 / 7.2, residual 5.9 / 7.4.
 //
 // LayerNorm is not among them: its sums keep the order of the stand-alone kernel's lanes (32 for 1152
 // channels), and sixteen tokens of two passes each per workgroup were 5 to 15 % slower than two launches.
