@@ -12,6 +12,8 @@
 // messages and exception types are part of the package's interface.
 #include <Python.h>
 
+#include <type_traits>
+
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -160,27 +162,36 @@ void* stream_of(PyObject* stream) {
     return s;
 }
 
-// Enqueues without the interpreter lock (other threads go on, as under ctypes) and turns a
-// status into VqError.
-template <class Call>
-void enqueue(const char* where, Call call) {
-    int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = call();
-    Py_END_ALLOW_THREADS
-    if (status != VQ_OK) {
-        PyObject* e = PyObject_CallFunction(g_vq_error, "is", status, where);
-        if (e) {
-            PyErr_SetObject(g_vq_error, e);
-            Py_DECREF(e);
-        }
-        throw Raised{};
+[[noreturn]] void raise_status(int status, const char* where) {
+    PyObject* e = PyObject_CallFunction(g_vq_error, "is", status, where);
+    if (e) {
+        PyErr_SetObject(g_vq_error, e);
+        Py_DECREF(e);
     }
+    throw Raised{};
 }
 
-[[noreturn]] void raise_status(int status, const char* where) {
-    enqueue(where, [&] { return status; });
-    throw Raised{};
+// The interpreter lock is given up while this lives, and taken back however its scope is left.
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+// Enqueues without the interpreter lock (other threads go on, as under ctypes) and turns a
+// status into VqError.  The arguments are plain values, all taken before the lock is given up: a
+// tensor without storage (under a functorch transform, say) throws where its address is asked for.
+template <class... P, class... A>
+void enqueue(const char* where, int (*entry)(P...), A... args) {
+    static_assert(sizeof...(P) == sizeof...(A));
+    static_assert((std::is_scalar_v<A> && ...), "addresses and numbers");
+    int status;
+    {
+        Unlocked unlocked;
+        status = entry(static_cast<P>(args)...);
+    }
+    if (status != VQ_OK) raise_status(status, where);
 }
 
 double number(PyObject* o) {
@@ -264,8 +275,7 @@ PyObject* quantize_per_token(PyObject* const* a) {  // x chan_mul xq x_scale str
     const Rows r = matrix(x);
     Codes c(x, r, a[1], a[2], a[3]);
     void* st = stream_of(a[4]);
-    enqueue("vq_quantize_per_token",
-            [&] { return g_lib.quantize_per_token(ptr(x), c.cm(), c.q(), c.s(), (int)r.n, (int)r.k, st); });
+    enqueue("vq_quantize_per_token", g_lib.quantize_per_token, ptr(x), c.cm(), c.q(), c.s(), (int)r.n, (int)r.k, st);
     return tuple_of(c.xq.release(), c.x_scale.release());
 }
 
@@ -275,8 +285,7 @@ PyObject* gelu_quantize(PyObject* const* a) {  // h approximate chan_mul xq x_sc
     Codes c(x, r, a[2], a[3], a[4]);
     const int approximate = truth(a[1]);
     void* st = stream_of(a[5]);
-    enqueue("vq_gelu_quantize",
-            [&] { return g_lib.gelu_quantize(ptr(x), approximate, c.cm(), c.q(), c.s(), (int)r.n, (int)r.k, st); });
+    enqueue("vq_gelu_quantize", g_lib.gelu_quantize, ptr(x), approximate, c.cm(), c.q(), c.s(), (int)r.n, (int)r.k, st);
     return tuple_of(c.xq.release(), c.x_scale.release());
 }
 
@@ -289,10 +298,8 @@ PyObject* layernorm_quantize(PyObject* const* a) {  // x mod_scale mod_shift T e
     Codes c(x, r, a[5], a[6], a[7]);
     const float eps = (float)number(a[4]);
     void* st = stream_of(a[8]);
-    enqueue("vq_layernorm_quantize", [&] {
-        return g_lib.layernorm_quantize(ptr(x), as<float>(scale), as<float>(shift), T, eps, c.cm(), c.q(), c.s(), (int)r.n,
-                                        (int)r.k, st);
-    });
+    enqueue("vq_layernorm_quantize", g_lib.layernorm_quantize, ptr(x), as<float>(scale), as<float>(shift), T, eps, c.cm(),
+            c.q(), c.s(), (int)r.n, (int)r.k, st);
     return tuple_of(c.xq.release(), c.x_scale.release());
 }
 
@@ -306,10 +313,8 @@ PyObject* residual_quantize(PyObject* const* a) {  // x y gate T r chan_mul xq x
     Output res(a[4], {r.n, r.k}, at::kHalf, "r", "r must have the shape of x", x);
     Codes c(x, r, a[5], a[6], a[7]);
     void* st = stream_of(a[8]);
-    enqueue("vq_residual_quantize", [&] {
-        return g_lib.residual_quantize(ptr(x), ptr(y), as<float>(gate), T, ptr(res.t), c.cm(), c.q(), c.s(), (int)r.n,
-                                       (int)r.k, st);
-    });
+    enqueue("vq_residual_quantize", g_lib.residual_quantize, ptr(x), ptr(y), as<float>(gate), T, ptr(res.t), c.cm(), c.q(),
+            c.s(), (int)r.n, (int)r.k, st);
     return tuple_of(res.release(), c.xq.release(), c.x_scale.release());
 }
 
@@ -318,8 +323,7 @@ PyObject* hadamard_quantize(PyObject* const* a) {  // x chan_mul xq x_scale stre
     const Rows r = matrix(x);
     Codes c(x, r, a[1], a[2], a[3]);
     void* st = stream_of(a[4]);
-    enqueue("vq_hadamard_quantize",
-            [&] { return g_lib.hadamard_quantize(ptr(x), c.cm(), c.q(), c.s(), (int)r.n, (int)r.k, st); });
+    enqueue("vq_hadamard_quantize", g_lib.hadamard_quantize, ptr(x), c.cm(), c.q(), c.s(), (int)r.n, (int)r.k, st);
     return tuple_of(c.xq.release(), c.x_scale.release());
 }
 
@@ -330,9 +334,8 @@ PyObject* quantize_static(PyObject* const* a) {  // x scale chan_mul xq stream
     Output xq(a[3], {r.n, r.k}, at::kChar, "xq", "xq must have shape [M,K]", x);
     const float scale = (float)number(a[1]);
     void* st = stream_of(a[4]);
-    enqueue("vq_quantize_static", [&] {
-        return g_lib.quantize_static(ptr(x), as<float>(cm), scale, as<int8_t>(xq.t), (int)r.n, (int)r.k, st);
-    });
+    enqueue("vq_quantize_static", g_lib.quantize_static, ptr(x), as<float>(cm), scale, as<int8_t>(xq.t), (int)r.n,
+            (int)r.k, st);
     return xq.release();
 }
 
@@ -347,9 +350,8 @@ PyObject* channel_absmax(PyObject* const* a) {  // a amax accumulate stream
     if (a[1] == Py_None && accumulate) fail(PyExc_ValueError, "accumulate needs the running amax");
     Output amax(a[1], {r.k}, at::kFloat, "amax", "amax must have shape [K]", m);
     void* st = stream_of(a[3]);
-    enqueue("vq_channel_absmax", [&] {
-        return g_lib.channel_absmax(ptr(m), dtype == at::kFloat, as<float>(amax.t), (int)r.n, (int)r.k, accumulate, st);
-    });
+    enqueue("vq_channel_absmax", g_lib.channel_absmax, ptr(m), (int)(dtype == at::kFloat), as<float>(amax.t), (int)r.n,
+            (int)r.k, accumulate, st);
     return amax.release();
 }
 
@@ -361,9 +363,8 @@ PyObject* balance_mask(PyObject* const* a) {  // amax_x amax_w alpha stream
     Output s(Py_None, {K}, at::kFloat, "s", "", ax), cm(Py_None, {K}, at::kFloat, "chan_mul", "", ax);
     const float alpha = (float)number(a[2]);
     void* st = stream_of(a[3]);
-    enqueue("vq_balance_mask", [&] {
-        return g_lib.balance_mask(as<float>(ax), as<float>(aw), alpha, as<float>(s.t), as<float>(cm.t), (int)K, st);
-    });
+    enqueue("vq_balance_mask", g_lib.balance_mask, as<float>(ax), as<float>(aw), alpha, as<float>(s.t), as<float>(cm.t),
+            (int)K, st);
     return tuple_of(s.release(), cm.release());
 }
 
@@ -373,8 +374,7 @@ PyObject* rotate_weight(PyObject* const* a) {  // w chan_s out stream
     const at::Tensor* s = channel_vector(a[1], r.k, "chan_s");
     Output out(a[2], {r.n, r.k}, at::kFloat, "out", "out must have the shape of w", w);
     void* st = stream_of(a[3]);
-    enqueue("vq_rotate_weight",
-            [&] { return g_lib.rotate_weight(as<float>(w), as<float>(s), as<float>(out.t), (int)r.n, (int)r.k, st); });
+    enqueue("vq_rotate_weight", g_lib.rotate_weight, as<float>(w), as<float>(s), as<float>(out.t), (int)r.n, (int)r.k, st);
     return out.release();
 }
 
@@ -387,9 +387,8 @@ PyObject* quantize_weight(PyObject* const* a) {  // w chan_s w_bits stream
                           : Output(Py_None, {r.n, r.k / 2}, at::kByte, "wq", "", w);
     Output ws(Py_None, {r.n}, at::kFloat, "w_scale", "", w);
     void* st = stream_of(a[3]);
-    enqueue("vq_quantize_weight", [&] {
-        return g_lib.quantize_weight(as<float>(w), as<float>(s), bits, ptr(wq.t), as<float>(ws.t), (int)r.n, (int)r.k, st);
-    });
+    enqueue("vq_quantize_weight", g_lib.quantize_weight, as<float>(w), as<float>(s), bits, ptr(wq.t), as<float>(ws.t),
+            (int)r.n, (int)r.k, st);
     return tuple_of(wq.release(), ws.release());
 }
 
@@ -403,8 +402,7 @@ PyObject* gemm_f16(PyObject* const* a) {  // x w bias y stream
     if (bias && !is_vector(*bias, N)) fail(PyExc_ValueError, "bias must have shape [N]");
     Output y(a[3], {r.n, N}, at::kHalf, "y", "y must have shape [M,N]", x);
     void* st = stream_of(a[4]);
-    enqueue("vq_gemm_f16",
-            [&] { return g_lib.gemm_f16(ptr(x), ptr(w), ptr(bias), ptr(y.t), (int)r.n, (int)N, (int)r.k, st); });
+    enqueue("vq_gemm_f16", g_lib.gemm_f16, ptr(x), ptr(w), ptr(bias), ptr(y.t), (int)r.n, (int)N, (int)r.k, st);
     return y.release();
 }
 
@@ -427,15 +425,11 @@ PyObject* gemm(PyObject* const* a, int bits) {  // xq x_scale w w_scale bias y r
     int32_t* acc_ptr = want_acc ? as<int32_t>(acc.t) : nullptr;
     void* st = stream_of(a[7]);
     if (bits == 8)
-        enqueue("vq_gemm_w8a8", [&] {
-            return g_lib.gemm_w8a8(as<int8_t>(xq), as<float>(x_scale), as<int8_t>(w), as<float>(w_scale), ptr(bias), ptr(y.t),
-                                   acc_ptr, (int)r.n, (int)N, (int)r.k, st);
-        });
+        enqueue("vq_gemm_w8a8", g_lib.gemm_w8a8, as<int8_t>(xq), as<float>(x_scale), as<int8_t>(w), as<float>(w_scale),
+                ptr(bias), ptr(y.t), acc_ptr, (int)r.n, (int)N, (int)r.k, st);
     else
-        enqueue("vq_gemm_w4a8", [&] {
-            return g_lib.gemm_w4a8(as<int8_t>(xq), as<float>(x_scale), as<uint8_t>(w), as<float>(w_scale), ptr(bias),
-                                   ptr(y.t), acc_ptr, (int)r.n, (int)N, (int)r.k, st);
-        });
+        enqueue("vq_gemm_w4a8", g_lib.gemm_w4a8, as<int8_t>(xq), as<float>(x_scale), as<uint8_t>(w), as<float>(w_scale),
+                ptr(bias), ptr(y.t), acc_ptr, (int)r.n, (int)N, (int)r.k, st);
     return want_acc ? tuple_of(y.release(), acc.release()) : y.release();
 }
 PyObject* gemm_w8a8(PyObject* const* a) { return gemm(a, 8); }
@@ -485,19 +479,16 @@ PyObject* linear(PyObject* const* a) {  // x chan_mul w w_bits w_scale bias y wo
     Layer l(a[0], a[1], a[2], a[3], a[4], a[5], a[6], "vq_linear");
     l.take_workspace(a[7]);
     void* st = stream_of(a[8]);
-    enqueue("vq_linear", [&] {
-        return g_lib.linear(ptr(l.x), l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t), ptr(l.workspace),
-                            l.workspace_bytes(), l.M, l.N, l.K, st);
-    });
+    enqueue("vq_linear", g_lib.linear, ptr(l.x), l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t),
+            ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
     return l.y.release();
 }
 
 PyObject* linear_static(PyObject* const* a) {  // x chan_mul w w_bits w_scale bias y stream
     Layer l(a[0], a[1], a[2], a[3], a[4], a[5], a[6], "vq_linear_static");
     void* st = stream_of(a[7]);
-    enqueue("vq_linear_static", [&] {
-        return g_lib.linear_static(ptr(l.x), l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t), l.M, l.N, l.K, st);
-    });
+    enqueue("vq_linear_static", g_lib.linear_static, ptr(l.x), l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t),
+            l.M, l.N, l.K, st);
     return l.y.release();
 }
 
@@ -509,10 +500,8 @@ PyObject* layernorm_linear(PyObject* const* a) {  // x w w_bits w_scale mod_scal
     l.take_workspace(a[11]);
     const float eps = (float)number(a[7]);
     void* st = stream_of(a[12]);
-    enqueue("vq_layernorm_linear", [&] {
-        return g_lib.layernorm_linear(ptr(l.x), as<float>(scale), as<float>(shift), T, eps, l.cm(), ptr(l.w), l.bits, l.ws(),
-                                      ptr(l.bias), ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
-    });
+    enqueue("vq_layernorm_linear", g_lib.layernorm_linear, ptr(l.x), as<float>(scale), as<float>(shift), T, eps, l.cm(),
+            ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
     return l.y.release();
 }
 
@@ -521,10 +510,8 @@ PyObject* gelu_linear(PyObject* const* a) {  // h w w_bits w_scale approximate c
     l.take_workspace(a[8]);
     const int approximate = truth(a[4]);
     void* st = stream_of(a[9]);
-    enqueue("vq_gelu_linear", [&] {
-        return g_lib.gelu_linear(ptr(l.x), approximate, l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t),
-                                 ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
-    });
+    enqueue("vq_gelu_linear", g_lib.gelu_linear, ptr(l.x), approximate, l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias),
+            ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
     return l.y.release();
 }
 
@@ -537,10 +524,8 @@ PyObject* residual_linear(PyObject* const* a) {  // x y_in w w_bits w_scale gate
     Output r(a[7], {l.M, l.K}, at::kHalf, "r", "r must have the shape of x", *l.x);
     l.take_workspace(a[11]);
     void* st = stream_of(a[12]);
-    enqueue("vq_residual_linear", [&] {
-        return g_lib.residual_linear(ptr(l.x), ptr(y_in), as<float>(gate), T, ptr(r.t), l.cm(), ptr(l.w), l.bits, l.ws(),
-                                     ptr(l.bias), ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
-    });
+    enqueue("vq_residual_linear", g_lib.residual_linear, ptr(l.x), ptr(y_in), as<float>(gate), T, ptr(r.t), l.cm(),
+            ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
     return tuple_of(r.release(), l.y.release());
 }
 
@@ -548,10 +533,8 @@ PyObject* hadamard_linear(PyObject* const* a) {  // x chan_mul w w_bits w_scale 
     Layer l(a[0], a[1], a[2], a[3], a[4], a[5], a[6], "vq_hadamard_linear");
     l.take_workspace(a[7]);
     void* st = stream_of(a[8]);
-    enqueue("vq_hadamard_linear", [&] {
-        return g_lib.hadamard_linear(ptr(l.x), l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t), ptr(l.workspace),
-                                     l.workspace_bytes(), l.M, l.N, l.K, st);
-    });
+    enqueue("vq_hadamard_linear", g_lib.hadamard_linear, ptr(l.x), l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias),
+            ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
     return l.y.release();
 }
 
@@ -591,6 +574,8 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
     } catch (const Raised&) {
     } catch (const std::exception&) {  // torch's own (out of memory, ...)
         torch::translate_exception_to_python(std::current_exception());
+    } catch (...) {
+        PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
     }
     return nullptr;
 }
