@@ -12,6 +12,7 @@
 // messages and exception types are part of the package's interface.
 #include <Python.h>
 
+#include <climits>
 #include <type_traits>
 
 #include <ATen/ATen.h>
@@ -215,20 +216,24 @@ bool truth(PyObject* o) {
     return t != 0;
 }
 
-// Tokens that share a row of the per-sample arrays: all of them if not given.
-int tokens_per_sample(PyObject* o, int64_t M) {
+// Tokens that share a row of the per-sample arrays: all of them if not given.  What does not fit the
+// library's int is VQ_ERR_SHAPE here: narrowed, it would be another length, or 0.
+int tokens_per_sample(PyObject* o, int64_t M, const char* where) {
     if (!truth(o)) return (int)std::max<int64_t>(M, 1);
     PyObject* l = PyNumber_Long(o);
     if (!l) throw Raised{};
-    const long v = PyLong_AsLong(l);
+    int overflow = 0;
+    const long v = PyLong_AsLongAndOverflow(l, &overflow);
     Py_DECREF(l);
     if (v == -1 && PyErr_Occurred()) throw Raised{};
+    if (overflow || v < INT_MIN || v > INT_MAX) raise_status(VQ_ERR_SHAPE, where);
     return (int)v;
 }
 
 const at::Tensor* per_sample(PyObject* o, int64_t M, int64_t K, int T, const char* name) {
     const at::Tensor* t = device_tensor(o, at::kFloat, name);
-    if (!t) return nullptr;
+    if (!t) return nullptr;   // (a length that is not positive is left to the library's check)
+    if (T == 0) fail(PyExc_ZeroDivisionError, "integer division or modulo by zero");   // (0.5, say)
     const int64_t up = M + T - 1, q = up / T, rows = q - (up % T != 0 && (up < 0) != (T < 0));  // floor
     if (!is_matrix(*t, rows, K)) {
         PyErr_Format(PyExc_ValueError, "%s must have shape [ceil(M / tokens_per_sample), K]", name);
@@ -292,7 +297,7 @@ PyObject* gelu_quantize(PyObject* const* a) {  // h approximate chan_mul xq x_sc
 PyObject* layernorm_quantize(PyObject* const* a) {  // x mod_scale mod_shift T eps chan_mul xq x_scale stream
     const at::Tensor& x = required(a[0], at::kHalf, "x");
     const Rows r = matrix(x);
-    const int T = tokens_per_sample(a[3], r.n);
+    const int T = tokens_per_sample(a[3], r.n, "vq_layernorm_quantize");
     const at::Tensor* scale = per_sample(a[1], r.n, r.k, T, "mod_scale");
     const at::Tensor* shift = per_sample(a[2], r.n, r.k, T, "mod_shift");
     Codes c(x, r, a[5], a[6], a[7]);
@@ -308,7 +313,7 @@ PyObject* residual_quantize(PyObject* const* a) {  // x y gate T r chan_mul xq x
     const at::Tensor* y = device_tensor(a[1], at::kHalf, "y");
     if (!y || y->sizes() != x.sizes()) fail(PyExc_ValueError, "y must have the shape of x");
     const Rows r = matrix(x);
-    const int T = tokens_per_sample(a[3], r.n);
+    const int T = tokens_per_sample(a[3], r.n, "vq_residual_quantize");
     const at::Tensor* gate = per_sample(a[2], r.n, r.k, T, "gate");
     Output res(a[4], {r.n, r.k}, at::kHalf, "r", "r must have the shape of x", x);
     Codes c(x, r, a[5], a[6], a[7]);
@@ -494,7 +499,7 @@ PyObject* linear_static(PyObject* const* a) {  // x chan_mul w w_bits w_scale bi
 
 PyObject* layernorm_linear(PyObject* const* a) {  // x w w_bits w_scale mod_scale mod_shift T eps chan_mul bias y workspace stream
     Layer l(a[0], a[8], a[1], a[2], a[3], a[9], a[10], "vq_layernorm_linear");
-    const int T = tokens_per_sample(a[6], l.M);
+    const int T = tokens_per_sample(a[6], l.M, "vq_layernorm_linear");
     const at::Tensor* scale = per_sample(a[4], l.M, l.K, T, "mod_scale");
     const at::Tensor* shift = per_sample(a[5], l.M, l.K, T, "mod_shift");
     l.take_workspace(a[11]);
@@ -519,7 +524,7 @@ PyObject* residual_linear(PyObject* const* a) {  // x y_in w w_bits w_scale gate
     Layer l(a[0], a[8], a[2], a[3], a[4], a[9], a[10], "vq_residual_linear");
     const at::Tensor* y_in = device_tensor(a[1], at::kHalf, "y_in");
     if (!y_in || !is_matrix(*y_in, l.M, l.K)) fail(PyExc_ValueError, "y_in must have the shape of x");
-    const int T = tokens_per_sample(a[6], l.M);
+    const int T = tokens_per_sample(a[6], l.M, "vq_residual_linear");
     const at::Tensor* gate = per_sample(a[5], l.M, l.K, T, "gate");
     Output r(a[7], {l.M, l.K}, at::kHalf, "r", "r must have the shape of x", *l.x);
     l.take_workspace(a[11]);

@@ -88,3 +88,28 @@ def test_tensors_without_an_address_raise():
     """)
     assert len(got) == 19 + 17
     assert all(v.startswith("RuntimeError: ") for v in got.values()), got
+
+
+def test_sample_lengths_that_round_to_zero_or_exceed_an_int():
+    # 2**32 + 4 narrowed to an int is the length that the vectors have; -1 fits, and no vector has that many rows
+    got = child("""
+        with FakeTensorMode():
+            st = Stream()
+            x, r, v, w, ws = fake(M, K), fake(M, K), fake(1, K, dtype=f32), fake(N, K, dtype=i8), fake(N, dtype=f32)
+            q, s, y, wk = fake(M, K, dtype=i8), fake(M, dtype=f32), fake(M, N), fake(4096, dtype=u8)
+            for T in (0.5, -1, 2**31, 2**32, 2**32 + 4, 2**70, -2**40):
+                for name, call in {
+                    "layernorm_quantize": lambda: vq.vq_layernorm_quantize(x, v, None, T, 1e-6, None, q, s, stream=st),
+                    "residual_quantize": lambda: vq.vq_residual_quantize(x, r, v, T, r, None, q, s, stream=st),
+                    "layernorm_linear": lambda: vq.vq_layernorm_linear(x, w, 8, ws, None, v, T, y=y, workspace=wk, stream=st),
+                    "residual_linear": lambda: vq.vq_residual_linear(x, r, w, 8, ws, v, T, r, y=y, workspace=wk, stream=st),
+                }.items():
+                    print(f"{name} {T}", outcome(call), sep="=", flush=True)
+            print("fits", outcome(lambda: vq.vq_layernorm_quantize(x, v, None, 2**31 - 1, 1e-6, None, q, s, stream=st)), sep="=")
+    """)
+    assert len(got) == 4 * 7 + 1
+    assert "VQ_ERR_NULL" in got.pop("fits")   # (a fake tensor's address is null: the length was accepted)
+    for k, v in got.items():
+        T = k.split()[1]
+        want = {"0.5": "ZeroDivisionError: ", "-1": "ValueError: "}.get(T, f"VqError: vq_{k.split()[0]}: VQ_ERR_SHAPE")
+        assert v.startswith(want), (k, v)
