@@ -195,9 +195,12 @@ void enqueue(const char* where, int (*entry)(P...), A... args) {
     if (status != VQ_OK) raise_status(status, where);
 }
 
+// What float() takes, texts included.
 double number(PyObject* o) {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Raised{};
+    PyObject* f = PyNumber_Float(o);
+    if (!f) throw Raised{};
+    const double v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
     return v;
 }
 

@@ -113,3 +113,18 @@ def test_sample_lengths_that_round_to_zero_or_exceed_an_int():
         T = k.split()[1]
         want = {"0.5": "ZeroDivisionError: ", "-1": "ValueError: "}.get(T, f"VqError: vq_{k.split()[0]}: VQ_ERR_SHAPE")
         assert v.startswith(want), (k, v)
+
+
+def test_numbers_as_float_takes_them():
+    got = child("""
+        with FakeTensorMode():
+            st = Stream()
+            x, q, s = fake(M, K), fake(M, K, dtype=i8), fake(M, dtype=f32)
+            for text in ("0.5", "half"):
+                print("eps " + text, outcome(lambda: vq.vq_layernorm_quantize(x, eps=text, xq=q, x_scale=s, stream=st)), sep="=")
+                print("scale " + text, outcome(lambda: vq.vq_quantize_static(x, text, None, q, stream=st)), sep="=")
+            print("eps None", outcome(lambda: vq.vq_layernorm_quantize(x, eps=None, xq=q, x_scale=s, stream=st)), sep="=")
+    """)
+    assert all("VQ_ERR_NULL" in got[k] for k in ("eps 0.5", "scale 0.5")), got   # (accepted: null is the fake address)
+    assert all(got[k].startswith("ValueError: ") for k in ("eps half", "scale half")), got
+    assert got["eps None"].startswith("TypeError: ")
