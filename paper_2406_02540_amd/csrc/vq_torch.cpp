@@ -16,8 +16,11 @@
 #include <type_traits>
 
 #include <ATen/ATen.h>
+#include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
+#include <c10/core/StreamGuard.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/Stream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "vq.h"
@@ -125,9 +128,50 @@ void* ptr(const at::Tensor* t) { return t ? t->data_ptr() : nullptr; }
 template <class T, class A>
 T* as(const A& a) { return static_cast<T*>(ptr(a)); }
 
-at::Tensor empty(at::IntArrayRef shape, at::ScalarType dtype, const at::Tensor& like) {
-    return at::empty(shape, like.options().dtype(dtype).requires_grad(false));
-}
+// The stream that a call enqueues on: the argument, or the current one.  Memory that the call allocates
+// comes from that stream's: the caching allocator hands memory of the current stream out again without
+// waiting for work on another, so scratch taken there would be given to the next allocation while this
+// call's kernels still use it, and what it held before would be overwritten ahead of its readers.
+class CallStream {
+    PyObject* given_;
+
+    void* given_handle() const {
+        PyObject* raw = PyObject_GetAttrString(given_, "cuda_stream");
+        if (!raw) throw Raised{};
+        void* s = PyLong_AsVoidPtr(raw);
+        Py_DECREF(raw);
+        if (!s && PyErr_Occurred()) throw Raised{};
+        return s;
+    }
+    c10::Stream given_stream(void* handle, c10::DeviceIndex device) const {
+        if (THPStream_Check(given_)) {
+            const THPStream* s = (const THPStream*)given_;
+            return c10::Stream::unpack3(s->stream_id, (c10::DeviceIndex)s->device_index, (c10::DeviceType)s->device_type);
+        }
+        return c10::hip::getStreamFromExternalMasqueradingAsCUDA((hipStream_t)handle, device).unwrap();
+    }
+
+  public:
+    explicit CallStream(PyObject* given) : given_(given) {}
+    void* handle() const { return given_ == Py_None ? c10::hip::getCurrentHIPStream().stream() : given_handle(); }
+
+    // `for_caller`: the current stream reads it next (behind whatever orders the two streams), and may
+    // still do so when the caller lets go of it.
+    at::Tensor empty(at::IntArrayRef shape, at::ScalarType dtype, const at::Tensor& like, bool for_caller) const {
+        const auto options = like.options().dtype(dtype).requires_grad(false);
+        if (given_ == Py_None) return at::empty(shape, options);
+        void* const handle = given_handle();
+        const auto current = c10::hip::getCurrentHIPStreamMasqueradingAsCUDA(like.device().index());
+        if (current.stream() == handle) return at::empty(shape, options);
+        at::Tensor t;
+        {
+            const c10::StreamGuard guard(given_stream(handle, like.device().index()));
+            t = at::empty(shape, options);
+        }
+        if (for_caller) t.record_stream(current.unwrap());
+        return t;
+    }
+};
 
 // An output: the caller's tensor (checked), or a new one.
 struct Output {
@@ -135,9 +179,9 @@ struct Output {
     at::Tensor t;
     Output() = default;
     Output(PyObject* o, at::IntArrayRef shape, at::ScalarType dtype, const char* name, const char* shape_error,
-           const at::Tensor& like) {
+           const at::Tensor& like, const CallStream& stream) {
         if (o == Py_None) {
-            t = empty(shape, dtype, like);
+            t = stream.empty(shape, dtype, like, true);
         } else {
             given = o;
             t = *device_tensor(o, dtype, name);
@@ -152,16 +196,6 @@ struct Output {
         return THPVariable_Wrap(std::move(t));
     }
 };
-
-void* stream_of(PyObject* stream) {
-    if (stream == Py_None) return c10::hip::getCurrentHIPStream().stream();
-    PyObject* raw = PyObject_GetAttrString(stream, "cuda_stream");
-    if (!raw) throw Raised{};
-    void* s = PyLong_AsVoidPtr(raw);
-    Py_DECREF(raw);
-    if (!s && PyErr_Occurred()) throw Raised{};
-    return s;
-}
 
 [[noreturn]] void raise_status(int status, const char* where) {
     PyObject* e = PyObject_CallFunction(g_vq_error, "is", status, where);
@@ -266,10 +300,10 @@ PyObject* tuple_of(PyObject* a, PyObject* b, PyObject* c = nullptr) {
 struct Codes {
     const at::Tensor* chan_mul;
     Output xq, x_scale;
-    Codes(const at::Tensor& x, Rows r, PyObject* cm, PyObject* xq_o, PyObject* xs_o) {
+    Codes(const at::Tensor& x, Rows r, PyObject* cm, PyObject* xq_o, PyObject* xs_o, const CallStream& st) {
         chan_mul = channel_vector(cm, r.k, "chan_mul");
-        xq = Output(xq_o, {r.n, r.k}, at::kChar, "xq", "output shapes", x);
-        x_scale = Output(xs_o, {r.n}, at::kFloat, "x_scale", "output shapes", x);
+        xq = Output(xq_o, {r.n, r.k}, at::kChar, "xq", "output shapes", x, st);
+        x_scale = Output(xs_o, {r.n}, at::kFloat, "x_scale", "output shapes", x, st);
     }
     const float* cm() const { return as<float>(chan_mul); }
     int8_t* q() const { return as<int8_t>(xq.t); }
@@ -279,75 +313,78 @@ struct Codes {
 // ---- entry points: positional arguments only, as binding.py passes them -----------------------
 
 PyObject* quantize_per_token(PyObject* const* a) {  // x chan_mul xq x_scale stream
+    const CallStream st(a[4]);
     const at::Tensor& x = required(a[0], at::kHalf, "x");
     const Rows r = matrix(x);
-    Codes c(x, r, a[1], a[2], a[3]);
-    void* st = stream_of(a[4]);
-    enqueue("vq_quantize_per_token", g_lib.quantize_per_token, ptr(x), c.cm(), c.q(), c.s(), (int)r.n, (int)r.k, st);
+    Codes c(x, r, a[1], a[2], a[3], st);
+    enqueue("vq_quantize_per_token", g_lib.quantize_per_token, ptr(x), c.cm(), c.q(), c.s(), (int)r.n, (int)r.k,
+            st.handle());
     return tuple_of(c.xq.release(), c.x_scale.release());
 }
 
 PyObject* gelu_quantize(PyObject* const* a) {  // h approximate chan_mul xq x_scale stream
+    const CallStream st(a[5]);
     const at::Tensor& x = required(a[0], at::kHalf, "h");
     const Rows r = matrix(x);
-    Codes c(x, r, a[2], a[3], a[4]);
+    Codes c(x, r, a[2], a[3], a[4], st);
     const int approximate = truth(a[1]);
-    void* st = stream_of(a[5]);
-    enqueue("vq_gelu_quantize", g_lib.gelu_quantize, ptr(x), approximate, c.cm(), c.q(), c.s(), (int)r.n, (int)r.k, st);
+    enqueue("vq_gelu_quantize", g_lib.gelu_quantize, ptr(x), approximate, c.cm(), c.q(), c.s(), (int)r.n, (int)r.k,
+            st.handle());
     return tuple_of(c.xq.release(), c.x_scale.release());
 }
 
 PyObject* layernorm_quantize(PyObject* const* a) {  // x mod_scale mod_shift T eps chan_mul xq x_scale stream
+    const CallStream st(a[8]);
     const at::Tensor& x = required(a[0], at::kHalf, "x");
     const Rows r = matrix(x);
     const int T = tokens_per_sample(a[3], r.n, "vq_layernorm_quantize");
     const at::Tensor* scale = per_sample(a[1], r.n, r.k, T, "mod_scale");
     const at::Tensor* shift = per_sample(a[2], r.n, r.k, T, "mod_shift");
-    Codes c(x, r, a[5], a[6], a[7]);
+    Codes c(x, r, a[5], a[6], a[7], st);
     const float eps = (float)number(a[4]);
-    void* st = stream_of(a[8]);
     enqueue("vq_layernorm_quantize", g_lib.layernorm_quantize, ptr(x), as<float>(scale), as<float>(shift), T, eps, c.cm(),
-            c.q(), c.s(), (int)r.n, (int)r.k, st);
+            c.q(), c.s(), (int)r.n, (int)r.k, st.handle());
     return tuple_of(c.xq.release(), c.x_scale.release());
 }
 
 PyObject* residual_quantize(PyObject* const* a) {  // x y gate T r chan_mul xq x_scale stream
+    const CallStream st(a[8]);
     const at::Tensor& x = required(a[0], at::kHalf, "x");
     const at::Tensor* y = device_tensor(a[1], at::kHalf, "y");
     if (!y || y->sizes() != x.sizes()) fail(PyExc_ValueError, "y must have the shape of x");
     const Rows r = matrix(x);
     const int T = tokens_per_sample(a[3], r.n, "vq_residual_quantize");
     const at::Tensor* gate = per_sample(a[2], r.n, r.k, T, "gate");
-    Output res(a[4], {r.n, r.k}, at::kHalf, "r", "r must have the shape of x", x);
-    Codes c(x, r, a[5], a[6], a[7]);
-    void* st = stream_of(a[8]);
+    Output res(a[4], {r.n, r.k}, at::kHalf, "r", "r must have the shape of x", x, st);
+    Codes c(x, r, a[5], a[6], a[7], st);
     enqueue("vq_residual_quantize", g_lib.residual_quantize, ptr(x), ptr(y), as<float>(gate), T, ptr(res.t), c.cm(), c.q(),
-            c.s(), (int)r.n, (int)r.k, st);
+            c.s(), (int)r.n, (int)r.k, st.handle());
     return tuple_of(res.release(), c.xq.release(), c.x_scale.release());
 }
 
 PyObject* hadamard_quantize(PyObject* const* a) {  // x chan_mul xq x_scale stream
+    const CallStream st(a[4]);
     const at::Tensor& x = required(a[0], at::kHalf, "x");
     const Rows r = matrix(x);
-    Codes c(x, r, a[1], a[2], a[3]);
-    void* st = stream_of(a[4]);
-    enqueue("vq_hadamard_quantize", g_lib.hadamard_quantize, ptr(x), c.cm(), c.q(), c.s(), (int)r.n, (int)r.k, st);
+    Codes c(x, r, a[1], a[2], a[3], st);
+    enqueue("vq_hadamard_quantize", g_lib.hadamard_quantize, ptr(x), c.cm(), c.q(), c.s(), (int)r.n, (int)r.k, st.handle());
     return tuple_of(c.xq.release(), c.x_scale.release());
 }
 
 PyObject* quantize_static(PyObject* const* a) {  // x scale chan_mul xq stream
+    const CallStream st(a[4]);
     const at::Tensor& x = required(a[0], at::kHalf, "x");
     const Rows r = matrix(x);
     const at::Tensor* cm = channel_vector(a[2], r.k, "chan_mul");
-    Output xq(a[3], {r.n, r.k}, at::kChar, "xq", "xq must have shape [M,K]", x);
+    Output xq(a[3], {r.n, r.k}, at::kChar, "xq", "xq must have shape [M,K]", x, st);
     const float scale = (float)number(a[1]);
-    void* st = stream_of(a[4]);
     enqueue("vq_quantize_static", g_lib.quantize_static, ptr(x), as<float>(cm), scale, as<int8_t>(xq.t), (int)r.n,
-            (int)r.k, st);
+            (int)r.k, st.handle());
     return xq.release();
 }
 
 PyObject* channel_absmax(PyObject* const* a) {  // a amax accumulate stream
+    const CallStream st(a[3]);
     if (!THPVariable_Check(a[0]) || (THPVariable_Unpack(a[0]).scalar_type() != at::kHalf &&
                                      THPVariable_Unpack(a[0]).scalar_type() != at::kFloat))
         fail(PyExc_TypeError, "a: expected a float16 or float32 device tensor");
@@ -356,51 +393,52 @@ PyObject* channel_absmax(PyObject* const* a) {  // a amax accumulate stream
     const Rows r = matrix(m);
     const int accumulate = truth(a[2]);
     if (a[1] == Py_None && accumulate) fail(PyExc_ValueError, "accumulate needs the running amax");
-    Output amax(a[1], {r.k}, at::kFloat, "amax", "amax must have shape [K]", m);
-    void* st = stream_of(a[3]);
+    Output amax(a[1], {r.k}, at::kFloat, "amax", "amax must have shape [K]", m, st);
     enqueue("vq_channel_absmax", g_lib.channel_absmax, ptr(m), (int)(dtype == at::kFloat), as<float>(amax.t), (int)r.n,
-            (int)r.k, accumulate, st);
+            (int)r.k, accumulate, st.handle());
     return amax.release();
 }
 
 PyObject* balance_mask(PyObject* const* a) {  // amax_x amax_w alpha stream
+    const CallStream st(a[3]);
     const at::Tensor& ax = required(a[0], at::kFloat, "amax_x");
     const at::Tensor& aw = required(a[1], at::kFloat, "amax_w");
     const int64_t K = first_size(ax);
     if (!is_vector(ax, K) || !is_vector(aw, K)) fail(PyExc_ValueError, "statistics must have shape [K]");
-    Output s(Py_None, {K}, at::kFloat, "s", "", ax), cm(Py_None, {K}, at::kFloat, "chan_mul", "", ax);
+    Output s(Py_None, {K}, at::kFloat, "s", "", ax, st), cm(Py_None, {K}, at::kFloat, "chan_mul", "", ax, st);
     const float alpha = (float)number(a[2]);
-    void* st = stream_of(a[3]);
     enqueue("vq_balance_mask", g_lib.balance_mask, as<float>(ax), as<float>(aw), alpha, as<float>(s.t), as<float>(cm.t),
-            (int)K, st);
+            (int)K, st.handle());
     return tuple_of(s.release(), cm.release());
 }
 
 PyObject* rotate_weight(PyObject* const* a) {  // w chan_s out stream
+    const CallStream st(a[3]);
     const at::Tensor& w = required(a[0], at::kFloat, "w");
     const Rows r = matrix(w);
     const at::Tensor* s = channel_vector(a[1], r.k, "chan_s");
-    Output out(a[2], {r.n, r.k}, at::kFloat, "out", "out must have the shape of w", w);
-    void* st = stream_of(a[3]);
-    enqueue("vq_rotate_weight", g_lib.rotate_weight, as<float>(w), as<float>(s), as<float>(out.t), (int)r.n, (int)r.k, st);
+    Output out(a[2], {r.n, r.k}, at::kFloat, "out", "out must have the shape of w", w, st);
+    enqueue("vq_rotate_weight", g_lib.rotate_weight, as<float>(w), as<float>(s), as<float>(out.t), (int)r.n, (int)r.k,
+            st.handle());
     return out.release();
 }
 
 PyObject* quantize_weight(PyObject* const* a) {  // w chan_s w_bits stream
+    const CallStream st(a[3]);
     const at::Tensor& w = required(a[0], at::kFloat, "w");
     const Rows r = matrix(w);
     const at::Tensor* s = channel_vector(a[1], r.k, "chan_s");
     const int bits = weight_bits(a[2], "vq_quantize_weight");
-    Output wq = bits == 8 ? Output(Py_None, {r.n, r.k}, at::kChar, "wq", "", w)
-                          : Output(Py_None, {r.n, r.k / 2}, at::kByte, "wq", "", w);
-    Output ws(Py_None, {r.n}, at::kFloat, "w_scale", "", w);
-    void* st = stream_of(a[3]);
+    Output wq = bits == 8 ? Output(Py_None, {r.n, r.k}, at::kChar, "wq", "", w, st)
+                          : Output(Py_None, {r.n, r.k / 2}, at::kByte, "wq", "", w, st);
+    Output ws(Py_None, {r.n}, at::kFloat, "w_scale", "", w, st);
     enqueue("vq_quantize_weight", g_lib.quantize_weight, as<float>(w), as<float>(s), bits, ptr(wq.t), as<float>(ws.t),
-            (int)r.n, (int)r.k, st);
+            (int)r.n, (int)r.k, st.handle());
     return tuple_of(wq.release(), ws.release());
 }
 
 PyObject* gemm_f16(PyObject* const* a) {  // x w bias y stream
+    const CallStream st(a[4]);
     const at::Tensor& x = required(a[0], at::kHalf, "x");
     const at::Tensor& w = required(a[1], at::kHalf, "w");
     const Rows r = matrix(x);
@@ -408,13 +446,13 @@ PyObject* gemm_f16(PyObject* const* a) {  // x w bias y stream
     if (!is_matrix(w, N, r.k)) fail(PyExc_ValueError, "weight shape does not match K");
     const at::Tensor* bias = device_tensor(a[2], at::kHalf, "bias");
     if (bias && !is_vector(*bias, N)) fail(PyExc_ValueError, "bias must have shape [N]");
-    Output y(a[3], {r.n, N}, at::kHalf, "y", "y must have shape [M,N]", x);
-    void* st = stream_of(a[4]);
-    enqueue("vq_gemm_f16", g_lib.gemm_f16, ptr(x), ptr(w), ptr(bias), ptr(y.t), (int)r.n, (int)N, (int)r.k, st);
+    Output y(a[3], {r.n, N}, at::kHalf, "y", "y must have shape [M,N]", x, st);
+    enqueue("vq_gemm_f16", g_lib.gemm_f16, ptr(x), ptr(w), ptr(bias), ptr(y.t), (int)r.n, (int)N, (int)r.k, st.handle());
     return y.release();
 }
 
 PyObject* gemm(PyObject* const* a, int bits) {  // xq x_scale w w_scale bias y return_acc stream
+    const CallStream st(a[7]);
     const at::Tensor& xq = required(a[0], at::kChar, "xq");
     const Rows r = matrix(xq);
     const at::Tensor& w = required(a[2], bits == 8 ? at::kChar : at::kByte, "w");
@@ -426,18 +464,17 @@ PyObject* gemm(PyObject* const* a, int bits) {  // xq x_scale w w_scale bias y r
     if (!x_scale || !w_scale) fail(PyExc_AttributeError, "'NoneType' object has no attribute 'shape'");
     if (!is_vector(*x_scale, r.n) || !is_vector(*w_scale, N) || (bias && !is_vector(*bias, N)))
         fail(PyExc_ValueError, "scale / bias shapes");
-    Output y(a[5], {r.n, N}, at::kHalf, "y", "y shape", xq);
+    Output y(a[5], {r.n, N}, at::kHalf, "y", "y shape", xq, st);
     const bool want_acc = truth(a[6]);
     Output acc;
-    if (want_acc) acc = Output(Py_None, {r.n, N}, at::kInt, "acc", "", xq);
+    if (want_acc) acc = Output(Py_None, {r.n, N}, at::kInt, "acc", "", xq, st);
     int32_t* acc_ptr = want_acc ? as<int32_t>(acc.t) : nullptr;
-    void* st = stream_of(a[7]);
     if (bits == 8)
         enqueue("vq_gemm_w8a8", g_lib.gemm_w8a8, as<int8_t>(xq), as<float>(x_scale), as<int8_t>(w), as<float>(w_scale),
-                ptr(bias), ptr(y.t), acc_ptr, (int)r.n, (int)N, (int)r.k, st);
+                ptr(bias), ptr(y.t), acc_ptr, (int)r.n, (int)N, (int)r.k, st.handle());
     else
         enqueue("vq_gemm_w4a8", g_lib.gemm_w4a8, as<int8_t>(xq), as<float>(x_scale), as<uint8_t>(w), as<float>(w_scale),
-                ptr(bias), ptr(y.t), acc_ptr, (int)r.n, (int)N, (int)r.k, st);
+                ptr(bias), ptr(y.t), acc_ptr, (int)r.n, (int)N, (int)r.k, st.handle());
     return want_acc ? tuple_of(y.release(), acc.release()) : y.release();
 }
 PyObject* gemm_w8a8(PyObject* const* a) { return gemm(a, 8); }
@@ -454,7 +491,7 @@ struct Layer {
     int bits, M, N, K;
     at::Tensor workspace;
     Layer(PyObject* x_o, PyObject* cm_o, PyObject* w_o, PyObject* bits_o, PyObject* ws_o, PyObject* bias_o, PyObject* y_o,
-          const char* where) {
+          const CallStream& st, const char* where) {
         x = &required(x_o, at::kHalf, "x");
         const Rows r = matrix(*x);
         bits = weight_bits(bits_o, where);
@@ -467,13 +504,13 @@ struct Layer {
         bias = device_tensor(bias_o, at::kHalf, "bias");
         if ((chan_mul && !is_vector(*chan_mul, r.k)) || !is_vector(*w_scale, n) || (bias && !is_vector(*bias, n)))
             fail(PyExc_ValueError, "chan_mul / scale / bias shapes");
-        y = Output(y_o, {r.n, n}, at::kHalf, "y", "y shape", *x);
+        y = Output(y_o, {r.n, n}, at::kHalf, "y", "y shape", *x, st);
         M = (int)r.n, N = (int)n, K = (int)r.k;
     }
-    void take_workspace(PyObject* o) {
+    void take_workspace(PyObject* o, const CallStream& st) {
         if (o == Py_None) {
             const int64_t need = (int64_t)g_lib.linear_workspace_bytes(M, N, K, bits);
-            workspace = empty({std::max<int64_t>(need, 16)}, at::kByte, *x);
+            workspace = st.empty({std::max<int64_t>(need, 16)}, at::kByte, *x, false);
         } else {
             workspace = *device_tensor(o, at::kByte, "workspace");
         }
@@ -484,65 +521,65 @@ struct Layer {
 };
 
 PyObject* linear(PyObject* const* a) {  // x chan_mul w w_bits w_scale bias y workspace stream
-    Layer l(a[0], a[1], a[2], a[3], a[4], a[5], a[6], "vq_linear");
-    l.take_workspace(a[7]);
-    void* st = stream_of(a[8]);
+    const CallStream st(a[8]);
+    Layer l(a[0], a[1], a[2], a[3], a[4], a[5], a[6], st, "vq_linear");
+    l.take_workspace(a[7], st);
     enqueue("vq_linear", g_lib.linear, ptr(l.x), l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t),
-            ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
+            ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st.handle());
     return l.y.release();
 }
 
 PyObject* linear_static(PyObject* const* a) {  // x chan_mul w w_bits w_scale bias y stream
-    Layer l(a[0], a[1], a[2], a[3], a[4], a[5], a[6], "vq_linear_static");
-    void* st = stream_of(a[7]);
+    const CallStream st(a[7]);
+    Layer l(a[0], a[1], a[2], a[3], a[4], a[5], a[6], st, "vq_linear_static");
     enqueue("vq_linear_static", g_lib.linear_static, ptr(l.x), l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t),
-            l.M, l.N, l.K, st);
+            l.M, l.N, l.K, st.handle());
     return l.y.release();
 }
 
 PyObject* layernorm_linear(PyObject* const* a) {  // x w w_bits w_scale mod_scale mod_shift T eps chan_mul bias y workspace stream
-    Layer l(a[0], a[8], a[1], a[2], a[3], a[9], a[10], "vq_layernorm_linear");
+    const CallStream st(a[12]);
+    Layer l(a[0], a[8], a[1], a[2], a[3], a[9], a[10], st, "vq_layernorm_linear");
     const int T = tokens_per_sample(a[6], l.M, "vq_layernorm_linear");
     const at::Tensor* scale = per_sample(a[4], l.M, l.K, T, "mod_scale");
     const at::Tensor* shift = per_sample(a[5], l.M, l.K, T, "mod_shift");
-    l.take_workspace(a[11]);
+    l.take_workspace(a[11], st);
     const float eps = (float)number(a[7]);
-    void* st = stream_of(a[12]);
     enqueue("vq_layernorm_linear", g_lib.layernorm_linear, ptr(l.x), as<float>(scale), as<float>(shift), T, eps, l.cm(),
-            ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
+            ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st.handle());
     return l.y.release();
 }
 
 PyObject* gelu_linear(PyObject* const* a) {  // h w w_bits w_scale approximate chan_mul bias y workspace stream
-    Layer l(a[0], a[5], a[1], a[2], a[3], a[6], a[7], "vq_gelu_linear");
-    l.take_workspace(a[8]);
+    const CallStream st(a[9]);
+    Layer l(a[0], a[5], a[1], a[2], a[3], a[6], a[7], st, "vq_gelu_linear");
+    l.take_workspace(a[8], st);
     const int approximate = truth(a[4]);
-    void* st = stream_of(a[9]);
     enqueue("vq_gelu_linear", g_lib.gelu_linear, ptr(l.x), approximate, l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias),
-            ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
+            ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st.handle());
     return l.y.release();
 }
 
 PyObject* residual_linear(PyObject* const* a) {  // x y_in w w_bits w_scale gate T r chan_mul bias y workspace stream
-    Layer l(a[0], a[8], a[2], a[3], a[4], a[9], a[10], "vq_residual_linear");
+    const CallStream st(a[12]);
+    Layer l(a[0], a[8], a[2], a[3], a[4], a[9], a[10], st, "vq_residual_linear");
     const at::Tensor* y_in = device_tensor(a[1], at::kHalf, "y_in");
     if (!y_in || !is_matrix(*y_in, l.M, l.K)) fail(PyExc_ValueError, "y_in must have the shape of x");
     const int T = tokens_per_sample(a[6], l.M, "vq_residual_linear");
     const at::Tensor* gate = per_sample(a[5], l.M, l.K, T, "gate");
-    Output r(a[7], {l.M, l.K}, at::kHalf, "r", "r must have the shape of x", *l.x);
-    l.take_workspace(a[11]);
-    void* st = stream_of(a[12]);
+    Output r(a[7], {l.M, l.K}, at::kHalf, "r", "r must have the shape of x", *l.x, st);
+    l.take_workspace(a[11], st);
     enqueue("vq_residual_linear", g_lib.residual_linear, ptr(l.x), ptr(y_in), as<float>(gate), T, ptr(r.t), l.cm(),
-            ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
+            ptr(l.w), l.bits, l.ws(), ptr(l.bias), ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st.handle());
     return tuple_of(r.release(), l.y.release());
 }
 
 PyObject* hadamard_linear(PyObject* const* a) {  // x chan_mul w w_bits w_scale bias y workspace stream
-    Layer l(a[0], a[1], a[2], a[3], a[4], a[5], a[6], "vq_hadamard_linear");
-    l.take_workspace(a[7]);
-    void* st = stream_of(a[8]);
+    const CallStream st(a[8]);
+    Layer l(a[0], a[1], a[2], a[3], a[4], a[5], a[6], st, "vq_hadamard_linear");
+    l.take_workspace(a[7], st);
     enqueue("vq_hadamard_linear", g_lib.hadamard_linear, ptr(l.x), l.cm(), ptr(l.w), l.bits, l.ws(), ptr(l.bias),
-            ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st);
+            ptr(l.y.t), ptr(l.workspace), l.workspace_bytes(), l.M, l.N, l.K, st.handle());
     return l.y.release();
 }
 

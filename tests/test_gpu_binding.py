@@ -80,3 +80,53 @@ def test_stream_argument(vq):
         by_context = vq.vq_linear(x, cm, w, 8, ws, b)
     torch.cuda.synchronize()
     assert torch.equal(by_argument, want) and torch.equal(by_context, want)
+
+
+def test_memory_taken_for_a_call_on_another_stream(vq):
+    # Scratch and outputs that the call allocates belong to the stream that it runs on: held back behind a wait, two
+    # streams' layers (two launches each, through the scratch) and the current stream's allocations of the same sizes
+    # stay apart, and an output that the current stream reads is not handed out while it does.
+    M, K, N = 700, 1152, 520
+    x0, cm, w, ws, b = _layer(M, K, N)
+    xs = [x0 * f for f in (1.0, 2.0, -3.0, 0.5)]
+    want = [vq.vq_linear(x, cm, w, 8, ws, b) for x in xs]
+    size = vq.vq_linear_workspace_bytes(M, N, K, 8)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for s in streams:
+        with torch.cuda.stream(s):
+            torch.cuda._sleep(2000000)
+    got, between = [], []
+    for i, x in enumerate(xs):
+        got.append(vq.vq_linear(x, cm, w, 8, ws, b, stream=streams[i % 2]))
+        between += [torch.full((size,), 77, dtype=torch.uint8, device="cuda"),
+                    torch.full((M, N), 7.0, dtype=torch.float16, device="cuda")]
+    torch.cuda.synchronize()
+    for i in range(4):
+        assert torch.equal(got[i], want[i])
+    assert all((t == (77 if t.dtype == torch.uint8 else 7.0)).all() for t in between)
+    owner = {}
+    for seg in torch.cuda.memory_snapshot():
+        for y in got:
+            if seg["address"] <= y.data_ptr() < seg["address"] + seg["total_size"]:
+                owner[y.data_ptr()] = seg["stream"]
+    for i, y in enumerate(got):
+        assert owner[y.data_ptr()] == streams[i % 2].cuda_stream
+    # an output let go of while the current stream still has to read it
+    s = streams[0]
+    y = vq.vq_linear(xs[0], cm, w, 8, ws, b, stream=s)
+    torch.cuda.current_stream().wait_stream(s)
+    torch.cuda._sleep(2000000)
+    copy = y.clone()
+    del y
+    again = [vq.vq_linear(x, cm, w, 8, ws, b, stream=s) for x in xs]
+    torch.cuda.synchronize()
+    assert torch.equal(copy, want[0]) and all(torch.equal(a, t) for a, t in zip(again, want))
+    # a stream known by its handle only, and the current one given
+    class Handle:
+        cuda_stream = s.cuda_stream
+
+    by_handle = vq.vq_linear(xs[1], cm, w, 8, ws, b, stream=Handle())
+    by_current = vq.vq_linear(xs[2], cm, w, 8, ws, b, stream=torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert torch.equal(by_handle, want[1]) and torch.equal(by_current, want[2])
