@@ -148,23 +148,38 @@ vq::ProducerArgs residual_args(const void* x, const void* y, const float* gate, 
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Whether `out`, of `out_bytes`, shares memory with the layer's activations (or the residual's branch).
-bool overlaps(const void* out, size_t out_bytes, const void* in, size_t in_bytes) {
-    const uintptr_t o = (uintptr_t)out, i = (uintptr_t)in;
-    return in && o < i + in_bytes && i < o + out_bytes;
+struct Range {
+    const void* first;
+    size_t bytes;
+    bool meets(const Range& o) const {
+        const uintptr_t a = (uintptr_t)first, b = (uintptr_t)o.first;
+        return first && o.first && a < b + o.bytes && b < a + bytes;
+    }
+};
+
+// Whether the layer in one launch would write what another of its workgroups still reads.  In two launches
+// the quantizer is through with its operands when y is written, and r is written when the GEMM reads its
+// own, so a caller may have y, say, in the memory of a vector that only the quantizer needs.
+bool writes_over_reads(const vq::ProducerArgs& p, const void* w, int w_bits, const float* w_scale, const void* bias_f16,
+                       const void* y_f16, int M, int N, int K) {
+    const size_t rows = 2 * (size_t)M * K, vec = 4 * (size_t)K;
+    const size_t samples = ((size_t)M + p.tokens_per_sample - 1) / p.tokens_per_sample;
+    const Range y{y_f16, 2 * (size_t)M * N}, r{p.r, rows};
+    for (const Range& in : {Range{p.x, rows}, Range{p.y, rows}, Range{p.chan_mul, vec}, Range{p.mod_a, samples * vec},
+                            Range{p.mod_b, samples * vec}})
+        if (y.meets(in) || r.meets(in)) return true;
+    for (const Range& in : {Range{w, (size_t)N * K * w_bits / 8}, Range{w_scale, 4 * (size_t)N}, Range{bias_f16, 2 * (size_t)N}})
+        if (r.meets(in)) return true;
+    return y.meets(r);
 }
 
-// The layer behind its producer, operands validated: in one launch where that is the faster way, otherwise
-// the quantizer into xq and x_scale and the GEMM behind it.  (The one launch reads a token several times,
-// so nothing that it writes may be a part of what it reads.)
+// The layer behind its producer, operands validated: in one launch where that is the faster way and nothing
+// that it writes is a part of what it reads, otherwise the quantizer into xq and x_scale and the GEMM behind it.
 int enqueue_layer(const vq::ProducerArgs& p, const void* w, int w_bits, const float* w_scale, const void* bias_f16,
                   void* y_f16, int8_t* xq, float* x_scale, int M, int N, int K, int num_cus, hipStream_t stream) {
-    if (vq::small_layer(p.producer, M, N, K, w_bits, num_cus)) {
-        const size_t in = 2 * (size_t)M * K, out = 2 * (size_t)M * N;
-        if (!overlaps(y_f16, out, p.x, in) && !overlaps(y_f16, out, p.y, in) && !overlaps(y_f16, out, p.r, in) &&
-            !overlaps(p.x, in, p.r, in) && !overlaps(p.y, in, p.r, in))
-            return launch_status(vq::launch_linear_small(p, w, w_bits, w_scale, bias_f16, y_f16, M, N, K, stream));
-    }
+    if (vq::small_layer(p.producer, M, N, K, w_bits, num_cus) &&
+        !writes_over_reads(p, w, w_bits, w_scale, bias_f16, y_f16, M, N, K))
+        return launch_status(vq::launch_linear_small(p, w, w_bits, w_scale, bias_f16, y_f16, M, N, K, stream));
     const int v = launch_status(vq::launch_producer_quantize(p, xq, x_scale, M, K, stream));
     if (v != VQ_OK) return v;
     return launch_status(vq::launch_gemm(xq, x_scale, w, w_bits, w_scale, bias_f16, y_f16, nullptr, M, N, K, num_cus,

@@ -86,3 +86,28 @@ def test_outputs_over_inputs_take_two_launches(vq):
     _, y2 = vq.vq_residual_linear(inplace, y_in, w, 8, ws, r=inplace)
     torch.cuda.synchronize()
     assert torch.equal(over, want) and torch.equal(inplace, r) and torch.equal(y2, y)
+
+
+@pytest.mark.parametrize("vector", ["chan_mul", "gate"])
+def test_output_over_a_vector_of_the_quantizer_takes_two_launches(vq, vector):
+    # the quantizer is through with its vectors when the GEMM writes y: y may take their memory.  (In one launch the
+    # workspace is left alone.)
+    M, K, N = 16, 512, 64
+    g = torch.Generator(device="cuda").manual_seed(77)
+    x, y_in = torch.randn((M, K), generator=g, device="cuda").half(), torch.randn((M, K), generator=g, device="cuda").half()
+    w, ws = vq.vq_quantize_weight(torch.randn((N, K), generator=g, device="cuda") * 0.02, None, 8)
+    v = torch.exp(torch.randn(K, generator=g, device="cuda") * 0.3)
+
+    def call(vec, y, wk):
+        if vector == "chan_mul":
+            return vq.vq_linear(x, vec, w, 8, ws, None, y, wk)
+        return vq.vq_residual_linear(x, y_in, w, 8, ws, vec.view(1, K), M, None, None, None, y, wk)[1]
+
+    apart = torch.full((vq.vq_linear_workspace_bytes(M, N, K, 8),), 0xA5, dtype=torch.uint8, device="cuda")
+    shared = apart.clone()
+    want = call(v, None, apart)
+    over = v.clone()
+    got = call(over, over.view(torch.float16)[: M * N].view(M, N), shared)
+    torch.cuda.synchronize()
+    assert (apart == 0xA5).all() and (shared != 0xA5).any()
+    assert torch.equal(got, want)
