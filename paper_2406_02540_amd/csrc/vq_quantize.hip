@@ -68,7 +68,10 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_tokens_generic(
 // Static quantizer (the comparison point: one scale for the whole tensor, fixed beforehand).
 // Rows of whole 16-byte chunks: a wavefront takes CHUNKS KiB of contiguous input, a thread
 // its chunks one wavefront width apart (every load and store instruction of a wavefront is
-// contiguous), all loads first.
+// contiguous), all loads first: a thread's chunks are four registers each and the eight wavefronts per SIMD
+// leave 64, so with chan_mul nine chunks are the most that fit.  (Ten spilled 16 registers: 40000 x 2048 with
+// chan_mul 58.4 us, 46.0 as it is; 10000 x 4096 35.7 and 26.3.  Stepping the chunk of the row instead of one
+// division per chunk: 8192 x 1152 9.0 and 8.1.)
 template <bool HAS_MUL, int CHUNKS>
 __global__ __launch_bounds__(kQuantThreads, 8) void quantize_static_chunks(
     const half8* __restrict__ x, const float4v* __restrict__ chan_mul, float inv, int2v* __restrict__ xq,
@@ -82,24 +85,30 @@ __global__ __launch_bounds__(kQuantThreads, 8) void quantize_static_chunks(
         if (c < chunks) v[i] = __builtin_nontemporal_load(x + c);
     }
     int2v o[CHUNKS];
+    unsigned k8 = HAS_MUL ? base % K8 : 0u;   // chunk of its row, stepped by a wavefront's width
+    const unsigned step = HAS_MUL ? kWave % K8 : 0u;
 #pragma unroll
     for (int i = 0; i < CHUNKS; ++i) {
         const unsigned c = base + i * kWave;
         if (c < chunks) {
-            float t[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) t[j] = (float)v[i][j];
-            if (HAS_MUL) {
-                const unsigned k8 = c % K8;
-                const float4v m0 = chan_mul[2 * k8], m1 = chan_mul[2 * k8 + 1];
+            for (int h = 0; h < 2; ++h) {   // (four values and factors at a time: fewer registers)
+                float t[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    t[j] = t[j] * m0[j];
-                    t[4 + j] = t[4 + j] * m1[j];
+                for (int j = 0; j < 4; ++j) t[j] = (float)v[i][4 * h + j];
+                if (HAS_MUL) {
+                    const float4v m = chan_mul[2 * k8 + h];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) t[j] = t[j] * m[j];
                 }
+                int q = quantize4(t[0], t[1], t[2], t[3], inv);
+                if (HAS_MUL) asm volatile("" : "+v"(q) : : "memory");
+                o[i][h] = q;
             }
-            o[i].x = quantize4(t[0], t[1], t[2], t[3], inv);
-            o[i].y = quantize4(t[4], t[5], t[6], t[7], inv);
+        }
+        if (HAS_MUL) {
+            k8 += step;
+            if (k8 >= K8) k8 -= K8;
         }
     }
     // the stores leave together, behind the last load (reads and writes in bursts, not mixed)
@@ -396,12 +405,15 @@ hipError_t launch_static_chunks(const void* x_f16, const float* chan_mul, float 
                                 unsigned chunks, unsigned K8, hipStream_t stream) {
     constexpr unsigned per_block = kQuantThreads * CHUNKS;
     const dim3 grid((chunks + per_block - 1) / per_block), block(kQuantThreads);
-    if (chan_mul)
-        hipLaunchKernelGGL((quantize_static_chunks<true, CHUNKS>), grid, block, 0, stream, (const half8*)x_f16,
-                           (const float4v*)chan_mul, inv_scale, (int2v*)xq, chunks, K8);
-    else
+    if (!chan_mul) {
         hipLaunchKernelGGL((quantize_static_chunks<false, CHUNKS>), grid, block, 0, stream, (const half8*)x_f16,
                            (const float4v*)nullptr, inv_scale, (int2v*)xq, chunks, K8);
+    } else if constexpr (CHUNKS < 10) {
+        hipLaunchKernelGGL((quantize_static_chunks<true, CHUNKS>), grid, block, 0, stream, (const half8*)x_f16,
+                           (const float4v*)chan_mul, inv_scale, (int2v*)xq, chunks, K8);
+    } else {
+        return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
@@ -410,11 +422,12 @@ hipError_t launch_quantize_static(const void* x_f16, const float* chan_mul, floa
     const long total = (long)M * K;
     if (K % 8 == 0 && total / 8 < (1L << 31)) {
         // Chunks per thread: the count whose grid wastes least of its last round of resident
-        // workgroups (8 per compute unit, 256 units).
+        // workgroups (8 per compute unit, 256 units), of those that the registers hold.
         const long chunks = total / 8, slots = 8 * 256;
         int best = 8;
         long best_cost = 1L << 62;
         for (int u : {8, 9, 10}) {
+            if (chan_mul && u == 10) break;
             const long blocks = (chunks + kQuantThreads * u - 1) / (kQuantThreads * u);
             const long cost = (blocks + slots - 1) / slots * u;
             if (cost < best_cost) {

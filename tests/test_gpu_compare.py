@@ -111,6 +111,21 @@ def test_quantize_static_bit_exact(vq, oracle, M, K, with_mul):
         assert np.array_equal(host(q), ref)
 
 
+# rows of one chunk, about a wavefront's width of chunks, and several; the sizes that take nine (4100 x 8200) and,
+# without chan_mul, ten chunks per thread (9400 x 4096)
+@pytest.mark.parametrize("M,K", [(700, 8), (31, 72), (77, 504), (77, 512), (77, 520), (129, 1032), (2500, 1000), (4100, 8200), (9400, 4096)])
+def test_quantize_static_chunks_of_a_row(vq, M, K):
+    say(f"quantize_static chunks M={M} K={K}")
+    g = torch.Generator(device="cuda").manual_seed(640 + M + K)
+    x = (torch.randn((M, K), generator=g, device="cuda") * 2).half()
+    cm = torch.exp(torch.randn(K, generator=g, device="cuda"))
+    inv = float(np.float32(1) / np.float32(0.037))
+    for c in (None, cm):   # every fp32 step rounds on its own, halves to even: the same in torch
+        t = x.float() if c is None else x.float() * c
+        want = (t * inv).clamp(-127, 127).round().to(torch.int8)
+        assert torch.equal(vq.vq_quantize_static(x, 0.037, c), want)
+
+
 def test_static_w8a8_layer_matches_the_oracle_pipeline(vq, oracle):
     from parity_util import assert_fp16_close
     g = np.random.default_rng(79)
