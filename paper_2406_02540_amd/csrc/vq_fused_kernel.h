@@ -177,9 +177,10 @@ struct Vec8 { float4v lo, hi; };   // one chunk of a vector
 // Read from memory, every lane its chunks: four bytes per element and vector through the load path, for
 // each token again.
 // BY_CHUNK: so is the residual's branch, in fewer registers, instead of up front with the token.
-template <bool BY_CHUNK = false>
+// SCALE, SHIFT: LayerNorm has them (or reads an empty buffer's zeros, which takes the load path as long).
+template <bool BY_CHUNK = false, bool SCALE = true, bool SHIFT = true>
 struct VectorsFromMemory {
-    static constexpr bool kByChunk = BY_CHUNK;
+    static constexpr bool kByChunk = BY_CHUNK, kScale = SCALE, kShift = SHIFT;
     __device__ __forceinline__ bool staged(int) const { return false; }
     __device__ __forceinline__ Vec8 chunk(int, int) const { return {}; }
     template <class Rs>
@@ -196,7 +197,7 @@ struct VectorsFromMemory {
 // Hadamard 103.4 / 81.5, balanced 85.4 / 76.0.  1001 x 1152: balanced 4.5 / 3.1, LayerNorm 4.8 / 4.2.
 template <int PRODUCER, int CHUNKS, int THREADS>
 struct VectorsInLds {
-    static constexpr bool kByChunk = false;
+    static constexpr bool kByChunk = false, kScale = true, kShift = true;
     static constexpr int kVecs = vector_count(PRODUCER), kFloat4 = 2 * CHUNKS;
     static constexpr int kPer = (kFloat4 + THREADS - 1) / THREADS;
     float4v* lds;        // [kVecs][2][CHUNKS]
@@ -405,23 +406,44 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
         const float rstd = 1.0f / __builtin_sqrtf(var + a.eps);
         // t = (x - mean) rstd (1 + scale) + shift as one multiply and one fma per element (a missing scale
         // or shift is an empty buffer, which reads as zero)
-        Vec8 nxt_a = vec_chunk(kVecA, b, 0), nxt_b = vec_chunk(kVecB, b, 0);
+        if constexpr (Vectors::kScale && Vectors::kShift) {
+            Vec8 nxt_a = vec_chunk(kVecA, b, 0), nxt_b = vec_chunk(kVecB, b, 0);
 #pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-            if (i >= used) continue;
-            const Vec8 sc = nxt_a, sh = nxt_b;
-            if (i + 1 < NCH) nxt_a = vec_chunk(kVecA, b, i + 1), nxt_b = vec_chunk(kVecB, b, i + 1);
-            float mul[8], add[8];
+            for (int i = 0; i < NCH; ++i) {
+                if (i >= used) continue;
+                const Vec8 sc = nxt_a, sh = nxt_b;
+                if (i + 1 < NCH) nxt_a = vec_chunk(kVecA, b, i + 1), nxt_b = vec_chunk(kVecB, b, i + 1);
+                float mul[8], add[8];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                mul[j] = rstd * (1.0f + sc.lo[j]);
-                mul[4 + j] = rstd * (1.0f + sc.hi[j]);
-                add[j] = sh.lo[j];
-                add[4 + j] = sh.hi[j];
+                for (int j = 0; j < 4; ++j) {
+                    mul[j] = rstd * (1.0f + sc.lo[j]);
+                    mul[4 + j] = rstd * (1.0f + sc.hi[j]);
+                    add[j] = sh.lo[j];
+                    add[4 + j] = sh.hi[j];
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) t[i][j] = __builtin_fmaf(t[i][j], mul[j], add[j]);
+                chunk_done(t[i]);
             }
+        } else {
+            constexpr int kGiven = Vectors::kScale ? kVecA : kVecB;
+            Vec8 nxt{};
+            if constexpr (Vectors::kScale || Vectors::kShift) nxt = vec_chunk(kGiven, b, 0);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) t[i][j] = __builtin_fmaf(t[i][j], mul[j], add[j]);
-            chunk_done(t[i]);
+            for (int i = 0; i < NCH; ++i) {
+                if (i >= used) continue;
+                const Vec8 v = nxt;
+                if constexpr (Vectors::kScale || Vectors::kShift)
+                    if (i + 1 < NCH) nxt = vec_chunk(kGiven, b, i + 1);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float e = j < 4 ? v.lo[j & 3] : v.hi[j & 3];
+                    if constexpr (Vectors::kScale) t[i][j] = t[i][j] * (rstd * (1.0f + e));
+                    else if constexpr (Vectors::kShift) t[i][j] = __builtin_fmaf(t[i][j], rstd, e);
+                    else t[i][j] = t[i][j] * rstd;
+                }
+                if constexpr (Vectors::kScale || Vectors::kShift) chunk_done(t[i]);
+            }
         }
     }
 
@@ -521,7 +543,7 @@ struct RowsInMemory {
 // 4608 11.8 and 9.1).
 constexpr int kFewVectorBytes = 20 * 1024, kManyVectorBytes = 56 * 1024, kManyTokens = 4096;
 constexpr int vector_bytes(int producer, int nch, int lanes) { return vector_count(producer) * nch * lanes * 32; }
-enum Staging { kNotStaged, kStaged, kStagedWide, kByChunk };
+enum Staging { kNotStaged, kStaged, kStagedWide, kByChunk, kNoScale, kNoShift, kNeither };
 constexpr Staging staging(int producer, int nch, int lanes) {   // (from kManyTokens on; below, the last two are kNotStaged)
     const int bytes = vector_bytes(producer, nch, lanes);
     if (producer == kLayerNorm && nch <= 2) return kNotStaged;
@@ -559,7 +581,9 @@ __global__ __launch_bounds__(fused_threads(STAGING), PRODUCER == kLayerNorm && N
         vectors.used[kVecA] = vectors.used[kVecB] = sample;
         produce_and_quantize<PRODUCER, NCH, LANES, true>(a, w_first, lane, true, vectors, out);
     } else {
-        produce_and_quantize<PRODUCER, NCH, LANES, true>(a, w_first, lane, true, VectorsFromMemory<STAGING == kByChunk>{}, out);
+        typedef VectorsFromMemory<STAGING == kByChunk, STAGING != kNoScale && STAGING != kNeither,
+                                  STAGING != kNoShift && STAGING != kNeither> FromMemory;
+        produce_and_quantize<PRODUCER, NCH, LANES, true>(a, w_first, lane, true, FromMemory{}, out);
     }
 }
 
@@ -575,6 +599,15 @@ hipError_t launch_fused(const FusedArgs& a, hipStream_t stream) {
     constexpr Staging kind = staging(PRODUCER, NCH, LANES);
     if constexpr (kind == kStagedWide || kind == kByChunk)
         if (a.M < kManyTokens) return launch_fused_staging<PRODUCER, NCH, LANES, kNotStaged>(a, stream);
+    if constexpr (PRODUCER == kLayerNorm && kind == kNotStaged && NCH > 2) {
+        // Rows too long to stage, many of them: a missing scale or shift is not asked for (us, asked for / as it
+        // is, 20000 x 6144: neither given 85.1 / 66.1, shift only 103.5 / 92.5, scale only 86.4 / 76.1; with few
+        // tokens there is nothing to gain, and a run-time branch around each load cost the kernel that has both 10
+        // to 20 %).
+        if (a.M >= kManyTokens && !a.mod_a && !a.mod_b) return launch_fused_staging<PRODUCER, NCH, LANES, kNeither>(a, stream);
+        if (a.M >= kManyTokens && !a.mod_a) return launch_fused_staging<PRODUCER, NCH, LANES, kNoScale>(a, stream);
+        if (a.M >= kManyTokens && !a.mod_b) return launch_fused_staging<PRODUCER, NCH, LANES, kNoShift>(a, stream);
+    }
     return launch_fused_staging<PRODUCER, NCH, LANES, kind>(a, stream);
 }
 

@@ -404,3 +404,25 @@ def test_large_calls_match_small_ones(vq, producer, K, T):
         torch.cuda.synchronize()
         for w, p in zip(whole, part):
             assert torch.equal(w[lo:hi], p)
+
+
+# Many rows too long for their vectors to be staged: a missing scale or shift is a kernel of its own, and gives the
+# bits of the one that reads zeros.  The first length of its kind, one with a partly filled last chunk, the longest.
+@pytest.mark.parametrize("K", [4736, 5128, 8192])
+@pytest.mark.parametrize("missing", ["scale", "shift", "both"])
+@pytest.mark.parametrize("balanced", [False, True])
+def test_layernorm_long_rows_without_scale_or_shift(vq, K, missing, balanced):
+    say(f"layernorm long rows K={K} missing={missing} balanced={balanced}")
+    M, T = 4099, 2050
+    g = torch.Generator(device="cuda").manual_seed(8200 + K)
+
+    def n(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+
+    x, cm = (n(M, K) * 3).half(), torch.exp(n(K) * 0.3) if balanced else None
+    given = {k: n(2, K) * 0.3 for k in ("scale", "shift") if missing not in (k, "both")}
+    zeros = torch.zeros((2, K), device="cuda")
+    q, s = vq.vq_layernorm_quantize(x, given.get("scale"), given.get("shift"), T, 1e-6, cm)
+    q0, s0 = vq.vq_layernorm_quantize(x, given.get("scale", zeros), given.get("shift", zeros), T, 1e-6, cm)
+    torch.cuda.synchronize()
+    assert torch.equal(q, q0) and torch.equal(s, s0)
