@@ -147,6 +147,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_static_elems(
 // thread, 2 or 4 bytes per load and each load waited for: 48.8 and 27.3 us.
 constexpr int kAbsmaxThreads = 512, kAbsmaxCols = 16, kAbsmaxRows = kAbsmaxThreads / kAbsmaxCols, kAbsmaxUnroll = 4;
 constexpr int kAbsmaxOneSlab = 256;   // so few rows that a slab of their own costs less than clearing amax first (a launch, 2 us)
+constexpr int kAbsmaxFewRows = 4;
 template <typename T>
 struct AbsmaxChunk { typedef half8 type; };
 template <>
@@ -191,8 +192,8 @@ __global__ __launch_bounds__(kAbsmaxThreads, 8) void channel_absmax_chunks(const
     else atomicMax((int*)amax + k, __builtin_bit_cast(int, (float)best));
 }
 
-// The same for rows that are not whole 16-byte chunks (K % 8 in fp16, K % 4 in fp32): thread t of a
-// block owns column 256 b_x + t for a slab of rows.
+// The same for rows that are not whole 16-byte chunks (K % 8 in fp16, K % 4 in fp32), and for a few rows
+// more: thread t of a block owns column 256 b_x + t for a slab of rows.
 template <typename T>
 __global__ __launch_bounds__(kQuantThreads) void channel_absmax_cols(const T* __restrict__ a,
                                                                      float* __restrict__ amax, int R, int K,
@@ -351,7 +352,9 @@ hipError_t launch_channel_absmax(const void* a, int is_f32, float* amax, int R, 
                                  hipStream_t stream) {
     const dim3 block(kQuantThreads);
     const int elems = is_f32 ? 4 : 8;
-    const bool chunks = R > 0 && K % elems == 0;
+    // (a few more rows for a running maximum: one load of a thread per row is sooner done than the meeting in
+    // LDS: 1 x 1152 fp16 1.75 us, 2.00 through LDS; 4 x 1152 1.79 and 1.98; 8 x 1152 2.17 and 2.03)
+    const bool chunks = R > 0 && K % elems == 0 && !(accumulate && R <= kAbsmaxFewRows);
     const bool overwrite = chunks && !accumulate && R <= kAbsmaxOneSlab;
     if (!accumulate && !overwrite) {
         hipLaunchKernelGGL(fill_zero_f32, dim3((unsigned)((K + kQuantThreads - 1) / kQuantThreads)), block, 0,

@@ -181,8 +181,8 @@ def test_channel_absmax_bit_exact(vq, oracle, R, K):
     assert np.array_equal(host(got), oracle.channel_absmax(np.concatenate([x, x2])))
 
 
-# one slab and the first size past it, a row group's edges, partly filled column blocks, many slabs
-@pytest.mark.parametrize("R,K", [(1, 8), (31, 4), (32, 120), (33, 136), (256, 128), (257, 128), (129, 1144), (40000, 72)])
+# the few rows that a running maximum takes by column, one slab and the first size past it, a row group's edges, partly filled column blocks, many slabs
+@pytest.mark.parametrize("R,K", [(1, 8), (4, 72), (5, 72), (31, 4), (32, 120), (33, 136), (256, 128), (257, 128), (129, 1144), (40000, 72)])
 def test_channel_absmax_chunks(vq, R, K):
     say(f"channel_absmax chunks R={R} K={K}")
     g = np.random.default_rng(720 + R + K)
