@@ -349,6 +349,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     _Float16* const ytile = a.y + (long)tok0 * a.N + ch0;
     const bool whole = c0 + 8 <= rows_w;
     typedef v4i v4i_any __attribute__((aligned(2)));   // (rows of Y start at any even address)
+    constexpr int kAccShift = (W_BITS == 4) ? 4 : 0;   // (the 4-bit path summed 16 * w)
 #pragma unroll 1
     for (int t = tid / kPerRow; t < rows_x; t += kRowStep) {
         v4i v0 = {0, 0, 0, 0}, v1 = v0;
@@ -375,9 +376,15 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         }
         if (a.acc_out) {
             int32_t* const arow = a.acc_out + (long)(tok0 + t) * a.N + ch0 + c0;
+            if (whole) {
+                typedef v4i v4i_any4 __attribute__((aligned(4)));
+                *(v4i_any4*)arow = v0 >> kAccShift;
+                *(v4i_any4*)(arow + 4) = v1 >> kAccShift;
+            } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (c0 + e < rows_w) arow[e] = (e < 4 ? v0[e & 3] : v1[e & 3]) >> ((W_BITS == 4) ? 4 : 0);
+                for (int e = 0; e < 8; ++e)
+                    if (c0 + e < rows_w) arow[e] = (e < 4 ? v0[e & 3] : v1[e & 3]) >> kAccShift;
+            }
         }
     }
 }
