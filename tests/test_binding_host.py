@@ -34,6 +34,8 @@ def outcome(call):
     try:
         call()
         return "returned"
+    except torch.AcceleratorError:   # (an allocation on a given stream asks for the current one: there is no device here)
+        return "RuntimeError: no device"
     except Exception as e:
         return type(e).__name__ + ": " + str(e).splitlines()[0]
 """
