@@ -12,8 +12,9 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import re
 
-import torch  # noqa: F401  (the extension resolves against its libraries)
+import torch
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 # the in-tree build; VQ_LIBVIDIQ_PATH names another build of the same sources (e.g. one with host sanitizers)
@@ -97,8 +98,15 @@ def _load():
         raise RuntimeError(f"{EXT_PATH} not found: build it with `python -m paper_2406_02540_amd.build`")
     loader = importlib.machinery.ExtensionFileLoader("_vq_torch", EXT_PATH)
     spec = importlib.util.spec_from_file_location("_vq_torch", EXT_PATH, loader=loader)
-    ext = importlib.util.module_from_spec(spec)
-    loader.exec_module(ext)
+    rebuild = "build it again with `python -m paper_2406_02540_amd.build`"
+    try:
+        ext = importlib.util.module_from_spec(spec)
+        loader.exec_module(ext)
+    except ImportError as e:  # (symbols of another torch)
+        raise RuntimeError(f"{EXT_PATH} does not load: {rebuild}") from e
+    # the extension holds the layout of the torch that it was compiled against
+    if ext.TORCH_VERSION != re.match(r"[\d.]*\d", torch.__version__).group():
+        raise RuntimeError(f"{EXT_PATH} was built for torch {ext.TORCH_VERSION}, this is {torch.__version__}: {rebuild}")
     ext.bind(VqError, tuple(ctypes.cast(getattr(handle, n), ctypes.c_void_p).value for n in _BOUND))
     _ext = ext
     return ext

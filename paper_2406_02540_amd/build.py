@@ -4,7 +4,9 @@ Usage: python -m paper_2406_02540_amd.build
 """
 from __future__ import annotations
 
+import importlib.util
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -40,11 +42,20 @@ def hipcc() -> str:
     return "hipcc"
 
 
+def cxx() -> str:
+    """The C++ compiler of the torch extension: $CXX, g++, or the clang++ that hipcc drives."""
+    clang = os.path.join(os.path.dirname(os.path.realpath(shutil.which(hipcc()) or hipcc())), "amdclang++")
+    for cand in (os.environ.get("CXX"), "g++", clang):
+        if cand and shutil.which(cand.split()[0]):
+            return cand
+    return "c++"
+
+
 def ext_command(out: str) -> list:
     """The compiler call for the torch extension (plain C++ against torch's headers)."""
     import torch
     root = os.path.dirname(torch.__file__)
-    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+    return [*cxx().split(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
             "-I", os.path.join(ROOT, "include"), "-I", os.path.join(root, "include"),
             "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-I", "/opt/rocm/include",
@@ -53,14 +64,21 @@ def ext_command(out: str) -> list:
 
 
 def build(verbose: bool = True) -> str:
-    """Compiles every source for gfx950 and links the shared library, then the torch extension. Always recompiles."""
+    """Compiles every source for gfx950 and links the shared library, then the torch extension. Always recompiles.
+
+    The library needs hipcc only: without torch it is built alone, and it is in place before the extension is.
+    """
     objs = []
     procs = []
-    ext_tmp = EXT_PATH + ".tmp.%d" % os.getpid()
-    cmd = ext_command(ext_tmp)
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    ext = subprocess.Popen(cmd)
+    ext = None
+    if importlib.util.find_spec("torch") is None:
+        print("torch is not installed: libvidiq.so is built without its Python binding", flush=True)
+    else:
+        ext_tmp = EXT_PATH + ".tmp.%d" % os.getpid()
+        cmd = ext_command(ext_tmp)
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        ext = subprocess.Popen(cmd)
     for src in SOURCES:
         obj = os.path.join(CSRC, src.replace(".hip", ".o"))
         cmd = [hipcc(), *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
@@ -78,9 +96,10 @@ def build(verbose: bool = True) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, LIB_PATH)
-    if ext.wait() != 0:
-        raise RuntimeError("g++ failed on vq_torch.cpp")
-    os.replace(ext_tmp, EXT_PATH)
+    if ext is not None:
+        if ext.wait() != 0:
+            raise RuntimeError(f"{cxx()} failed on vq_torch.cpp")
+        os.replace(ext_tmp, EXT_PATH)
     # the ceilings probe (register-only MFMA loop, copy kernel): its own small executable
     tmp = CEILINGS_PATH + ".tmp.%d" % os.getpid()
     cmd = [hipcc(), *[f for f in HIPCC_FLAGS if f != "-fPIC"], os.path.join(CSRC, "vq_ceilings.hip"), "-o", tmp]

@@ -22,6 +22,7 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/Stream.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include "vq.h"
 
@@ -653,4 +654,8 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_vq_torch", nullptr, -1, g_metho
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__vq_torch(void) { return PyModule_Create(&g_module); }
+PyMODINIT_FUNC PyInit__vq_torch(void) {
+    PyObject* m = PyModule_Create(&g_module);
+    if (m && PyModule_AddStringConstant(m, "TORCH_VERSION", TORCH_VERSION) < 0) Py_CLEAR(m);
+    return m;
+}
