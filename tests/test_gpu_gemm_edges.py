@@ -43,9 +43,11 @@ def check_gemm(vq, bits, M, N, K, seed=3):
     assert torch.equal(y2, want) and torch.equal(acc2.double(), acc)
 
 
-# tiles of 256 tokens (both widths), rows of Y at odd addresses: N % 8 = 1, 3, 7, 4
+# rows of Y at odd addresses, N % 8 = 1, 3, 4, 7: tiles of 256 x 192 in one round (the first three) and in two,
+# of 256 x 256 in two rounds and in three, of 128 x 256
 @pytest.mark.parametrize("bits", [8, 4])
-@pytest.mark.parametrize("M,N,K", [(2891, 2817, 160), (2900, 3075, 128), (5003, 1151, 96), (2305, 4612, 288)])
+@pytest.mark.parametrize("M,N,K", [(2891, 2817, 160), (2900, 3075, 128), (2305, 4612, 288), (4999, 3075, 160),
+                                   (5003, 4999, 96), (5003, 4993, 160), (9000, 4095, 96), (5003, 1151, 96)])
 def test_unaligned_output_rows(vq, bits, M, N, K):
     check_gemm(vq, bits, M, N, K)
 

@@ -151,11 +151,9 @@ def _gemm_case(vq, oracle, M, N, K, bits, seed, bias=True, full_range=True):
     return worst, np.array_equal(host(y).view(np.uint16), y_ref.view(np.uint16))
 
 
-# The library picks its small-tile kernel when 256 x 256 tiles would fill less than half of
-# the CUs and a persistent large-tile kernel otherwise (>= 129 such tiles on a 256-CU part): the
-# 256 x 192 tile where that saves rounds of tiles (the first four shapes), else the 256 x 256 one
-# (the next three: two rounds of 256 x 256 against three of 256 x 192).  Both sets are ragged in
-# M, N (also N % 8 != 0) and K.
+# The library picks the tile by a fitted cost: on 256 CUs 256 x 192 for the first four shapes, 256 x 256 (two
+# rounds against three of 256 x 192) for the next three, one small tile per workgroup for the others.  All sets
+# are ragged in M, N (also N % 8 != 0) and K.
 GEMM_SHAPES = [(2891, 2824, 144), (2891, 2820, 208), (2600, 3080, 128), (4099, 2056, 48),
                (5003, 5000, 144), (5003, 4996, 80), (4900, 5112, 128),
                (1, 8, 16), (1, 8, 32), (33, 24, 96), (64, 128, 64), (256, 128, 128), (256, 1152, 1152),
@@ -174,10 +172,12 @@ def test_gemm_parity(vq, oracle, M, N, K, bits):
 
 
 @pytest.mark.parametrize("bits,M,N,K", [(8, 700, 392, 1184), (4, 700, 392, 1184), (8, 300, 136, 224),
-                                        (8, 2900, 2824, 1152), (4, 2900, 2824, 1152), (8, 2891, 2824, 144)])
+                                        (8, 2900, 2824, 1152), (4, 2900, 2824, 1152), (8, 2891, 2824, 144),
+                                        (8, 5003, 4999, 144), (4, 5003, 5000, 96), (8, 1001, 1157, 416),
+                                        (4, 1100, 2050, 320), (8, 1025, 4097, 96)])
 def test_dequantization_rounds_once(vq, oracle, bits, M, N, K):
-    """The rounding the header states for the epilogue, to the bit, in every GEMM kernel (small
-    tiles, 256 x 192, 256 x 256): s = fp32(x_scale * w_scale), y = fp16(float(acc) * s + bias) with
+    """The rounding the header states for the epilogue, to the bit, in every GEMM kernel (64 x 64, 32 x 32,
+    256 x 192, 256 x 256, 128 x 64, 128 x 128, 128 x 256): s = fp32(x_scale * w_scale), y = fp16(float(acc) * s + bias) with
     the multiply-add exact.  The host evaluates it in fp64, where acc * s is exact (24 + 24 bits)
     and the sum with the bias is off by at most 2^-53 relative: a double rounding through fp64
     could only differ for a sum within 2^-41 fp16 ulps of a tie, which these draws do not hit."""

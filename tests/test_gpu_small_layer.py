@@ -15,6 +15,7 @@ def vq():
 
 
 def _layer(vq, producer, M, K, N, bits, seed):
+    """The layer against its two calls.  Whether it was one launch: that leaves the workspace as it was."""
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
 
@@ -29,40 +30,44 @@ def _layer(vq, producer, M, K, N, bits, seed):
     B = (M + T - 1) // T
     cm, sc, sh, y_in = torch.exp(n(K) * 0.3), n(B, K) * 0.2, n(B, K) * 0.5, n(M, K).half()
     gemm = vq.vq_gemm_w8a8 if bits == 8 else vq.vq_gemm_w4a8
-    r = None
+    wk = torch.full((vq.vq_linear_workspace_bytes(M, N, K, bits),), 0xA5, dtype=torch.uint8, device="cuda")
     if producer in ("plain", "balanced"):
         c = cm if producer == "balanced" else None
-        one, q = vq.vq_linear(x, c, w, bits, ws, b), vq.vq_quantize_per_token(x, c)
+        one, q = vq.vq_linear(x, c, w, bits, ws, b, None, wk), vq.vq_quantize_per_token(x, c)
     elif producer == "layernorm":
-        one, q = vq.vq_layernorm_linear(x, w, bits, ws, sc, sh, T, 1e-6, cm, b), vq.vq_layernorm_quantize(x, sc, sh, T, 1e-6, cm)
+        one = vq.vq_layernorm_linear(x, w, bits, ws, sc, sh, T, 1e-6, cm, b, None, wk)
+        q = vq.vq_layernorm_quantize(x, sc, sh, T, 1e-6, cm)
     elif producer == "layernorm_bare":
-        one, q = vq.vq_layernorm_linear(x, w, bits, ws, None, None, None, 1e-6, None, b), vq.vq_layernorm_quantize(x, None, None, None, 1e-6, None)
+        one = vq.vq_layernorm_linear(x, w, bits, ws, None, None, None, 1e-6, None, b, None, wk)
+        q = vq.vq_layernorm_quantize(x, None, None, None, 1e-6, None)
     elif producer in ("gelu", "gelu_erf"):
         t = producer == "gelu"
-        one, q = vq.vq_gelu_linear(x, w, bits, ws, t, cm, b), vq.vq_gelu_quantize(x, t, cm)
+        one, q = vq.vq_gelu_linear(x, w, bits, ws, t, cm, b, None, wk), vq.vq_gelu_quantize(x, t, cm)
     elif producer == "residual":
-        r1, one = vq.vq_residual_linear(x, y_in, w, bits, ws, sc, T, None, cm, b)
+        r1, one = vq.vq_residual_linear(x, y_in, w, bits, ws, sc, T, None, cm, b, None, wk)
         r, *q = vq.vq_residual_quantize(x, y_in, sc, T, None, cm)
         assert torch.equal(r1, r)
     else:
-        one, q = vq.vq_hadamard_linear(x, cm, w, bits, ws, b), vq.vq_hadamard_quantize(x, cm)
+        one, q = vq.vq_hadamard_linear(x, cm, w, bits, ws, b, None, wk), vq.vq_hadamard_quantize(x, cm)
     two = gemm(q[0], q[1], w, ws, b)
     torch.cuda.synchronize()
     assert np.array_equal(one.cpu().numpy().view(np.uint16), two.cpu().numpy().view(np.uint16))
+    return bool((wk == 0xA5).all())
 
 
 PRODUCERS = ("plain", "balanced", "layernorm", "layernorm_bare", "gelu", "gelu_erf", "residual", "hadamard")
 
 
 # one token, a tile of tokens and one past it, partly filled channel tiles and rows of any alignment, K of one
-# chunk group and up to the longest row; the last four lie past the rule (two launches on both sides)
+# chunk group and up to the longest row; the last four lie past the rule, LayerNorm is not in it (two launches on both sides)
 @pytest.mark.parametrize("producer", PRODUCERS)
 @pytest.mark.parametrize("M,K,N", [(1, 128, 1), (8, 1152, 64), (9, 1152, 65), (3, 256, 2304), (30, 1024, 510), (4, 1536, 72),
                                    (61, 512, 300), (2, 1664, 72), (250, 1152, 1100), (40, 4608, 1152), (2, 8192, 64)])
 @pytest.mark.parametrize("bits", [8, 4])
 def test_one_launch_gives_the_bits_of_two(vq, producer, M, K, N, bits):
     print(f"small layer {producer} {M}x{K}->{N} w{bits}", flush=True)
-    _layer(vq, producer, M, K, N, bits, 9000 + M + K + N)
+    past = (M, K, N) in ((2, 1664, 72), (250, 1152, 1100), (40, 4608, 1152), (2, 8192, 64))
+    assert _layer(vq, producer, M, K, N, bits, 9000 + M + K + N) == (not producer.startswith("layernorm") and not past)
 
 
 # K that is no multiple of the stage, of a chunk group or (8 bits) of 32
@@ -70,7 +75,7 @@ def test_one_launch_gives_the_bits_of_two(vq, producer, M, K, N, bits):
 @pytest.mark.parametrize("K,bits", [(16, 8), (512, 8), (1008, 8), (1168, 8), (1520, 8), (32, 4), (544, 4), (1184, 4), (1504, 4)])
 def test_one_launch_k_tails(vq, producer, K, bits):
     print(f"small layer {producer} 21x{K}->100 w{bits}", flush=True)
-    _layer(vq, producer, 21, K, 100, bits, 9500 + K)
+    assert _layer(vq, producer, 21, K, 100, bits, 9500 + K) == (not producer.startswith("layernorm"))
 
 
 def test_outputs_over_inputs_take_two_launches(vq):
