@@ -177,7 +177,7 @@ bool writes_over_reads(const vq::ProducerArgs& p, const void* w, int w_bits, con
 // that it writes is a part of what it reads, otherwise the quantizer into xq and x_scale and the GEMM behind it.
 int enqueue_layer(const vq::ProducerArgs& p, const void* w, int w_bits, const float* w_scale, const void* bias_f16,
                   void* y_f16, int8_t* xq, float* x_scale, int M, int N, int K, int num_cus, hipStream_t stream) {
-    if (vq::small_layer(p.producer, M, N, K, w_bits, num_cus) &&
+    if (vq::small_layer(p.producer, M, N, K, num_cus) &&
         !writes_over_reads(p, w, w_bits, w_scale, bias_f16, y_f16, M, N, K))
         return launch_status(vq::launch_linear_small(p, w, w_bits, w_scale, bias_f16, y_f16, M, N, K, stream));
     const int v = launch_status(vq::launch_producer_quantize(p, xq, x_scale, M, K, stream));

@@ -59,8 +59,8 @@ inline FusedArgs fused_args(const ProducerArgs& p, int8_t* xq, float* x_scale, i
     return a;
 }
 
-// The producers are compiled in two translation units (each (producer, chunks, lanes) combination
-// is a kernel of its own, 48 per producer).
+// The stand-alone quantizers are compiled in two translation units: each combination of producer, chunks and
+// lanes is a kernel of its own, some in two or more ways to read their vectors.
 hipError_t launch_producer_gelu(int producer, const FusedArgs& a, hipStream_t stream);   // vq_fused_gelu.hip: both GELU forms
 hipError_t launch_producer_other(int producer, const FusedArgs& a, hipStream_t stream);  // vq_fused.hip
 

@@ -13,8 +13,8 @@ typedef TileShape<2, 4, 4> Tile256;  // 2 x 4 wavefronts of 128 tokens x 64 chan
 // `per_cu` workgroups fixed + stage * (stages of 128 bytes of K), plus the same of a last filling
 // with one workgroup only.  Fitted by least squares over 720 random problems (1 to 12000 tokens, 32
 // to 4608 channels, K 256 to 4608, 8- and 4-bit weights), each timed with every tile in captured
-// graphs: mean error 6 to 11 %, and the tile chosen by it is on average 0.14 % slower than the best
-// one of each problem (9 % in the worst problem of 1152 channels' K, 16 % in one of 720).
+// graphs: mean error 6 to 11 %.  On another 22000 problems of the same ranges (M to 32768), with the kernels
+// as they are, the tile chosen by it is on average 0.4 % slower than the best one of each problem.
 struct TileCost {
     int tile_t, tile_c, per_cu;
     double base, fixed, stage, fixed_one, stage_one;

@@ -63,17 +63,6 @@ __device__ __forceinline__ void load_to_lds_16(v4i rsrc, unsigned lds_addr, int 
         : "memory", "m0");
 }
 
-// 4 bytes per lane from buffer offset voff + soff into LDS at lds_addr + 4 * lane.
-__device__ __forceinline__ void load_to_lds_4(v4i rsrc, unsigned lds_addr, int voff, int soff) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "buffer_load_dword %1, %2, %3 offen lds"
-        :
-        : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
-        : "memory", "m0");
-}
-
 #pragma clang diagnostic pop
 
 // The same for a stage at byte k0 of the rows.  K a multiple of the stage: k0 rides in the scalar

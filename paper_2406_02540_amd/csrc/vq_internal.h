@@ -61,7 +61,7 @@ hipError_t launch_gemm_tiles(int tile_t, int tile_c, const int8_t* xq, const flo
 
 // A layer of few tokens in one launch (vq_linear_small.hip): quantizer, with its producer, and GEMM.
 // small_layer: whether it is the faster way for these sizes.
-bool small_layer(int producer, int M, int N, int K, int w_bits, int num_cus);
+bool small_layer(int producer, int M, int N, int K, int num_cus);
 hipError_t launch_linear_small(const ProducerArgs& p, const void* w, int w_bits, const float* w_scale, const void* bias_f16,
                                void* y_f16, int M, int N, int K, hipStream_t stream);
 

@@ -12,7 +12,7 @@ namespace vq {
 //   Hadamard  13 %;  8 %; -3 %    up to 160 x 1152,
 //   residual  16 %; 11 %; -6 %    up to 96 x 1152 (it also reads the branch and writes the sum),
 // and beside that one launch less is 2 us less of the host's time.  Beyond num_cus workgroups some wait.
-bool small_layer(int producer, int M, int N, int K, int w_bits, int num_cus) {
+bool small_layer(int producer, int M, int N, int K, int num_cus) {
     if (producer == kLayerNorm || K > kSmallNch * kSmallLanes * 8) return false;
     const long tiles = (long)((M + kSmallWaves - 1) / kSmallWaves) * ((N + SmallTile::kC - 1) / SmallTile::kC);
     const int line = producer == kPlain ? 256 : producer == kResidual ? 96 : 160;
