@@ -161,10 +161,18 @@ __device__ __forceinline__ v16f mfma_block(v4i w, v4i x, v16f c) {
 }
 
 // K_TAIL:  K is a multiple of 16 but not of 128 (the last stage is partly past K).
-// GENERIC: any N and an optional copy of the integer sums; rows of Y start at any even address.
-//          The other variant needs N % 8 == 0 and writes whole, aligned lines.
-template <class S, int W_BITS, bool K_TAIL, bool GENERIC>
+// OUT:     how rows of Y are written.
+//   kHalfLines: rows start on 64-byte boundaries (N % 32 == 0): past the caches (nontemporal).
+//   kChunks:    rows of whole 16-byte chunks (N % 8 == 0): through the caches.  A piece of 128 bytes that
+//               begins elsewhere than a memory sector does is two part-written sectors, which the L2 puts
+//               together with those of the neighbouring pieces and memory does not: 20120 x 352 -> 3464
+//               104 us past the caches, 67 through them; 8192 x 1152 -> 3472 58.5 and 45.2; 32768 x 1152 ->
+//               1168 71.5 and 63.9; with rows on 64-byte boundaries past them is 2 to 6 % faster.
+//   kAnyRow:    any N, rows start at any even address, and an optional copy of the integer sums.
+enum Out { kHalfLines, kChunks, kAnyRow };
+template <class S, int W_BITS, bool K_TAIL, Out OUT>
 __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant(const GemmArgs a) {
+    constexpr bool GENERIC = OUT == kAnyRow;
     constexpr int TB = S::TB;
     constexpr int kXStage = S::kXStage, kWStage = S::kWStage, kLdsBytes = S::kLdsBytes;
     __shared__ __attribute__((aligned(1024))) int8_t lds[kLdsBytes + kScaleBytes + S::kEpiBytes];
@@ -618,7 +626,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                         if (!GENERIC) {
                             __builtin_amdgcn_raw_buffer_store_b128(
                                 rows[i], rsrc_y, y_off0 + (unsigned)((tb * 32 + p * 16 + i * 8) * a.N * 2), 0,
-                                2 /* nontemporal */);
+                                OUT == kHalfLines ? 2 /* nontemporal */ : 0);
                             continue;
                         }
                         // Rows of Y that start at any even address: the same 16 bytes per lane,
@@ -671,19 +679,29 @@ hipError_t launch_gemm_shape(GemmArgs a, int w_bits, int num_cus, hipStream_t st
     a.slots = a.tiles_per_xcd < cus_per_xcd ? a.tiles_per_xcd : cus_per_xcd;
     const dim3 grid((unsigned)(a.slots * kXcds)), block(S::kThreads);
     const bool tail = ((w_bits == 16 ? 2 * a.K : a.K) % kTileK) != 0;  // (in bytes of an activation row)
-    const bool generic = (a.N % 8) != 0 || a.acc_out != nullptr || a.N >= (1 << 21);
-#define VQ_LAUNCH_GEMM(BITS, TAIL, GEN) \
-    hipLaunchKernelGGL((gemm_i8_dequant<S, BITS, TAIL, GEN>), grid, block, 0, stream, a)
-    if (w_bits == 8) {
-        if (tail) { if (generic) VQ_LAUNCH_GEMM(8, true, true); else VQ_LAUNCH_GEMM(8, true, false); }
-        else      { if (generic) VQ_LAUNCH_GEMM(8, false, true); else VQ_LAUNCH_GEMM(8, false, false); }
-    } else if (w_bits == 16) {
-        if (tail) { if (generic) VQ_LAUNCH_GEMM(16, true, true); else VQ_LAUNCH_GEMM(16, true, false); }
-        else      { if (generic) VQ_LAUNCH_GEMM(16, false, true); else VQ_LAUNCH_GEMM(16, false, false); }
-    } else {
-        if (tail) { if (generic) VQ_LAUNCH_GEMM(4, true, true); else VQ_LAUNCH_GEMM(4, true, false); }
-        else      { if (generic) VQ_LAUNCH_GEMM(4, false, true); else VQ_LAUNCH_GEMM(4, false, false); }
+    Out out = kAnyRow;
+    if (a.N % 8 == 0 && !a.acc_out && a.N < (1 << 21)) {
+        if (a.N % 32 == 0 && (uintptr_t)a.y % 64 == 0) out = kHalfLines;
+        else if (w_bits != 16) out = kChunks;
     }
+#define VQ_LAUNCH_GEMM(BITS, TAIL, OUT) \
+    hipLaunchKernelGGL((gemm_i8_dequant<S, BITS, TAIL, OUT>), grid, block, 0, stream, a)
+#define VQ_LAUNCH_OUT(BITS, TAIL)                                           \
+    do {                                                                    \
+        if (out == kHalfLines) VQ_LAUNCH_GEMM(BITS, TAIL, kHalfLines);      \
+        else if (out == kAnyRow) VQ_LAUNCH_GEMM(BITS, TAIL, kAnyRow);       \
+        else if constexpr (BITS != 16) VQ_LAUNCH_GEMM(BITS, TAIL, kChunks); \
+    } while (0)
+#define VQ_LAUNCH_BITS(BITS)                  \
+    do {                                      \
+        if (tail) VQ_LAUNCH_OUT(BITS, true);  \
+        else VQ_LAUNCH_OUT(BITS, false);      \
+    } while (0)
+    if (w_bits == 8) VQ_LAUNCH_BITS(8);
+    else if (w_bits == 16) VQ_LAUNCH_BITS(16);
+    else VQ_LAUNCH_BITS(4);
+#undef VQ_LAUNCH_BITS
+#undef VQ_LAUNCH_OUT
 #undef VQ_LAUNCH_GEMM
     return hipGetLastError();
 }
