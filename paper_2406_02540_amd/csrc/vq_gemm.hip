@@ -1,7 +1,7 @@
 // The int8 (and packed 4-bit, and fp16 comparison) GEMM with the dequantization epilogue:
 // the 256 x 256 workgroup tile of the kernel template in vq_gemm_kernel.h, and the choice
-// between it, the 256 x 192 tile (vq_gemm_192.hip) and the smaller tiles of
-// vq_gemm_tiles.hip for a given problem.
+// between it, the 256 x 192 tile (vq_gemm_192.hip) and the smaller tiles of vq_gemm_tiles.hip and
+// vq_gemm_split.hip for a given problem.
 #include "vq_gemm_kernel.h"
 
 namespace vq {
@@ -9,24 +9,38 @@ namespace vq {
 namespace {
 typedef TileShape<2, 4, 4> Tile256;  // 2 x 4 wavefronts of 128 tokens x 64 channels
 
-// How long a launch takes, in microseconds: `base`, plus for every time a CU is filled with
-// `per_cu` workgroups fixed + stage * (stages of 128 bytes of K), plus the same of a last filling
-// with one workgroup only.  Fitted by least squares over 720 random problems (1 to 12000 tokens, 32
-// to 4608 channels, K 256 to 4608, 8- and 4-bit weights), each timed with every tile in captured
-// graphs: mean error 6 to 11 %.  On another 22000 problems of the same ranges (M to 32768), with the kernels
-// as they are, the tile chosen by it is on average 0.4 % slower than the best one of each problem.
+// How long a launch takes, in microseconds.  Tiles that all wavefronts of a workgroup share: `base`, plus for
+// every time a CU is filled with `per_cu` workgroups fixed + stage * (stages of 128 bytes of K), plus the
+// same of a last filling with one workgroup only; widen is what 4-bit weights add to a stage.
+// Both tables fitted by least squares over 20000 random problems (1 to 32768 tokens, 32 to 4608 channels, K 256
+// to 4608, 8- and 4-bit weights), each timed with every tile in captured graphs, where the tile was within
+// 15 % of the best: error 6 to 9 %.  Over those problems the tile chosen is on average 0.1 % (above 1e9
+// multiply-adds) and 0.8 % (below 6e9) slower than the best one.
 struct TileCost {
     int tile_t, tile_c, per_cu;
-    double base, fixed, stage, fixed_one, stage_one;
+    double base, fixed, stage, widen, fixed_one, stage_one, widen_one;
 };
 constexpr TileCost kTileCosts[] = {
-    {32, 32, 2, 2.08, 2.01, 0.194, 1.50, 0.147},
-    {64, 64, 2, 2.24, 2.69, 0.376, 1.49, 0.213},
-    {128, 64, 2, 2.31, 3.69, 0.566, 1.76, 0.321},
-    {128, 128, 1, 0.0, 4.90, 0.413, 0.0, 0.0},
-    {128, 256, 1, 0.0, 5.40, 0.692, 0.0, 0.0},
-    {256, 192, 1, 0.0, 5.91, 0.966, 0.0, 0.0},
-    {256, 256, 1, 0.0, 7.16, 1.000, 0.0, 0.0},
+    {64, 64, 2, 2.352, 1.976, 0.356, 0.090, 1.094, 0.214, 0.091},
+    {128, 64, 2, 2.853, 3.099, 0.524, 0.044, 1.402, 0.348, 0.049},
+    {128, 128, 1, 1.755, 4.338, 0.447, 0.011, 0.0, 0.0, 0.0},
+    {128, 256, 1, 2.172, 4.888, 0.799, 0.106, 0.0, 0.0, 0.0},
+    {256, 192, 1, 2.793, 4.331, 1.175, 0.0, 0.0, 0.0, 0.0},
+    {256, 256, 1, 2.092, 5.635, 1.313, 0.0, 0.0, 0.0, 0.0},
+};
+// Tiles whose K the `waves` wavefronts of a workgroup divide: `base`, plus for every workgroup of a CU `fixed`
+// and, per line of K, `line` and `load` for every 8 KiB that it loads, plus `turn` for every line that a
+// wavefront takes in each filling.
+struct SplitCost {
+    int tile_t, tile_c, waves, per_cu;
+    double base, fixed, load, turn, line;
+};
+constexpr SplitCost kSplitCosts[] = {
+    {32, 32, 8, 2, 2.6115, 0.4736, 0.0452, 0.0, 0.0256},
+    {64, 32, 4, 3, 2.6745, 0.3895, 0.0652, 0.1934, 0.0098},
+    {32, 32, 3, 4, 2.6668, 0.1790, 0.0475, 0.1583, 0.0130},
+    {64, 64, 8, 1, 0.9718, 2.9382, 0.0767, 0.0, 0.0308},
+    {32, 32, 6, 3, 2.6853, 0.3465, 0.0392, 0.0, 0.0346},
 };
 
 // Workgroups of the busiest CU: every XCD takes an equal run of tiles.
@@ -37,12 +51,19 @@ long tiles_per_cu(int M, int N, int tile_t, int tile_c, int num_cus) {
     return (per_xcd + cus_per_xcd - 1) / cus_per_xcd;
 }
 
-double launch_cost(const TileCost& c, int M, int N, int K, int num_cus) {
+double launch_cost(const TileCost& c, int w_bits, int M, int N, int K, int num_cus) {
     const long rounds = tiles_per_cu(M, N, c.tile_t, c.tile_c, num_cus);
-    const long nk = (K + kTileK - 1) / kTileK;
-    double t = c.base + (double)(rounds / c.per_cu) * (c.fixed + c.stage * (double)nk);
-    if (rounds % c.per_cu) t += c.fixed_one + c.stage_one * (double)nk;
+    const double nk = (double)((K + kTileK - 1) / kTileK), wide = w_bits == 4 ? 1.0 : 0.0;
+    double t = c.base + (double)(rounds / c.per_cu) * (c.fixed + (c.stage + wide * c.widen) * nk);
+    if (rounds % c.per_cu) t += c.fixed_one + (c.stage_one + wide * c.widen_one) * nk;
     return t;
+}
+
+double launch_cost(const SplitCost& c, int w_bits, int M, int N, int K, int num_cus) {
+    const long rounds = tiles_per_cu(M, N, c.tile_t, c.tile_c, num_cus), nl = (K + kTileK - 1) / kTileK;
+    const double loaded = ((M < c.tile_t ? M : c.tile_t) + c.tile_c * w_bits / 8.0) / 64.0;   // (rows past M are not loaded)
+    return c.base + (double)rounds * (c.fixed + (double)nl * (c.line + c.load * loaded)) +
+           (double)((rounds + c.per_cu - 1) / c.per_cu * ((nl + c.waves - 1) / c.waves)) * c.turn;
 }
 }  // namespace
 
@@ -55,15 +76,36 @@ hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, in
         if (w_bits == 16 && c.tile_t != 256) continue;  // (the fp16 layer has the persistent kernel only)
         // fp16: rounds of tiles, the narrower tile (a sixth more operand bytes per multiply-add) only where it saves some
         const double cost = w_bits == 16 ? (double)tiles_per_cu(M, N, 256, c.tile_c, num_cus) * c.tile_c * (c.tile_c == 192 ? 1.05 : 1.0)
-                                         : launch_cost(c, M, N, K, num_cus);
+                                         : launch_cost(c, w_bits, M, N, K, num_cus);
         if (!best || cost <= best_cost) {
             best = &c;
             best_cost = cost;
         }
     }
-    if (best->tile_t != 256)
-        return launch_gemm_tiles(best->tile_t, best->tile_c, xq, x_scale, w, w_bits, w_scale, bias_f16, y_f16, acc_out, M, N,
-                                 K, stream);
+    const SplitCost* split = nullptr;
+    if (w_bits != 16)
+        for (const SplitCost& c : kSplitCosts) {
+            const double cost = launch_cost(c, w_bits, M, N, K, num_cus);
+            if (cost < best_cost) {
+                split = &c;
+                best_cost = cost;
+            }
+        }
+    if (split || best->tile_t != 256) {
+        TileArgs t{};
+        t.xq = xq;
+        t.x_scale = x_scale;
+        t.w = w;
+        t.w_scale = w_scale;
+        t.bias = (const _Float16*)bias_f16;
+        t.y = (_Float16*)y_f16;
+        t.acc_out = acc_out;
+        t.M = M;
+        t.N = N;
+        t.K = K;
+        if (split) return launch_gemm_split(split->tile_t, split->tile_c, split->waves, t, w_bits, stream);
+        return launch_gemm_tiles(best->tile_t, best->tile_c, t, w_bits, stream);
+    }
     GemmArgs a;
     a.xq = xq;
     a.x_scale = x_scale;

@@ -143,4 +143,99 @@ __device__ __forceinline__ int opaque(int v) {
     return v;
 }
 
+// ---- kernels that take one tile per workgroup ------------------------------------------------
+// ceil(2^32 / d): the high half of n times this is n / d for 2 <= d and n * d < 2^32 (the product exceeds
+// n / d by less than n / 2^32 < 1 / d).  The kernel begins with two divisions, and a division by a number
+// that is not known is 25 dependent instructions.
+inline unsigned reciprocal_of(unsigned d) { return 0xFFFFFFFFu / d + 1u; }
+
+constexpr int kTileXcds = 8;
+constexpr int kTileBand = 8;     // token tiles per band in the tile order
+
+struct TileGrid {
+    int tiles, tiles_per_xcd, tiles_c, tiles_t;
+    unsigned div_band, div_last;   // reciprocals of a band's tiles and of the last band's rows (reciprocal_of), or 0
+};
+
+// The grid for tiles of t x c outputs; false if there are too many.
+inline bool tile_grid(TileGrid& g, int M, int N, int t, int c) {
+    g.tiles_t = (M + t - 1) / t;
+    g.tiles_c = (N + c - 1) / c;
+    const long tiles = (long)g.tiles_t * g.tiles_c;
+    if (tiles > 0x7FFFFF00l) return false;
+    g.tiles = (int)tiles;
+    g.tiles_per_xcd = (g.tiles + kTileXcds - 1) / kTileXcds;
+    const int last = g.tiles_t % kTileBand;
+    const bool small = g.tiles < 65536 && kTileBand * (long)g.tiles_c < 65536;
+    g.div_band = small ? reciprocal_of((unsigned)(kTileBand * g.tiles_c)) : 0;
+    g.div_last = small && last > 1 ? reciprocal_of((unsigned)last) : 0;
+    return true;
+}
+
+struct TileArgs {
+    const int8_t* xq;
+    const float* x_scale;
+    const void* w;
+    const float* w_scale;
+    const _Float16* bias;
+    _Float16* y;
+    int32_t* acc_out;
+    int M, N, K;
+    TileGrid grid;
+};
+
+// vq_gemm_tiles.hip: 64 x 64, 128 x 64, 128 x 128 or 128 x 256, the wavefronts sharing the tile.  w_bits 8 or 4.
+hipError_t launch_gemm_tiles(int tile_t, int tile_c, const TileArgs& a, int w_bits, hipStream_t stream);
+// vq_gemm_split.hip: 32 x 32 (3, 6 or 8 wavefronts), 64 x 32 (4) or 64 x 64 (8), the wavefronts dividing K.
+hipError_t launch_gemm_split(int tile_t, int tile_c, int waves, const TileArgs& a, int w_bits, hipStream_t stream);
+
+// The workgroup's tile, or false.  Workgroup ids are dealt round-robin to the XCDs: each gets a contiguous
+// run of tiles, in bands of token tiles, column by column within a band, so that its L2 sees few panels.
+__device__ __forceinline__ bool locate_tile(const TileGrid& g, int& row, int& col) {
+    const int logical = (blockIdx.x % kTileXcds) * g.tiles_per_xcd + blockIdx.x / kTileXcds;
+    if ((int)(blockIdx.x / kTileXcds) >= g.tiles_per_xcd || logical >= g.tiles) return false;
+    const int band_tiles = kTileBand * g.tiles_c;
+    const int band = g.div_band ? (int)__umulhi((unsigned)logical, g.div_band) : logical / band_tiles;
+    const int in_band = logical - band * band_tiles;
+    const int band_rows = min(g.tiles_t - band * kTileBand, kTileBand);
+    if (band_rows == kTileBand) col = in_band / kTileBand;
+    else if (g.div_last) col = (int)__umulhi((unsigned)in_band, g.div_last);
+    else col = in_band / band_rows;
+    row = band * kTileBand + in_band - col * band_rows;
+    return true;
+}
+
+// Eight neighbouring channels of a token: sums, dequantized and written; `left` of them exist.
+// (Rows of Y start at any even address.  The 4-bit path summed 16 * w.)
+template <int W_BITS>
+__device__ __forceinline__ void write_eight(v4i v0, v4i v1, float xs, v4f s0, v4f s1, v4i bias8, int left, _Float16* y, int32_t* acc) {
+    typedef v4i v4i_any __attribute__((aligned(2)));
+    typedef v4i v4i_any4 __attribute__((aligned(4)));
+    constexpr int kAccShift = (W_BITS == 4) ? 4 : 0;
+    xs *= (W_BITS == 4) ? 0.0625f : 1.0f;
+    v4i out;
+    out[0] = (int)dequant_pair((float)v0[0], xs * s0[0], (float)v0[1], xs * s0[1], (unsigned)bias8[0]);
+    out[1] = (int)dequant_pair((float)v0[2], xs * s0[2], (float)v0[3], xs * s0[3], (unsigned)bias8[1]);
+    out[2] = (int)dequant_pair((float)v1[0], xs * s1[0], (float)v1[1], xs * s1[1], (unsigned)bias8[2]);
+    out[3] = (int)dequant_pair((float)v1[2], xs * s1[2], (float)v1[3], xs * s1[3], (unsigned)bias8[3]);
+    if (left >= 8) {
+        *(v4i_any*)y = out;
+    } else {
+        const half8 o = (half8)out;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (e < left) y[e] = o[e];
+    }
+    if (acc) {
+        if (left >= 8) {
+            *(v4i_any4*)acc = v0 >> kAccShift;
+            *(v4i_any4*)(acc + 4) = v1 >> kAccShift;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (e < left) acc[e] = (e < 4 ? v0[e & 3] : v1[e & 3]) >> kAccShift;
+        }
+    }
+}
+
 }  // namespace vq

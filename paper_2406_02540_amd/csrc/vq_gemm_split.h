@@ -1,0 +1,236 @@
+// int8 x int8 -> int32 MFMA GEMM with the dequantization epilogue for the smallest problems (same
+// arithmetic as vq_gemm_kernel.h; ViDiT-Q appendix "Hardware implementation of quantized linear
+// layers"): one tile per workgroup, and the wavefronts of a workgroup divide K, not the tile.
+//
+// A wavefront takes every KW-th line (128 bytes of K) of the tile's rows: it loads the line into LDS
+// space of its own, waits for its own loads, multiplies the whole tile over that line and asks for its
+// next one.  Nothing is shared until the sums meet at the end, so there is one workgroup barrier in
+// the kernel and none per stage; a wavefront that waits for memory holds up nobody, and every operand
+// byte is read from LDS once.
+//
+// What bounds such a launch is the way to the first load, one memory latency and the CU's load path (54
+// bytes per cycle).  Where the wavefronts share the tile (vq_gemm_tiles_kernel.h) a stage of a 32 x 32
+// tile took 350 cycles, for barrier, LDS latency and one product each, and with 4-bit weights 500.  In a
+// captured graph, where an empty kernel is 1.7 us, with 32 x 32 (64 x 32, 64 x 64) tiles, us:
+//   tokens x K -> channels   W8 shared / divided   W4 shared / divided
+//   16 x 1152 -> 1152            3.9 / 3.05            4.5 / 3.1
+//   16 x 4608 -> 1152            7.05 / 4.25           9.4 / 4.1
+//   100 x 512 -> 700             3.2 / 3.15            3.5 / 3.2
+//   256 x 1152 -> 1152           4.65 / 3.7            5.1 / 3.6
+//   240 x 4096 -> 2304           9.7 / 9.1            12.1 / 8.3
+// A wavefront's next loads leave in a burst as soon as its operands are in registers, ahead of its
+// products; dealt out between the products they were up to 10 % later with 32 x 32 tiles.  Above 100 channel
+// and token tiles per XCD the operand bytes count, and sharing the tile wins.
+#pragma once
+#include <type_traits>
+
+#include "vq_gemm_common.h"
+#include "vq_internal.h"
+
+namespace vq {
+namespace {
+
+constexpr int kLine = 128;        // K bytes per line
+
+// (32 BT) tokens x (32 BC) channels, KW wavefronts; WGS workgroups share a CU.
+template <int BT_, int BC_, int KW_, int WGS_>
+struct SplitTile {
+    static constexpr int BT = BT_, BC = BC_, KW = KW_, WGS = WGS_;
+    static constexpr int kThreads = 64 * KW;
+    static constexpr int kWavesPerSimd = (KW * WGS_ + 3) / 4;
+    static constexpr int kT = 32 * BT, kC = 32 * BC;
+    static constexpr int kSums = kT * kC * 4;
+    static constexpr int slot(int w_bits) {   // a wavefront's LDS: its line of both operands, then its sums
+        const int line = kT * kLine + kC * kLine * w_bits / 8;
+        return line > kSums ? line : kSums;
+    }
+};
+
+template <class S, int W_BITS, bool K_TAIL>
+__global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant_split(
+    const int8_t* xq, const void* w, int M, int N, int K, int tiles, int tiles_per_xcd, int tiles_c, int tiles_t,
+    unsigned div_band, unsigned div_last, const float* x_scale, const float* w_scale, const _Float16* bias, _Float16* y,
+    int32_t* acc_out) {
+    constexpr int BT = S::BT, BC = S::BC, KW = S::KW;
+    constexpr int kSlot = S::slot(W_BITS);
+    static_assert(kSlot * KW * S::WGS <= 160 * 1024, "LDS of one CU");
+    __shared__ __attribute__((aligned(1024))) int8_t lds[kSlot * KW];
+    int row, col;
+    if (!locate_tile(TileGrid{tiles, tiles_per_xcd, tiles_c, tiles_t, div_band, div_last}, row, col)) return;
+    const int tok0 = row * S::kT, ch0 = col * S::kC;   // (< M, < N)
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int kWDiv = (W_BITS == 8) ? 1 : 2;
+    const int rows_x = min(S::kT, M - tok0), rows_w = min(S::kC, N - ch0);
+    const int nl = (K + kLine - 1) / kLine;
+
+    // ---- global -> LDS: one load fills 1 KiB, 8 rows x 128 B (lane l: row l/8, physical chunk l%8
+    // holding logical chunk (l%8) ^ ((row/2)%8)) or, for packed nibbles, 16 rows x 64 B (row l/4, chunk
+    // (l%4) ^ ((row/4)%4)).  Rows past the tile's last one lie behind the buffers.
+    int8_t* const mine = lds + wave * kSlot;
+    const unsigned mine_addr = (unsigned)(uintptr_t)(lds_ptr)mine;
+    constexpr int kXLoads = 4 * BT, kWLoads = (W_BITS == 8) ? 4 * BC : 2 * BC, kWAt = S::kT * kLine;
+    const v4i rsrc_x = make_rsrc(xq + (long)tok0 * K, (unsigned)(rows_x * K));
+    const v4i rsrc_w = make_rsrc((const int8_t*)w + (long)ch0 * (K / kWDiv), (unsigned)(rows_w * (K / kWDiv)));
+    int vx[kXLoads], vw[kWLoads];
+    // (row groups all have the swizzle of row l/8 with bit 2 of row/2 from the group's parity)
+#pragma unroll
+    for (int g = 0; g < kXLoads; ++g) {
+        const int r = g * 8 + (lane >> 3);
+        vx[g] = __mul24(r, K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+    }
+#pragma unroll
+    for (int g = 0; g < kWLoads; ++g) {
+        if (W_BITS == 8) {
+            const int r = g * 8 + (lane >> 3);
+            vw[g] = __mul24(r, K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+        } else {
+            const int r = g * 16 + (lane >> 2);
+            vw[g] = __mul24(r, K / 2) + (((lane & 3) ^ ((r >> 2) & 3)) << 4);
+        }
+    }
+    constexpr int kLoads = kWLoads + kXLoads;
+    auto issue_one = [&](int line, int i) __attribute__((always_inline)) {
+        const int k0 = line * kLine;
+        if (i < kWLoads) {
+            constexpr int kRowsPer = (W_BITS == 8) ? 8 : 16;
+            const int at = (W_BITS == 8) ? ((lane & 7) ^ (((i * 8 + (lane >> 3)) >> 1) & 7)) << 4
+                                         : ((lane & 3) ^ (((i * 16 + (lane >> 2)) >> 2) & 3)) << 4;
+            if (i * kRowsPer < rows_w)   // (uniform)
+                load_stage_to_lds_16<K_TAIL>(rsrc_w, mine_addr + kWAt + i * 1024, vw[i], k0 / kWDiv, K / kWDiv - at);
+        } else {
+            const int g = i - kWLoads;
+            const int at = ((lane & 7) ^ (((g * 8 + (lane >> 3)) >> 1) & 7)) << 4;
+            if (g * 8 < rows_x) load_stage_to_lds_16<K_TAIL>(rsrc_x, mine_addr + g * 1024, vx[g], k0, K - at);
+        }
+    };
+    auto issue = [&](int line) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) issue_one(line, i);
+    };
+    if (wave < nl) issue(wave);
+
+    // What the way out needs, asked for here (in three loads: eight scales, eight biases and a token's scale one
+    // by one were 0.5 us of 3.7 at 16 x 1152 -> 1152): a thread takes eight consecutive channels of kItems tokens.
+    constexpr int kPerRow = S::kC / 8, kRowStep = S::kThreads / kPerRow;
+    constexpr int kItems = (S::kT + kRowStep - 1) / kRowStep;
+    static_assert(kRowStep * kPerRow == S::kThreads, "whole rows of threads");
+    const int c0 = (tid % kPerRow) * 8, t0 = tid / kPerRow;
+    // (range-checked, dword by dword: channels past N read as zero)
+    const __amdgpu_buffer_rsrc_t rs_ws = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w_scale), 0, N * 4, kRsrcFlags);
+    const v4f s0 = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs_ws, (ch0 + c0) * 4, 0, 0));
+    const v4f s1 = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs_ws, (ch0 + c0) * 4 + 16, 0, 0));
+    v4i bias8 = {0, 0, 0, 0};
+    if (bias) {
+        if (c0 + 8 <= rows_w) {
+            bias8 = *(const v4i*)(bias + ch0 + c0);
+        } else {
+            half8 b{};
+#pragma unroll
+            for (int e = 0; e < 7; ++e)
+                if (c0 + e < rows_w) b[e] = bias[ch0 + c0 + e];
+            bias8 = (v4i)b;
+        }
+    }
+    float xsc[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) xsc[i] = x_scale[tok0 + min(t0 + i * kRowStep, rows_x - 1)];
+
+    // ---- a line at a time ------------------------------------------------------------------
+    const int fr_row = lane & 31;
+    const int x_off0 = fr_row * kLine + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4);
+    const int w_off0 = kWAt + ((W_BITS == 8) ? x_off0 : fr_row * (kLine / 2) + (((fr_row >> 2) & 3) << 4) + (lane >> 5) * 8);
+    v16i acc[BC][BT];
+#pragma unroll
+    for (int cb = 0; cb < BC; ++cb)
+#pragma unroll
+        for (int tb = 0; tb < BT; ++tb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[cb][tb][r] = 0;
+    typedef typename std::conditional<W_BITS == 8, v4i, v2i>::type raw_t;
+#pragma unroll 1
+    for (int line = wave; line < nl; line += KW) {
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        v4i xf[4][BT];
+        raw_t wf[4][BC];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+            for (int cb = 0; cb < BC; ++cb)
+                wf[ks][cb] = *(const raw_t*)(mine + (w_off0 ^ (ks << (W_BITS == 8 ? 5 : 4))) + cb * 32 * (kLine / kWDiv));
+#pragma unroll
+            for (int tb = 0; tb < BT; ++tb) xf[ks][tb] = *(const v4i*)(mine + (x_off0 ^ (ks << 5)) + tb * 32 * kLine);
+        }
+        if (line + KW < nl) {   // (the operands are in registers: the space is free)
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+            issue(line + KW);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int cb = 0; cb < BC; ++cb) {
+                v4i wv;
+                if constexpr (W_BITS == 8) wv = wf[ks][cb];
+                else wv = widen_nibbles(wf[ks][cb]);
+#pragma unroll
+                for (int tb = 0; tb < BT; ++tb)
+                    acc[cb][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wv, xf[ks][tb], acc[cb][tb], 0, 0, 0);
+            }
+    }
+
+    // ---- the sums, through LDS, to rows of the output ------------------------------------------------
+    // Every wavefront leaves its sums where its lines were, as a row-major int32 tile, 16-byte chunks
+    // (four channels) XOR-ed by the row; a thread adds up eight consecutive channels of a token,
+    // dequantizes and writes 16 bytes.
+    constexpr int kXor = (S::kC / 4) % 16 == 0 ? 15 : 7;
+    constexpr int kRow = S::kC * 4;
+    if (wave < nl) {
+        int8_t* const row = mine + (lane & 31) * kRow;
+#pragma unroll
+        for (int cb = 0; cb < BC; ++cb)
+#pragma unroll
+            for (int tb = 0; tb < BT; ++tb)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {   // register 4j + i is channel 8j + 4 (lane/32) + i of the block
+                    const int chunk = cb * 8 + 2 * j + (lane >> 5);
+                    *(v4i*)(row + tb * 32 * kRow + ((chunk ^ (lane & kXor)) << 4)) =
+                        v4i{acc[cb][tb][4 * j], acc[cb][tb][4 * j + 1], acc[cb][tb][4 * j + 2], acc[cb][tb][4 * j + 3]};
+                }
+    }
+    wait_lds_and_barrier();
+    if (c0 >= rows_w) return;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+        const int t = t0 + i * kRowStep;
+        if (t >= rows_x) return;
+        v4i v0 = {0, 0, 0, 0}, v1 = v0;
+#pragma unroll
+        for (int g = 0; g < KW; ++g) {
+            if (g >= nl) break;   // (uniform)
+            const int8_t* sums = lds + g * kSlot + t * kRow;
+            v0 += *(const v4i*)(sums + (((c0 >> 2) ^ (t & kXor)) << 4));
+            v1 += *(const v4i*)(sums + ((((c0 >> 2) + 1) ^ (t & kXor)) << 4));
+        }
+        const long at = (long)(tok0 + t) * N + ch0 + c0;
+        write_eight<W_BITS>(v0, v1, xsc[i], s0, s1, bias8, rows_w - c0, y + at, acc_out ? acc_out + at : nullptr);
+    }
+}
+
+template <class S, int W_BITS>
+hipError_t launch_split_tile(const TileArgs& a, hipStream_t stream) {
+    TileGrid g;
+    if (!tile_grid(g, a.M, a.N, S::kT, S::kC)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(g.tiles_per_xcd * kTileXcds)), block(S::kThreads);
+#define VQ_SPLIT(TAIL)                                                                                                \
+    hipLaunchKernelGGL((gemm_i8_dequant_split<S, W_BITS, TAIL>), grid, block, 0, stream, a.xq, a.w, a.M, a.N, a.K,   \
+                       g.tiles, g.tiles_per_xcd, g.tiles_c, g.tiles_t, g.div_band, g.div_last, a.x_scale, a.w_scale, \
+                       a.bias, a.y, a.acc_out)
+    if (a.K % kLine) VQ_SPLIT(true);
+    else VQ_SPLIT(false);
+#undef VQ_SPLIT
+    return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace vq

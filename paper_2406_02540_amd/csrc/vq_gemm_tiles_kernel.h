@@ -32,29 +32,9 @@
 
 namespace vq {
 
-struct TileArgs {
-    const int8_t* xq;
-    const float* x_scale;
-    const void* w;
-    const float* w_scale;
-    const _Float16* bias;
-    _Float16* y;
-    int32_t* acc_out;
-    int M, N, K;
-    int tiles_t, tiles_c, tiles, tiles_per_xcd;
-    unsigned div_band, div_last;   // reciprocals of a band's tiles and of the last band's rows (reciprocal_of), or 0
-};
-
-// ceil(2^32 / d): the high half of n times this is n / d for 2 <= d and n * d < 2^32 (the product exceeds
-// n / d by less than n / 2^32 < 1 / d).  The kernel begins with two divisions, and a division by a number
-// that is not known is 25 dependent instructions.
-inline unsigned reciprocal_of(unsigned d) { return 0xFFFFFFFFu / d + 1u; }
-
 namespace {
 
 constexpr int kStageK = 128;      // K bytes per stage
-constexpr int kTileXcds = 8;
-constexpr int kTileBand = 8;     // token tiles per band in the tile order
 
 template <int WT_, int WC_, int BT_, int BC_, int KW_, int RING_, int WGS_>
 struct OneTile {
@@ -110,20 +90,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     const unsigned lds_x_addr = (unsigned)(uintptr_t)(lds_ptr)lds_x;
     const unsigned lds_w_addr = (unsigned)(uintptr_t)(lds_ptr)lds_w;
 
-    // Workgroup ids are dealt round-robin to the XCDs: each gets a contiguous run of tiles, in
-    // bands of token tiles, column by column within a band, so that its L2 sees few panels.
-    const int logical = (blockIdx.x % kTileXcds) * a.tiles_per_xcd + blockIdx.x / kTileXcds;
-    if ((int)(blockIdx.x / kTileXcds) >= a.tiles_per_xcd || logical >= a.tiles) return;
-    const int band_tiles = kTileBand * a.tiles_c;
-    const int band = a.div_band ? (int)__umulhi((unsigned)logical, a.div_band) : logical / band_tiles;
-    const int in_band = logical - band * band_tiles;
-    const int band_rows = min(a.tiles_t - band * kTileBand, kTileBand);
-    int col;
-    if (band_rows == kTileBand) col = in_band / kTileBand;
-    else if (a.div_last) col = (int)__umulhi((unsigned)in_band, a.div_last);
-    else col = in_band / band_rows;
-    const int tok0 = (band * kTileBand + in_band - col * band_rows) * kRows;   // (< M)
-    const int ch0 = col * S::kC;                                               // (< N)
+    int row, col;
+    if (!locate_tile(a.grid, row, col)) return;
+    const int tok0 = row * kRows, ch0 = col * S::kC;   // (< M, < N)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -346,10 +315,6 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     if (c0 >= rows_w) return;
     const v4f s0 = *(const v4f*)(lds_sc + c0 * 4), s1 = *(const v4f*)(lds_sc + c0 * 4 + 16);
     const v4i bias8 = *(const v4i*)(lds_sc + S::kC * 4 + S::kT * 4 + c0 * 2);
-    _Float16* const ytile = a.y + (long)tok0 * a.N + ch0;
-    const bool whole = c0 + 8 <= rows_w;
-    typedef v4i v4i_any __attribute__((aligned(2)));   // (rows of Y start at any even address)
-    constexpr int kAccShift = (W_BITS == 4) ? 4 : 0;   // (the 4-bit path summed 16 * w)
 #pragma unroll 1
     for (int t = tid / kPerRow; t < rows_x; t += kRowStep) {
         v4i v0 = {0, 0, 0, 0}, v1 = v0;
@@ -359,50 +324,17 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             v0 += *(const v4i*)(row + (((c0 >> 2) ^ (t & kXor)) << 4));
             v1 += *(const v4i*)(row + ((((c0 >> 2) + 1) ^ (t & kXor)) << 4));
         }
-        const float xsc = *(const float*)(lds_sc + S::kC * 4 + t * 4) * ((W_BITS == 4) ? 0.0625f : 1.0f);
-        v4i out;
-        out[0] = (int)dequant_pair((float)v0[0], xsc * s0[0], (float)v0[1], xsc * s0[1], (unsigned)bias8[0]);
-        out[1] = (int)dequant_pair((float)v0[2], xsc * s0[2], (float)v0[3], xsc * s0[3], (unsigned)bias8[1]);
-        out[2] = (int)dequant_pair((float)v1[0], xsc * s1[0], (float)v1[1], xsc * s1[1], (unsigned)bias8[2]);
-        out[3] = (int)dequant_pair((float)v1[2], xsc * s1[2], (float)v1[3], xsc * s1[3], (unsigned)bias8[3]);
-        _Float16* const yrow = ytile + (long)t * a.N + c0;
-        if (whole) {
-            *(v4i_any*)yrow = out;
-        } else {
-            const half8 o = (half8)out;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (c0 + e < rows_w) yrow[e] = o[e];
-        }
-        if (a.acc_out) {
-            int32_t* const arow = a.acc_out + (long)(tok0 + t) * a.N + ch0 + c0;
-            if (whole) {
-                typedef v4i v4i_any4 __attribute__((aligned(4)));
-                *(v4i_any4*)arow = v0 >> kAccShift;
-                *(v4i_any4*)(arow + 4) = v1 >> kAccShift;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (c0 + e < rows_w) arow[e] = (e < 4 ? v0[e & 3] : v1[e & 3]) >> kAccShift;
-            }
-        }
+        const float xsc = *(const float*)(lds_sc + S::kC * 4 + t * 4);
+        const long at = (long)(tok0 + t) * a.N + ch0 + c0;
+        write_eight<W_BITS>(v0, v1, xsc, s0, s1, bias8, rows_w - c0, a.y + at, a.acc_out ? a.acc_out + at : nullptr);
     }
 }
 
 template <class S, class Q, int W_BITS>
 hipError_t launch_tile_shape(TileArgs a, const typename Q::Args& qa, hipStream_t stream) {
     constexpr int rows = Q::kQuantizes ? Q::kRows : S::kT;
-    a.tiles_t = (a.M + rows - 1) / rows;
-    a.tiles_c = (a.N + S::kC - 1) / S::kC;
-    const long tiles = (long)a.tiles_t * a.tiles_c;
-    if (tiles > 0x7FFFFF00l) return hipErrorInvalidValue;
-    a.tiles = (int)tiles;
-    a.tiles_per_xcd = (a.tiles + kTileXcds - 1) / kTileXcds;
-    const int last = a.tiles_t % kTileBand;
-    const bool small = a.tiles < 65536 && kTileBand * (long)a.tiles_c < 65536;
-    a.div_band = small ? reciprocal_of((unsigned)(kTileBand * a.tiles_c)) : 0;
-    a.div_last = small && last > 1 ? reciprocal_of((unsigned)last) : 0;
-    const dim3 grid((unsigned)(a.tiles_per_xcd * kTileXcds)), block(S::kThreads);
+    if (!tile_grid(a.grid, a.M, a.N, rows, S::kC)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(a.grid.tiles_per_xcd * kTileXcds)), block(S::kThreads);
     // (a workgroup that quantizes is not slowed by the tail's two instructions per load: one kernel for both)
     if (Q::kQuantizes || a.K % kStageK) {
         hipLaunchKernelGGL((gemm_i8_dequant_tile<S, Q, W_BITS, true>), grid, block, 0, stream, a, qa);

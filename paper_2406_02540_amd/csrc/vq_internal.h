@@ -53,12 +53,6 @@ hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, in
                        const float* w_scale, const void* bias_f16, void* y_f16, int32_t* acc_out,
                        int M, int N, int K, int num_cus, hipStream_t stream);
 
-// The one-tile-per-workgroup kernel that launch_gemm switches to below the persistent kernel's
-// sizes; tile_t x tile_c: 32 x 32, 64 x 64, 128 x 64, 128 x 128 or 128 x 256.  w_bits 8 or 4.
-hipError_t launch_gemm_tiles(int tile_t, int tile_c, const int8_t* xq, const float* x_scale, const void* w, int w_bits,
-                             const float* w_scale, const void* bias_f16, void* y_f16, int32_t* acc_out,
-                             int M, int N, int K, hipStream_t stream);
-
 // A layer of few tokens in one launch (vq_linear_small.hip): quantizer, with its producer, and GEMM.
 // small_layer: whether it is the faster way for these sizes.
 bool small_layer(int producer, int M, int N, int K, int num_cus);

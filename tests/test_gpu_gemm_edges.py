@@ -17,7 +17,7 @@ def vq():
     return pkg
 
 
-def check_gemm(vq, bits, M, N, K, seed=3):
+def check_gemm(vq, bits, M, N, K, seed=3, at=0):
     """Integer sums from float64 products (exact: |sum| <= K * 127^2 < 2^53), outputs from them in
     float64 rounded once: the dequantization is one rounding of an exact multiply-add."""
     print(f"w{bits}a8 M={M} N={N} K={K}", flush=True)
@@ -34,11 +34,11 @@ def check_gemm(vq, bits, M, N, K, seed=3):
     want = (acc * xs.double()[:, None] * ws.double()[None] + b.double()).half()
     gemm = vq.vq_gemm_w8a8 if bits == 8 else vq.vq_gemm_w4a8
     guard = 64
-    buf = torch.full((M * N + guard,), 7.0, dtype=torch.float16, device="cuda")
-    y = buf[:M * N].view(M, N)
+    buf = torch.full((at + M * N + guard,), 7.0, dtype=torch.float16, device="cuda")
+    y = buf[at:at + M * N].view(M, N)
     gemm(xq, xs, w, ws, b, y=y)
     assert torch.equal(y, want), (y != want).sum().item()
-    assert (buf[M * N:] == 7.0).all()
+    assert (buf[at + M * N:] == 7.0).all() and (buf[:at] == 7.0).all()
     y2, acc2 = gemm(xq, xs, w, ws, b, return_acc=True)
     assert torch.equal(y2, want) and torch.equal(acc2.double(), acc)
 
@@ -52,6 +52,15 @@ def test_unaligned_output_rows(vq, bits, M, N, K):
     check_gemm(vq, bits, M, N, K)
 
 
+# rows of whole 16-byte chunks that do not start on 64-byte boundaries, by N or by Y's address: tiles of 256 x 192
+# and of 256 x 256 in one round and in several, full and ragged
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N,K,at", [(2891, 2824, 160, 0), (2304, 4616, 288, 0), (5003, 5000, 96, 0), (9000, 4104, 96, 0),
+                                      (8192, 1152, 128, 8), (5003, 3456, 160, 8)])
+def test_output_rows_of_whole_chunks(vq, bits, M, N, K, at):
+    check_gemm(vq, bits, M, N, K, at=at)
+
+
 # one tile per workgroup, each size the launcher can choose: 32 x 32, 64 x 64, 128 x 64, 128 x 128,
 # 128 x 256, with ragged last tiles, K of one stage, of a ring's length more or less, and a tail
 @pytest.mark.parametrize("bits", [8, 4])
@@ -61,4 +70,14 @@ def test_unaligned_output_rows(vq, bits, M, N, K):
                                    (1100, 2050, 320), (1500, 2000, 1152), (2000, 1999, 4608),
                                    (1001, 4609, 1152), (1030, 4600, 128), (1025, 4097, 96)])
 def test_one_tile_per_workgroup(vq, bits, M, N, K):
+    check_gemm(vq, bits, M, N, K)
+
+
+# wavefronts that divide K, each size the launcher can choose (32 x 32 with three, six and eight of them, 64 x 32,
+# 64 x 64): fewer lines of K than wavefronts, a line more than they share evenly, tails of a line, ragged last tiles
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N,K", [(100, 1000, 160), (100, 1001, 512), (1000, 200, 800), (999, 31, 4608), (16, 1152, 4608),
+                                   (61, 1001, 1184), (500, 4607, 512), (300, 1152, 4096), (257, 1149, 4128),
+                                   (239, 2301, 4000), (240, 2304, 4096), (257, 2300, 2080)])
+def test_wavefronts_divide_k(vq, bits, M, N, K):
     check_gemm(vq, bits, M, N, K)
