@@ -182,7 +182,7 @@ template <bool BY_CHUNK = false, bool SCALE = true, bool SHIFT = true>
 struct VectorsFromMemory {
     static constexpr bool kByChunk = BY_CHUNK, kScale = SCALE, kShift = SHIFT;
     __device__ __forceinline__ bool staged(int) const { return false; }
-    __device__ __forceinline__ Vec8 chunk(int, int) const { return {}; }
+    __device__ __forceinline__ Vec8 chunk(int, int, int) const { return {}; }
     template <class Rs>
     __device__ __forceinline__ void ask(const Rs&, const Rs&, const Rs&, int) {}
     __device__ __forceinline__ void park(int) {}
@@ -205,7 +205,7 @@ struct VectorsInLds {
     int row;             // the sample whose rows are staged
     float4v v[kVecs][kPer];
     __device__ __forceinline__ bool staged(int which) const { return which < kVecs && used[which]; }
-    __device__ __forceinline__ Vec8 chunk(int which, int c) const {
+    __device__ __forceinline__ Vec8 chunk(int which, int c, int) const {
         const float4v* p = lds + which * kFloat4 + c;
         return Vec8{p[0], p[CHUNKS]};
     }
@@ -290,7 +290,7 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
     // [rows][K] array (chunks past K take the last chunk's: finite values that meet only zeros).
     auto vec_chunk = [&](int which, int row, int i) {
         const int c = min(i * LANES + sub, K8 - 1);
-        if (vectors.staged(which)) return vectors.chunk(which, c);
+        if (vectors.staged(which)) return vectors.chunk(which, c, i);
         const __amdgpu_buffer_rsrc_t& rs = which == kVecMul ? rs_cm : which == kVecA ? rs_a : rs_b;
         const int off = (row * K8 + c) * 32;
         Vec8 v;
@@ -311,10 +311,10 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
     const int b = (int)((unsigned)(row_ok ? m : a.M - 1) / (unsigned)a.tokens_per_sample);
 
     vectors.ask(rs_cm, rs_a, rs_b, K8);
-    half8 raw[NCH];
+    half8 raw[NCH];   // (chunk groups past the row are asked for too: a branch would hide from the waits what is behind it)
 #pragma unroll
     for (int i = 0; i < NCH; ++i)
-        if (i < used) raw[i] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rs_x, voff[i], 0, 2 /* nontemporal */));
+        raw[i] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rs_x, voff[i], 0, 2 /* nontemporal */));
     constexpr bool kBranchFirst = PRODUCER == kResidual && !Vectors::kByChunk;   // the residual's branch with them
     auto branch_chunk = [&](int i) {
         return __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rs_y, voff[i], 0, 2 /* nontemporal */));
@@ -323,7 +323,7 @@ __device__ __forceinline__ void produce_and_quantize(const FusedArgs& a, long w_
     if constexpr (kBranchFirst) {
 #pragma unroll
         for (int i = 0; i < NCH; ++i)
-            if (i < used) branch[i] = branch_chunk(i);
+            branch[i] = branch_chunk(i);
     }
     vectors.park(K8);   // (a workgroup barrier where the vectors are staged: every wavefront gets here)
     if (ntok == 0) return;
@@ -591,8 +591,7 @@ template <int PRODUCER, int NCH, int LANES, Staging STAGING>
 hipError_t launch_fused_staging(const FusedArgs& a, hipStream_t stream) {
     constexpr int threads = fused_threads(STAGING), rows_per_block = threads / LANES;
     const dim3 grid((unsigned)((a.M + (long)rows_per_block - 1) / rows_per_block)), block(threads);
-    hipLaunchKernelGGL((produce_quantize_tokens<PRODUCER, NCH, LANES, STAGING>), grid, block, 0, stream, a);
-    return hipGetLastError();
+    return enqueue(produce_quantize_tokens<PRODUCER, NCH, LANES, STAGING>, grid, block, stream, a);
 }
 template <int PRODUCER, int NCH, int LANES>
 hipError_t launch_fused(const FusedArgs& a, hipStream_t stream) {

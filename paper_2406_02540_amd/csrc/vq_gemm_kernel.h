@@ -685,7 +685,7 @@ hipError_t launch_gemm_shape(GemmArgs a, int w_bits, int num_cus, hipStream_t st
         else if (w_bits != 16) out = kChunks;
     }
 #define VQ_LAUNCH_GEMM(BITS, TAIL, OUT) \
-    hipLaunchKernelGGL((gemm_i8_dequant<S, BITS, TAIL, OUT>), grid, block, 0, stream, a)
+    return enqueue(gemm_i8_dequant<S, BITS, TAIL, OUT>, grid, block, stream, a)
 #define VQ_LAUNCH_OUT(BITS, TAIL)                                           \
     do {                                                                    \
         if (out == kHalfLines) VQ_LAUNCH_GEMM(BITS, TAIL, kHalfLines);      \
@@ -703,7 +703,7 @@ hipError_t launch_gemm_shape(GemmArgs a, int w_bits, int num_cus, hipStream_t st
 #undef VQ_LAUNCH_BITS
 #undef VQ_LAUNCH_OUT
 #undef VQ_LAUNCH_GEMM
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 }  // namespace

@@ -47,18 +47,16 @@ struct SplitTile {
 };
 
 template <class S, int W_BITS, bool K_TAIL>
-__global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant_split(
-    const int8_t* xq, const void* w, int M, int N, int K, int tiles, int tiles_per_xcd, int tiles_c, int tiles_t,
-    unsigned div_band, unsigned div_last, const float* x_scale, const float* w_scale, const _Float16* bias, _Float16* y,
-    int32_t* acc_out) {
+__global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant_split(const TileArgs a) {
     constexpr int BT = S::BT, BC = S::BC, KW = S::KW;
     constexpr int kSlot = S::slot(W_BITS);
     static_assert(kSlot * KW * S::WGS <= 160 * 1024, "LDS of one CU");
     __shared__ __attribute__((aligned(1024))) int8_t lds[kSlot * KW];
     int row, col;
-    if (!locate_tile(TileGrid{tiles, tiles_per_xcd, tiles_c, tiles_t, div_band, div_last}, row, col)) return;
+    if (!locate_tile(a.grid, row, col)) return;
     const int tok0 = row * S::kT, ch0 = col * S::kC;   // (< M, < N)
 
+    const int M = a.M, N = a.N, K = a.K;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int kWDiv = (W_BITS == 8) ? 1 : 2;
@@ -71,8 +69,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     int8_t* const mine = lds + wave * kSlot;
     const unsigned mine_addr = (unsigned)(uintptr_t)(lds_ptr)mine;
     constexpr int kXLoads = 4 * BT, kWLoads = (W_BITS == 8) ? 4 * BC : 2 * BC, kWAt = S::kT * kLine;
-    const v4i rsrc_x = make_rsrc(xq + (long)tok0 * K, (unsigned)(rows_x * K));
-    const v4i rsrc_w = make_rsrc((const int8_t*)w + (long)ch0 * (K / kWDiv), (unsigned)(rows_w * (K / kWDiv)));
+    const v4i rsrc_x = make_rsrc(a.xq + (long)tok0 * K, (unsigned)(rows_x * K));
+    const v4i rsrc_w = make_rsrc((const int8_t*)a.w + (long)ch0 * (K / kWDiv), (unsigned)(rows_w * (K / kWDiv)));
     int vx[kXLoads], vw[kWLoads];
     // (row groups all have the swizzle of row l/8 with bit 2 of row/2 from the group's parity)
 #pragma unroll
@@ -118,24 +116,24 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     static_assert(kRowStep * kPerRow == S::kThreads, "whole rows of threads");
     const int c0 = (tid % kPerRow) * 8, t0 = tid / kPerRow;
     // (range-checked, dword by dword: channels past N read as zero)
-    const __amdgpu_buffer_rsrc_t rs_ws = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w_scale), 0, N * 4, kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rs_ws = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.w_scale), 0, N * 4, kRsrcFlags);
     const v4f s0 = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs_ws, (ch0 + c0) * 4, 0, 0));
     const v4f s1 = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs_ws, (ch0 + c0) * 4 + 16, 0, 0));
     v4i bias8 = {0, 0, 0, 0};
-    if (bias) {
+    if (a.bias) {
         if (c0 + 8 <= rows_w) {
-            bias8 = *(const v4i*)(bias + ch0 + c0);
+            bias8 = *(const v4i*)(a.bias + ch0 + c0);
         } else {
             half8 b{};
 #pragma unroll
             for (int e = 0; e < 7; ++e)
-                if (c0 + e < rows_w) b[e] = bias[ch0 + c0 + e];
+                if (c0 + e < rows_w) b[e] = a.bias[ch0 + c0 + e];
             bias8 = (v4i)b;
         }
     }
     float xsc[kItems];
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) xsc[i] = x_scale[tok0 + min(t0 + i * kRowStep, rows_x - 1)];
+    for (int i = 0; i < kItems; ++i) xsc[i] = a.x_scale[tok0 + min(t0 + i * kRowStep, rows_x - 1)];
 
     // ---- a line at a time ------------------------------------------------------------------
     const int fr_row = lane & 31;
@@ -213,23 +211,16 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             v1 += *(const v4i*)(sums + ((((c0 >> 2) + 1) ^ (t & kXor)) << 4));
         }
         const long at = (long)(tok0 + t) * N + ch0 + c0;
-        write_eight<W_BITS>(v0, v1, xsc[i], s0, s1, bias8, rows_w - c0, y + at, acc_out ? acc_out + at : nullptr);
+        write_eight<W_BITS>(v0, v1, xsc[i], s0, s1, bias8, rows_w - c0, a.y + at, a.acc_out ? a.acc_out + at : nullptr);
     }
 }
 
 template <class S, int W_BITS>
-hipError_t launch_split_tile(const TileArgs& a, hipStream_t stream) {
-    TileGrid g;
-    if (!tile_grid(g, a.M, a.N, S::kT, S::kC)) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(g.tiles_per_xcd * kTileXcds)), block(S::kThreads);
-#define VQ_SPLIT(TAIL)                                                                                                \
-    hipLaunchKernelGGL((gemm_i8_dequant_split<S, W_BITS, TAIL>), grid, block, 0, stream, a.xq, a.w, a.M, a.N, a.K,   \
-                       g.tiles, g.tiles_per_xcd, g.tiles_c, g.tiles_t, g.div_band, g.div_last, a.x_scale, a.w_scale, \
-                       a.bias, a.y, a.acc_out)
-    if (a.K % kLine) VQ_SPLIT(true);
-    else VQ_SPLIT(false);
-#undef VQ_SPLIT
-    return hipGetLastError();
+hipError_t launch_split_tile(TileArgs a, hipStream_t stream) {
+    if (!tile_grid(a.grid, a.M, a.N, S::kT, S::kC)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(a.grid.tiles_per_xcd * kTileXcds)), block(S::kThreads);
+    return enqueue(a.K % kLine ? gemm_i8_dequant_split<S, W_BITS, true> : gemm_i8_dequant_split<S, W_BITS, false>, grid, block,
+                   stream, a);
 }
 
 }  // namespace

@@ -15,7 +15,7 @@ typedef OneTile<2, 4, 2, 2, 1, 3, 1> Tile128x256;
 
 template <class S>
 hipError_t launch_bits(const TileArgs& a, int w_bits, hipStream_t stream) {
-    return w_bits == 8 ? launch_tile_shape<S, RowsOfCodes, 8>(a, {}, stream) : launch_tile_shape<S, RowsOfCodes, 4>(a, {}, stream);
+    return w_bits == 8 ? launch_tile_shape<S, 8>(a, stream) : launch_tile_shape<S, 4>(a, stream);
 }
 }  // namespace
 

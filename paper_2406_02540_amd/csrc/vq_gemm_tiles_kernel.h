@@ -52,16 +52,6 @@ struct OneTile {
     static_assert((4 / KW) * KW == 4, "K groups");
 };
 
-// Where the activations come from: rows of codes in memory, which go through the ring like the weights
-// (here), or the producer's input, quantized by the workgroup itself (vq_linear_small.h).
-struct RowsOfCodes {
-    struct Args {};
-    static constexpr bool kQuantizes = false;
-    static constexpr int kRows = 0, kXBytes = 0;   // (tokens of a tile and LDS bytes where they are not the tile's and the ring's)
-    template <int KT>
-    static __device__ __forceinline__ void quantize(const Args&, long, int, bool, int8_t*, float*) {}
-};
-
 // Stage loads younger than the one needed: LEFT stages of PER loads.
 template <int PER, int MAX_LEFT>
 __device__ __forceinline__ void wait_stages(int left) {
@@ -73,14 +63,10 @@ __device__ __forceinline__ void wait_stages(int left) {
     }
 }
 
-template <class S, class Q, int W_BITS, bool K_TAIL>
-__global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant_tile(const TileArgs a,
-                                                                                     const typename Q::Args qa) {
+template <class S, int W_BITS, bool K_TAIL>
+__global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant_tile(const TileArgs a) {
     constexpr int BT = S::BT, BC = S::BC, KW = S::KW, RING = S::RING;
-    constexpr int kRows = Q::kQuantizes ? Q::kRows : S::kT;               // tokens of the tile (a power of two)
-    constexpr int kXBlock = kRows * kStageK;                              // a stage's activations in LDS
-    constexpr int kXArea = Q::kQuantizes ? Q::kXBytes : RING * kXBlock;   // the whole of K, or the ring's
-    constexpr int kStaged = kXArea + RING * S::kWS;
+    constexpr int kXArea = RING * S::kXS, kStaged = RING * (S::kXS + S::kWS);
     constexpr int kBody = kStaged > S::kSums ? kStaged : S::kSums;
     static_assert((kBody + S::kScales) * S::kWgs <= 160 * 1024, "LDS of one CU");
     __shared__ __attribute__((aligned(1024))) int8_t lds[kBody + S::kScales];
@@ -92,7 +78,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 
     int row, col;
     if (!locate_tile(a.grid, row, col)) return;
-    const int tok0 = row * kRows, ch0 = col * S::kC;   // (< M, < N)
+    const int tok0 = row * S::kT, ch0 = col * S::kC;   // (< M, < N)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -100,7 +86,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     const int wave_t = sp % S::WT, wave_c = sp / S::WT;
     const int K = a.K;
     constexpr int kWDiv = (W_BITS == 8) ? 1 : 2;
-    const int rows_x = min(kRows, a.M - tok0);
+    const int rows_x = min(S::kT, a.M - tok0);
     const int rows_w = min(S::kC, a.N - ch0);
     const int nk = (K + kStageK - 1) / kStageK;
 
@@ -109,7 +95,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // chunk (l%8) ^ ((row/2)%8)) or, for packed nibbles, 16 rows x 64 B (row l/4, chunk (l%4) ^
     // ((row/4)%4)).  Row groups 0 .. kXG-1 are activations, the rest weights; wavefront w takes
     // groups w, w + kWaves, ...
-    constexpr int kXG = Q::kQuantizes ? 0 : S::kT / 8, kWG = (W_BITS == 8) ? S::kC / 8 : S::kC / 16;
+    constexpr int kXG = S::kT / 8, kWG = (W_BITS == 8) ? S::kC / 8 : S::kC / 16;
     constexpr int kGroups = kXG + kWG;
     constexpr int kPer = (kGroups + S::kWaves - 1) / S::kWaves;     // loads of a wavefront per stage
     constexpr int kFull = kGroups - (kPer - 1) * S::kWaves;          // wavefronts that have that many
@@ -141,7 +127,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         const int g = wave + S::kWaves * j;   // (wave-uniform)
         if (j == kPer - 1 && kFull < S::kWaves && wave >= kFull) return;
         if (g < kXG)
-            load_stage_to_lds_16<K_TAIL>(rsrc_x, lds_x_addr + slot * kXBlock + g * 1024, voff[j], k0, k_end[j]);
+            load_stage_to_lds_16<K_TAIL>(rsrc_x, lds_x_addr + slot * S::kXS + g * 1024, voff[j], k0, k_end[j]);
         else
             load_stage_to_lds_16<K_TAIL>(rsrc_w, lds_w_addr + slot * S::kWS + (g - kXG) * 1024, voff[j], k0 / kWDiv,
                                          k_end[j]);
@@ -172,15 +158,13 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     for (int p = 0; p < kPre; ++p) {
         const int i = tid + p * S::kThreads;
         pre_ws[p] = a.w_scale[ch0 + min(i, rows_w - 1)];
-        if (!Q::kQuantizes) pre_xs[p] = a.x_scale[tok0 + min(i, rows_x - 1)];
+        pre_xs[p] = a.x_scale[tok0 + min(i, rows_x - 1)];
         pre_b[p] = a.bias ? a.bias[ch0 + min(i, rows_w - 1)] : (_Float16)0.0f;
     }
 
     // ---- LDS -> MFMA operands ---------------------------------------------------------------
     const int fr_row = lane & 31;
-    // (a tile of fewer tokens than a block has rows: the rows behind them repeat, and are not written)
-    const int x_row = (wave_t * 32 * BT + fr_row) & (kRows - 1);
-    const int x_off0 = x_row * kStageK + (((lane >> 5) ^ ((x_row >> 1) & 7)) << 4);
+    const int x_off0 = (wave_t * 32 * BT + fr_row) * kStageK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4);
     const int w_off0 = (W_BITS == 8)
                            ? (wave_c * 32 * BC + fr_row) * kStageK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4)
                            : (wave_c * 32 * BC + fr_row) * (kStageK / 2) + (((fr_row >> 2) & 3) << 4) + (lane >> 5) * 8;
@@ -200,17 +184,13 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 #pragma unroll
     for (int cb = 0; cb < BC; ++cb) wf[1][cb] = v4i{0, 0, 0, 0};
 
-    // (the weights are on their way; the first stage's barrier is also this one's)
-    if constexpr (Q::kQuantizes)
-        Q::template quantize<kStageK>(qa, tok0, wave, col == 0, lds_x, (float*)(lds_sc + S::kC * 4));
-
     constexpr int kSteps = 4 / KW;   // K steps of a stage that are this group's
     auto stage = [&](int it, int slot, auto parity_tag) __attribute__((always_inline)) {
         constexpr int P = decltype(parity_tag)::value;
         wait_stage(it);
         const bool fetch = it + RING - 1 < nk;
         const int f_slot = slot == 0 ? RING - 1 : slot - 1, f_k0 = (it + RING - 1) * kStageK;
-        const int8_t* xs = lds_x + (Q::kQuantizes ? it : slot) * kXBlock;
+        const int8_t* xs = lds_x + slot * S::kXS;
         const int8_t* ws = lds_w + slot * S::kWS;
 #pragma unroll
         for (int s = 0; s < kSteps; ++s) {
@@ -287,7 +267,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     for (int p = 0; p < kPre; ++p) {
         const int i = tid + p * S::kThreads;
         if (i < S::kC) *(float*)(lds_sc + i * 4) = pre_ws[p];
-        if (!Q::kQuantizes && i < S::kT) *(float*)(lds_sc + S::kC * 4 + i * 4) = pre_xs[p];
+        if (i < S::kT) *(float*)(lds_sc + S::kC * 4 + i * 4) = pre_xs[p];
         if (i < S::kC) *(_Float16*)(lds_sc + S::kC * 4 + S::kT * 4 + i * 2) = pre_b[p];
     }
     wait_lds_and_barrier();   // nobody reads the stage buffers any more
@@ -330,18 +310,12 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     }
 }
 
-template <class S, class Q, int W_BITS>
-hipError_t launch_tile_shape(TileArgs a, const typename Q::Args& qa, hipStream_t stream) {
-    constexpr int rows = Q::kQuantizes ? Q::kRows : S::kT;
-    if (!tile_grid(a.grid, a.M, a.N, rows, S::kC)) return hipErrorInvalidValue;
+template <class S, int W_BITS>
+hipError_t launch_tile_shape(TileArgs a, hipStream_t stream) {
+    if (!tile_grid(a.grid, a.M, a.N, S::kT, S::kC)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(a.grid.tiles_per_xcd * kTileXcds)), block(S::kThreads);
-    // (a workgroup that quantizes is not slowed by the tail's two instructions per load: one kernel for both)
-    if (Q::kQuantizes || a.K % kStageK) {
-        hipLaunchKernelGGL((gemm_i8_dequant_tile<S, Q, W_BITS, true>), grid, block, 0, stream, a, qa);
-    } else if constexpr (!Q::kQuantizes) {
-        hipLaunchKernelGGL((gemm_i8_dequant_tile<S, Q, W_BITS, false>), grid, block, 0, stream, a, qa);
-    }
-    return hipGetLastError();
+    return enqueue(a.K % kStageK ? gemm_i8_dequant_tile<S, W_BITS, true> : gemm_i8_dequant_tile<S, W_BITS, false>, grid, block,
+                   stream, a);
 }
 
 }  // namespace
