@@ -9,37 +9,30 @@ namespace {
 // Weight side of the rotation, offline.  A block of 128 channels is 16 lanes; lane p holds its values
 // 4p .. 4p+3 and 64+4p .. 64+4p+3, so that every load and store covers whole cache lines, and the
 // stages run in the order of the channel's bits: two in registers, four across lanes, the last one
-// in registers; no LDS memory and no barrier.  Memory-bound (8 bytes per element); a thread takes
-// kRotateBlocks blocks a workgroup's width apart, asked for first.
-// 4608 x 1152: 12.0-12.9 us (21.4 as a workgroup per row with the stages in LDS and a barrier after
-// each; 14.7-16.4 with eight consecutive values per lane, that is half of every line per load).
-constexpr int kRotateBlocks = 2, kRotateWidth = kQuantThreads / 16;   // blocks of 128 per workgroup and step
+// in registers; no LDS memory and no barrier.  Memory-bound (8 bytes per element).
+// 4608 x 1152: 7.65 us (12.0 with a 64-bit division in front of the loads, 8.3 without it and with two blocks
+// per thread, 9.1 with four; 14.7-16.4 with eight consecutive values per lane, that is half of every line per load).
+constexpr int kRotateWidth = kQuantThreads / 16;   // blocks of 128 per workgroup
 __global__ __launch_bounds__(kQuantThreads) void rotate_weight_blocks(const float4v* w,
                                                                       const float4v* __restrict__ chan_s,
                                                                       float4v* out, long blocks, int K128) {
-    const long first = (long)blockIdx.x * (kRotateWidth * kRotateBlocks);
     const int blk = threadIdx.x >> 4, sub = threadIdx.x & 15;
-    const int col0 = (int)(first % K128);   // block of its row that this workgroup begins with
-    float t[kRotateBlocks][8];              // (w and out may be one buffer: a thread writes what it read)
-#pragma unroll
-    for (int i = 0; i < kRotateBlocks; ++i) {
-        const long at = first + i * kRotateWidth + blk;
-        float4v lo{}, hi{};
-        if (at < blocks) {   // (groups of 16 lanes are wholly in or out)
-            lo = w[32 * at + sub];
-            hi = w[32 * at + 16 + sub];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) t[i][j] = lo[j], t[i][4 + j] = hi[j];
+    const long at = (long)blockIdx.x * kRotateWidth + blk;
+    if (at >= blocks) return;   // (groups of 16 lanes are wholly in or out)
+    float t[1][8];              // (w and out may be one buffer: a thread writes what it read)
+    const float4v lo = w[32 * at + sub], hi = w[32 * at + 16 + sub];
+    float4v slo, shi;
+    if (chan_s) {
+        // the block's place in its row, from remainders that stay small (K128 <= 64)
+        const unsigned col = ((blockIdx.x % (unsigned)K128) * (unsigned)kRotateWidth + (unsigned)blk) % (unsigned)K128;
+        slo = chan_s[32 * col + sub];
+        shi = chan_s[32 * col + 16 + sub];
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[0][j] = lo[j], t[0][4 + j] = hi[j];
     if (chan_s) {
 #pragma unroll
-        for (int i = 0; i < kRotateBlocks; ++i) {
-            const int col = (col0 + i * kRotateWidth + blk) % K128;
-            const float4v lo = chan_s[32 * col + sub], hi = chan_s[32 * col + 16 + sub];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) t[i][j] = t[i][j] * lo[j], t[i][4 + j] = t[i][4 + j] * hi[j];
-        }
+        for (int j = 0; j < 4; ++j) t[0][j] = t[0][j] * slo[j], t[0][4 + j] = t[0][4 + j] * shi[j];
     }
     hadamard_register_stages<0, 2>(t);
     hadamard_lane_stage<1>(t, sub);
@@ -48,16 +41,11 @@ __global__ __launch_bounds__(kQuantThreads) void rotate_weight_blocks(const floa
     hadamard_lane_stage<8>(t, sub);
     hadamard_register_stages<2, 3>(t);
     const float scale = hadamard_sign(sub) * kHadamardScale;
+    float4v olo, ohi;
 #pragma unroll
-    for (int i = 0; i < kRotateBlocks; ++i) {
-        const long at = first + i * kRotateWidth + blk;
-        if (at >= blocks) continue;
-        float4v lo, hi;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) lo[j] = t[i][j] * scale, hi[j] = t[i][4 + j] * scale;
-        out[32 * at + sub] = lo;
-        out[32 * at + 16 + sub] = hi;
-    }
+    for (int j = 0; j < 4; ++j) olo[j] = t[0][j] * scale, ohi[j] = t[0][4 + j] * scale;
+    out[32 * at + sub] = olo;
+    out[32 * at + 16 + sub] = ohi;
 }
 
 }  // namespace
@@ -90,7 +78,7 @@ hipError_t launch_plain_quantize(const void* x_f16, const float* chan_mul, int8_
 
 hipError_t launch_rotate_weight(const float* w, const float* chan_s, float* w_rot, int N, int K,
                                 hipStream_t stream) {
-    const long blocks = (long)N * (K / 128), per_wg = kRotateWidth * kRotateBlocks;
+    const long blocks = (long)N * (K / 128), per_wg = kRotateWidth;
     hipLaunchKernelGGL(rotate_weight_blocks, dim3((unsigned)((blocks + per_wg - 1) / per_wg)), dim3(kQuantThreads), 0,
                        stream, (const float4v*)w, (const float4v*)chan_s, (float4v*)w_rot, blocks, K / 128);
     return hipGetLastError();
