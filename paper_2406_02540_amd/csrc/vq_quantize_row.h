@@ -53,11 +53,21 @@ __device__ __forceinline__ int quantize4(float t0, float t1, float t2, float t3,
 // Sum (or maximum) over the LANES lanes of a token; every lane gets the result.
 // Data moves between lanes without LDS round trips where the hardware allows it: DPP quad
 // permutes (lane ^ 1, lane ^ 2), then the mirrored lane of the other half of 8 and of 16
-// lanes (by then both halves are uniform, so any lane of the other half will do), a
-// ds_swizzle for lane ^ 16 and a permute through LDS only for lane ^ 32.
+// lanes (by then both halves are uniform, so any lane of the other half will do), and the swaps of
+// rows of 16 and of halves of 32 lanes between two registers: with the same value in both, one ends up
+// with the lower row's (half's) everywhere and the other with the upper one's.  (Through LDS, a swizzle and
+// a permute, the last two steps took 100 to 130 cycles each, on the way of every token.)
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+// op(lower, upper) of the two rows of 16 (halves of 32) lanes, in every lane of both.
+template <int ROW, class Op>
+__device__ __forceinline__ float op_swapped(float v, Op op) {
+    unsigned a = __builtin_bit_cast(unsigned, v), b = a;
+    asm("" : "+v"(b));   // (a second register for the compiler: of one value in both it returns one result)
+    const auto r = ROW == 16 ? __builtin_amdgcn_permlane16_swap(a, b, false, false) : __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    return op(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
 }
 template <int LANES, class Op>
 __device__ __forceinline__ float group_reduce(float v, Op op) {
@@ -66,9 +76,8 @@ __device__ __forceinline__ float group_reduce(float v, Op op) {
     v = op(v, dpp_move<0x4E>(v));   // quad_perm [2,3,0,1]
     v = op(v, dpp_move<0x141>(v));  // row_half_mirror
     v = op(v, dpp_move<0x140>(v));  // row_mirror
-    if (LANES >= 32)
-        v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), (16 << 10) | 0x1F)));
-    if (LANES >= 64) v = op(v, __shfl_xor(v, 32, kWave));
+    if (LANES >= 32) v = op_swapped<16>(v, op);
+    if (LANES >= 64) v = op_swapped<32>(v, op);
     return v;
 }
 template <int LANES>
