@@ -111,13 +111,15 @@ struct TileShape {
     static constexpr int kXStage = kTileT * kTileK;   // 32 KiB
     static constexpr int kWStage = kTileC * kTileK;   // (half of it used by packed 4-bit weights)
     static constexpr int kLdsBytes = kStages * (kXStage + kWStage);
-    // Global -> LDS loads of 1 KiB (8 rows of int8, 16 rows of nibbles).  The X tile is 32 of them,
-    // four for each of the first eight waves.  With eight waves every wave also takes its share
-    // of the W tile; with twelve, waves 8..11 load the W tile and nothing else.
-    static constexpr bool kSplitRoles = kWaves > 8;
-    static constexpr int kWLoaders = kSplitRoles ? kWaves - 8 : 8;
-    static constexpr int kWPer8 = kTileC / 8 / kWLoaders;    // int8 (and fp16) W loads per loading wave
-    static constexpr int kWPer4 = kTileC / 16 / kWLoaders;   // packed 4-bit W loads per loading wave
+    // Global -> LDS loads of 1 KiB (8 rows of int8, 16 rows of nibbles).  The X tile is 32 of them.  With
+    // eight waves each takes four of those and its share of the W tile; with more the loads of both tiles are
+    // one list (groups 0 .. 31 X, the rest W), dealt round.
+    static constexpr bool kOneList = kWaves > 8;
+    static constexpr int groups(int w_bits) { return 32 + kTileC / (w_bits == 4 ? 16 : 8); }
+    static constexpr int kStage = kXStage + kWStage;         // X tile, then W tile
+    static constexpr int kWLoaders = 8;
+    static constexpr int kWPer8 = kOneList ? 0 : kTileC / 8 / kWLoaders;    // int8 (and fp16) W loads per loading wave
+    static constexpr int kWPer4 = kOneList ? 0 : kTileC / 16 / kWLoaders;   // packed 4-bit W loads per loading wave
     // Epilogue: every wave has a staging area of its own behind the stage buffers, 16 token
     // rows x 128 B, through which half a block of 32 tokens x 64 channels of fp16 is turned at
     // a time.  (The stage buffers themselves are busy: the next tile's first two stages land
@@ -128,7 +130,8 @@ struct TileShape {
     static constexpr int kStoresPerTile = TB * 4;            // 128-bit stores of a wave's epilogue
     static_assert(kTileT == 256, "scales are fetched by threads 0..255, one token each");
     static_assert(kTileC <= 256 && kWaves % 4 == 0 && kWaves >= 8, "tile shape");
-    static_assert(kTileC / 8 % kWLoaders == 0 && kTileC / 16 % kWLoaders == 0, "W loads divide evenly");
+    static_assert(kOneList || (kTileC / 8 % kWLoaders == 0 && kTileC / 16 % kWLoaders == 0), "W loads divide evenly");
+    static_assert(!kOneList || (kWaves % 2 == 0 && 2 * kWaves <= 32 && 3 * kWaves >= 32), "one turn of the list is mixed, and a wave's groups have its parity");
     static_assert(kLdsBytes + kScaleBytes + kEpiBytes <= 160 * 1024, "LDS of one CU");
 };
 
@@ -140,7 +143,7 @@ struct TilePos {
 // What this wave's share of a tile's loads needs: buffer descriptors and per-lane offsets.
 struct TileLoads {
     v4i rsrc_x, rsrc_w;
-    int voff_x[4], voff_w[6];
+    int voff_x[4], voff_w[6];   // (one list: voff_w alone, by turn)
     int k_end_x, k_end_w;   // (used with a K tail only: see load_stage_to_lds_16)
 };
 
@@ -174,12 +177,13 @@ template <class S, int W_BITS, bool K_TAIL, Out OUT>
 __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant(const GemmArgs a) {
     constexpr bool GENERIC = OUT == kAnyRow;
     constexpr int TB = S::TB;
-    constexpr int kXStage = S::kXStage, kWStage = S::kWStage, kLdsBytes = S::kLdsBytes;
+    constexpr int kXStage = S::kXStage, kLdsBytes = S::kLdsBytes;
     __shared__ __attribute__((aligned(1024))) int8_t lds[kLdsBytes + kScaleBytes + S::kEpiBytes];
-    // layout: [X buffer 0][X buffer 1][W buffer 0][W buffer 1][scales][epilogue staging]; a W
+    // layout: [X buffer 0][W buffer 0][X buffer 1][W buffer 1][scales][epilogue staging]; a W
     // buffer is [rows][128 B] of int8 or, for 4-bit weights, [rows][64 B] of nibbles.
     int8_t* const lds_x = lds;
-    int8_t* const lds_w = lds + kStages * kXStage;
+    int8_t* const lds_w = lds + kXStage;
+    constexpr int kStage = S::kStage;
     const unsigned lds_x_addr = (unsigned)(uintptr_t)(lds_ptr)lds_x;
     const unsigned lds_w_addr = (unsigned)(uintptr_t)(lds_ptr)lds_w;
     int8_t* const lds_sc = lds + kLdsBytes;  // w_scale | bias | x_scale of the current tile
@@ -200,10 +204,10 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 
     // What this wave loads per stage.
     constexpr int kWPer = (W_BITS != 4) ? S::kWPer8 : S::kWPer4;
-    const bool loads_x = !S::kSplitRoles || wave < 8;
-    const bool loads_w = !S::kSplitRoles || wave >= 8;
-    const int w_loader = S::kSplitRoles ? wave - 8 : wave;
-    const int n_singles = S::kSplitRoles ? (wave < 8 ? 4 : kWPer) : 4 + kWPer;
+    constexpr int kGroups = S::groups(W_BITS), kTurns = (kGroups + S::kWaves - 1) / S::kWaves;   // (one list)
+    constexpr int kMixed = 32 / S::kWaves;   // the turn in which some waves load X and some W
+    const bool mixed_x = wave + kMixed * S::kWaves < 32;
+    const int w_loader = wave;
 
     // ---- global -> LDS mapping ---------------------------------------------
     // One direct load fills 1 KiB; lane l writes bytes [16 l, 16 l + 16).
@@ -256,27 +260,29 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         if (full && ld_full) return;
         ld_full = full;
         const int l = opaque(lane);
-        if (loads_x) {
-            const int ld_chunk16 = ((l & 7) ^ ((4 * (wave & 1) + (l >> 4)) & 7)) << 4;
-            ld.k_end_x = K - ld_chunk16;
+        const int ld_chunk16 = ((l & 7) ^ ((4 * (wave & 1) + (l >> 4)) & 7)) << 4;
+        const int ld_chunk16_w4 = ((l & 3) ^ (l >> 4)) << 4;
+        ld.k_end_x = K - ld_chunk16;
+        ld.k_end_w = W_BITS != 4 ? K - ld_chunk16 : K / 2 - ld_chunk16_w4;
+        auto x_offset = [&](int g) {
+            return __mul24(min(g * 8 + (l >> 3), t.rows_x - 1), K) + ld_chunk16;
+        };
+        auto w_offset = [&](int g) {
+            if (W_BITS != 4) return __mul24(min(w_row_to_channel(g * 8 + (l >> 3)), t.rows_w - 1), K) + ld_chunk16;
+            return __mul24(min(w_row_to_channel(g * 16 + (l >> 2)), t.rows_w - 1), K / 2) + ld_chunk16_w4;
+        };
+        if constexpr (S::kOneList) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = (wave + 8 * j) * 8 + (l >> 3);
-                ld.voff_x[j] = __mul24(min(r, t.rows_x - 1), K) + ld_chunk16;
+            for (int j = 0; j < kTurns; ++j) {
+                const int g = wave + j * S::kWaves;
+                if (j < kMixed || (j == kMixed && mixed_x)) ld.voff_w[j] = x_offset(g);
+                else ld.voff_w[j] = w_offset(g - 32);
             }
-        }
-        if (loads_w) {
-            const int ld_chunk16 = ((l & 7) ^ ((4 * (w_loader & 1) + (l >> 4)) & 7)) << 4;
-            const int ld_chunk16_w4 = ((l & 3) ^ (l >> 4)) << 4;
-            ld.k_end_w = W_BITS != 4 ? K - ld_chunk16 : K / 2 - ld_chunk16_w4;
+        } else {
 #pragma unroll
-            for (int j = 0; j < kWPer; ++j) {
-                const int g = w_loader + S::kWLoaders * j;   // row group of this load
-                if (W_BITS != 4)
-                    ld.voff_w[j] = __mul24(min(w_row_to_channel(g * 8 + (l >> 3)), t.rows_w - 1), K) + ld_chunk16;
-                else
-                    ld.voff_w[j] = __mul24(min(w_row_to_channel(g * 16 + (l >> 2)), t.rows_w - 1), K / 2) + ld_chunk16_w4;
-            }
+            for (int j = 0; j < 4; ++j) ld.voff_x[j] = x_offset(wave + 8 * j);
+#pragma unroll
+            for (int j = 0; j < kWPer; ++j) ld.voff_w[j] = w_offset(w_loader + S::kWLoaders * j);
         }
     };
     auto tile_exists = [&](int idx) {
@@ -286,25 +292,29 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // One load of a wave's share of a stage.  A wave with both kinds alternates them (X, W, X,
     // W, ...) as long as it has W loads left.
     auto issue_x = [&](const TileLoads& ld, int buf, int k0, int j) {
-        load_stage_to_lds_16<K_TAIL>(ld.rsrc_x, lds_x_addr + buf * kXStage + (wave + 8 * j) * 1024, ld.voff_x[j], k0,
+        load_stage_to_lds_16<K_TAIL>(ld.rsrc_x, lds_x_addr + buf * kStage + (wave + 8 * j) * 1024, ld.voff_x[j], k0,
                                      ld.k_end_x);
     };
     auto issue_w = [&](const TileLoads& ld, int buf, int k0, int j) {
-        load_stage_to_lds_16<K_TAIL>(ld.rsrc_w, lds_w_addr + buf * kWStage + (w_loader + S::kWLoaders * j) * 1024,
+        load_stage_to_lds_16<K_TAIL>(ld.rsrc_w, lds_w_addr + buf * kStage + (w_loader + S::kWLoaders * j) * 1024,
                                      ld.voff_w[j], W_BITS != 4 ? k0 : k0 / 2, ld.k_end_w);
     };
+    constexpr int kMaxSingles = S::kOneList ? kTurns : 4 + kWPer;
+    const int n_singles = S::kOneList ? (wave < kGroups - (kTurns - 1) * S::kWaves ? kTurns : kTurns - 1) : 4 + kWPer;
     auto issue_single = [&](const TileLoads& ld, int buf, int k0, int s) {
-        if (S::kSplitRoles) {
-            // (s is a compile-time constant at every call; the role is wave-uniform)
-            if (wave < 8) { if (s < 4) issue_x(ld, buf, k0, s); }
-            else          { if (s < kWPer) issue_w(ld, buf, k0, s); }
+        if constexpr (S::kOneList) {
+            // (s is a compile-time constant at every call; a mixed turn's kind is wave-uniform)
+            const unsigned at = lds_x_addr + buf * kStage + (wave + s * S::kWaves) * 1024;
+            if (s < kMixed || (s == kMixed && mixed_x))
+                load_stage_to_lds_16<K_TAIL>(ld.rsrc_x, at, ld.voff_w[s], k0, ld.k_end_x);
+            else
+                load_stage_to_lds_16<K_TAIL>(ld.rsrc_w, at, ld.voff_w[s], W_BITS != 4 ? k0 : k0 / 2, ld.k_end_w);
         } else if (s < 2 * kWPer) {
             if (s & 1) issue_w(ld, buf, k0, s >> 1); else issue_x(ld, buf, k0, s >> 1);
         } else {
             issue_x(ld, buf, k0, s - kWPer);
         }
     };
-    constexpr int kMaxSingles = S::kSplitRoles ? (kWPer > 4 ? kWPer : 4) : 4 + kWPer;
     auto issue_all = [&](const TileLoads& ld, int buf, int k0) {
 #pragma unroll
         for (int s = 0; s < kMaxSingles; ++s)
@@ -418,8 +428,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             }
             const int fk0 = more ? (it + 1) * kTileK : 0;
 
-            const int8_t* xs = lds_x + buf * kXStage;
-            const int8_t* ws = lds_w + buf * kWStage;
+            const int8_t* xs = lds_x + buf * kStage;
+            const int8_t* ws = lds_w + buf * kStage;
             // Operand registers are double buffered: the LDS reads of K step ks+1 are issued
             // among the MFMAs of step ks, which cover their latency.
             // A K step = 2 TB MFMAs in TB pieces of two.  A piece carries at most one global load
