@@ -21,12 +21,12 @@ struct TileCost {
     double base, fixed, stage, widen, fixed_one, stage_one, widen_one;
 };
 constexpr TileCost kTileCosts[] = {
-    {64, 64, 2, 2.352, 1.976, 0.356, 0.090, 1.094, 0.214, 0.091},
-    {128, 64, 2, 2.853, 3.099, 0.524, 0.044, 1.402, 0.348, 0.049},
-    {128, 128, 1, 1.755, 4.338, 0.447, 0.011, 0.0, 0.0, 0.0},
-    {128, 256, 1, 2.172, 4.888, 0.799, 0.106, 0.0, 0.0, 0.0},
-    {256, 192, 1, 2.793, 4.331, 1.175, 0.0, 0.0, 0.0, 0.0},
-    {256, 256, 1, 2.092, 5.635, 1.313, 0.0, 0.0, 0.0, 0.0},
+    {64, 64, 2, 2.344, 1.947, 0.364, 0.090, 1.091, 0.215, 0.092},
+    {128, 64, 2, 2.852, 3.152, 0.518, 0.052, 1.378, 0.355, 0.048},
+    {128, 128, 1, 1.695, 4.391, 0.451, 0.010, 0.0, 0.0, 0.0},
+    {128, 256, 1, 1.833, 5.233, 0.804, 0.112, 0.0, 0.0, 0.0},
+    {256, 192, 1, 2.416, 4.455, 1.130, 0.0, 0.0, 0.0, 0.0},
+    {256, 256, 1, 1.784, 5.817, 1.326, 0.0, 0.0, 0.0, 0.0},
 };
 // Tiles whose K the `waves` wavefronts of a workgroup divide: `base`, plus for every workgroup of a CU `fixed`
 // and, per line of K, `line` and `load` for every 8 KiB that it loads, plus `turn` for every line that a
