@@ -14,19 +14,19 @@ typedef TileShape<2, 4, 4> Tile256;  // 2 x 4 wavefronts of 128 tokens x 64 chan
 // same of a last filling with one workgroup only; widen is what 4-bit weights add to a stage.
 // Both tables fitted by least squares over 20000 random problems (1 to 32768 tokens, 32 to 4608 channels, K 256
 // to 4608, 8- and 4-bit weights), each timed with every tile in captured graphs, where the tile was within
-// 15 % of the best: error 6 to 9 %.  Over those problems the tile chosen is on average 0.1 % (above 1e9
-// multiply-adds) and 0.8 % (below 6e9) slower than the best one.
+// 15 % of the best: error 6 to 9 %.  Over those problems the tile chosen is on average 0.2 % (above 1e9
+// multiply-adds) and 0.7 % (below 6e9) slower than the best one.
 struct TileCost {
     int tile_t, tile_c, per_cu;
     double base, fixed, stage, widen, fixed_one, stage_one, widen_one;
 };
 constexpr TileCost kTileCosts[] = {
-    {64, 64, 2, 2.344, 1.947, 0.364, 0.090, 1.091, 0.215, 0.092},
-    {128, 64, 2, 2.852, 3.152, 0.518, 0.052, 1.378, 0.355, 0.048},
-    {128, 128, 1, 1.695, 4.391, 0.451, 0.010, 0.0, 0.0, 0.0},
-    {128, 256, 1, 1.833, 5.233, 0.804, 0.112, 0.0, 0.0, 0.0},
-    {256, 192, 1, 2.416, 4.455, 1.130, 0.0, 0.0, 0.0, 0.0},
-    {256, 256, 1, 1.784, 5.817, 1.326, 0.0, 0.0, 0.0, 0.0},
+    {64, 64, 2, 2.210, 1.940, 0.361, 0.067, 1.068, 0.215, 0.065},
+    {128, 64, 2, 2.671, 3.085, 0.516, 0.018, 1.419, 0.339, 0.023},
+    {128, 128, 1, 1.710, 4.068, 0.471, 0.011, 0.0, 0.0, 0.0},
+    {128, 256, 1, 2.127, 4.866, 0.778, 0.079, 0.0, 0.0, 0.0},
+    {256, 192, 1, 2.571, 4.325, 1.131, 0.0, 0.0, 0.0, 0.0},
+    {256, 256, 1, 2.177, 5.544, 1.325, 0.0, 0.0, 0.0, 0.0},
 };
 // Tiles whose K the `waves` wavefronts of a workgroup divide: `base`, plus for every workgroup of a CU `fixed`
 // and, per line of K, `line` and `load` for every 8 KiB that it loads, plus `turn` for every line that a
@@ -36,11 +36,11 @@ struct SplitCost {
     double base, fixed, load, turn, line;
 };
 constexpr SplitCost kSplitCosts[] = {
-    {32, 32, 8, 2, 2.6115, 0.4736, 0.0452, 0.0, 0.0256},
-    {64, 32, 4, 3, 2.6745, 0.3895, 0.0652, 0.1934, 0.0098},
-    {32, 32, 3, 4, 2.6668, 0.1790, 0.0475, 0.1583, 0.0130},
-    {64, 64, 8, 1, 0.9718, 2.9382, 0.0767, 0.0, 0.0308},
-    {32, 32, 6, 3, 2.6853, 0.3465, 0.0392, 0.0, 0.0346},
+    {32, 32, 8, 2, 2.6057, 0.4853, 0.0430, 0.0, 0.0268},
+    {64, 32, 4, 3, 2.6815, 0.3912, 0.0646, 0.1748, 0.0119},
+    {32, 32, 3, 4, 2.6742, 0.1803, 0.0448, 0.1433, 0.0166},
+    {64, 64, 8, 1, 0.7061, 3.1354, 0.0908, 0.0, 0.0123},
+    {32, 32, 6, 3, 2.6642, 0.3712, 0.0372, 0.0, 0.0346},
 };
 
 // Workgroups of the busiest CU: every XCD takes an equal run of tiles.
