@@ -1,5 +1,5 @@
 // Device helpers shared by the GEMM kernels of this library (vq_gemm.hip: large
-// persistent tiles; vq_gemm_tiles.hip: one tile per workgroup for problems that do not fill the
+// persistent tiles; vq_gemm_tiles.hip, vq_gemm_split.hip: one tile per workgroup for problems that do not fill the
 // chip).  gfx950 only.
 #pragma once
 #include <hip/hip_runtime.h>

@@ -19,8 +19,9 @@
 //   256 x 1152 -> 1152           4.65 / 3.7            5.1 / 3.6
 //   240 x 4096 -> 2304           9.7 / 9.1            12.1 / 8.3
 // A wavefront's next loads leave in a burst as soon as its operands are in registers, ahead of its
-// products; dealt out between the products they were up to 10 % later with 32 x 32 tiles.  Above 100 channel
-// and token tiles per XCD the operand bytes count, and sharing the tile wins.
+// products; dealt out between the products they were up to 10 % later with 32 x 32 tiles.  With many tiles per CU
+// the operand bytes count, and larger shared tiles win (512 x 1152 -> 1152: 64 x 64 4.6 us, 32 x 32 here 4.5; 1001 x 1152
+// -> 4608: 128 x 256 12.0, here 16).
 #pragma once
 #include <type_traits>
 

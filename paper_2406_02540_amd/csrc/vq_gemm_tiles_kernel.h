@@ -14,16 +14,11 @@
 // (0.26 us for the 32 KiB of a 128 x 128 stage out of L2, against 0.21 us for its products), and
 // only as many bytes as the ring holds per memory latency (about 0.9 us beyond L2).
 //
-// Measured against the 64 x 64 tile this kernel replaces (four wavefronts, every K step on its own
-// LDS latency, one workgroup per CU), GEMM alone in a captured graph, us:
-//   tokens x K -> channels   before   now        tokens x K -> channels   before   now
-//   1 x 1152 -> 1152           5.5    3.9        1001 x 1152 -> 4608       24.9   13.2
-//   64 x 4608 -> 1152         12.9    7.0        2048 x 1152 -> 1152       16.2    9.4
-//   256 x 1152 -> 1152         5.7    4.6        4096 x 1152 -> 1152       25.5   13.1
-//   240 x 4096 -> 2304        12.7    9.9        4096 x 4608 -> 1152       62     30 (now 256 x 192)
-// The last 0.3 us of the small ones are the way to the first load: reciprocals instead of two divisions,
-// 32-bit instead of 64-bit tile arithmetic, and scales asked for behind the first stages instead of ahead
-// of them.
+// GEMM alone in a captured graph, us (8-bit / 4-bit weights): 240 x 4096 -> 2304 in 64 x 64 tiles 9.35 / 11.4, 1001 x
+// 1152 -> 4608 in 128 x 256 12.05 / 13.3, 2048 x 1152 -> 1152 in 128 x 128 8.65 / 9.0, 4096 x 1152 -> 1152 in 128 x 256 12.0
+// / 13.3.  Of the 12 us at 1001 x 1152 -> 4608 1.4 are the way to the first stage (start, six loads per wavefront at the load
+// path's rate), nine stages 0.63 each against 0.43 of products, 0.9 the turn of the sums and 1.5 the stores (144 CUs write
+// 9.2 MB).  Problems of fewer or smaller tiles: vq_gemm_split.h.
 #pragma once
 #include <type_traits>
 
