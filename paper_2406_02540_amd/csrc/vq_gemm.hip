@@ -45,7 +45,7 @@ constexpr SplitCost kSplitCosts[] = {
 
 // Workgroups of the busiest CU: every XCD takes an equal run of tiles.
 long tiles_per_cu(int M, int N, int tile_t, int tile_c, int num_cus) {
-    const long tiles = (long)((M + tile_t - 1) / tile_t) * ((N + tile_c - 1) / tile_c);
+    const long tiles = (((long)M + tile_t - 1) / tile_t) * (((long)N + tile_c - 1) / tile_c);
     const long per_xcd = (tiles + kXcds - 1) / kXcds;
     const int cus_per_xcd = num_cus >= kXcds ? num_cus / kXcds : 1;
     return (per_xcd + cus_per_xcd - 1) / cus_per_xcd;
@@ -67,31 +67,38 @@ double launch_cost(const SplitCost& c, int w_bits, int M, int N, int K, int num_
 }
 }  // namespace
 
-hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, int w_bits,
-                       const float* w_scale, const void* bias_f16, void* y_f16, int32_t* acc_out,
-                       int M, int N, int K, int num_cus, hipStream_t stream) {
-    const TileCost* best = nullptr;
+// The cheapest of the tiles that one launch takes.  (The persistent kernel's grid does not grow with the problem.)
+GemmChoice choose_gemm(int w_bits, int M, int N, int K, int num_cus) {
+    GemmChoice best{0, 0, 0};
     double best_cost = 0.0;
     for (const TileCost& c : kTileCosts) {
-        if (w_bits == 16 && c.tile_t != 256) continue;  // (the fp16 layer has the persistent kernel only)
+        if (c.tile_t != 256 && (w_bits == 16 || !tiles_launchable(M, N, c.tile_t, c.tile_c, kSharedTileThreads)))
+            continue;  // (the fp16 layer has the persistent kernel only)
         // fp16: rounds of tiles, the narrower tile (a sixth more operand bytes per multiply-add) only where it saves some
         const double cost = w_bits == 16 ? (double)tiles_per_cu(M, N, 256, c.tile_c, num_cus) * c.tile_c * (c.tile_c == 192 ? 1.05 : 1.0)
                                          : launch_cost(c, w_bits, M, N, K, num_cus);
-        if (!best || cost <= best_cost) {
-            best = &c;
+        if (!best.tile_t || cost <= best_cost) {
+            best = {c.tile_t, c.tile_c, 0};
             best_cost = cost;
         }
     }
-    const SplitCost* split = nullptr;
     if (w_bits != 16)
         for (const SplitCost& c : kSplitCosts) {
+            if (!tiles_launchable(M, N, c.tile_t, c.tile_c, 64 * c.waves)) continue;
             const double cost = launch_cost(c, w_bits, M, N, K, num_cus);
             if (cost < best_cost) {
-                split = &c;
+                best = {c.tile_t, c.tile_c, c.waves};
                 best_cost = cost;
             }
         }
-    if (split || best->tile_t != 256) {
+    return best;
+}
+
+hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, int w_bits,
+                       const float* w_scale, const void* bias_f16, void* y_f16, int32_t* acc_out,
+                       int M, int N, int K, int num_cus, hipStream_t stream) {
+    const GemmChoice c = choose_gemm(w_bits, M, N, K, num_cus);
+    if (c.waves || c.tile_t != 256) {
         TileArgs t{};
         t.xq = xq;
         t.x_scale = x_scale;
@@ -103,8 +110,8 @@ hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, in
         t.M = M;
         t.N = N;
         t.K = K;
-        if (split) return launch_gemm_split(split->tile_t, split->tile_c, split->waves, t, w_bits, stream);
-        return launch_gemm_tiles(best->tile_t, best->tile_c, t, w_bits, stream);
+        if (c.waves) return launch_gemm_split(c.tile_t, c.tile_c, c.waves, t, w_bits, stream);
+        return launch_gemm_tiles(c.tile_t, c.tile_c, t, w_bits, stream);
     }
     GemmArgs a;
     a.xq = xq;
@@ -118,8 +125,15 @@ hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, in
     a.N = N;
     a.K = K;
     a.tiles_t = a.tiles_c = a.tiles = a.tiles_per_xcd = a.slots = 0;  // (set for the chosen tile)
-    if (best->tile_c == 192) return launch_gemm_192(a, w_bits, num_cus, stream);
+    if (c.tile_c == 192) return launch_gemm_192(a, w_bits, num_cus, stream);
     return launch_gemm_shape<Tile256>(a, w_bits, num_cus, stream);
 }
 
 }  // namespace vq
+
+extern "C" void vq_internal_gemm_choice(int w_bits, int M, int N, int K, int num_cus, int choice[3]) {
+    const vq::GemmChoice c = vq::choose_gemm(w_bits, M, N, K, num_cus);
+    choice[0] = c.tile_t;
+    choice[1] = c.tile_c;
+    choice[2] = c.waves;
+}

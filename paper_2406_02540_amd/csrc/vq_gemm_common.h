@@ -157,12 +157,18 @@ struct TileGrid {
     unsigned div_band, div_last;   // reciprocals of a band's tiles and of the last band's rows (reciprocal_of), or 0
 };
 
-// The grid for tiles of t x c outputs; false if there are too many.
-inline bool tile_grid(TileGrid& g, int M, int N, int t, int c) {
-    g.tiles_t = (M + t - 1) / t;
-    g.tiles_c = (N + c - 1) / c;
+// Whether tiles of t x c outputs, a workgroup of so many threads each, are one launch: HIP takes less than 2^32 threads.
+inline bool tiles_launchable(int M, int N, int t, int c, int threads) {
+    const long tiles = (((long)M + t - 1) / t) * (((long)N + c - 1) / c);
+    return tiles <= 0x7FFFFF00l && (tiles + kTileXcds - 1) / kTileXcds * kTileXcds * threads < (1l << 32);
+}
+
+// The grid for tiles of t x c outputs; false if they are more than a launch takes.
+inline bool tile_grid(TileGrid& g, int M, int N, int t, int c, int threads) {
+    if (!tiles_launchable(M, N, t, c, threads)) return false;
+    g.tiles_t = (int)(((long)M + t - 1) / t);
+    g.tiles_c = (int)(((long)N + c - 1) / c);
     const long tiles = (long)g.tiles_t * g.tiles_c;
-    if (tiles > 0x7FFFFF00l) return false;
     g.tiles = (int)tiles;
     g.tiles_per_xcd = (g.tiles + kTileXcds - 1) / kTileXcds;
     const int last = g.tiles_t % kTileBand;
@@ -185,6 +191,7 @@ struct TileArgs {
 };
 
 // vq_gemm_tiles.hip: 64 x 64, 128 x 64, 128 x 128 or 128 x 256, the wavefronts sharing the tile.  w_bits 8 or 4.
+constexpr int kSharedTileThreads = 512;
 hipError_t launch_gemm_tiles(int tile_t, int tile_c, const TileArgs& a, int w_bits, hipStream_t stream);
 // vq_gemm_split.hip: 32 x 32 (3, 6 or 8 wavefronts), 64 x 32 (4) or 64 x 64 (8), the wavefronts dividing K.
 hipError_t launch_gemm_split(int tile_t, int tile_c, int waves, const TileArgs& a, int w_bits, hipStream_t stream);

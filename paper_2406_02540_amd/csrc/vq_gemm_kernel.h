@@ -678,6 +678,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 // Enqueues the kernel for tile shape S; `a` holds the operands and sizes.
 template <class S>
 hipError_t launch_gemm_shape(GemmArgs a, int w_bits, int num_cus, hipStream_t stream) {
+    if (a.M > 0x7FFFFF00 || a.N > 0x7FFFFF00) return hipErrorInvalidValue;  // (rows and channels of a last tile fit an int)
     a.tiles_t = (a.M + S::kTileT - 1) / S::kTileT;
     a.tiles_c = (a.N + S::kTileC - 1) / S::kTileC;
     const long tiles = (long)a.tiles_t * a.tiles_c;

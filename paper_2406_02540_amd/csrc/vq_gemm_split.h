@@ -218,7 +218,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 
 template <class S, int W_BITS>
 hipError_t launch_split_tile(TileArgs a, hipStream_t stream) {
-    if (!tile_grid(a.grid, a.M, a.N, S::kT, S::kC)) return hipErrorInvalidValue;
+    if (!tile_grid(a.grid, a.M, a.N, S::kT, S::kC, S::kThreads)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(a.grid.tiles_per_xcd * kTileXcds)), block(S::kThreads);
     return enqueue(a.K % kLine ? gemm_i8_dequant_split<S, W_BITS, true> : gemm_i8_dequant_split<S, W_BITS, false>, grid, block,
                    stream, a);

@@ -45,6 +45,7 @@ struct OneTile {
     static constexpr int kScales = kC * 4 + kT * 4 + kC * 2;
     static constexpr int kWgs = WGS_;
     static_assert((4 / KW) * KW == 4, "K groups");
+    static_assert(kThreads == kSharedTileThreads, "what launch_gemm counts with");
 };
 
 // Stage loads younger than the one needed: LEFT stages of PER loads.
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 
 template <class S, int W_BITS>
 hipError_t launch_tile_shape(TileArgs a, hipStream_t stream) {
-    if (!tile_grid(a.grid, a.M, a.N, S::kT, S::kC)) return hipErrorInvalidValue;
+    if (!tile_grid(a.grid, a.M, a.N, S::kT, S::kC, S::kThreads)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(a.grid.tiles_per_xcd * kTileXcds)), block(S::kThreads);
     return enqueue(a.K % kStageK ? gemm_i8_dequant_tile<S, W_BITS, true> : gemm_i8_dequant_tile<S, W_BITS, false>, grid, block,
                    stream, a);

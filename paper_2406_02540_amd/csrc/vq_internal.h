@@ -63,6 +63,11 @@ hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, in
                        const float* w_scale, const void* bias_f16, void* y_f16, int32_t* acc_out,
                        int M, int N, int K, int num_cus, hipStream_t stream);
 
+// The kernel that launch_gemm takes: tiles of tokens x channels, and the number of wavefronts that divide K (0:
+// the workgroup shares the tile; with 256 tokens it is the persistent kernel).
+struct GemmChoice { int tile_t, tile_c, waves; };
+GemmChoice choose_gemm(int w_bits, int M, int N, int K, int num_cus);
+
 // A layer of few tokens in one launch (vq_linear_small.hip): quantizer, with its producer, and GEMM.
 // small_layer: whether it is the faster way for these sizes.
 bool small_layer(int producer, int M, int N, int K, int num_cus);
@@ -70,3 +75,6 @@ hipError_t launch_linear_small(const ProducerArgs& p, const void* w, int w_bits,
                                void* y_f16, int M, int N, int K, hipStream_t stream);
 
 }  // namespace vq
+
+// choose_gemm for the tests, which name the kernels that they mean to reach.  Not a part of vq.h.
+extern "C" void vq_internal_gemm_choice(int w_bits, int M, int N, int K, int num_cus, int choice[3]);

@@ -186,7 +186,7 @@ __global__ __launch_bounds__(64 * kSmallWaves, kSmallWaves / 4) void linear_smal
 
 template <int PRODUCER>
 hipError_t launch_small_producer(SmallArgs a, int w_bits, hipStream_t stream) {
-    if (!tile_grid(a.t.grid, a.t.M, a.t.N, kSmallTokens, kSmallChannels)) return hipErrorInvalidValue;
+    if (!tile_grid(a.t.grid, a.t.M, a.t.N, kSmallTokens, kSmallChannels, 64 * kSmallWaves)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(a.t.grid.tiles_per_xcd * kTileXcds)), block(64 * kSmallWaves);
     return enqueue(w_bits == 8 ? linear_small<PRODUCER, 8> : linear_small<PRODUCER, 4>, grid, block, stream, a);
 }

@@ -1,0 +1,33 @@
+"""Which GEMM kernel a problem reaches: the choice is made on the host and needs no GPU."""
+import ctypes
+import os
+
+import pytest
+
+from paper_2406_02540_amd import binding, build
+
+CUS = 256   # of an MI355X
+
+
+@pytest.fixture(scope="module", autouse=True)
+def built():
+    if not (os.path.exists(binding.LIB_PATH) and os.path.exists(binding.EXT_PATH)):
+        build.build(verbose=False)
+
+
+def choice(bits, M, N, K):
+    """(tokens, channels, wavefronts that divide K or 0) of the tile that launch_gemm takes."""
+    out = (ctypes.c_int * 3)()
+    binding.lib().vq_internal_gemm_choice(bits, M, N, K, CUS, out)
+    return tuple(out)
+
+
+# few channels, few sums and very many tokens (or the other way round): the tiles that divide K take 192 threads for 32 tokens
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N", [(700_000_000, 8), (750_000_000, 8), (1_000_000_000, 32), (1_100_000_000, 1),
+                                 (1, 700_000_000), (1, 750_000_000)])
+def test_launch_stays_below_2_to_32_threads(bits, M, N):
+    t, c, waves = choice(bits, M, N, 32)
+    if waves or t != 256:   # (the persistent kernel has a workgroup per CU)
+        tiles = -(-M // t) * -(-N // c)
+        assert -(-tiles // 8) * 8 * (64 * waves or 512) < 2 ** 32
