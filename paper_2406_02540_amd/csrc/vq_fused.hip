@@ -78,10 +78,17 @@ hipError_t launch_plain_quantize(const void* x_f16, const float* chan_mul, int8_
 
 hipError_t launch_rotate_weight(const float* w, const float* chan_s, float* w_rot, int N, int K,
                                 hipStream_t stream) {
-    const long blocks = (long)N * (K / 128), per_wg = kRotateWidth;
-    hipLaunchKernelGGL(rotate_weight_blocks, dim3((unsigned)((blocks + per_wg - 1) / per_wg)), dim3(kQuantThreads), 0,
-                       stream, (const float4v*)w, (const float4v*)chan_s, (float4v*)w_rot, blocks, K / 128);
-    return hipGetLastError();
+    // HIP takes less than 2^32 threads: from 2^35 elements on several launches, of whole rows (chan_s begins with each)
+    constexpr long most = ((1l << 32) / kQuantThreads - 1) * kRotateWidth;
+    const long rows = min((long)N, most / (K / 128));
+    for (long n = 0; n < N; n += rows) {
+        const long blocks = min(rows, N - n) * (K / 128), at = n * (K / 4);
+        hipLaunchKernelGGL(rotate_weight_blocks, dim3((unsigned)((blocks + kRotateWidth - 1) / kRotateWidth)), dim3(kQuantThreads), 0,
+                           stream, (const float4v*)w + at, (const float4v*)chan_s, (float4v*)w_rot + at, blocks, K / 128);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace vq

@@ -51,3 +51,22 @@ def test_gemm_of_very_many_tokens(vq, room, M):
         assert torch.equal(y[at:at + part], want), at
     # every other row is the bias: so many of them equal it
     assert all(int((y[:, n] == b[n]).sum()) >= M - 3 * part for n in range(N))
+
+
+# 2^35 elements and a few rows, in place: one launch would be 2^32 threads.  Rows at both ends and where the second
+# launch begins, against the same rows rotated by themselves
+def test_rotation_of_a_very_large_weight(vq, room):
+    K, N = 8192, (1 << 22) + 37
+    room(N * K * 4)
+    print(f"rotate weight {N} x {K} in place", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    s = torch.exp(torch.randn(K, generator=g, device="cuda") * 0.3)
+    w = torch.empty((N, K), device="cuda")
+    spots = [0, N // 2, (1 << 22) - 5, N - 8]
+    want = []
+    for at in spots:
+        w[at:at + 8] = torch.randn((8, K), generator=g, device="cuda")
+        want.append(vq.vq_rotate_weight(w[at:at + 8].clone(), s))
+    vq.vq_rotate_weight(w, s, w)
+    for at, rows in zip(spots, want):
+        assert torch.equal(w[at:at + 8], rows), at
