@@ -137,3 +137,5 @@ extern "C" void vq_internal_gemm_choice(int w_bits, int M, int N, int K, int num
     choice[1] = c.tile_c;
     choice[2] = c.waves;
 }
+
+extern "C" int vq_internal_gemm_out(int N, const void* y, const void* acc_out) { return vq::rows_out(N, y, acc_out); }

@@ -143,6 +143,21 @@ __device__ __forceinline__ int opaque(int v) {
     return v;
 }
 
+// ---- how the persistent kernel writes rows of Y, whatever its operands are -------------------------
+//   kHalfLines: rows start on 64-byte boundaries (N % 32 == 0): past the caches (nontemporal).
+//   kChunks:    rows of whole 16-byte chunks (N % 8 == 0): through the caches.  A piece of 128 bytes that
+//               begins elsewhere than a memory sector does is two part-written sectors, which the L2 puts
+//               together with those of the neighbouring pieces and memory does not: 20120 x 352 -> 3464
+//               104 us past the caches, 67 through them; 8192 x 1152 -> 3472 58.5 and 45.2; 32768 x 1152 ->
+//               1168 71.5 and 63.9; with rows on 64-byte boundaries past them is 2 to 6 % faster.  fp16
+//               operands: 109.7 and 72.1, 75.6 and 64.4, 104.3 and 92.0 (as any row 73.9, 66.3 and 95.3).
+//   kAnyRow:    any N, rows start at any even address, and an optional copy of the integer sums.
+enum Out { kHalfLines, kChunks, kAnyRow };
+inline Out rows_out(int N, const void* y, const void* acc_out) {
+    if (N % 8 != 0 || acc_out || N >= (1 << 21)) return kAnyRow;   // (a tile's rows within 2^31 bytes)
+    return N % 32 == 0 && (uintptr_t)y % 64 == 0 ? kHalfLines : kChunks;
+}
+
 // ---- kernels that take one tile per workgroup ------------------------------------------------
 // ceil(2^32 / d): the high half of n times this is n / d for 2 <= d and n * d < 2^32 (the product exceeds
 // n / d by less than n / 2^32 < 1 / d).  The kernel begins with two divisions, and a division by a number

@@ -164,15 +164,7 @@ __device__ __forceinline__ v16f mfma_block(v4i w, v4i x, v16f c) {
 }
 
 // K_TAIL:  K is a multiple of 16 but not of 128 (the last stage is partly past K).
-// OUT:     how rows of Y are written.
-//   kHalfLines: rows start on 64-byte boundaries (N % 32 == 0): past the caches (nontemporal).
-//   kChunks:    rows of whole 16-byte chunks (N % 8 == 0): through the caches.  A piece of 128 bytes that
-//               begins elsewhere than a memory sector does is two part-written sectors, which the L2 puts
-//               together with those of the neighbouring pieces and memory does not: 20120 x 352 -> 3464
-//               104 us past the caches, 67 through them; 8192 x 1152 -> 3472 58.5 and 45.2; 32768 x 1152 ->
-//               1168 71.5 and 63.9; with rows on 64-byte boundaries past them is 2 to 6 % faster.
-//   kAnyRow:    any N, rows start at any even address, and an optional copy of the integer sums.
-enum Out { kHalfLines, kChunks, kAnyRow };
+// OUT:     how rows of Y are written (vq_gemm_common.h).
 template <class S, int W_BITS, bool K_TAIL, Out OUT>
 __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant(const GemmArgs a) {
     constexpr bool GENERIC = OUT == kAnyRow;
@@ -690,18 +682,14 @@ hipError_t launch_gemm_shape(GemmArgs a, int w_bits, int num_cus, hipStream_t st
     a.slots = a.tiles_per_xcd < cus_per_xcd ? a.tiles_per_xcd : cus_per_xcd;
     const dim3 grid((unsigned)(a.slots * kXcds)), block(S::kThreads);
     const bool tail = ((w_bits == 16 ? 2 * a.K : a.K) % kTileK) != 0;  // (in bytes of an activation row)
-    Out out = kAnyRow;
-    if (a.N % 8 == 0 && !a.acc_out && a.N < (1 << 21)) {
-        if (a.N % 32 == 0 && (uintptr_t)a.y % 64 == 0) out = kHalfLines;
-        else if (w_bits != 16) out = kChunks;
-    }
+    const Out out = rows_out(a.N, a.y, a.acc_out);
 #define VQ_LAUNCH_GEMM(BITS, TAIL, OUT) \
     return enqueue(gemm_i8_dequant<S, BITS, TAIL, OUT>, grid, block, stream, a)
-#define VQ_LAUNCH_OUT(BITS, TAIL)                                           \
-    do {                                                                    \
-        if (out == kHalfLines) VQ_LAUNCH_GEMM(BITS, TAIL, kHalfLines);      \
-        else if (out == kAnyRow) VQ_LAUNCH_GEMM(BITS, TAIL, kAnyRow);       \
-        else if constexpr (BITS != 16) VQ_LAUNCH_GEMM(BITS, TAIL, kChunks); \
+#define VQ_LAUNCH_OUT(BITS, TAIL)                                      \
+    do {                                                               \
+        if (out == kHalfLines) VQ_LAUNCH_GEMM(BITS, TAIL, kHalfLines); \
+        else if (out == kChunks) VQ_LAUNCH_GEMM(BITS, TAIL, kChunks);  \
+        else VQ_LAUNCH_GEMM(BITS, TAIL, kAnyRow);                      \
     } while (0)
 #define VQ_LAUNCH_BITS(BITS)                  \
     do {                                      \

@@ -76,5 +76,7 @@ hipError_t launch_linear_small(const ProducerArgs& p, const void* w, int w_bits,
 
 }  // namespace vq
 
-// choose_gemm for the tests, which name the kernels that they mean to reach.  Not a part of vq.h.
+// For the tests, which name the kernels that they mean to reach: choose_gemm, and how the persistent kernel
+// writes its rows (Out, vq_gemm_common.h).  Not a part of vq.h.
 extern "C" void vq_internal_gemm_choice(int w_bits, int M, int N, int K, int num_cus, int choice[3]);
+extern "C" int vq_internal_gemm_out(int N, const void* y, const void* acc_out);

@@ -31,3 +31,11 @@ def test_launch_stays_below_2_to_32_threads(bits, M, N):
     if waves or t != 256:   # (the persistent kernel has a workgroup per CU)
         tiles = -(-M // t) * -(-N // c)
         assert -(-tiles // 8) * 8 * (64 * waves or 512) < 2 ** 32
+
+
+# how the persistent kernel writes rows, of int8, packed and fp16 operands alike: those of whole chunks never as any row
+@pytest.mark.parametrize("N,at,sums,want", [(1152, 0, 0, 0), (32, 64, 0, 0), (1152, 16, 0, 1), (1160, 0, 0, 1), (8, 0, 0, 1),
+                                            (3464, 48, 0, 1), (1153, 0, 0, 2), (1156, 0, 0, 2), (1152, 0, 1, 2),
+                                            ((1 << 21) - 8, 0, 0, 1), (1 << 21, 0, 0, 2)])
+def test_rows_of_whole_chunks_go_out_in_chunks(N, at, sums, want):
+    assert binding.lib().vq_internal_gemm_out(N, ctypes.c_void_p(4096 + at), ctypes.c_void_p(4096 if sums else None)) == want

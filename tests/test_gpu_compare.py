@@ -84,6 +84,24 @@ def test_gemm_f16_exact_integers_and_identity(vq):
     assert np.array_equal(y.view(np.uint16), x.view(np.uint16))
 
 
+# rows of whole 16-byte chunks that do not start on 64-byte boundaries, by N or by Y's address: tiles of 256 x 192 in
+# one round, of 256 x 256 in several, with and without a K tail; sums of small integers, exact in fp32 and fp16
+@pytest.mark.parametrize("M,N,K,at", [(1, 8, 72, 0), (257, 264, 64, 0), (2891, 2824, 200, 0), (5003, 5000, 64, 0),
+                                      (9000, 4104, 72, 0), (8192, 1152, 64, 8), (5003, 3456, 136, 24)])
+def test_gemm_f16_rows_of_whole_chunks(vq, M, N, K, at):
+    say(f"gemm_f16 chunks M={M} N={N} K={K} at={at}")
+    g = torch.Generator(device="cuda").manual_seed(83 + M + N)
+    x = torch.randint(-3, 4, (M, K), generator=g, device="cuda").half()
+    w = torch.randint(-2, 3, (N, K), generator=g, device="cuda").half()
+    b = torch.randint(-50, 51, (N,), generator=g, device="cuda").half()
+    want = (x.float() @ w.float().t() + b.float()).half()   # (|sum| <= 6 K + 50 < 2048)
+    buf = torch.full((at + M * N + 64,), 7.5, dtype=torch.float16, device="cuda")
+    y = buf[at:at + M * N].view(M, N)
+    vq.vq_gemm_f16(x, w, b, y)
+    assert torch.equal(y, want)
+    assert (buf[:at] == 7.5).all() and (buf[at + M * N:] == 7.5).all()
+
+
 def test_gemm_f16_full_size_sampled_rows(vq, oracle):
     M, N, K = 32768, 4608, 1152
     say(f"full size gemm_f16 {M}x{K}->{N}")
