@@ -5,6 +5,7 @@ import os
 import pytest
 
 from paper_2406_02540_amd import binding, build
+from gemm_shapes import EVERY_TILE, EVERY_TILE_CASES, ONE_OF_EACH_TILE
 
 CUS = 256   # of an MI355X
 
@@ -39,3 +40,20 @@ def test_launch_stays_below_2_to_32_threads(bits, M, N):
                                             ((1 << 21) - 8, 0, 0, 1), (1 << 21, 0, 0, 2)])
 def test_rows_of_whole_chunks_go_out_in_chunks(N, at, sums, want):
     assert binding.lib().vq_internal_gemm_out(N, ctypes.c_void_p(4096 + at), ctypes.c_void_p(4096 if sums else None)) == want
+
+
+# what the GPU tests run to reach each kernel reaches it, in both widths, with whole lines of K and with a tail
+def test_shapes_reach_their_tiles():
+    for tile, M, N, K in EVERY_TILE_CASES + [(tuple(c[:3]), *c[3:]) for c in ONE_OF_EACH_TILE]:
+        for bits in (8, 4):
+            assert choice(bits, M, N, K) == tile, (bits, M, N, K)
+    assert {tuple(c[:3]) for c in ONE_OF_EACH_TILE} == set(EVERY_TILE)
+    for tile, shapes in EVERY_TILE.items():
+        assert {K % 128 != 0 for _, _, K in shapes} == {True, False}, tile
+
+
+# ... and no kernel is left out: what is picked over a spread of problems
+def test_every_tile_has_shapes():
+    steps = (1, 7, 33, 64, 129, 256, 300, 500, 700, 1001, 1500, 2100, 3000, 5003, 9000)
+    picked = {choice(bits, M, N, K) for bits in (8, 4) for M in steps for N in steps for K in (32, 128, 512, 1152, 2080, 4096)}
+    assert picked == set(EVERY_TILE)

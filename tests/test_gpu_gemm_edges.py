@@ -2,6 +2,8 @@
 output against the exact integer sums, and nothing written outside the output."""
 import pytest
 
+from gemm_shapes import EVERY_TILE_CASES
+
 torch = pytest.importorskip("torch")
 
 pytestmark = pytest.mark.gpu
@@ -61,8 +63,16 @@ def test_output_rows_of_whole_chunks(vq, bits, M, N, K, at):
     check_gemm(vq, bits, M, N, K, at=at)
 
 
-# one tile per workgroup, each size the launcher can choose: 32 x 32, 64 x 64, 128 x 64, 128 x 128,
-# 128 x 256, with ragged last tiles, K of one stage, of a ring's length more or less, and a tail
+# every kernel by the tile that it is picked with (test_gemm_choice.py asks whether it still is): ragged last tiles, K of
+# one stage, of a few and of many, and a tail
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("tile,M,N,K", EVERY_TILE_CASES)
+def test_every_tile(vq, bits, tile, M, N, K):
+    check_gemm(vq, bits, M, N, K)
+
+
+# one tile per workgroup at the edges of sizes: one token, one channel, one more and one less than a tile's, single
+# stages and long K; most run in tiles whose wavefronts divide K, some in shared ones of 64 x 64 to 128 x 256
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K", [(1, 8, 32), (1, 1, 32), (31, 33, 64), (33, 31, 4608), (65, 129, 1152), (32, 32, 1024),
                                    (63, 4607, 96), (300, 2000, 1152), (256, 4608, 512),
@@ -73,8 +83,8 @@ def test_one_tile_per_workgroup(vq, bits, M, N, K):
     check_gemm(vq, bits, M, N, K)
 
 
-# wavefronts that divide K, each size the launcher can choose (32 x 32 with three, six and eight of them, 64 x 32,
-# 64 x 64): fewer lines of K than wavefronts, a line more than they share evenly, tails of a line, ragged last tiles
+# wavefronts that divide K (32 x 32 with three, six and eight of them, 64 x 32, 64 x 64; the last shape in 8 bits is a shared
+# tile): fewer lines of K than wavefronts, a line more than they share evenly, tails of a line, ragged last tiles
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K", [(100, 1000, 160), (100, 1001, 512), (1000, 200, 800), (999, 31, 4608), (16, 1152, 4608),
                                    (61, 1001, 1184), (500, 4607, 512), (300, 1152, 4096), (257, 1149, 4128),

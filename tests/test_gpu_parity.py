@@ -7,6 +7,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from gemm_shapes import ONE_OF_EACH_TILE  # noqa: E402
 from parity_util import assert_fp16_close, freivalds_check  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -174,10 +175,11 @@ def test_gemm_parity(vq, oracle, M, N, K, bits):
 @pytest.mark.parametrize("bits,M,N,K", [(8, 700, 392, 1184), (4, 700, 392, 1184), (8, 300, 136, 224),
                                         (8, 2900, 2824, 1152), (4, 2900, 2824, 1152), (8, 2891, 2824, 144),
                                         (8, 5003, 4999, 144), (4, 5003, 5000, 96), (8, 1001, 1157, 416),
-                                        (4, 1100, 2050, 320), (8, 1025, 4097, 96)])
+                                        (4, 1100, 2050, 320), (8, 1025, 4097, 96)]
+                         + [(bits, *c[3:]) for c in ONE_OF_EACH_TILE for bits in (8, 4)])
 def test_dequantization_rounds_once(vq, oracle, bits, M, N, K):
-    """The rounding the header states for the epilogue, to the bit, in every GEMM kernel (64 x 64, 32 x 32,
-    256 x 192, 256 x 256, 128 x 64, 128 x 128, 128 x 256): s = fp32(x_scale * w_scale), y = fp16(float(acc) * s + bias) with
+    """The rounding the header states for the epilogue, to the bit, in every GEMM kernel (ONE_OF_EACH_TILE;
+    the shapes before it run on the persistent tiles and on some that divide K): s = fp32(x_scale * w_scale), y = fp16(float(acc) * s + bias) with
     the multiply-add exact.  The host evaluates it in fp64, where acc * s is exact (24 + 24 bits)
     and the sum with the bias is off by at most 2^-53 relative: a double rounding through fp64
     could only differ for a sum within 2^-41 fp16 ulps of a tie, which these draws do not hit."""

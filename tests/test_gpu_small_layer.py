@@ -70,6 +70,16 @@ def test_one_launch_gives_the_bits_of_two(vq, producer, M, K, N, bits):
     assert _layer(vq, producer, M, K, N, bits, 9000 + M + K + N) == (not producer.startswith("layernorm") and not past)
 
 
+# near the rule's lines: a workgroup on nearly every CU, in two bands of token tiles and in sixteen, the last one of
+# partial height; rows above 1152 channels where tiles x K ends the rule (208 tiles; 216 are past it)
+@pytest.mark.parametrize("producer", PRODUCERS)
+@pytest.mark.parametrize("M,K,N", [(100, 1152, 1152), (1001, 1152, 100), (100, 1408, 1000), (24, 1408, 4608)])
+@pytest.mark.parametrize("bits", [8, 4])
+def test_one_launch_fills_the_chip(vq, producer, M, K, N, bits):
+    print(f"small layer {producer} {M}x{K}->{N} w{bits}", flush=True)
+    assert _layer(vq, producer, M, K, N, bits, 9700 + M + K + N) == (not producer.startswith("layernorm") and (M, N) != (24, 4608))
+
+
 # K that is no multiple of the stage, of a chunk group or (8 bits) of 32
 @pytest.mark.parametrize("producer", [p for p in PRODUCERS if p != "hadamard"])
 @pytest.mark.parametrize("K,bits", [(16, 8), (512, 8), (1008, 8), (1168, 8), (1520, 8), (32, 4), (544, 4), (1184, 4), (1504, 4)])
