@@ -116,10 +116,12 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     constexpr int kItems = (S::kT + kRowStep - 1) / kRowStep;
     static_assert(kRowStep * kPerRow == S::kThreads, "whole rows of threads");
     const int c0 = (tid % kPerRow) * 8, t0 = tid / kPerRow;
-    // (range-checked, dword by dword: channels past N read as zero)
-    const __amdgpu_buffer_rsrc_t rs_ws = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.w_scale), 0, N * 4, kRsrcFlags);
-    const v4f s0 = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs_ws, (ch0 + c0) * 4, 0, 0));
-    const v4f s1 = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs_ws, (ch0 + c0) * 4 + 16, 0, 0));
+    // (the tile's own scales: 4 N is past an int from 2^29 channels on; range-checked, dword by dword: channels past N
+    // read as zero)
+    const __amdgpu_buffer_rsrc_t rs_ws =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.w_scale) + ch0, 0, rows_w * 4, kRsrcFlags);
+    const v4f s0 = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs_ws, c0 * 4, 0, 0));
+    const v4f s1 = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs_ws, c0 * 4 + 16, 0, 0));
     v4i bias8 = {0, 0, 0, 0};
     if (a.bias) {
         if (c0 + 8 <= rows_w) {

@@ -53,6 +53,33 @@ def test_gemm_of_very_many_tokens(vq, room, M):
     assert all(int((y[:, n] == b[n]).sum()) >= M - 3 * part for n in range(N))
 
 
+# more channels than four times as many fit an int: the scales' bytes and their places are counted in more
+def test_gemm_of_very_many_channels(vq, room):
+    M, N, K = 3, 600_000_003, 16
+    room(N * (K + 4 + 2 + 2 * M + 3))
+    print(f"gemm w8a8 M={M} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    part = 4096 + 77
+    xq = torch.randint(-127, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    xs = torch.exp2(torch.randint(-12, -8, (M,), generator=g, device="cuda").float())
+    wq = torch.zeros((N, K), dtype=torch.int8, device="cuda")
+    ws = torch.full((N,), 2.0 ** -9, device="cuda")
+    b = torch.full((N,), 0.5, dtype=torch.float16, device="cuda")
+    spots = [0, (1 << 29) - part // 2, N - part]
+    for at in spots:
+        wq[at:at + part] = torch.randint(-127, 128, (part, K), generator=g, device="cuda", dtype=torch.int8)
+        ws[at:at + part] = torch.exp2(torch.randint(-8, -4, (part,), generator=g, device="cuda").float())
+        b[at:at + part] = torch.randn(part, generator=g, device="cuda").half()
+    y = torch.full((M, N), 7.0, dtype=torch.float16, device="cuda")
+    vq.vq_gemm_w8a8(xq, xs, wq, ws, b, y=y)
+    for at in spots:
+        acc = xq.double() @ wq[at:at + part].double().t()
+        want = (acc * xs.double()[:, None] * ws[at:at + part].double()[None] + b[at:at + part].double()).half()
+        assert torch.equal(y[:, at:at + part], want), at
+    # every other output is its bias
+    assert all(int((y[m] == b).sum()) >= N - 3 * part for m in range(M))
+
+
 # 2^35 elements and a few rows, in place: one launch would be 2^32 threads.  Rows at both ends and where the second
 # launch begins, against the same rows rotated by themselves
 def test_rotation_of_a_very_large_weight(vq, room):
