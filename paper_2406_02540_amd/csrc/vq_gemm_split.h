@@ -20,8 +20,8 @@
 //   240 x 4096 -> 2304           9.7 / 9.1            12.1 / 8.3
 // A wavefront's next loads leave in a burst as soon as its operands are in registers, ahead of its
 // products; dealt out between the products they were up to 10 % later with 32 x 32 tiles.  With many tiles per CU
-// the operand bytes count, and larger shared tiles win (512 x 1152 -> 1152: 64 x 64 4.6 us, 32 x 32 here 4.5; 1001 x 1152
-// -> 4608: 128 x 256 12.0, here 16).
+// the operand bytes count, and larger shared tiles catch up (512 x 1152 -> 1152: 32 x 32 here 4.5 us, 64 x 64 shared 4.6) and
+// win (1001 x 1152 -> 4608: here 16, 128 x 256 shared 12.0).
 #pragma once
 #include <type_traits>
 

@@ -5,7 +5,7 @@
 namespace vq {
 
 namespace {
-// Eight wavefronts of 32 x 32 that split K two ways (64 x 64, 128 x 64), of 64 x 64 (128 x 128) and eight of
+// Eight wavefronts that split K two ways, of 32 x 32 (64 x 64), 64 x 32 (128 x 64) or 64 x 64 (128 x 128), and eight of
 // 64 x 64 that share it (128 x 256).  The first two leave room for a second workgroup on the CU; the ring is as
 // deep as the LDS allows.
 typedef OneTile<2, 2, 1, 1, 2, 4, 2> Tile64x64;

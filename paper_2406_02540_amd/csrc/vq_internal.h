@@ -7,7 +7,7 @@
 
 namespace vq {
 
-// A kernel of one argument.  (An argument costs the host 0.04 us, the <<<>>> stub 0.15 us of the 2.6 that a launch
+// A kernel of one argument.  (An argument costs the host 0.04 us, the <<<>>> stub 0.15 us beyond the 2.1 that a launch
 // takes; small layers are host-bound.)
 template <class Args>
 inline hipError_t enqueue(void (*kernel)(Args), dim3 grid, dim3 block, hipStream_t stream, const Args& a) {

@@ -4,16 +4,20 @@
 namespace vq {
 
 // Every workgroup has a CU to itself, so the line is drawn at their number; with more of them some would wait for
-// a second round of everything.  Beyond 256 x 1152 tiles x K (rows above 1152 channels) the residual layer, which also
-// reads the branch and writes the sum, is no faster.  Over 31000 problems of 1 to 256 tokens, K 256 to 1536 and 32 to
-// 4608 channels, in captured graphs, one launch takes of the two launches' time (mean, 98th percentile; in the last
-// quarter before the line)
-//   plain 0.75, 0.90; 0.81, 0.94    GELU 0.79, 0.95; 0.89, 1.00    residual 0.80, 1.01; 0.90, 1.05    Hadamard 0.82, 0.98;
-//   0.89, 1.03,
-// and beside that one launch less is 2.8 us less of the host's time.
+// a second round of everything.  Rows above 1152 channels end at 256 x 1152 tiles x K.  In captured graphs of 24 layers of 1
+// to 300 tokens, K 256 to 1536 and 32 to 4608 channels, 300 to 500 problems each, one launch takes of the two launches' time
+// (mean, 98th percentile), with every layer's weights in L2, in the memory-side cache and in memory,
+//   plain         0.78, 0.84    0.86, 0.98    0.84, 0.96
+//   GELU tanh     0.82, 0.91    0.91, 1.10    0.87, 1.02
+//   GELU erf      0.73, 0.93    0.82, 1.07    0.80, 1.00
+//   residual      0.80, 0.93    0.90, 1.10    0.85, 1.03
+//   Hadamard      0.84, 0.93    0.94, 1.11    0.90, 1.02.
+// The slower ones are rows above 1280 channels behind a producer, with weights in the memory-side cache (1.00, 1.13; in L2
+// 0.89, 0.95, in memory 0.95, 1.06): a line of 96, 128 or 160 x 1152 for those rows gave up more in the other two states than
+// it won there.  Called one by one such layers took 6.5 us where two launches had taken 8.0: a launch is 2.1 us of the host's time.
 bool small_layer(int producer, int M, int N, int K, int num_cus) {
     if (producer == kLayerNorm || K > kSmallNch * kSmallLanes * 8) return false;
-    const long tiles = (long)((M + kSmallTokens - 1) / kSmallTokens) * ((N + kSmallChannels - 1) / kSmallChannels);
+    const long tiles = (((long)M + kSmallTokens - 1) / kSmallTokens) * (((long)N + kSmallChannels - 1) / kSmallChannels);
     return tiles <= num_cus && tiles * K <= 256l * 1152;
 }
 
