@@ -9,88 +9,112 @@ namespace vq {
 namespace {
 typedef TileShape<2, 4, 4> Tile256;  // 2 x 4 wavefronts of 128 tokens x 64 channels
 
-// How long a launch takes, in microseconds.  Tiles that all wavefronts of a workgroup share: `base`, plus for
-// every time a CU is filled with `per_cu` workgroups fixed + stage * (stages of 128 bytes of K), plus the
-// same of a last filling with one workgroup only; widen is what 4-bit weights add to a stage.
-// Both tables fitted by least squares over 20000 random problems (1 to 32768 tokens, 32 to 4608 channels, K 256
-// to 4608, 8- and 4-bit weights), each timed with every tile in captured graphs, where the tile was within
-// 15 % of the best: error 6 to 9 %.  Over those problems the tile chosen is on average 0.2 % (above 1e9
-// multiply-adds) and 0.7 % (below 6e9) slower than the best one.
+// How long a launch takes, in microseconds: `base`; for every MB that moves once, of activations, outputs and weights,
+// and for every MB of operands that all the tiles together ask for (Traffic); and what the busiest CU spends on its
+// workgroups.  Where all wavefronts share the tile that is, for every time the CU is filled with `per_cu` workgroups, fixed +
+// stage * (stages of 128 bytes of K), plus the same of a last filling with one workgroup only; widen is what 4-bit weights
+// add to a stage.  Where the `waves` wavefronts divide K it is `fixed` for every workgroup and, for every line of K, `line` and
+// `load` for every 8 KiB of it; and in every filling `fill` and `turn` for each line that a wavefront takes.
+//
+// Fitted to 14000 random problems (1 to 65536 tokens, 8 to 16384 channels, K 16 to 8192, most within 32768, 4608 and 256 to
+// 4608; 8- and 4-bit weights), each timed with every tile in captured graphs: by least squares where a tile was within 25 % of
+// the best, then by descent on what the tile chosen costs over the best.  That is, on average (98th percentile), 0.6 % (6 %)
+// below 1e8 multiply-adds, 0.9 % (8 %) to 6e9 and 0.2 % (3 %) above; with many tokens and few channels (8 to 400) 1.4 % (11 %).
+// Without the bytes, and fitted to problems few of which had few channels, the rule took 2.2 % (17 %) there: 17964 x 3744 -> 88
+// 29.8 us in tiles of 32 x 32, 20.3 in 128 x 128.
+struct Traffic { double x, y, w, l2; };
 struct TileCost {
     int tile_t, tile_c, per_cu;
     double base, fixed, stage, widen, fixed_one, stage_one, widen_one;
+    Traffic mb;
 };
 constexpr TileCost kTileCosts[] = {
-    {64, 64, 2, 2.210, 1.940, 0.361, 0.067, 1.068, 0.215, 0.065},
-    {128, 64, 2, 2.671, 3.085, 0.516, 0.018, 1.419, 0.339, 0.023},
-    {128, 128, 1, 1.710, 4.068, 0.471, 0.011, 0.0, 0.0, 0.0},
-    {128, 256, 1, 2.127, 4.866, 0.778, 0.079, 0.0, 0.0, 0.0},
-    {256, 192, 1, 2.571, 4.325, 1.131, 0.0, 0.0, 0.0, 0.0},
-    {256, 256, 1, 2.177, 5.544, 1.325, 0.0, 0.0, 0.0, 0.0},
+    {32, 32, 2, 1.42, 1.47, 0.172, 0.0256, 0.71, 0.184, 0.0641, {0.0332, 0.0347, 0.0573, 0}},
+    {64, 64, 2, 1.67, 2.01, 0.346, 0.0715, 0.801, 0.21, 0.0902, {0.027, 0.00705, 0.0277, 0}},
+    {128, 64, 2, 2.25, 1.55, 0.566, 0.0288, 1.24, 0.24, 0.058, {0.0359, 0.0842, 0, 0.00432}},
+    {128, 128, 1, 0.00486, 4.46, 0.308, 0.0528, 0, 0, 0, {0.027, 0.00585, 0, 0.0261}},
+    {128, 256, 1, 0.226, 4.08, 0.548, 0.146, 0, 0, 0, {0.00305, 0.112, 0, 0.029}},
+    {256, 192, 1, 1.75, 4.2, 0.721, 0.0922, 0, 0, 0, {0, 0.031, 0.14, 0.0366}},
+    {256, 256, 1, 2.81, 2.96, 1.07, 0.0625, 0, 0, 0, {0, 0.108, 0.133, 0.0238}},
 };
-// Tiles whose K the `waves` wavefronts of a workgroup divide: `base`, plus for every workgroup of a CU `fixed`
-// and, per line of K, `line` and `load` for every 8 KiB that it loads, plus `turn` for every line that a
-// wavefront takes in each filling.
 struct SplitCost {
     int tile_t, tile_c, waves, per_cu;
-    double base, fixed, load, turn, line;
+    double base, fixed, line, load, fill, turn;
+    Traffic mb;
 };
 constexpr SplitCost kSplitCosts[] = {
-    {32, 32, 8, 2, 2.6057, 0.4853, 0.0430, 0.0, 0.0268},
-    {64, 32, 4, 3, 2.6815, 0.3912, 0.0646, 0.1748, 0.0119},
-    {32, 32, 3, 4, 2.6742, 0.1803, 0.0448, 0.1433, 0.0166},
-    {64, 64, 8, 1, 0.7061, 3.1354, 0.0908, 0.0, 0.0123},
-    {32, 32, 6, 3, 2.6642, 0.3712, 0.0372, 0.0, 0.0346},
+    {32, 32, 3, 4, 2.03, 0.165, 0.00313, 0.00566, 0.00119, 0.267, {0.0345, 0.0123, 0.00271, 0.0223}},
+    {32, 32, 6, 3, 1.83, 0.361, 0.0523, 0.0113, 0.274, 0, {0.0287, 0.0341, 0.00143, 0.0125}},
+    {32, 32, 8, 2, 1.66, 0.586, 0.0218, 0.0189, 0.658, 0, {0.0227, 0.00199, 0, 0.0135}},
+    {64, 32, 4, 3, 2.36, 0.00171, 0.035, 0.0401, 0.516, 0.0839, {0.0689, 0.262, 0, 0.00146}},
+    {64, 64, 8, 1, 0.928, 2.44, 0.0467, 0.0338, 0, 0, {0.06, 0.188, 0.0218, 0.0144}},
 };
 
-// Workgroups of the busiest CU: every XCD takes an equal run of tiles.
-long tiles_per_cu(int M, int N, int tile_t, int tile_c, int num_cus) {
-    const long tiles = (((long)M + tile_t - 1) / tile_t) * (((long)N + tile_c - 1) / tile_c);
-    const long per_xcd = (tiles + kXcds - 1) / kXcds;
-    const int cus_per_xcd = num_cus >= kXcds ? num_cus / kXcds : 1;
-    return (per_xcd + cus_per_xcd - 1) / cus_per_xcd;
-}
+// What of a problem the costs depend on.
+struct Problem {
+    int w_bits, M, N, K, cus_per_xcd;
+    long lines;                    // of K
+    bool small;                    // a launch of any tiles is below 2^32 threads
+    double x_mb, y_mb, w_mb;
+    Problem(int w_bits, int M, int N, int K, int num_cus)
+        : w_bits(w_bits), M(M), N(N), K(K), cus_per_xcd(num_cus >= kXcds ? num_cus / kXcds : 1), lines((K + kTileK - 1) / kTileK),
+          small((M / 32 + 1l) * (N / 32 + 1l) < (1l << 22)),
+          x_mb((double)M * K * 1e-6), y_mb((double)M * N * 2e-6), w_mb((double)N * K * w_bits * 0.125e-6) {}
+    long tiles(int t, int c) const { return (long)(((unsigned)M + t - 1) / t) * (((unsigned)N + c - 1) / c); }
+    // Workgroups of the busiest CU: every XCD takes an equal run of tiles.
+    long per_cu(long tiles) const { return ((tiles + kXcds - 1) / kXcds + cus_per_xcd - 1) / cus_per_xcd; }
+    // bytes of a tile's operands per byte of K (rows past M not counted)
+    double rows(int t, int c) const { return (M < t ? M : t) + c * w_bits * 0.125; }
+    double traffic(const Traffic& mb, long tiles, double rows) const {
+        return x_mb * mb.x + y_mb * mb.y + w_mb * mb.w + (double)tiles * rows * (double)lines * (kTileK * 1e-6) * mb.l2;
+    }
+};
 
-double launch_cost(const TileCost& c, int w_bits, int M, int N, int K, int num_cus) {
-    const long rounds = tiles_per_cu(M, N, c.tile_t, c.tile_c, num_cus);
-    const double nk = (double)((K + kTileK - 1) / kTileK), wide = w_bits == 4 ? 1.0 : 0.0;
+double launch_cost(const TileCost& c, const Problem& p) {
+    const long tiles = p.tiles(c.tile_t, c.tile_c), rounds = p.per_cu(tiles);
+    const double nk = (double)p.lines, wide = p.w_bits == 4 ? 1.0 : 0.0;
     double t = c.base + (double)(rounds / c.per_cu) * (c.fixed + (c.stage + wide * c.widen) * nk);
     if (rounds % c.per_cu) t += c.fixed_one + (c.stage_one + wide * c.widen_one) * nk;
-    return t;
+    return t + p.traffic(c.mb, tiles, p.rows(c.tile_t, c.tile_c));
 }
 
-double launch_cost(const SplitCost& c, int w_bits, int M, int N, int K, int num_cus) {
-    const long rounds = tiles_per_cu(M, N, c.tile_t, c.tile_c, num_cus), nl = (K + kTileK - 1) / kTileK;
-    const double loaded = ((M < c.tile_t ? M : c.tile_t) + c.tile_c * w_bits / 8.0) / 64.0;   // (rows past M are not loaded)
-    return c.base + (double)rounds * (c.fixed + (double)nl * (c.line + c.load * loaded)) +
-           (double)((rounds + c.per_cu - 1) / c.per_cu * ((nl + c.waves - 1) / c.waves)) * c.turn;
+double launch_cost(const SplitCost& c, const Problem& p) {
+    const long tiles = p.tiles(c.tile_t, c.tile_c), rounds = p.per_cu(tiles);
+    const double rows = p.rows(c.tile_t, c.tile_c);
+    return c.base + (double)rounds * (c.fixed + (double)p.lines * (c.line + c.load * rows * (1.0 / 64.0))) +
+           (double)((rounds + c.per_cu - 1) / c.per_cu) * (c.fill + c.turn * (double)((p.lines + c.waves - 1) / c.waves)) +
+           p.traffic(c.mb, tiles, rows);
 }
 }  // namespace
 
 // The cheapest of the tiles that one launch takes.  (The persistent kernel's grid does not grow with the problem.)
 GemmChoice choose_gemm(int w_bits, int M, int N, int K, int num_cus) {
+    const Problem p(w_bits, M, N, K, num_cus);
     GemmChoice best{0, 0, 0};
     double best_cost = 0.0;
+#pragma unroll   // (the sizes are constants then: 0.07 us of host time, 0.13 with divisions by variables)
     for (const TileCost& c : kTileCosts) {
-        if (c.tile_t != 256 && (w_bits == 16 || !tiles_launchable(M, N, c.tile_t, c.tile_c, kSharedTileThreads)))
-            continue;  // (the fp16 layer has the persistent kernel only)
+        if (c.tile_t != 256 && w_bits == 16) continue;  // (the fp16 layer has the persistent kernel only)
+        if (c.tile_t != 256 && !p.small && !tiles_launchable(M, N, c.tile_t, c.tile_c, shared_tile_threads(c.tile_t))) continue;
         // fp16: rounds of tiles, the narrower tile (a sixth more operand bytes per multiply-add) only where it saves some
-        const double cost = w_bits == 16 ? (double)tiles_per_cu(M, N, 256, c.tile_c, num_cus) * c.tile_c * (c.tile_c == 192 ? 1.05 : 1.0)
-                                         : launch_cost(c, w_bits, M, N, K, num_cus);
+        const double cost = w_bits == 16 ? (double)p.per_cu(p.tiles(256, c.tile_c)) * c.tile_c * (c.tile_c == 192 ? 1.05 : 1.0)
+                                         : launch_cost(c, p);
         if (!best.tile_t || cost <= best_cost) {
             best = {c.tile_t, c.tile_c, 0};
             best_cost = cost;
         }
     }
-    if (w_bits != 16)
+    if (w_bits != 16) {
+#pragma unroll
         for (const SplitCost& c : kSplitCosts) {
-            if (!tiles_launchable(M, N, c.tile_t, c.tile_c, 64 * c.waves)) continue;
-            const double cost = launch_cost(c, w_bits, M, N, K, num_cus);
+            if (!p.small && !tiles_launchable(M, N, c.tile_t, c.tile_c, 64 * c.waves)) continue;
+            const double cost = launch_cost(c, p);
             if (cost < best_cost) {
                 best = {c.tile_t, c.tile_c, c.waves};
                 best_cost = cost;
             }
         }
+    }
     return best;
 }
 

@@ -45,7 +45,7 @@ struct OneTile {
     static constexpr int kScales = kC * 4 + kT * 4 + kC * 2;
     static constexpr int kWgs = WGS_;
     static_assert((4 / KW) * KW == 4, "K groups");
-    static_assert(kThreads == kSharedTileThreads, "what launch_gemm counts with");
+    static_assert(kThreads == shared_tile_threads(kT), "what launch_gemm counts with");
 };
 
 // Stage loads younger than the one needed: LEFT stages of PER loads.

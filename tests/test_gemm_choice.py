@@ -5,7 +5,7 @@ import os
 import pytest
 
 from paper_2406_02540_amd import binding, build
-from gemm_shapes import EVERY_TILE, EVERY_TILE_CASES, ONE_OF_EACH_TILE
+from gemm_shapes import EIGHT_BIT_TILES, EVERY_TILE, EVERY_TILE_CASES, ONE_OF_EACH_TILE
 
 CUS = 256   # of an MI355X
 
@@ -47,6 +47,8 @@ def test_shapes_reach_their_tiles():
     for tile, M, N, K in EVERY_TILE_CASES + [(tuple(c[:3]), *c[3:]) for c in ONE_OF_EACH_TILE]:
         for bits in (8, 4):
             assert choice(bits, M, N, K) == tile, (bits, M, N, K)
+    for tile, M, N, K in EIGHT_BIT_TILES:
+        assert choice(8, M, N, K) == tile, (M, N, K)
     assert {tuple(c[:3]) for c in ONE_OF_EACH_TILE} == set(EVERY_TILE)
     for tile, shapes in EVERY_TILE.items():
         assert {K % 128 != 0 for _, _, K in shapes} == {True, False}, tile
@@ -57,3 +59,12 @@ def test_every_tile_has_shapes():
     steps = (1, 7, 33, 64, 129, 256, 300, 500, 700, 1001, 1500, 2100, 3000, 5003, 9000)
     picked = {choice(bits, M, N, K) for bits in (8, 4) for M in steps for N in steps for K in (32, 128, 512, 1152, 2080, 4096)}
     assert picked == set(EVERY_TILE)
+
+
+# many tokens and few channels: memory sets the time, and tiles that ask for the same activations several times over, or
+# few of them at a time, take a quarter to two fifths longer
+@pytest.mark.parametrize("bits,M,N,K,tile", [(8, 17964, 88, 3744, (128, 128, 0)), (8, 19294, 78, 2080, (128, 128, 0)),
+                                             (8, 35115, 136, 3216, (256, 192, 0)), (4, 22909, 643, 4000, (256, 192, 0)),
+                                             (8, 14654, 48, 4608, (64, 64, 0)), (4, 23559, 64, 2848, (128, 64, 0))])
+def test_many_tokens_and_few_channels(bits, M, N, K, tile):
+    assert choice(bits, M, N, K) == tile

@@ -2,7 +2,7 @@
 output against the exact integer sums, and nothing written outside the output."""
 import pytest
 
-from gemm_shapes import EVERY_TILE_CASES
+from gemm_shapes import EIGHT_BIT_TILES, EVERY_TILE_CASES
 
 torch = pytest.importorskip("torch")
 
@@ -71,8 +71,13 @@ def test_every_tile(vq, bits, tile, M, N, K):
     check_gemm(vq, bits, M, N, K)
 
 
+@pytest.mark.parametrize("tile,M,N,K", EIGHT_BIT_TILES)
+def test_tiles_of_eight_bit_weights(vq, tile, M, N, K):
+    check_gemm(vq, 8, M, N, K)
+
+
 # one tile per workgroup at the edges of sizes: one token, one channel, one more and one less than a tile's, single
-# stages and long K; most run in tiles whose wavefronts divide K, some in shared ones of 64 x 64 to 128 x 256
+# stages and long K; in tiles whose wavefronts divide K and in shared ones of 32 x 32 to 128 x 256
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K", [(1, 8, 32), (1, 1, 32), (31, 33, 64), (33, 31, 4608), (65, 129, 1152), (32, 32, 1024),
                                    (63, 4607, 96), (300, 2000, 1152), (256, 4608, 512),
@@ -83,8 +88,8 @@ def test_one_tile_per_workgroup(vq, bits, M, N, K):
     check_gemm(vq, bits, M, N, K)
 
 
-# wavefronts that divide K (32 x 32 with three, six and eight of them, 64 x 32, 64 x 64; the last shape in 8 bits is a shared
-# tile): fewer lines of K than wavefronts, a line more than they share evenly, tails of a line, ragged last tiles
+# wavefronts that divide K (32 x 32 with three, six and eight of them, 64 x 32, 64 x 64; a few of the shapes run in shared
+# tiles): fewer lines of K than wavefronts, a line more than they share evenly, tails of a line, ragged last tiles
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K", [(100, 1000, 160), (100, 1001, 512), (1000, 200, 800), (999, 31, 4608), (16, 1152, 4608),
                                    (61, 1001, 1184), (500, 4607, 512), (300, 1152, 4096), (257, 1149, 4128),
