@@ -19,7 +19,8 @@ typedef TileShape<2, 4, 4> Tile256;  // 2 x 4 wavefronts of 128 tokens x 64 chan
 // Fitted to 14000 random problems (1 to 65536 tokens, 8 to 16384 channels, K 16 to 8192, most within 32768, 4608 and 256 to
 // 4608; 8- and 4-bit weights), each timed with every tile in captured graphs: by least squares where a tile was within 25 % of
 // the best, then by descent on what the tile chosen costs over the best.  That is, on average (98th percentile), 0.6 % (6 %)
-// below 1e8 multiply-adds, 0.9 % (8 %) to 6e9 and 0.2 % (3 %) above; with many tokens and few channels (8 to 400) 1.4 % (11 %).
+// below 1e8 multiply-adds, 0.8 % (5 %) to 1e9, 0.9 % (10 %) to 6e9 and 0.2 % (3 %) above; with many tokens and few channels (8
+// to 400) 1.4 % (11 %).
 // Without the bytes, and fitted to problems few of which had few channels, the rule took 2.2 % (17 %) there: 17964 x 3744 -> 88
 // 29.8 us in tiles of 32 x 32, 20.3 in 128 x 128.
 struct Traffic { double x, y, w, l2; };

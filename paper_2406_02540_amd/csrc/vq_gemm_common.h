@@ -164,6 +164,7 @@ inline Out rows_out(int N, const void* y, const void* acc_out) {
 // that is not known is 25 dependent instructions.
 inline unsigned reciprocal_of(unsigned d) { return 0xFFFFFFFFu / d + 1u; }
 
+constexpr int kLine = 128;       // K bytes per line of the kernels whose wavefronts divide K
 constexpr int kTileXcds = 8;
 constexpr int kTileBand = 8;     // token tiles per band in the tile order
 

@@ -31,8 +31,6 @@
 namespace vq {
 namespace {
 
-constexpr int kLine = 128;        // K bytes per line
-
 // (32 BT) tokens x (32 BC) channels, KW wavefronts; WGS workgroups share a CU.
 template <int BT_, int BC_, int KW_, int WGS_>
 struct SplitTile {

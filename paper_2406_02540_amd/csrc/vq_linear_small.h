@@ -26,7 +26,6 @@ namespace {
 
 constexpr int kSmallWaves = 8, kSmallTokens = 8, kSmallChannels = 64;   // a token per wavefront
 constexpr int kSmallNch = 3, kSmallLanes = 64;                          // of up to 1536 channels
-constexpr int kLine = 128;                                              // K bytes per line
 constexpr int kSmallLines = kSmallNch * kSmallLanes * 8 / kLine, kSmallTurns = (kSmallLines + kSmallWaves - 1) / kSmallWaves;
 
 // Codes and scales of a wavefront's token into the workgroup's LDS: lines of [tokens][128], 16-byte pieces
