@@ -17,15 +17,9 @@ typedef __attribute__((address_space(3))) void* lds_ptr;
 constexpr unsigned kRsrcFlags = 0x00020000;  // raw buffer, 32-bit data format
 
 // LDS row r of the weight tile holds which output channel of the tile.
-// Rows are kept in MFMA order: r = slab*64 + b*32 + rho with rho = 8j + 4h + i
-// the row index inside MFMA block b; the accumulator register 4j + i of lanes
-// with lane/32 == h holds that row.  Sending channel slab*64 + 32h + 16b + 4j + i
-// there gives lane half h the 32 consecutive channels slab*64 + 32h .. +31.
-__device__ __forceinline__ int w_row_to_channel(int r) {
-    const int slab = r >> 6, b = (r >> 5) & 1, rho = r & 31;
-    const int j = rho >> 3, h = (rho >> 2) & 1, i = rho & 3;
-    return slab * 64 + 32 * h + 16 * b + 4 * j + i;
-}
+// Rows are kept in MFMA order: r = slab*64 + b*32 + c, with c the column of MFMA block b and the lane (of both halves)
+// that holds its sums.  Sending channel slab*64 + 2c + b there gives a lane two neighbouring channels.
+__device__ __forceinline__ int w_row_to_channel(int r) { return (r & ~63) + 2 * (r & 31) + ((r >> 5) & 1); }
 
 __device__ __forceinline__ unsigned clamp_u32(long v) {
     return v > 0xFFFFFFFFl ? 0xFFFFFFFFu : (unsigned)v;

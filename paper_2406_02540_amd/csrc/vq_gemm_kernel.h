@@ -37,18 +37,25 @@
 //   - LDS tiles are [row][128 B] with the eight 16-byte chunks of a row XOR-ed
 //     by (row/2)%8, which makes the 16-lane groups of a ds_read_b128 hit 16
 //     different bank groups.
-//   - The weights are the MFMA row operand and the tokens the column operand,
-//     so a lane owns one token and, by permuting which weight row sits in
-//     which MFMA row, 32 consecutive output channels of it.  The epilogue
-//     scales and narrows in registers, turns each wavefront's block
-//     through LDS and writes whole 128-byte lines of Y, bypassing the caches'
-//     retention (nontemporal): the operands keep the L2.
+//   - The tokens are the MFMA row operand and the weights the column operand, so a lane owns one
+//     column of each of its two blocks and, by permuting which weight row sits in which column, two
+//     neighbouring output channels, for 16 TB tokens.  The epilogue narrows them to one dword in
+//     registers and stores it: a store of a wave is two token rows x 128 bytes, whole lines,
+//     bypassing the caches' retention (nontemporal: the operands keep the L2).  Nothing is turned
+//     through LDS, a channel's scale and bias are one register each, and a token's scale is read
+//     for two outputs of every lane at once.
+//     What bounds the way out is vector instructions, about 15 cycles of a SIMD for an output of
+//     64 lanes (conversion 4.4, product of the scales 2.4, mixed multiply-add 8.5; nothing of it
+//     runs under MFMAs of the same SIMD): 3900 of the 29000 cycles that a 256 x 256 tile of nine
+//     stages takes, 18400 of them MFMAs.  With a lane owning 32 channels of one token, staged
+//     through LDS to be written as 16 bytes a lane, it was 33500: 20 LDS instructions of 16 bytes a
+//     lane for 32 outputs bound it.  us, then / now: 32768 x 1152 -> 4608 171 / 159, -> 3456 133 /
+//     126, 32768 x 384 -> 3456 73 / 62, 8192 x 1152 -> 3456 with 4-bit weights 37.2 / 33.7.
 //   - The kernel is persistent: one workgroup per CU walks a list of tiles.
 //     The first stage of the next tile is requested while the last stage of
-//     the current one is multiplied, its second stage right behind that stage's
-//     barrier, ahead of the epilogue's stores; the epilogue turns its blocks through
-//     a small LDS area of its own, so the waves go from it into the next tile without
-//     meeting at a barrier.
+//     the current one is multiplied, its second stage in the first pieces of the epilogue (all
+//     at once ahead of it they kept every wave in the load queue for 850 cycles); the waves go
+//     from the epilogue into the next tile without meeting at a barrier.
 //   - Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; each
 //     XCD gets a contiguous run of tiles, ordered in bands of 8 token tiles,
 //     and the workgroups of an XCD take them in turn, so that its L2 sees each
@@ -120,19 +127,14 @@ struct TileShape {
     static constexpr int kWLoaders = 8;
     static constexpr int kWPer8 = kOneList ? 0 : kTileC / 8 / kWLoaders;    // int8 (and fp16) W loads per loading wave
     static constexpr int kWPer4 = kOneList ? 0 : kTileC / 16 / kWLoaders;   // packed 4-bit W loads per loading wave
-    // Epilogue: every wave has a staging area of its own behind the stage buffers, 16 token
-    // rows x 128 B, through which half a block of 32 tokens x 64 channels of fp16 is turned at
-    // a time.  (The stage buffers themselves are busy: the next tile's first two stages land
-    // there while the epilogue runs.)
-    static constexpr int kEpiRows = 16;
-    static constexpr int kEpiWave = kEpiRows * 128;
-    static constexpr int kEpiBytes = kWaves * kEpiWave;
-    static constexpr int kStoresPerTile = TB * 4;            // 128-bit stores of a wave's epilogue
+    // The epilogue is 4 TB pieces of four stores; the next tile's loads go into all but the last four, so at least this
+    // many of a wave's stores are behind them.
+    static constexpr int kPieces = 4 * TB, kStoresBehind = 16;
     static_assert(kTileT == 256, "scales are fetched by threads 0..255, one token each");
     static_assert(kTileC <= 256 && kWaves % 4 == 0 && kWaves >= 8, "tile shape");
     static_assert(kOneList || (kTileC / 8 % kWLoaders == 0 && kTileC / 16 % kWLoaders == 0), "W loads divide evenly");
     static_assert(!kOneList || (kWaves % 2 == 0 && 2 * kWaves <= 32 && 3 * kWaves >= 32), "one turn of the list is mixed, and a wave's groups have its parity");
-    static_assert(kLdsBytes + kScaleBytes + kEpiBytes <= 160 * 1024, "LDS of one CU");
+    static_assert(kLdsBytes + kScaleBytes <= 160 * 1024, "LDS of one CU");
 };
 
 // Where a tile sits in the output (wave-uniform).
@@ -155,12 +157,12 @@ template <int W_BITS>
 struct AccOf { typedef v16i type; };
 template <>
 struct AccOf<16> { typedef v16f type; };
-__device__ __forceinline__ v16i mfma_block(v4i w, v4i x, v16i c) {
-    return __builtin_amdgcn_mfma_i32_32x32x32_i8(w, x, c, 0, 0, 0);
+__device__ __forceinline__ v16i mfma_block(v4i x, v4i w, v16i c) {
+    return __builtin_amdgcn_mfma_i32_32x32x32_i8(x, w, c, 0, 0, 0);
 }
-__device__ __forceinline__ v16f mfma_block(v4i w, v4i x, v16f c) {
+__device__ __forceinline__ v16f mfma_block(v4i x, v4i w, v16f c) {
     // (a cast between vector types of one size reinterprets the bits)
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16((half8)w, (half8)x, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16((half8)x, (half8)w, c, 0, 0, 0);
 }
 
 // K_TAIL:  K is a multiple of 16 but not of 128 (the last stage is partly past K).
@@ -170,7 +172,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     constexpr bool GENERIC = OUT == kAnyRow;
     constexpr int TB = S::TB;
     constexpr int kXStage = S::kXStage, kLdsBytes = S::kLdsBytes;
-    __shared__ __attribute__((aligned(1024))) int8_t lds[kLdsBytes + kScaleBytes + S::kEpiBytes];
+    __shared__ __attribute__((aligned(1024))) int8_t lds[kLdsBytes + kScaleBytes];
     // layout: [X buffer 0][W buffer 0][X buffer 1][W buffer 1][scales][epilogue staging]; a W
     // buffer is [rows][128 B] of int8 or, for 4-bit weights, [rows][64 B] of nibbles.
     int8_t* const lds_x = lds;
@@ -292,6 +294,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                                      ld.voff_w[j], W_BITS != 4 ? k0 : k0 / 2, ld.k_end_w);
     };
     constexpr int kMaxSingles = S::kOneList ? kTurns : 4 + kWPer;
+    static_assert(kMaxSingles <= 3 * TB, "three K steps carry a stage's loads");
     const int n_singles = S::kOneList ? (wave < kGroups - (kTurns - 1) * S::kWaves ? kTurns : kTurns - 1) : 4 + kWPer;
     auto issue_single = [&](const TileLoads& ld, int buf, int k0, int s) {
         if constexpr (S::kOneList) {
@@ -335,8 +338,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     locate_tile(idx);
     decode_tile(cur, ld);
     int buf = 0;  // LDS buffer of the stage about to be multiplied
-    bool requested1 = false;        // the current tile's second stage was requested before the previous epilogue
-    bool stores_in_flight = false;  // this wave wrote outputs in the previous epilogue (kStoresPerTile stores)
+    bool requested1 = false;        // the current tile's second stage was requested in the previous epilogue
+    bool stores_in_flight = false;  // this wave wrote outputs in the previous epilogue, kStoresBehind or more behind its loads
     issue_all(ld, 0, 0);
     // Every line of the weight matrix is asked for once, here, by the whole grid (one dword per
     // 128-byte line and lane, 8 KiB per wave and round): the weights are a few MB that every XCD
@@ -391,8 +394,12 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 const int i = wave * 64 + opaque(lane);
                 *(float*)(lds_sc + i * 4) = pre_ws;
                 *(_Float16*)(lds_sc + 1024 + i * 2) = pre_b;
-                *(float*)(lds_sc + 2048 + i * 4) = pre_xs;
+                // the 4-bit path accumulates 16 * w: the exact 1/16 rides on the token scale
+                *(float*)(lds_sc + 2048 + i * 4) = pre_xs * (W_BITS == 4 ? 0.0625f : 1.0f);
             }
+            // (They have arrived for every wave, which the compiler is told here, ahead of a wait for all loads: it
+            // would otherwise wait for the next tile's second stage where it takes their registers for something else.)
+            asm volatile("" : : "v"(pre_ws), "v"(pre_xs), "v"((int)__builtin_bit_cast(unsigned short, pre_b)));
         };
 
         typedef typename AccOf<W_BITS>::type acc_t;
@@ -412,13 +419,18 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             constexpr bool LAST = decltype(last_tag)::value;
             // what to request while this stage is multiplied: the next stage of this tile,
             // or the first stage of the next tile
-            const bool more = it + 1 < nk;
-            const bool fetch = (more || has_next) && !requested;
-            if (!more && has_next) {
-                step_tile();
-                decode_tile(nxt, ld);
-            }
-            const int fk0 = more ? (it + 1) * kTileK : 0;
+            const bool fetch = (!LAST || has_next) && !requested;
+            // (In a stage of its own the next tile is located behind the first products: ahead of them every wave
+            // of the CU would be at it at once and the matrix cores idle.)
+            constexpr bool kLate = LAST && !FIRST;
+            auto next_tile = [&]() __attribute__((always_inline)) {
+                if (LAST && has_next) {
+                    step_tile();
+                    decode_tile(nxt, ld);
+                }
+            };
+            if (!kLate) next_tile();
+            const int fk0 = LAST ? 0 : (it + 1) * kTileK;
 
             const int8_t* xs = lds_x + buf * kStage;
             const int8_t* ws = lds_w + buf * kStage;
@@ -446,9 +458,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             auto mfma_one = [&](int i, const v4i(&xi)[TB], const v4i(&wi)[2], auto zero_tag) __attribute__((always_inline)) {
                 const int cb = i / TB, tb = i % TB;
                 if constexpr (decltype(zero_tag)::value)
-                    acc[cb][tb] = mfma_block(wi[cb], xi[tb], kZero16);
+                    acc[cb][tb] = mfma_block(xi[tb], wi[cb], kZero16);
                 else
-                    acc[cb][tb] = mfma_block(wi[cb], xi[tb], acc[cb][tb]);
+                    acc[cb][tb] = mfma_block(xi[tb], wi[cb], acc[cb][tb]);
             };
             // read_ks < 0: nothing left to read (the tile's last K step); first_load < 0: no loads
             auto k_step = [&](const v4i(&xi)[TB], const v4i(&wi)[2], auto zero_tag, int read_ks, v4i(&xo)[TB],
@@ -485,29 +497,131 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 k_step(xf[1], wf[1], kAccumulate, 2, xf[0], wf[0], TB);      // K step 1
                 k_step(xf[0], wf[0], kAccumulate, 3, xf[1], wf[1], 2 * TB);  // K step 2
             } else {
-                k_step(xf[1], wf[1], kAccumulate, 0, xf[0], wf[0], 0);       // K step 3 of the previous stage
-                k_step(xf[0], wf[0], kAccumulate, 1, xf[1], wf[1], TB);      // K step 0
-                k_step(xf[1], wf[1], kAccumulate, 2, xf[0], wf[0], 2 * TB);  // K step 1
-                k_step(xf[0], wf[0], kAccumulate, 3, xf[1], wf[1], 3 * TB);  // K step 2
+                constexpr int kAt = kLate ? -TB : 0;
+                k_step(xf[1], wf[1], kAccumulate, 0, xf[0], wf[0], kAt);           // K step 3 of the previous stage
+                if (kLate) {
+                    next_tile();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                k_step(xf[0], wf[0], kAccumulate, 1, xf[1], wf[1], kAt + TB);      // K step 0
+                k_step(xf[1], wf[1], kAccumulate, 2, xf[0], wf[0], kAt + 2 * TB);  // K step 1
+                k_step(xf[0], wf[0], kAccumulate, 3, xf[1], wf[1], kAt + 3 * TB);  // K step 2
             }
             // K step 3 (otherwise at the start of the next stage)
-            if (LAST) k_step(xf[1], wf[1], kAccumulate, -1, xf[0], wf[0], -1);
-            if (!more) park_scales();
+            if (LAST) {
+                k_step(xf[1], wf[1], kAccumulate, -1, xf[0], wf[0], -1);
+                park_scales();
+            }
             // The stage requested above has landed for every wave and every wave is done
             // reading this one.  After the last stage this also says: the scales are in LDS,
             // the next tile's first stage is in, and only stores can be outstanding later.
-            // (A stage whose loads were requested before the previous tile's epilogue has this
-            // wave's stores of that epilogue behind them, and nothing else: the stores may stay
-            // in flight.  Vector memory operations complete in the order they were issued.)
+            // (A stage whose loads were requested in the previous tile's epilogue has stores of this
+            // wave behind them: those may stay in flight.  Vector memory operations complete in the
+            // order they were issued.)
             if (requested && stores_in_flight)
-                wait_loads_before_and_barrier<S::kStoresPerTile>();
+                wait_loads_before_and_barrier<S::kStoresBehind>();
             else
                 wait_loads_and_barrier();
             buf ^= 1;
         };
         constexpr std::true_type kYes{};
         constexpr std::false_type kNo{};
-        if (!wave_live) {
+        // (the next tile's second stage is requested before this tile ends)
+        const bool request1 = has_next && nk >= 2;
+        if (wave_live) {
+            if (nk == 1) {
+                stage(0, kYes, kYes, false);
+            } else {
+                stage(0, kYes, kNo, requested1);
+#pragma unroll 1
+                for (int it = 1; it < nk - 1; ++it) stage(it, kNo, kNo, false);
+                stage(nk - 1, kNo, kYes, false);
+            }
+
+            // ---- epilogue ------------------------------------------------------------
+            // Lane (h = lane/32, c = lane%32) holds channels 2c and 2c + 1 of the wavefront's 64 (accumulator blocks 0 and
+            // 1) for the tokens 8j + 4h + i of each of its TB token blocks (register 4j + i).  Two neighbouring outputs are
+            // one dword, and a store of one dword per lane is a whole 128-byte line of two token rows.
+            const int el = opaque(lane);  // (the epilogue's per-lane values are not kept across the mainloop)
+            const int h = el >> 5, pair = wave_c * 64 + 2 * (el & 31);   // the lane's first channel within the tile
+            const int left = cur.rows_w - pair;                          // channels from there on that exist
+            const int row0 = wave_t * 32 * TB;                           // the wave's first token within the tile
+            const float ws0 = *(const float*)(lds_sc + pair * 4), ws1 = *(const float*)(lds_sc + pair * 4 + 4);
+            const unsigned bias2 = *(const unsigned*)(lds_sc + 1024 + pair * 2);
+            const int8_t* const sc_x = lds_sc + 2048 + (row0 + 4 * h) * 4;
+            // Stores are range-checked, relative to the first of eight token rows: rows past M fall behind the end of
+            // the buffer, lanes whose channels lie past N get an offset behind it (N < 2^21 on this path, so nothing
+            // wraps).
+            const unsigned y_place = left > 0 ? (unsigned)(__mul24(4 * h, GENERIC ? 0 : a.N) + (int)cur.ch0 + pair) * 2u : 0x80000000u;
+            unsigned y_off[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y_off[i] = y_place + (unsigned)(i * a.N) * 2u;
+            const _Float16* y_row = a.y + (cur.tok0 + row0) * a.N;
+            int y_bytes = GENERIC ? 0 : (cur.rows_x - row0) * a.N * 2;   // from there to the end of the tile's rows
+            // (any row: token rows of the wave below which the lane has two channels to write, or one; its place in them)
+            const int rows_live = cur.rows_x - row0 - 4 * h;
+            const int rows_pair = left > 1 ? rows_live : 0, rows_single = left == 1 ? rows_live : 0;
+            long y_any[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y_any[i] = (4 * h + i) * (long)a.N + cur.ch0 + pair;
+            if (GENERIC && a.acc_out) {
+                int32_t* acc_row = a.acc_out + (cur.tok0 + row0) * a.N;
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (tb * 32 + 8 * j + i < rows_live && left > 0) {
+                                constexpr int kShift = (W_BITS == 4) ? 4 : 0;
+                                acc_row[y_any[i]] = (int)acc[0][tb][4 * j + i] >> kShift;
+                                if (left > 1) acc_row[y_any[i] + 1] = (int)acc[1][tb][4 * j + i] >> kShift;
+                            }
+                        acc_row += 8 * (long)a.N;
+                        asm volatile("" : "+s"(acc_row));
+                    }
+            }
+            v4f xs = *(const v4f*)sc_x;
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    // the next tile's second stage, a few loads at a time
+#pragma unroll
+                    for (int l = 0; l < kMaxSingles; ++l)
+                        if (l * (S::kPieces - 4) / kMaxSingles == 4 * tb + j && l < n_singles && request1) issue_single(ld, buf ^ 1, kTileK, l);
+                    v4f xs_next = xs;
+                    if (tb < TB - 1 || j < 3) xs_next = *(const v4f*)(sc_x + (tb * 32 + 8 * (j + 1)) * 4);
+                    const __amdgpu_buffer_rsrc_t rsrc_y =
+                        __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(y_row), 0, max(y_bytes, 0), kRsrcFlags);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int r = 4 * j + i;
+                        unsigned out;
+                        // y = fp16(float(acc) * (x_scale * w_scale) + bias): the product of the two scales rounded to
+                        // fp32, the rest exact and rounded once (dequant_pair)
+                        if constexpr (W_BITS == 16)  // the fp32 sum of the fp16 products, plus the bias
+                            out = add_bias_pair(acc[0][tb][r], acc[1][tb][r], bias2);
+                        else
+                            out = dequant_pair((float)acc[0][tb][r], xs[i] * ws0, (float)acc[1][tb][r], xs[i] * ws1, bias2);
+                        if (!GENERIC) {
+                            __builtin_amdgcn_raw_buffer_store_b32((int)out, rsrc_y, y_off[i], 0, OUT == kHalfLines ? 2 /* nontemporal */ : 0);
+                            continue;
+                        }
+                        // Rows of Y that start at any even address; the last channel of an odd N alone.
+                        typedef unsigned u_any __attribute__((aligned(2)));
+                        if (tb * 32 + 8 * j + i < rows_pair) *(u_any*)(y_row + y_any[i]) = out;
+                        if ((cur.rows_w & 1) && tb * 32 + 8 * j + i < rows_single)
+                            *(unsigned short*)(y_row + y_any[i]) = (unsigned short)out;
+                    }
+                    xs = xs_next;
+                    y_row += 8 * (long)a.N;
+                    y_bytes -= 8 * a.N * 2;
+                    if (GENERIC) asm volatile("" : "+s"(y_row), "+v"(xs));   // (nothing is made up ahead of its use)
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        } else {
             // nothing to multiply in this tile, but this wave's share of the loads is needed
 #pragma unroll 1
             for (int it = 0; it < nk; ++it) {
@@ -521,141 +635,10 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 wait_loads_and_barrier();
                 buf ^= 1;
             }
-        } else if (nk == 1) {
-            stage(0, kYes, kYes, false);
-        } else {
-            stage(0, kYes, kNo, requested1);
-#pragma unroll 1
-            for (int it = 1; it < nk - 1; ++it) stage(it, kNo, kNo, false);
-            stage(nk - 1, kNo, kYes, false);
+            if (request1) issue_all(ld, buf ^ 1, kTileK);
         }
-        // `buf` now names the buffer that holds the next tile's first stage and the other one
-        // is free: the next tile's second stage is requested into it here, ahead of the
-        // epilogue's stores, so that it arrives while the epilogue computes.
-        requested1 = has_next && nk >= 2;
-        if (requested1) issue_all(ld, buf ^ 1, kTileK);
-        stores_in_flight = false;
-
-        // ---- epilogue ------------------------------------------------------------
-        // Lane (h = lane/32, t = lane%32) holds, for each of its TB token blocks, the
-        // 32 channels chl .. chl+31: accumulator block b, register r <-> chl + 16 b + r.
-        if (wave_live) {
-            stores_in_flight = !GENERIC;
-            const int el = opaque(lane);  // (the epilogue's per-lane values are not kept across the mainloop)
-            const int h = el >> 5;
-            const long chw = cur.ch0 + wave_c * 64;  // first channel of this wave
-            // the 4-bit path accumulated 16 * w: the exact 1/16 rides on the token scale
-            const float xmul = (W_BITS == 4) ? 0.0625f : 1.0f;
-            // channel scales are read from LDS where they are used (32 registers fewer across
-            // the epilogue); the bias is kept as it is stored, two fp16 values to a register
-            const int8_t* sc_w = lds_sc + (wave_c * 64 + 32 * h) * 4;
-            const int8_t* sc_b = lds_sc + 1024 + (wave_c * 64 + 32 * h) * 2;
-            v4i bias2[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) bias2[g] = *(const v4i*)(sc_b + 16 * g);
-
-            // staging: [16 token rows][128 B] of this wave, 16-byte chunks XOR-ed by (row/2)%8
-            // (byte offsets into `lds`; the area is 1 KiB aligned, so the XORs below stay inside
-            // the chunk bits)
-            const int stg = kLdsBytes + kScaleBytes + wave * S::kEpiWave;
-            // writes: this lane's token row (el%16 of its half block), logical chunk 4h+g
-            const int st_wr = stg + (el & 15) * 128 + ((4 * h ^ ((el >> 1) & 7)) << 4);
-            // flush reads: row 8i + el/8, logical chunk el%8 (its XOR mask alternates with i)
-            const int st_rd = stg + (el >> 3) * 128 + (((el & 7) ^ (el >> 4)) << 4);
-            // Flush stores are range-checked buffer stores relative to the tile's first token
-            // row: rows past M fall behind the end of the buffer, lanes whose channels lie past
-            // N get an offset behind it (N < 2^21 on this path, so nothing wraps).
-            const int cl = (int)chw + (el & 7) * 8;
-            const __amdgpu_buffer_rsrc_t rsrc_y = __builtin_amdgcn_make_buffer_rsrc(
-                a.y + cur.tok0 * a.N, 0, (int)clamp_u32((long)cur.rows_x * a.N * 2), kRsrcFlags);
-            const unsigned y_off0 =
-                (cl < a.N) ? (unsigned)(((wave_t * 32 * TB + (el >> 3)) * a.N + cl) * 2) : 0x80000000u;
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb) {
-                const int tl = wave_t * 32 * TB + tb * 32 + (el & 31);  // token within the tile
-                const float xsc = *(const float*)(lds_sc + 2048 + tl * 4) * xmul;
-                v4i out[4];  // eight fp16 outputs each
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int b = g >> 1, r0 = (g & 1) * 8;
-                    // y = fp16(float(acc) * (x_scale * w_scale) + bias): the product of the two
-                    // scales rounded to fp32, the rest exact and rounded once (dequant_pair)
-                    float sp[8];
-                    if (W_BITS != 16) {
-                        const v4f s0 = *(const v4f*)(sc_w + 32 * g), s1 = *(const v4f*)(sc_w + 32 * g + 16);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) sp[e] = xsc * s0[e], sp[4 + e] = xsc * s1[e];
-                    }
-#pragma unroll
-                    for (int e = 0; e < 8; e += 2) {
-                        if (W_BITS == 16)  // the fp32 sum of the fp16 products, plus the bias
-                            out[g][e / 2] = (int)add_bias_pair((float)acc[b][tb][r0 + e], (float)acc[b][tb][r0 + e + 1],
-                                                               (unsigned)bias2[g][e / 2]);
-                        else
-                            out[g][e / 2] = (int)dequant_pair((float)acc[b][tb][r0 + e], sp[e], (float)acc[b][tb][r0 + e + 1],
-                                                              sp[e + 1], (unsigned)bias2[g][e / 2]);
-                    }
-                    if (GENERIC && a.acc_out && tl < cur.rows_x) {
-                        int32_t* const arow = a.acc_out + (cur.tok0 + tl) * a.N;
-                        const long c0 = chw + 32 * h + 8 * g;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            if (c0 + e < a.N) {
-                                const int v = (int)acc[b][tb][r0 + e];
-                                arow[c0 + e] = (W_BITS == 4) ? (v >> 4) : v;
-                            }
-                        }
-                    }
-                }
-                // The block goes out in two halves of 16 token rows: the lanes that hold them
-                // stage their 64 bytes each, then the wave writes the 16 rows x 128 B out, a
-                // full line per 8 lanes.  Only this wave touches its staging area and the LDS
-                // operations of a wave execute in order; the fences only keep the compiler
-                // from reordering them.
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    if (((el >> 4) & 1) == p) {
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) *(v4i*)(lds + (st_wr ^ (g << 4))) = out[g];
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    v4i rows[2];
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) rows[i] = *(const v4i*)(lds + (st_rd ^ (i << 6)) + i * 1024);
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        if (!GENERIC) {
-                            __builtin_amdgcn_raw_buffer_store_b128(
-                                rows[i], rsrc_y, y_off0 + (unsigned)((tb * 32 + p * 16 + i * 8) * a.N * 2), 0,
-                                OUT == kHalfLines ? 2 /* nontemporal */ : 0);
-                            continue;
-                        }
-                        // Rows of Y that start at any even address: the same 16 bytes per lane,
-                        // unaligned; a lane whose eight channels straddle N writes those that exist.
-                        // Through the caches, not past them: neighbouring waves share the lines that
-                        // a row's ends fall into.  2891 x 1168 -> 2820: 64 us when every lane wrote its
-                        // elements one by one, 26 with these stores past the caches, 23 as it is.
-                        const int row = wave_t * 32 * TB + tb * 32 + p * 16 + i * 8 + (el >> 3);
-                        const int left = a.N - cl;
-                        if (row < cur.rows_x && left > 0) {
-                            typedef v4i v4i_any __attribute__((aligned(2)));
-                            _Float16* const dst = a.y + (cur.tok0 + row) * a.N + cl;
-                            if (left >= 8) {
-                                *(v4i_any*)dst = rows[i];
-                            } else {
-                                const half8 o = (half8)rows[i];
-#pragma unroll
-                                for (int e = 0; e < 7; ++e)
-                                    if (e < left) dst[e] = o[e];
-                            }
-                        }
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                }
-            }
-        }
+        requested1 = request1;
+        stores_in_flight = wave_live && !GENERIC;
         if (!has_next) break;
         // A one-stage tile parks its scales before its only barrier: nobody may still be
         // reading this tile's.  (Otherwise the waves go on without meeting: every wave stages
