@@ -137,7 +137,7 @@ __device__ __forceinline__ int opaque(int v) {
     return v;
 }
 
-// ---- how the persistent kernel writes rows of Y, whatever its operands are -------------------------
+// ---- how rows of Y are written by the kernels that store them from the registers -------------------------
 //   kHalfLines: rows start on 64-byte boundaries (N % 32 == 0): past the caches (nontemporal).
 //   kChunks:    rows of whole 16-byte chunks (N % 8 == 0): through the caches.  A piece of 128 bytes that
 //               begins elsewhere than a memory sector does is two part-written sectors, which the L2 puts

@@ -14,11 +14,11 @@
 // (0.26 us for the 32 KiB of a 128 x 128 stage out of L2, against 0.21 us for its products), and
 // only as many bytes as the ring holds per memory latency (about 0.9 us beyond L2).
 //
-// GEMM alone in a captured graph, us (8-bit / 4-bit weights): 240 x 4096 -> 2304 in 64 x 64 tiles 9.35 / 11.4, 1001 x
-// 1152 -> 4608 in 128 x 256 12.05 / 13.3, 2048 x 1152 -> 1152 in 128 x 128 8.65 / 9.0, 4096 x 1152 -> 1152 in 128 x 256 12.0
-// / 13.3.  Of the 12 us at 1001 x 1152 -> 4608 1.4 are the way to the first stage (start, six loads per wavefront at the load
-// path's rate), nine stages 0.63 each against 0.43 of products, 0.9 the turn of the sums and 1.5 the stores (144 CUs write
-// 9.2 MB).  Problems of fewer or smaller tiles: vq_gemm_split.h.
+// GEMM alone in a captured graph, us (8-bit / 4-bit weights): 240 x 4096 -> 2304 in 64 x 64 tiles 9.2 / 11.4, 1001 x
+// 1152 -> 4608 in 128 x 256 11.1 / 12.2, 2048 x 1152 -> 1152 in 128 x 128 8.4 / 8.7, 4096 x 1152 -> 1152 in 128 x 256 11.2.
+// Of the 11 us at 1001 x 1152 -> 4608 1.7 are the launch, 1.7 the way to the first stage (start, twelve loads per wavefront at
+// the load path's rate, memory), nine stages 0.63 each against 0.43 of products, and 1.9 the way out (0.8 of vector
+// instructions, the rest stores: 144 CUs write 9.2 MB).  Problems of fewer or smaller tiles: vq_gemm_split.h.
 #pragma once
 #include <type_traits>
 
@@ -41,10 +41,16 @@ struct OneTile {
     static constexpr int kT = WT * BT * 32;               // tokens of the tile
     static constexpr int kC = WC * BC * 32;               // channels of the tile
     static constexpr int kXS = kT * kStageK, kWS = kC * kStageK;
-    static constexpr int kSums = KW * kT * kC * 4;        // every K group's int32 tile, once the stages are done
+    // The way out: through LDS, or straight from the registers of wavefronts with two blocks of channels.  There the K
+    // groups share the tile's token rows, eight at a time: kMine such pieces are a wavefront's own.
+    static constexpr bool kDirect = BC == 2;
+    static constexpr int kMine = 4 * BT / KW;
+    // int32 sums in LDS once the stages are done: every K group's tile, or what the groups hand to each other
+    static constexpr int kSums = kDirect ? kWaves * (KW - 1) * kMine * BC * 1024 : KW * kT * kC * 4;
     static constexpr int kScales = kC * 4 + kT * 4 + kC * 2;
     static constexpr int kWgs = WGS_;
     static_assert((4 / KW) * KW == 4, "K groups");
+    static_assert(BC <= 2, "blocks of channels");
     static_assert(kThreads == shared_tile_threads(kT), "what launch_gemm counts with");
 };
 
@@ -59,7 +65,8 @@ __device__ __forceinline__ void wait_stages(int left) {
     }
 }
 
-template <class S, int W_BITS, bool K_TAIL>
+// OUT: how rows of Y are written where they leave from the registers (vq_gemm_common.h; kAnyRow otherwise).
+template <class S, int W_BITS, bool K_TAIL, Out OUT>
 __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant_tile(const TileArgs a) {
     constexpr int BT = S::BT, BC = S::BC, KW = S::KW, RING = S::RING;
     constexpr int kXArea = RING * S::kXS, kStaged = RING * (S::kXS + S::kWS);
@@ -101,9 +108,11 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     int voff[kPer], k_end[kPer];   // (k_end: used with a K tail only)
     // (Every turn of the list loads one operand, which the compiler is told: with a branch on the wavefront's number in
     // front of every load the 64 x 64 tile took 2 to 4 % longer, with 4-bit weights 5 to 7 %, 128 x 256 2 %.  With 4-bit weights
-    // the groups of 32 x 32, 64 x 64 and 128 x 64 fill the last turn in part, which keeps the branch and a second wait count.)
+    // the groups of 32 x 32, 64 x 64 and 128 x 64 fill the last turn in part, which keeps the branch and a second wait count.
     static_assert(kXG % S::kWaves == 0, "whole turns of activations");
     constexpr int kXTurns = kXG / S::kWaves;
+    // (two blocks of channels are interleaved: a lane then owns two neighbours)
+    auto channel_of = [](int r) { return S::kDirect ? w_row_to_channel(r) : r; };
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
         const int g = wave + S::kWaves * j;
@@ -115,12 +124,12 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         } else if (W_BITS == 8) {
             const int r = (g - kXG) * 8 + (lane >> 3);
             const int at = ((lane & 7) ^ ((r >> 1) & 7)) << 4;
-            voff[j] = __mul24(min(r, rows_w - 1), K) + at;
+            voff[j] = __mul24(min(channel_of(r), rows_w - 1), K) + at;
             k_end[j] = K - at;
         } else {
             const int r = (g - kXG) * 16 + (lane >> 2);
             const int at = ((lane & 3) ^ ((r >> 2) & 3)) << 4;
-            voff[j] = __mul24(min(r, rows_w - 1), K / 2) + at;
+            voff[j] = __mul24(min(channel_of(r), rows_w - 1), K / 2) + at;
             k_end[j] = K / 2 - at;
         }
     }
@@ -163,6 +172,16 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         pre_b[p] = a.bias ? a.bias[ch0 + min(i, rows_w - 1)] : (_Float16)0.0f;
     }
 
+    auto park_scales = [&]() {
+#pragma unroll
+        for (int p = 0; p < kPre; ++p) {
+            const int i = tid + p * S::kThreads;
+            if (i < S::kC) *(float*)(lds_sc + i * 4) = pre_ws[p];
+            if (i < S::kT) *(float*)(lds_sc + S::kC * 4 + i * 4) = pre_xs[p];
+            if (i < S::kC) *(_Float16*)(lds_sc + S::kC * 4 + S::kT * 4 + i * 2) = pre_b[p];
+        }
+    };
+
     // ---- LDS -> MFMA operands ---------------------------------------------------------------
     const int fr_row = lane & 31;
     const int x_off0 = (wave_t * 32 * BT + fr_row) * kStageK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4);
@@ -177,6 +196,10 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         for (int tb = 0; tb < BT; ++tb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[cb][tb][r] = 0;
+    // (the rows of a block are its first operand: tokens where the outputs leave from the registers)
+    auto product = [&](v4i w, v4i x, v16i c) __attribute__((always_inline)) {
+        return __builtin_amdgcn_mfma_i32_32x32x32_i8(S::kDirect ? x : w, S::kDirect ? w : x, c, 0, 0, 0);
+    };
     // Operand registers are double buffered: the products of a K step are issued behind the LDS
     // reads of the step after it, across the stage barrier too.
     v4i xf[2][BT], wf[2][BC];
@@ -188,6 +211,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     constexpr int kSteps = 4 / KW;   // K steps of a stage that are this group's
     auto stage = [&](int it, int slot, auto parity_tag) __attribute__((always_inline)) {
         constexpr int P = decltype(parity_tag)::value;
+        if (S::kDirect && it == nk - 1) park_scales();   // (a barrier of the stages is behind them)
         wait_stage(it);
         const bool fetch = it + RING - 1 < nk;
         const int f_slot = slot == 0 ? RING - 1 : slot - 1, f_k0 = (it + RING - 1) * kStageK;
@@ -217,7 +241,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 for (int j = 0; j < kPer; ++j)
                     if (j * kProducts / kPer == at && fetch) issue_one(f_slot, f_k0, j);
                 const int cb = m / BT, tb = m % BT;
-                acc[cb][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[cur ^ 1][cb], xf[cur ^ 1][tb], acc[cb][tb], 0, 0, 0);
+                acc[cb][tb] = product(wf[cur ^ 1][cb], xf[cur ^ 1][tb], acc[cb][tb]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -228,7 +252,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         for (int cb = 0; cb < BC; ++cb)
 #pragma unroll
             for (int tb = 0; tb < BT; ++tb)
-                acc[cb][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[P][cb], xf[P][tb], acc[cb][tb], 0, 0, 0);
+                acc[cb][tb] = product(wf[P][cb], xf[P][tb], acc[cb][tb]);
     };
     typedef std::integral_constant<int, 0> P0;
     typedef std::integral_constant<int, 1> P1;
@@ -258,19 +282,118 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         }
     }
 
+    if constexpr (S::kDirect) {
+        // ---- sums of the K groups, dequantization, rows of the output ------------------------------------------------
+        // Lane (h = lane/32, c = lane%32) holds channels 2c and 2c + 1 of the wavefront's 64 for the tokens 8j + 4h + i of
+        // each of its blocks (register 4j + i): two neighbouring outputs are one dword, stored from the registers.  Pieces
+        // of eight token rows are numbered 4 tb + j; group g takes kMine of them from g kMine on: it hands the others their
+        // share of its sums through LDS (16 bytes a lane, as they lie in the registers) and adds theirs to its own.
+        // All sums through LDS, in the loop below, were 7000 of the 27000 cycles of 1001 x 1152 -> 4608 in 128 x 256: 13.4 us, 11.1
+        // as it is (4-bit weights 14.4 and 12.2), 2048 x 1152 -> 1152 in 128 x 128 9.3 and 8.4, in 128 x 64 9.3 and 8.6.  The
+        // instructions are seen once, so how rows are written is a template parameter: as a branch the first took 13.1 us again.
+        // With one block of channels a dword is two lanes' outputs, and the loop's few instructions are the faster way: 512 x
+        // 1152 -> 1152 in 64 x 64 4.8 us through LDS, 5.2 from the registers.
+        constexpr int kMine = S::kMine;
+        v4i mine[kMine][BC];
+        auto sums = [&](int q, int cb) __attribute__((always_inline)) {
+            const int tb = q >> 2, j = q & 3;
+            return v4i{acc[cb][tb][4 * j], acc[cb][tb][4 * j + 1], acc[cb][tb][4 * j + 2], acc[cb][tb][4 * j + 3]};
+        };
+        if constexpr (KW > 1) {
+            // what group `from` (one of the others, numbered without the taker) hands to group `to` of its piece p
+            auto handed = [&](int to, int from, int p, int cb) {
+                return (v4i*)(lds + ((((to * S::kSpatial + sp) * (KW - 1) + from) * kMine + p) * BC + cb) * 1024 + lane * 16);
+            };
+            wait_lds_and_barrier();   // nobody reads the stage buffers any more
+#pragma unroll
+            for (int g = 0; g < KW; ++g) {
+                if (kg == g) continue;   // (uniform)
+#pragma unroll
+                for (int p = 0; p < kMine; ++p)
+#pragma unroll
+                    for (int cb = 0; cb < BC; ++cb) *handed(g, kg - (kg > g), p, cb) = sums(g * kMine + p, cb);
+            }
+            wait_lds_and_barrier();
+#pragma unroll
+            for (int g = 0; g < KW; ++g)
+                if (kg == g)
+#pragma unroll
+                    for (int p = 0; p < kMine; ++p)
+#pragma unroll
+                        for (int cb = 0; cb < BC; ++cb) mine[p][cb] = sums(g * kMine + p, cb);
+#pragma unroll
+            for (int from = 0; from < KW - 1; ++from)
+#pragma unroll
+                for (int p = 0; p < kMine; ++p)
+#pragma unroll
+                    for (int cb = 0; cb < BC; ++cb) mine[p][cb] += *handed(kg, from, p, cb);
+        } else {
+#pragma unroll
+            for (int p = 0; p < kMine; ++p)
+#pragma unroll
+                for (int cb = 0; cb < BC; ++cb) mine[p][cb] = sums(p, cb);
+        }
+        const int row0 = wave_t * 32 * BT + 8 * kMine * kg;   // the wavefront's first token row within the tile
+        if (row0 >= rows_x) return;
+        const int h = lane >> 5, pair = wave_c * 64 + 2 * (lane & 31), left = rows_w - pair;   // the lane's channels that exist
+        const long y_first = (long)(tok0 + row0) * a.N + ch0;
+        long y_at[4];   // a piece's four token rows, the lane's place in them
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y_at[i] = (long)(4 * h + i) * a.N + pair;
+        if (OUT == kAnyRow && a.acc_out) {
+            constexpr int kShift = (W_BITS == 4) ? 4 : 0;
+#pragma unroll
+            for (int p = 0; p < kMine; ++p)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    int32_t* const at = a.acc_out + y_first + 8 * p * (long)a.N + y_at[i];
+#pragma unroll
+                    for (int cb = 0; cb < BC; ++cb)
+                        if (row0 + 8 * p + 4 * h + i < rows_x && left > cb) at[cb] = mine[p][cb][i] >> kShift;
+                }
+        }
+        const int8_t* const sc_x = lds_sc + S::kC * 4 + (row0 + 4 * h) * 4;
+        const float ws0 = *(const float*)(lds_sc + pair * 4), ws1 = *(const float*)(lds_sc + pair * 4 + 4);
+        const unsigned bias2 = *(const unsigned*)(lds_sc + S::kC * 4 + S::kT * 4 + pair * 2);
+        _Float16* y_row = a.y + y_first;
+        int y_bytes = OUT == kAnyRow ? 0 : ((rows_x - row0) * a.N - ch0) * 2;   // from there to the end of the tile's rows
+#pragma unroll
+        for (int p = 0; p < kMine; ++p) {
+            // (the 4-bit path summed 16 * w)
+            const v4f xs = *(const v4f*)(sc_x + p * 32) * (W_BITS == 4 ? 0.0625f : 1.0f);
+            unsigned out[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                out[i] = dequant_pair((float)mine[p][0][i], xs[i] * ws0, (float)mine[p][1][i], xs[i] * ws1, bias2);
+            if (OUT != kAnyRow) {
+                // (range-checked: rows past M and, by an offset behind the buffer, channels past N are not written)
+                const __amdgpu_buffer_rsrc_t rsrc_y = __builtin_amdgcn_make_buffer_rsrc(y_row, 0, max(y_bytes, 0), kRsrcFlags);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    __builtin_amdgcn_raw_buffer_store_b32((int)out[i], rsrc_y, left > 0 ? (int)y_at[i] * 2 : (int)0x80000000, 0,
+                                                          OUT == kHalfLines ? 2 /* nontemporal */ : 0);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    typedef unsigned u_any __attribute__((aligned(2)));
+                    const bool row = row0 + 8 * p + 4 * h + i < rows_x;
+                    if (row && left > 1) *(u_any*)(y_row + y_at[i]) = out[i];
+                    if (row && left == 1) *(unsigned short*)(y_row + y_at[i]) = (unsigned short)out[i];
+                }
+            }
+            y_row += 8 * (long)a.N;
+            y_bytes -= 8 * a.N * 2;
+        }
+        return;
+    }
+
     // ---- the sums, through LDS, to rows of the output ------------------------------------------------
     // Every group leaves its sums as a row-major int32 tile, 16-byte chunks (four channels) XOR-ed by
     // the row; then a thread takes eight consecutive channels of a row at a time, adds the groups'
     // sums, dequantizes and writes 16 bytes, consecutive threads along the row.  A thread's channels
     // are the same in every row it takes, so their scales and biases stay in registers.  (The code is
     // short on purpose: it runs once per workgroup, and instructions not seen before come from L2.)
-#pragma unroll
-    for (int p = 0; p < kPre; ++p) {
-        const int i = tid + p * S::kThreads;
-        if (i < S::kC) *(float*)(lds_sc + i * 4) = pre_ws[p];
-        if (i < S::kT) *(float*)(lds_sc + S::kC * 4 + i * 4) = pre_xs[p];
-        if (i < S::kC) *(_Float16*)(lds_sc + S::kC * 4 + S::kT * 4 + i * 2) = pre_b[p];
-    }
+    park_scales();
     wait_lds_and_barrier();   // nobody reads the stage buffers any more
     constexpr int kXor = (S::kC / 4) % 16 == 0 ? 15 : 7;
     constexpr int kRow = S::kC * 4;
@@ -315,8 +438,17 @@ template <class S, int W_BITS>
 hipError_t launch_tile_shape(TileArgs a, hipStream_t stream) {
     if (!tile_grid(a.grid, a.M, a.N, S::kT, S::kC, S::kThreads)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(a.grid.tiles_per_xcd * kTileXcds)), block(S::kThreads);
-    return enqueue(a.K % kStageK ? gemm_i8_dequant_tile<S, W_BITS, true> : gemm_i8_dequant_tile<S, W_BITS, false>, grid, block,
-                   stream, a);
+    auto launch = [&](auto out_tag) {
+        constexpr Out OUT = decltype(out_tag)::value;
+        return enqueue(a.K % kStageK ? gemm_i8_dequant_tile<S, W_BITS, true, OUT> : gemm_i8_dequant_tile<S, W_BITS, false, OUT>, grid,
+                       block, stream, a);
+    };
+    if constexpr (S::kDirect) {
+        const Out out = rows_out(a.N, a.y, a.acc_out);
+        if (out == kHalfLines) return launch(std::integral_constant<Out, kHalfLines>{});
+        if (out == kChunks) return launch(std::integral_constant<Out, kChunks>{});
+    }
+    return launch(std::integral_constant<Out, kAnyRow>{});
 }
 
 }  // namespace

@@ -71,6 +71,26 @@ def test_every_tile(vq, bits, tile, M, N, K):
     check_gemm(vq, bits, M, N, K)
 
 
+# the tiles whose outputs leave from the registers, by how they write rows (0: on 64-byte boundaries, 1: whole 16-byte chunks;
+# the others above are 2, any row): whole and ragged tiles of tokens and channels, with a tail of K and without
+ROWS_OF_TILES = [((128, 64, 0), 0, 1401, 1856, 128), ((128, 64, 0), 0, 809, 2240, 160), ((128, 64, 0), 1, 982, 2728, 128),
+                 ((128, 64, 0), 1, 658, 2392, 416), ((128, 128, 0), 0, 2376, 1632, 128), ((128, 128, 0), 0, 490, 4160, 672),
+                 ((128, 128, 0), 1, 1541, 1720, 384), ((128, 128, 0), 1, 2790, 984, 160), ((128, 256, 0), 0, 1175, 3680, 128),
+                 ((128, 256, 0), 0, 1911, 2464, 160), ((128, 256, 0), 1, 1417, 3304, 128), ((128, 256, 0), 1, 931, 4656, 160)]
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("tile,rows,M,N,K", ROWS_OF_TILES)
+def test_tiles_write_rows_by_alignment(vq, bits, tile, rows, M, N, K):
+    import ctypes
+
+    from paper_2406_02540_amd import binding
+    choice = (ctypes.c_int * 3)()
+    binding.lib().vq_internal_gemm_choice(bits, M, N, K, 256, choice)
+    assert tuple(choice) == tile and binding.lib().vq_internal_gemm_out(N, None, None) == rows
+    check_gemm(vq, bits, M, N, K)
+
+
 @pytest.mark.parametrize("tile,M,N,K", EIGHT_BIT_TILES)
 def test_tiles_of_eight_bit_weights(vq, tile, M, N, K):
     check_gemm(vq, 8, M, N, K)
