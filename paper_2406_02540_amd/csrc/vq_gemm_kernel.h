@@ -321,14 +321,20 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // chosen by l/32; a stage holds four such K steps (chunks 2ks and 2ks+1).
     // The chunk index of K step ks is (2 ks + l/32) ^ swizzle = ((l/32) ^ swizzle) ^ 2 ks, so the
     // byte offset of step ks is that of step 0 with 32 ks XOR-ed in.
+    // 4-bit weights: two K steps 2j and 2j + 1 share one read of 16 bytes of nibbles, chunk 2j + l/32 of the row, whose
+    // first half the lane widens for the one and second half for the other.  The activations follow: chunk 4j + 2 (l/32)
+    // for the first, the one behind it for the second.  (Which 32 bytes of K a step takes does not change the sums.)
+    // With a read of 8 bytes per step the 32 lanes served together took every other 8 bytes of their rows, half of the
+    // banks, and the widening waited for LDS between the products.  us, then / now, in 256 x 192: 32768 x 4608 -> 1152 158 /
+    // 152, 32768 x 1152 -> 1152 45.9 / 44.5, 8192 x 4096 -> 2304 76.4 / 73.8; in 256 x 256 32768 x 1152 -> 4608 161 / 159,
+    // 8192 x 1152 -> 3456 33.3 / 32.9.
     const int fr_row = lane & 31;
-    const int x_off0 = (wave_t * 32 * TB + fr_row) * kTileK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4);
+    const int x_off0 = (wave_t * 32 * TB + fr_row) * kTileK + (((W_BITS != 4 ? lane >> 5 : lane >> 5 << 1) ^ ((fr_row >> 1) & 7)) << 4);
     const int w_off0 = (W_BITS != 4)
                            ? (wave_c * 64 + fr_row) * kTileK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4)
-                           // 8 bytes of nibbles: 16-byte chunk ks (swizzled by (row/4)%4), half l/32
-                           : (wave_c * 64 + fr_row) * (kTileK / 2) + (((fr_row >> 2) & 3) << 4) + (lane >> 5) * 8;
-    auto x_off = [&](int ks) { return x_off0 ^ (ks << 5); };
-    auto w_off = [&](int ks) { return w_off0 ^ (ks << (W_BITS != 4 ? 5 : 4)); };
+                           : (wave_c * 64 + fr_row) * (kTileK / 2) + (((lane >> 5) ^ ((fr_row >> 2) & 3)) << 4);
+    auto x_off = [&](int ks) { return x_off0 ^ (W_BITS != 4 ? ks << 5 : (ks >> 1 << 6) + ((ks & 1) << 4)); };
+    auto w_off = [&](int ks) { return w_off0 ^ (W_BITS != 4 ? ks << 5 : ks >> 1 << 5); };
 
     // ---- the tiles of this workgroup -------------------------------------------
     int idx = blockIdx.x / kXcds;
@@ -405,6 +411,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         typedef typename AccOf<W_BITS>::type acc_t;
         acc_t acc[2][TB];
         v4i xf[2][TB], wf[2][2];  // operand registers, double buffered; [1] carries K step 3 across stages
+        v4i nibbles[2];           // (4-bit weights: of the two K steps that are read together)
         const acc_t kZero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 
         // One stage = four K steps of 2 TB MFMAs per wave.  The schedule is skewed by one K step:
@@ -448,12 +455,17 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                     const int cb = (r == 0) ? 0 : 1;
                     if (W_BITS != 4)
                         wo[cb] = *(const v4i*)(ws + w_off(ks) + cb * 32 * kTileK);
-                    else
-                        wo[cb] = widen_nibbles(*(const v2i*)(ws + w_off(ks) + cb * 32 * (kTileK / 2)));
+                    else if (!(ks & 1))
+                        nibbles[cb] = *(const v4i*)(ws + w_off(ks) + cb * 32 * (kTileK / 2));
                 } else {
                     const int tb = r - 1;
                     xo[tb] = *(const v4i*)(xs + x_off(ks) + tb * 32 * kTileK);
                 }
+            };
+            auto widen = [&](int ks, v4i(&wo)[2]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+                    wo[cb] = widen_nibbles((ks & 1) ? v2i{nibbles[cb][2], nibbles[cb][3]} : v2i{nibbles[cb][0], nibbles[cb][1]});
             };
             auto mfma_one = [&](int i, const v4i(&xi)[TB], const v4i(&wi)[2], auto zero_tag) __attribute__((always_inline)) {
                 const int cb = i / TB, tb = i % TB;
@@ -482,6 +494,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                             __builtin_amdgcn_sched_group_barrier(0x100, kReadsPerPiece / 2, 0);
                         }
                     }
+                    // (in the last piece, which reads nothing: the nibbles have arrived behind the products before it)
+                    if (W_BITS == 4 && read_ks >= 0 && p == TB - 1) widen(read_ks, wo);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
@@ -492,6 +506,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 // nothing deferred to cover them: the first K step's operands are read up front
 #pragma unroll
                 for (int r = 0; r < kReads; ++r) read_one(0, r, xf[0], wf[0]);
+                if (W_BITS == 4) widen(0, wf[0]);
                 __builtin_amdgcn_sched_barrier(0);
                 k_step(xf[0], wf[0], first_tag, 1, xf[1], wf[1], 0);          // K step 0
                 k_step(xf[1], wf[1], kAccumulate, 2, xf[0], wf[0], TB);      // K step 1

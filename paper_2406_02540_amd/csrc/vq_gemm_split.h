@@ -138,8 +138,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 
     // ---- a line at a time ------------------------------------------------------------------
     const int fr_row = lane & 31;
-    const int x_off0 = fr_row * kLine + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4);
-    const int w_off0 = kWAt + ((W_BITS == 8) ? x_off0 : fr_row * (kLine / 2) + (((fr_row >> 2) & 3) << 4) + (lane >> 5) * 8);
+    // (4-bit weights: 16 bytes of nibbles serve two K steps, as in vq_gemm_kernel.h)
+    const int x_off0 = fr_row * kLine + (((W_BITS == 8 ? lane >> 5 : lane >> 5 << 1) ^ ((fr_row >> 1) & 7)) << 4);
+    const int w_off0 = kWAt + ((W_BITS == 8) ? x_off0 : fr_row * (kLine / 2) + (((lane >> 5) ^ ((fr_row >> 2) & 3)) << 4));
     v16i acc[BC][BT];
 #pragma unroll
     for (int cb = 0; cb < BC; ++cb)
@@ -147,19 +148,21 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         for (int tb = 0; tb < BT; ++tb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[cb][tb][r] = 0;
-    typedef typename std::conditional<W_BITS == 8, v4i, v2i>::type raw_t;
+    constexpr int kWReads = W_BITS == 8 ? 4 : 2;
 #pragma unroll 1
     for (int line = wave; line < nl; line += KW) {
         asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
         v4i xf[4][BT];
-        raw_t wf[4][BC];
+        v4i wf[kWReads][BC];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
+            if (ks % (4 / kWReads) == 0)
 #pragma unroll
-            for (int cb = 0; cb < BC; ++cb)
-                wf[ks][cb] = *(const raw_t*)(mine + (w_off0 ^ (ks << (W_BITS == 8 ? 5 : 4))) + cb * 32 * (kLine / kWDiv));
+                for (int cb = 0; cb < BC; ++cb)
+                    wf[ks * kWReads / 4][cb] = *(const v4i*)(mine + (w_off0 ^ (ks * kWReads / 4 << 5)) + cb * 32 * (kLine / kWDiv));
+            const int at = W_BITS == 8 ? ks << 5 : (ks >> 1 << 6) + (ks % 2 << 4);
 #pragma unroll
-            for (int tb = 0; tb < BT; ++tb) xf[ks][tb] = *(const v4i*)(mine + (x_off0 ^ (ks << 5)) + tb * 32 * kLine);
+            for (int tb = 0; tb < BT; ++tb) xf[ks][tb] = *(const v4i*)(mine + (x_off0 ^ at) + tb * 32 * kLine);
         }
         if (line + KW < nl) {   // (the operands are in registers: the space is free)
             asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
@@ -171,7 +174,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             for (int cb = 0; cb < BC; ++cb) {
                 v4i wv;
                 if constexpr (W_BITS == 8) wv = wf[ks][cb];
-                else wv = widen_nibbles(wf[ks][cb]);
+                else wv = widen_nibbles(ks % 2 ? v2i{wf[ks / 2][cb][2], wf[ks / 2][cb][3]} : v2i{wf[ks / 2][cb][0], wf[ks / 2][cb][1]});
 #pragma unroll
                 for (int tb = 0; tb < BT; ++tb)
                     acc[cb][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wv, xf[ks][tb], acc[cb][tb], 0, 0, 0);

@@ -183,10 +183,18 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     };
 
     // ---- LDS -> MFMA operands ---------------------------------------------------------------
+    // 4-bit weights, kPairs: one read of 16 bytes of nibbles for K steps 2j and 2j + 1, as in vq_gemm_kernel.h, widened behind
+    // the products that cover it.  1001 x 1152 -> 4608 in 128 x 256 11.75 us with a read per step, 11.55 so, 240 x 4096 ->
+    // 2304 in 128 x 128 18.5 and 18.15.  With one block of channels there is less to widen than to wait for: 128 x 64 there
+    // 13.85 and 14.2.
+    constexpr int kSteps = 4 / KW;   // K steps of a stage that are this group's
+    constexpr bool kPairs = W_BITS == 4 && kSteps > 1 && BC > 1;
     const int fr_row = lane & 31;
-    const int x_off0 = (wave_t * 32 * BT + fr_row) * kStageK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4);
+    const int x_off0 = (wave_t * 32 * BT + fr_row) * kStageK + (((kPairs ? lane >> 5 << 1 : lane >> 5) ^ ((fr_row >> 1) & 7)) << 4);
     const int w_off0 = (W_BITS == 8)
                            ? (wave_c * 32 * BC + fr_row) * kStageK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4)
+                       : kPairs
+                           ? (wave_c * 32 * BC + fr_row) * (kStageK / 2) + (((lane >> 5) ^ ((fr_row >> 2) & 3)) << 4)
                            : (wave_c * 32 * BC + fr_row) * (kStageK / 2) + (((fr_row >> 2) & 3) << 4) + (lane >> 5) * 8;
 
     v16i acc[BC][BT];
@@ -208,7 +216,6 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 #pragma unroll
     for (int cb = 0; cb < BC; ++cb) wf[1][cb] = v4i{0, 0, 0, 0};
 
-    constexpr int kSteps = 4 / KW;   // K steps of a stage that are this group's
     auto stage = [&](int it, int slot, auto parity_tag) __attribute__((always_inline)) {
         constexpr int P = decltype(parity_tag)::value;
         if (S::kDirect && it == nk - 1) park_scales();   // (a barrier of the stages is behind them)
@@ -217,6 +224,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         const int f_slot = slot == 0 ? RING - 1 : slot - 1, f_k0 = (it + RING - 1) * kStageK;
         const int8_t* xs = lds_x + slot * S::kXS;
         const int8_t* ws = lds_w + slot * S::kWS;
+        v4i nibbles[BC];
 #pragma unroll
         for (int s = 0; s < kSteps; ++s) {
             const int cur = (s + P) & 1;
@@ -225,11 +233,14 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             for (int cb = 0; cb < BC; ++cb) {
                 if (W_BITS == 8)
                     wf[cur][cb] = *(const v4i*)(ws + (w_off0 ^ (ks << 5)) + cb * 32 * kStageK);
-                else
+                else if (kPairs && s % 2 == 0)
+                    nibbles[cb] = *(const v4i*)(ws + (w_off0 ^ (ks >> 1 << 5)) + cb * 32 * (kStageK / 2));
+                else if (!kPairs)
                     wf[cur][cb] = widen_nibbles(*(const v2i*)(ws + (w_off0 ^ (ks << 4)) + cb * 32 * (kStageK / 2)));
             }
 #pragma unroll
-            for (int tb = 0; tb < BT; ++tb) xf[cur][tb] = *(const v4i*)(xs + (x_off0 ^ (ks << 5)) + tb * 32 * kStageK);
+            for (int tb = 0; tb < BT; ++tb)
+                xf[cur][tb] = *(const v4i*)(xs + (x_off0 ^ (kPairs ? (ks >> 1 << 6) + (s % 2 << 4) : ks << 5)) + tb * 32 * kStageK);
             __builtin_amdgcn_sched_barrier(0);
             // The stage's loads are spread over its products (the CU's load path takes 64 bytes per
             // cycle: a burst of loads keeps the wavefront from its products).
@@ -244,6 +255,11 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 acc[cb][tb] = product(wf[cur ^ 1][cb], xf[cur ^ 1][tb], acc[cb][tb]);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            // (behind the products, which cover the way from LDS)
+            if (kPairs)
+#pragma unroll
+                for (int cb = 0; cb < BC; ++cb)
+                    wf[cur][cb] = widen_nibbles(s % 2 ? v2i{nibbles[cb][2], nibbles[cb][3]} : v2i{nibbles[cb][0], nibbles[cb][1]});
         }
     };
     auto last_products = [&](auto parity_tag) __attribute__((always_inline)) {
