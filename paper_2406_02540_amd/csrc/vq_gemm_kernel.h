@@ -310,6 +310,13 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             issue_x(ld, buf, k0, s - kWPer);
         }
     };
+    // With three wavefronts to a SIMD the youngest one comes to its products last, and loads dealt out among them arrived
+    // late: it waited 240 of a stage's 2200 cycles for its own.  It asks for them ahead of its products.  us, then / now,
+    // with 8-bit weights: 8192 x 1152 -> 1152 14.7 / 14.3, 8192 x 4096 -> 2304 75.4 / 72.6, 32768 x 4608 -> 1152 162 / 158.6,
+    // 32768 x 1152 -> 1152 44.3 / 43.5.  The same for the middle one gives the gain back (75.8, 166, 44.2), as for the younger
+    // one of two in 256 x 256 (32768 x 1152 -> 4608 160, 171 so); 4-bit weights, half of the bytes, are in time as it is.
+    constexpr bool kYoungestFirst = S::kWavesPerSimd == 3 && W_BITS != 4;
+    const int n_paced = kYoungestFirst && wave >= S::kWaves - 4 ? 0 : n_singles;
     auto issue_all = [&](const TileLoads& ld, int buf, int k0) {
 #pragma unroll
         for (int s = 0; s < kMaxSingles; ++s)
@@ -479,7 +486,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                               v4i(&wo)[2], int first_load) __attribute__((always_inline)) {
 #pragma unroll
                 for (int p = 0; p < TB; ++p) {
-                    if (fetch && first_load >= 0 && first_load + p < kMaxSingles && first_load + p < n_singles)
+                    if (fetch && first_load >= 0 && first_load + p < kMaxSingles && first_load + p < n_paced)
                         issue_single(ld, buf ^ 1, fk0, first_load + p);
                     mfma_one(2 * p, xi, wi, zero_tag);
                     mfma_one(2 * p + 1, xi, wi, zero_tag);
@@ -506,6 +513,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 // nothing deferred to cover them: the first K step's operands are read up front
 #pragma unroll
                 for (int r = 0; r < kReads; ++r) read_one(0, r, xf[0], wf[0]);
+                if (kYoungestFirst && fetch && n_paced == 0) issue_all(ld, buf ^ 1, fk0);
                 if (W_BITS == 4) widen(0, wf[0]);
                 __builtin_amdgcn_sched_barrier(0);
                 k_step(xf[0], wf[0], first_tag, 1, xf[1], wf[1], 0);          // K step 0
@@ -513,9 +521,11 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 k_step(xf[0], wf[0], kAccumulate, 3, xf[1], wf[1], 2 * TB);  // K step 2
             } else {
                 constexpr int kAt = kLate ? -TB : 0;
+                if (kYoungestFirst && !kLate && fetch && n_paced == 0) issue_all(ld, buf ^ 1, fk0);
                 k_step(xf[1], wf[1], kAccumulate, 0, xf[0], wf[0], kAt);           // K step 3 of the previous stage
                 if (kLate) {
                     next_tile();
+                    if (kYoungestFirst && fetch && n_paced == 0) issue_all(ld, buf ^ 1, fk0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 k_step(xf[0], wf[0], kAccumulate, 1, xf[1], wf[1], kAt + TB);      // K step 0
