@@ -15,7 +15,7 @@
 // only as many bytes as the ring holds per memory latency (about 0.9 us beyond L2).
 //
 // GEMM alone in a captured graph, us (8-bit / 4-bit weights): 240 x 4096 -> 2304 in 64 x 64 tiles 9.2 / 11.4, 1001 x
-// 1152 -> 4608 in 128 x 256 11.1 / 12.2, 2048 x 1152 -> 1152 in 128 x 128 8.4 / 8.7, 4096 x 1152 -> 1152 in 128 x 256 11.2.
+// 1152 -> 4608 in 128 x 256 11.1 / 11.6, 2048 x 1152 -> 1152 in 128 x 128 8.4 / 8.7, 4096 x 1152 -> 1152 in 128 x 256 11.2.
 // Of the 11 us at 1001 x 1152 -> 4608 1.7 are the launch, 1.7 the way to the first stage (start, twelve loads per wavefront at
 // the load path's rate, memory), nine stages 0.63 each against 0.43 of products, and 1.9 the way out (0.8 of vector
 // instructions, the rest stores: 144 CUs write 9.2 MB).  Problems of fewer or smaller tiles: vq_gemm_split.h.
