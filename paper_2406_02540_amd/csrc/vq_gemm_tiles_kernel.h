@@ -356,16 +356,23 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         long y_at[4];   // a piece's four token rows, the lane's place in them
 #pragma unroll
         for (int i = 0; i < 4; ++i) y_at[i] = (long)(4 * h + i) * a.N + pair;
+        // (token rows below which the lane has two channels to write, or one)
+        const int rows_live = rows_x - row0 - 4 * h;
+        const int rows_pair = left > 1 ? rows_live : 0, rows_single = left == 1 ? rows_live : 0;
         if (OUT == kAnyRow && a.acc_out) {
+            // Two neighbours are one store of 8 bytes.  us with sums, through LDS in stores of 16 bytes / from the registers in
+            // two of 4 / as it is: 1001 x 1152 -> 4608 in 128 x 256 18.7 / 18.7 / 17.2, 2048 x 1152 -> 1152 in 128 x 128 12.7 /
+            // 13.1 / 12.3; 2800 random problems in these tiles, over the first way, 1.02 to 1.05 and 0.93 to 0.96 on average.
+            typedef v2i v2i_any4 __attribute__((aligned(4)));
             constexpr int kShift = (W_BITS == 4) ? 4 : 0;
 #pragma unroll
             for (int p = 0; p < kMine; ++p)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     int32_t* const at = a.acc_out + y_first + 8 * p * (long)a.N + y_at[i];
-#pragma unroll
-                    for (int cb = 0; cb < BC; ++cb)
-                        if (row0 + 8 * p + 4 * h + i < rows_x && left > cb) at[cb] = mine[p][cb][i] >> kShift;
+                    const int sum0 = mine[p][0][i] >> kShift, sum1 = mine[p][1][i] >> kShift;
+                    if (8 * p + i < rows_pair) *(v2i_any4*)at = v2i{sum0, sum1};
+                    if ((rows_w & 1) && 8 * p + i < rows_single) *at = sum0;
                 }
         }
         const int8_t* const sc_x = lds_sc + S::kC * 4 + (row0 + 4 * h) * 4;

@@ -91,6 +91,34 @@ def test_tiles_write_rows_by_alignment(vq, bits, tile, rows, M, N, K):
     check_gemm(vq, bits, M, N, K)
 
 
+# the sums leave these tiles in pairs of channels: an odd last channel alone, rows at any multiple of four bytes, and
+# nothing written behind the last one
+@pytest.mark.parametrize("bits,tile,M,N,K", [(8, (128, 64, 0), 1153, 2041, 128), (8, (128, 64, 0), 1153, 2042, 128)] + [
+    (bits, *case) for bits in (8, 4) for case in [((128, 128, 0), 1926, 1455, 160), ((128, 128, 0), 2153, 1630, 128),
+                                                  ((128, 256, 0), 1314, 4057, 128), ((128, 256, 0), 1001, 4608, 160)]])
+def test_sums_of_one_tile_per_workgroup(vq, bits, tile, M, N, K):
+    import ctypes
+
+    from paper_2406_02540_amd import binding
+    choice = (ctypes.c_int * 3)()
+    binding.lib().vq_internal_gemm_choice(bits, M, N, K, 256, choice)
+    assert tuple(choice) == tile
+    print(f"sums w{bits}a8 M={M} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    xq = torch.randint(-127, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    wq = torch.randint(-7, 8, (N, K), generator=g, device="cuda", dtype=torch.int8)
+    w = wq if bits == 8 else ((wq[:, ::2] & 15) | ((wq[:, 1::2] & 15) << 4)).view(torch.uint8).contiguous()
+    ones = torch.ones(max(M, N), device="cuda")
+    y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    sums = torch.full((M * N + 64,), 77, dtype=torch.int32, device="cuda")
+    gemm = binding.lib().vq_gemm_w8a8 if bits == 8 else binding.lib().vq_gemm_w4a8
+    p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert gemm(p(xq), p(ones), p(w), p(ones), None, p(y), p(sums), M, N, K, stream) == 0
+    assert torch.equal(sums[:M * N].view(M, N).double(), xq.double() @ wq.double().t())
+    assert (sums[M * N:] == 77).all()
+
+
 @pytest.mark.parametrize("tile,M,N,K", EIGHT_BIT_TILES)
 def test_tiles_of_eight_bit_weights(vq, tile, M, N, K):
     check_gemm(vq, 8, M, N, K)
