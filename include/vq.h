@@ -185,7 +185,7 @@ int vq_quantize_static(const void* x_f16, const float* chan_mul, float scale, in
  *   bias_f16 in  fp16 [N] or NULL (no bias)
  *   y_f16    out fp16 [M,N]
  *   acc_out  out int32 [M,N] or NULL: a copy of the integer sums, for checking
- * Requires K % 16 == 0.  Any M, N >= 1; N % 8 == 0 takes the vectorised store path.
+ * Requires K % 16 == 0.  Any M, N >= 1; rows of an even N without acc_out are written a little faster.
  */
 int vq_gemm_w8a8(const int8_t* xq, const float* x_scale, const int8_t* wq, const float* w_scale,
                  const void* bias_f16, void* y_f16, int32_t* acc_out,

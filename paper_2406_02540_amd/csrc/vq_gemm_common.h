@@ -138,18 +138,24 @@ __device__ __forceinline__ int opaque(int v) {
 }
 
 // ---- how rows of Y are written by the kernels that store them from the registers -------------------------
-//   kHalfLines: rows start on 64-byte boundaries (N % 32 == 0): past the caches (nontemporal).
-//   kChunks:    rows of whole 16-byte chunks (N % 8 == 0): through the caches.  A piece of 128 bytes that
-//               begins elsewhere than a memory sector does is two part-written sectors, which the L2 puts
-//               together with those of the neighbouring pieces and memory does not: 20120 x 352 -> 3464
-//               104 us past the caches, 67 through them; 8192 x 1152 -> 3472 58.5 and 45.2; 32768 x 1152 ->
-//               1168 71.5 and 63.9; with rows on 64-byte boundaries past them is 2 to 6 % faster.  fp16
-//               operands: 109.7 and 72.1, 75.6 and 64.4, 104.3 and 92.0 (as any row 73.9, 66.3 and 95.3).
-//   kAnyRow:    any N, rows start at any even address, and an optional copy of the integer sums.
-enum Out { kHalfLines, kChunks, kAnyRow };
+// A store is two token rows x 128 bytes, a dword (two channels) per lane.
+//   kHalfLines: rows start on 64-byte boundaries (N % 32 == 0): range-checked, past the caches (nontemporal).  Through them
+//               over random problems 2 to 6 % longer in the persistent kernel and in 128 x 128, 7 % in 128 x 256, 2 % in 128 x 64:
+//               32768 x 1152 -> 4608 with 4-bit weights 172 us and 160, 1001 x 1152 -> 4608 12.6 and 11.7.  A quantizer that
+//               reads Y right behind it doesn't change that: both together -1 to 3 % longer through them.
+//   kDwords:    rows start on dwords (N even): range-checked, through the caches.  A piece of 128 bytes that begins elsewhere
+//               than a memory sector does is two part-written sectors, which the L2 puts together with those of the
+//               neighbouring pieces and memory does not.  us past the caches / through them / as any row: 20120 x 352 -> 3464
+//               101 / 62 / 64, 8192 x 1152 -> 3472 50 / 43 / 44, 8192 x 1152 -> 1154 24.9 / 19.8 / 20.0, 1001 x 1152 -> 4610
+//               13.5 / 12.9 / 14.4; fp16 operands 20120 x 352 -> 3464 108 / 83 / 84.  Over random problems with N even, past
+//               them 1.27 to 1.35 in the persistent kernel, 1.01 to 1.05 in 128 x 128, 128 x 64 and 128 x 256; as any row 1.02 to
+//               1.05 and 1.03 to 1.10.
+//   kAnyRow:    odd N, whose every other row starts between dwords, N from 2^21, and an optional copy of the integer sums:
+//               64-bit addresses, and a comparison for every row.
+enum Out { kHalfLines, kDwords, kAnyRow };
 inline Out rows_out(int N, const void* y, const void* acc_out) {
-    if (N % 8 != 0 || acc_out || N >= (1 << 21)) return kAnyRow;   // (a tile's rows within 2^31 bytes)
-    return N % 32 == 0 && (uintptr_t)y % 64 == 0 ? kHalfLines : kChunks;
+    if (N % 2 != 0 || acc_out || N >= (1 << 21)) return kAnyRow;   // (a tile's rows within 2^31 bytes)
+    return N % 32 == 0 && (uintptr_t)y % 64 == 0 ? kHalfLines : kDwords;
 }
 
 // ---- kernels that take one tile per workgroup ------------------------------------------------

@@ -696,7 +696,7 @@ hipError_t launch_gemm_shape(GemmArgs a, int w_bits, int num_cus, hipStream_t st
 #define VQ_LAUNCH_OUT(BITS, TAIL)                                      \
     do {                                                               \
         if (out == kHalfLines) VQ_LAUNCH_GEMM(BITS, TAIL, kHalfLines); \
-        else if (out == kChunks) VQ_LAUNCH_GEMM(BITS, TAIL, kChunks);  \
+        else if (out == kDwords) VQ_LAUNCH_GEMM(BITS, TAIL, kDwords);  \
         else VQ_LAUNCH_GEMM(BITS, TAIL, kAnyRow);                      \
     } while (0)
 #define VQ_LAUNCH_BITS(BITS)                  \

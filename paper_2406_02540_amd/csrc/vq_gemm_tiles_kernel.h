@@ -399,9 +399,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     typedef unsigned u_any __attribute__((aligned(2)));
-                    const bool row = row0 + 8 * p + 4 * h + i < rows_x;
-                    if (row && left > 1) *(u_any*)(y_row + y_at[i]) = out[i];
-                    if (row && left == 1) *(unsigned short*)(y_row + y_at[i]) = (unsigned short)out[i];
+                    if (8 * p + i < rows_pair) *(u_any*)(y_row + y_at[i]) = out[i];
+                    if ((rows_w & 1) && 8 * p + i < rows_single) *(unsigned short*)(y_row + y_at[i]) = (unsigned short)out[i];
                 }
             }
             y_row += 8 * (long)a.N;
@@ -469,7 +468,7 @@ hipError_t launch_tile_shape(TileArgs a, hipStream_t stream) {
     if constexpr (S::kDirect) {
         const Out out = rows_out(a.N, a.y, a.acc_out);
         if (out == kHalfLines) return launch(std::integral_constant<Out, kHalfLines>{});
-        if (out == kChunks) return launch(std::integral_constant<Out, kChunks>{});
+        if (out == kDwords) return launch(std::integral_constant<Out, kDwords>{});
     }
     return launch(std::integral_constant<Out, kAnyRow>{});
 }

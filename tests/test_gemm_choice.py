@@ -36,9 +36,16 @@ def test_launch_stays_below_2_to_32_threads(bits, M, N):
 
 # how the persistent kernel writes rows, of int8, packed and fp16 operands alike: those of whole chunks never as any row
 @pytest.mark.parametrize("N,at,sums,want", [(1152, 0, 0, 0), (32, 64, 0, 0), (1152, 16, 0, 1), (1160, 0, 0, 1), (8, 0, 0, 1),
-                                            (3464, 48, 0, 1), (1153, 0, 0, 2), (1156, 0, 0, 2), (1152, 0, 1, 2),
+                                            (3464, 48, 0, 1), (1153, 0, 0, 2), (1152, 0, 1, 2),
                                             ((1 << 21) - 8, 0, 0, 1), (1 << 21, 0, 0, 2)])
 def test_rows_of_whole_chunks_go_out_in_chunks(N, at, sums, want):
+    assert binding.lib().vq_internal_gemm_out(N, ctypes.c_void_p(4096 + at), ctypes.c_void_p(4096 if sums else None)) == want
+
+
+# ... and a store is a dword per lane, so that rows of whole dwords (Y itself is 16-byte aligned) are none either
+@pytest.mark.parametrize("N,at,sums,want", [(1156, 0, 0, 1), (1154, 16, 0, 1), (2, 0, 0, 1), ((1 << 21) - 2, 0, 0, 1), (1, 0, 0, 2),
+                                            (1154, 0, 1, 2)])
+def test_rows_of_whole_dwords_go_out_in_dwords(N, at, sums, want):
     assert binding.lib().vq_internal_gemm_out(N, ctypes.c_void_p(4096 + at), ctypes.c_void_p(4096 if sums else None)) == want
 
 

@@ -89,7 +89,17 @@ def test_gemm_f16_exact_integers_and_identity(vq):
 @pytest.mark.parametrize("M,N,K,at", [(1, 8, 72, 0), (257, 264, 64, 0), (2891, 2824, 200, 0), (5003, 5000, 64, 0),
                                       (9000, 4104, 72, 0), (8192, 1152, 64, 8), (5003, 3456, 136, 24)])
 def test_gemm_f16_rows_of_whole_chunks(vq, M, N, K, at):
-    say(f"gemm_f16 chunks M={M} N={N} K={K} at={at}")
+    check_gemm_f16_rows(vq, M, N, K, at)
+
+
+# ... and rows of whole dwords
+@pytest.mark.parametrize("M,N,K,at", [(5, 2, 72, 0), (2891, 2820, 200, 0), (5003, 4994, 64, 0), (9000, 4098, 72, 8)])
+def test_gemm_f16_rows_of_whole_dwords(vq, M, N, K, at):
+    check_gemm_f16_rows(vq, M, N, K, at)
+
+
+def check_gemm_f16_rows(vq, M, N, K, at):
+    say(f"gemm_f16 rows M={M} N={N} K={K} at={at}")
     g = torch.Generator(device="cuda").manual_seed(83 + M + N)
     x = torch.randint(-3, 4, (M, K), generator=g, device="cuda").half()
     w = torch.randint(-2, 3, (N, K), generator=g, device="cuda").half()

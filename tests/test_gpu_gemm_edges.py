@@ -45,8 +45,8 @@ def check_gemm(vq, bits, M, N, K, seed=3, at=0):
     assert torch.equal(y2, want) and torch.equal(acc2.double(), acc)
 
 
-# rows of Y at odd addresses, N % 8 = 1, 3, 4, 7: tiles of 256 x 192 in one round (the first three) and in two,
-# of 256 x 256 in two rounds and in three, of 128 x 256
+# rows of Y that start at any even address (one of them, N % 8 = 4, on dwords): tiles of 256 x 192 in one round (the
+# first three) and in two, of 256 x 256 in two rounds and in three, of 128 x 256
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K", [(2891, 2817, 160), (2900, 3075, 128), (2305, 4612, 288), (4999, 3075, 160),
                                    (5003, 4999, 96), (5003, 4993, 160), (9000, 4095, 96), (5003, 1151, 96)])
@@ -63,6 +63,14 @@ def test_output_rows_of_whole_chunks(vq, bits, M, N, K, at):
     check_gemm(vq, bits, M, N, K, at=at)
 
 
+# ... and rows of whole dwords
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N,K,at", [(2891, 2820, 160, 0), (8192, 1154, 128, 8), (5003, 3458, 160, 0), (5003, 4994, 96, 0),
+                                      (9000, 4098, 128, 8)])
+def test_output_rows_of_whole_dwords(vq, bits, M, N, K, at):
+    check_gemm(vq, bits, M, N, K, at=at)
+
+
 # every kernel by the tile that it is picked with (test_gemm_choice.py asks whether it still is): ragged last tiles, K of
 # one stage, of a few and of many, and a tail
 @pytest.mark.parametrize("bits", [8, 4])
@@ -71,12 +79,16 @@ def test_every_tile(vq, bits, tile, M, N, K):
     check_gemm(vq, bits, M, N, K)
 
 
-# the tiles whose outputs leave from the registers, by how they write rows (0: on 64-byte boundaries, 1: whole 16-byte chunks;
-# the others above are 2, any row): whole and ragged tiles of tokens and channels, with a tail of K and without
+# the tiles whose outputs leave from the registers, by how they write rows (0: on 64-byte boundaries, 1: whole dwords, 2: any
+# row): whole and ragged tiles of tokens and channels, with a tail of K and without
 ROWS_OF_TILES = [((128, 64, 0), 0, 1401, 1856, 128), ((128, 64, 0), 0, 809, 2240, 160), ((128, 64, 0), 1, 982, 2728, 128),
-                 ((128, 64, 0), 1, 658, 2392, 416), ((128, 128, 0), 0, 2376, 1632, 128), ((128, 128, 0), 0, 490, 4160, 672),
-                 ((128, 128, 0), 1, 1541, 1720, 384), ((128, 128, 0), 1, 2790, 984, 160), ((128, 256, 0), 0, 1175, 3680, 128),
-                 ((128, 256, 0), 0, 1911, 2464, 160), ((128, 256, 0), 1, 1417, 3304, 128), ((128, 256, 0), 1, 931, 4656, 160)]
+                 ((128, 64, 0), 1, 658, 2392, 416), ((128, 64, 0), 1, 982, 2730, 128), ((128, 64, 0), 1, 658, 2390, 416),
+                 ((128, 64, 0), 2, 982, 2729, 128), ((128, 64, 0), 2, 658, 2391, 416), ((128, 128, 0), 0, 2376, 1632, 128),
+                 ((128, 128, 0), 0, 490, 4160, 672), ((128, 128, 0), 1, 1541, 1720, 384), ((128, 128, 0), 1, 2790, 984, 160),
+                 ((128, 128, 0), 1, 1541, 1722, 384), ((128, 128, 0), 1, 2790, 986, 160), ((128, 128, 0), 2, 1541, 1721, 384),
+                 ((128, 128, 0), 2, 2790, 985, 160), ((128, 256, 0), 0, 1175, 3680, 128), ((128, 256, 0), 0, 1911, 2464, 160),
+                 ((128, 256, 0), 1, 1417, 3304, 128), ((128, 256, 0), 1, 931, 4656, 160), ((128, 256, 0), 1, 1417, 3306, 128),
+                 ((128, 256, 0), 1, 931, 4654, 160), ((128, 256, 0), 2, 1417, 3305, 128), ((128, 256, 0), 2, 931, 4655, 160)]
 
 
 @pytest.mark.parametrize("bits", [8, 4])
