@@ -157,6 +157,13 @@ inline Out rows_out(int N, const void* y, const void* acc_out) {
     if (N % 2 != 0 || acc_out || N >= (1 << 21)) return kAnyRow;   // (a tile's rows within 2^31 bytes)
     return N % 32 == 0 && (uintptr_t)y % 64 == 0 ? kHalfLines : kDwords;
 }
+// `rows` rows of Y in bytes, where stores are range-checked: a tile's are within 2^31 there.  0 for any row: those are addressed in
+// 64 bits, and with their N the product may not fit (an overflow is undefined even where nothing uses it).
+template <Out OUT>
+__host__ __device__ constexpr int checked_bytes(int rows, int N) {
+    return OUT == kAnyRow ? 0 : rows * N * 2;
+}
+static_assert(checked_bytes<kDwords>(256, (1 << 21) - 1) > 0 && checked_bytes<kAnyRow>(256, 0x7FFFFFFF) == 0, "nothing overflows");
 
 // ---- kernels that take one tile per workgroup ------------------------------------------------
 // ceil(2^32 / d): the high half of n times this is n / d for 2 <= d and n * d < 2^32 (the product exceeds

@@ -580,9 +580,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             const unsigned y_place = left > 0 ? (unsigned)(__mul24(4 * h, GENERIC ? 0 : a.N) + (int)cur.ch0 + pair) * 2u : 0x80000000u;
             unsigned y_off[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) y_off[i] = y_place + (unsigned)(i * a.N) * 2u;
+            for (int i = 0; i < 4; ++i) y_off[i] = y_place + (unsigned)checked_bytes<OUT>(i, a.N);
             const _Float16* y_row = a.y + (cur.tok0 + row0) * a.N;
-            int y_bytes = GENERIC ? 0 : (cur.rows_x - row0) * a.N * 2;   // from there to the end of the tile's rows
+            int y_bytes = checked_bytes<OUT>(cur.rows_x - row0, a.N);   // from there to the end of the tile's rows
             // (any row: token rows of the wave below which the lane has two channels to write, or one; its place in them)
             const int rows_live = cur.rows_x - row0 - 4 * h;
             const int rows_pair = left > 1 ? rows_live : 0, rows_single = left == 1 ? rows_live : 0;
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                     }
                     xs = xs_next;
                     y_row += 8 * (long)a.N;
-                    y_bytes -= 8 * a.N * 2;
+                    y_bytes -= checked_bytes<OUT>(8, a.N);
                     if (GENERIC) asm volatile("" : "+s"(y_row), "+v"(xs));   // (nothing is made up ahead of its use)
                     __builtin_amdgcn_sched_barrier(0);
                 }

@@ -404,7 +404,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 }
             }
             y_row += 8 * (long)a.N;
-            y_bytes -= 8 * a.N * 2;
+            y_bytes -= checked_bytes<OUT>(8, a.N);
         }
         return;
     }
