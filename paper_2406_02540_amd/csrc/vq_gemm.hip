@@ -18,9 +18,12 @@ typedef TileShape<2, 4, 4> Tile256;  // 2 x 4 wavefronts of 128 tokens x 64 chan
 //
 // Fitted to 14000 random problems (1 to 65536 tokens, 8 to 16384 channels, K 16 to 8192, most within 32768, 4608 and 256 to
 // 4608; 8- and 4-bit weights), each timed with every tile in captured graphs: by least squares where a tile was within 25 % of
-// the best, then by descent on what the tile chosen costs over the best.  That is, on average (98th percentile), 0.6 % (6 %)
-// below 1e8 multiply-adds, 0.8 % (5 %) to 1e9, 0.9 % (10 %) to 6e9 and 0.2 % (3 %) above; with many tokens and few channels (8
-// to 400) 1.4 % (11 %).
+// the best, then by descent on what the tile chosen costs over the best one.  The kernels were those before outputs left from
+// the registers, which made 128 x 256 15 % faster on average, 128 x 128 8 %, 128 x 64 with 8-bit weights 4 %, the persistent tiles
+// 4 to 8 %, the others 1 % at most.  19580 other problems with the kernels as they are, the chosen one timed in each: over the best one on average
+// (98th percentile) 0.7 % (6 %) below 1e8 multiply-adds, 0.8 % (8 %) to 1e9, 0.9 % (8 %) to 6e9 and 0.1 % (3 %) above; with many
+// tokens and few channels (8 to 400) 1.4 % (11 %).  With 8-bit weights 256 x 256 is taken in 13 of 378 where 256 x 192 is more
+// than 5 % faster (13415 x 352 -> 4608 43.7 us and 39.2).
 // Without the bytes, and fitted to problems few of which had few channels, the rule took 2.2 % (17 %) there: 17964 x 3744 -> 88
 // 29.8 us in tiles of 32 x 32, 20.3 in 128 x 128.
 struct Traffic { double x, y, w, l2; };

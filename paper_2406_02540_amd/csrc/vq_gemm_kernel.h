@@ -173,7 +173,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     constexpr int TB = S::TB;
     constexpr int kXStage = S::kXStage, kLdsBytes = S::kLdsBytes;
     __shared__ __attribute__((aligned(1024))) int8_t lds[kLdsBytes + kScaleBytes];
-    // layout: [X buffer 0][W buffer 0][X buffer 1][W buffer 1][scales][epilogue staging]; a W
+    // layout: [X buffer 0][W buffer 0][X buffer 1][W buffer 1][scales]; a W
     // buffer is [rows][128 B] of int8 or, for 4-bit weights, [rows][64 B] of nibbles.
     int8_t* const lds_x = lds;
     int8_t* const lds_w = lds + kXStage;
@@ -665,10 +665,10 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         requested1 = request1;
         stores_in_flight = wave_live && !GENERIC;
         if (!has_next) break;
-        // A one-stage tile parks its scales before its only barrier: nobody may still be
-        // reading this tile's.  (Otherwise the waves go on without meeting: every wave stages
-        // in an area of its own, and a barrier of the next tile's first stage comes before its
-        // scales are parked.)
+        // Of LDS the epilogue reads the scales alone, and its loads go to the stage buffer that was free
+        // from the last stage's barrier on.  With two stages and more the barrier that ends the next
+        // tile's first one comes before that tile's scales are parked, so the waves go on without
+        // meeting; a one-stage tile parks them before its only barrier: nobody may still be reading.
         if (nk == 1) wait_lds_and_barrier();
         cur = nxt;
         idx = next_idx;

@@ -11,17 +11,18 @@
 // What bounds such a launch is the way to the first load, one memory latency and the CU's load path (54
 // bytes per cycle).  Where the wavefronts share the tile (vq_gemm_tiles_kernel.h) a stage of a 32 x 32
 // tile took 350 cycles, for barrier, LDS latency and one product each, and with 4-bit weights 500.  In a
-// captured graph, where an empty kernel is 1.7 us, with 32 x 32 (64 x 32, 64 x 64) tiles, us:
+// captured graph over four sets of operands, shared tiles of 32 x 32 (last line: of 64 x 64) / the best of the tiles here, us:
 //   tokens x K -> channels   W8 shared / divided   W4 shared / divided
-//   16 x 1152 -> 1152            3.9 / 3.05            4.5 / 3.1
-//   16 x 4608 -> 1152            7.05 / 4.25           9.4 / 4.1
-//   100 x 512 -> 700             3.2 / 3.15            3.5 / 3.2
-//   256 x 1152 -> 1152           4.65 / 3.7            5.1 / 3.6
-//   240 x 4096 -> 2304           9.7 / 9.1            12.1 / 8.3
+//   16 x 1152 -> 1152            4.0 / 3.35            4.5 / 3.3
+//   16 x 4608 -> 1152            6.7 / 5.0             9.0 / 4.35
+//   100 x 512 -> 700             3.3 / 3.45            3.55 / 3.45
+//   256 x 1152 -> 1152           4.7 / 3.9             5.25 / 3.85
+//   240 x 4096 -> 2304           9.15 / 9.15          11.5 / 8.5
+// 4-bit weights: a read of 16 bytes of nibbles for two K steps, 0.99 of the time with one of 8 bytes for each.
 // A wavefront's next loads leave in a burst as soon as its operands are in registers, ahead of its
 // products; dealt out between the products they were up to 10 % later with 32 x 32 tiles.  With many tiles per CU
-// the operand bytes count, and larger shared tiles catch up (512 x 1152 -> 1152: 32 x 32 here 4.5 us, 64 x 64 shared 4.6) and
-// win (1001 x 1152 -> 4608: here 16, 128 x 256 shared 12.0).
+// the operand bytes count, and larger shared tiles catch up (512 x 1152 -> 1152: 32 x 32 here 4.7 us, 64 x 64 shared 4.7) and
+// win (1001 x 1152 -> 4608: here 18.7, 128 x 256 shared 10.4).
 #pragma once
 #include <type_traits>
 

@@ -108,7 +108,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     int voff[kPer], k_end[kPer];   // (k_end: used with a K tail only)
     // (Every turn of the list loads one operand, which the compiler is told: with a branch on the wavefront's number in
     // front of every load the 64 x 64 tile took 2 to 4 % longer, with 4-bit weights 5 to 7 %, 128 x 256 2 %.  With 4-bit weights
-    // the groups of 32 x 32, 64 x 64 and 128 x 64 fill the last turn in part, which keeps the branch and a second wait count.
+    // the groups of 32 x 32, 64 x 64 and 128 x 64 fill the last turn in part, which keeps the branch and a second wait count.)
     static_assert(kXG % S::kWaves == 0, "whole turns of activations");
     constexpr int kXTurns = kXG / S::kWaves;
     // (two blocks of channels are interleaved: a lane then owns two neighbours)
