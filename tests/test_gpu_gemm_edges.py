@@ -80,7 +80,8 @@ def test_every_tile(vq, bits, tile, M, N, K):
 
 
 # the tiles whose outputs leave from the registers, by how they write rows (0: on 64-byte boundaries, 1: whole dwords, 2: any
-# row): whole and ragged tiles of tokens and channels, with a tail of K and without
+# row): whole and ragged tiles of tokens and channels, with a tail of K and without.  (128 x 64 with 4-bit weights goes through
+# LDS and knows one way only: its rows below are stores that end inside a row of eight channels, or don't.)
 ROWS_OF_TILES = [((128, 64, 0), 0, 1401, 1856, 128), ((128, 64, 0), 0, 809, 2240, 160), ((128, 64, 0), 1, 982, 2728, 128),
                  ((128, 64, 0), 1, 658, 2392, 416), ((128, 64, 0), 1, 982, 2730, 128), ((128, 64, 0), 1, 658, 2390, 416),
                  ((128, 64, 0), 2, 982, 2729, 128), ((128, 64, 0), 2, 658, 2391, 416), ((128, 128, 0), 0, 2376, 1632, 128),
@@ -91,16 +92,36 @@ ROWS_OF_TILES = [((128, 64, 0), 0, 1401, 1856, 128), ((128, 64, 0), 0, 809, 2240
                  ((128, 256, 0), 1, 931, 4654, 160), ((128, 256, 0), 2, 1417, 3305, 128), ((128, 256, 0), 2, 931, 4655, 160)]
 
 
-@pytest.mark.parametrize("bits", [8, 4])
-@pytest.mark.parametrize("tile,rows,M,N,K", ROWS_OF_TILES)
-def test_tiles_write_rows_by_alignment(vq, bits, tile, rows, M, N, K):
+def tile_picked(bits, M, N, K):
     import ctypes
 
     from paper_2406_02540_amd import binding
     choice = (ctypes.c_int * 3)()
     binding.lib().vq_internal_gemm_choice(bits, M, N, K, 256, choice)
-    assert tuple(choice) == tile and binding.lib().vq_internal_gemm_out(N, None, None) == rows
+    return tuple(choice)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("tile,rows,M,N,K", ROWS_OF_TILES)
+def test_tiles_write_rows_by_alignment(vq, bits, tile, rows, M, N, K):
+    from paper_2406_02540_amd import binding
+    assert tile_picked(bits, M, N, K) == tile
+    if bits == 8 or tile != (128, 64, 0):
+        assert binding.lib().vq_internal_gemm_out(N, None, None) == rows
     check_gemm(vq, bits, M, N, K)
+
+
+# ... and rows of N % 32 == 0 where Y itself begins off a 64-byte boundary: whole dwords
+@pytest.mark.parametrize("bits,tile,M,N,K", [(8, (128, 64, 0), 1401, 1856, 128), (8, (128, 64, 0), 809, 2240, 160)] + [
+    (bits, *case) for bits in (8, 4) for case in [((128, 128, 0), 2376, 1632, 128), ((128, 128, 0), 490, 4160, 672),
+                                                  ((128, 256, 0), 1175, 3680, 128), ((128, 256, 0), 1911, 2464, 160)]])
+def test_tiles_write_rows_by_address(vq, bits, tile, M, N, K):
+    import ctypes
+
+    from paper_2406_02540_amd import binding
+    assert tile_picked(bits, M, N, K) == tile
+    assert [binding.lib().vq_internal_gemm_out(N, ctypes.c_void_p(at), None) for at in (4096, 4096 + 16)] == [0, 1]
+    check_gemm(vq, bits, M, N, K, at=8)
 
 
 # the sums leave these tiles in pairs of channels: an odd last channel alone, rows at any multiple of four bytes, and
@@ -112,9 +133,7 @@ def test_sums_of_one_tile_per_workgroup(vq, bits, tile, M, N, K):
     import ctypes
 
     from paper_2406_02540_amd import binding
-    choice = (ctypes.c_int * 3)()
-    binding.lib().vq_internal_gemm_choice(bits, M, N, K, 256, choice)
-    assert tuple(choice) == tile
+    assert tile_picked(bits, M, N, K) == tile
     print(f"sums w{bits}a8 M={M} N={N} K={K}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(11)
     xq = torch.randint(-127, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
