@@ -66,7 +66,7 @@ def test_output_rows_of_whole_chunks(vq, bits, M, N, K, at):
 # ... and rows of whole dwords
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K,at", [(2891, 2820, 160, 0), (8192, 1154, 128, 8), (5003, 3458, 160, 0), (5003, 4994, 96, 0),
-                                      (9000, 4098, 128, 8)])
+                                      (9000, 4098, 128, 8), (260, (1 << 21) - 2, 32, 0)])   # (the last N that is taken there)
 def test_output_rows_of_whole_dwords(vq, bits, M, N, K, at):
     check_gemm(vq, bits, M, N, K, at=at)
 
