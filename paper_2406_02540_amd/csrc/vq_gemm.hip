@@ -7,7 +7,7 @@
 namespace vq {
 
 namespace {
-typedef TileShape<2, 4, 4> Tile256;  // 2 x 4 wavefronts of 128 tokens x 64 channels
+typedef TileShape<2, 4, 8, true> Tile256;  // 2 x 4 wavefronts of 128 tokens x 64 channels
 
 // How long a launch takes, in microseconds: `base`; for every MB that moves once, of activations, outputs and weights,
 // and for every MB of operands that all the tiles together ask for (Traffic); and what the busiest CU spends on its

@@ -56,10 +56,20 @@ __device__ __forceinline__ void load_to_lds_16(v4i rsrc, unsigned lds_addr, int 
         : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
         : "memory", "m0");
 }
+// The same with 4 bytes per lane, to lds_addr + 4 * lane.
+__device__ __forceinline__ void load_to_lds_4(v4i rsrc, unsigned lds_addr, int voff) {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "buffer_load_dword %1, %2, 0 offen lds"
+        :
+        : "s"(lds_addr), "v"(voff), "s"(rsrc)
+        : "memory", "m0");
+}
 
 #pragma clang diagnostic pop
 
-// The same for a stage at byte k0 of the rows.  K a multiple of the stage: k0 rides in the scalar
+// A 16-byte load for a stage at byte k0 of the rows.  K a multiple of the stage: k0 rides in the scalar
 // offset.  Otherwise (the last stage reaches past K) it is added to the per-lane offset, the part
 // of the address that the buffer's range check looks at, and the lanes whose piece lies at or past
 // the end of the row (k0 >= k_end, the row's bytes less the piece's place in the stage) get an
@@ -164,6 +174,45 @@ __host__ __device__ constexpr int checked_bytes(int rows, int N) {
     return OUT == kAnyRow ? 0 : rows * N * 2;
 }
 static_assert(checked_bytes<kDwords>(256, (1 << 21) - 1) > 0 && checked_bytes<kAnyRow>(256, 0x7FFFFFFF) == 0, "nothing overflows");
+
+// ---- persistent kernels: tiles of 256 tokens ---------------------------------------------------
+constexpr int kTileK = 128;                 // K bytes per stage (one cache line per row)
+constexpr int kBand = 8;                    // token tiles per band in the tile order
+constexpr int kXcds = 8;
+constexpr int kTouchRounds = 4;             // weight lines asked for up front: at most 4 x 8 KiB per wave (64 MiB per 256 CUs)
+
+struct GemmArgs {
+    const int8_t* xq;
+    const float* x_scale;
+    const void* w;
+    const float* w_scale;
+    const _Float16* bias;
+    _Float16* y;
+    int32_t* acc_out;
+    int M, N, K;
+    int tiles_t, tiles_c, tiles, tiles_per_xcd;
+    int slots;  // workgroups per XCD; workgroup (xcd, slot) takes tiles slot, slot + slots, ... of its XCD
+};
+
+// The grid for tiles of t x c outputs and the tile fields of `a`; false if they are more than the kernel counts.
+inline bool persistent_grid(GemmArgs& a, dim3& grid, int t, int c, int num_cus) {
+    if (a.M > 0x7FFFFF00 || a.N > 0x7FFFFF00) return false;  // (rows and channels of a last tile fit an int)
+    a.tiles_t = (a.M + t - 1) / t;
+    a.tiles_c = (a.N + c - 1) / c;
+    const long tiles = (long)a.tiles_t * a.tiles_c;
+    if (tiles > 0x7FFFFFF0l) return false;
+    a.tiles = (int)tiles;
+    a.tiles_per_xcd = (a.tiles + kXcds - 1) / kXcds;
+    // one workgroup per CU (the kernels need most of a CU's LDS), fewer if there are fewer tiles
+    const int cus_per_xcd = num_cus >= kXcds ? num_cus / kXcds : 1;
+    a.slots = a.tiles_per_xcd < cus_per_xcd ? a.tiles_per_xcd : cus_per_xcd;
+    grid = dim3((unsigned)(a.slots * kXcds));
+    return true;
+}
+
+// The 256 x 192 tile: 8-bit weights and fp16 operands (vq_gemm_192.hip), 4-bit weights (vq_gemm_192w4.hip).
+hipError_t launch_gemm_192(const GemmArgs& a, int w_bits, int num_cus, hipStream_t stream);
+hipError_t launch_gemm_192w4(GemmArgs a, int num_cus, hipStream_t stream);
 
 // ---- kernels that take one tile per workgroup ------------------------------------------------
 // ceil(2^32 / d): the high half of n times this is n / d for 2 <= d and n * d < 2^32 (the product exceeds

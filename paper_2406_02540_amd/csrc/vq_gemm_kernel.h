@@ -8,11 +8,11 @@
 //     y[m,n]   = fp16(float(acc) * x_scale[m] * w_scale[n] + bias[n])
 // W4A8 (appendix "Performance under lower bitwidth"): 4-bit weights are staged
 // in LDS packed and widened to int8 on their way from LDS into the MFMA operand
-// registers; the mainloop is otherwise the same.
+// registers; the mainloop is otherwise the same.  (256 x 192 with 4-bit weights: vq_gemm_192w4.hip.)
 //
 // Shape of the kernel
 //   - workgroup tile: 256 tokens x (64 WC) output channels, WT x WC wavefronts, each
-//     wavefront (32 TB) tokens x 64 channels = 2 x TB MFMA 32x32x32 blocks.  Two tiles:
+//     wavefront (16 XB) tokens x 64 channels = XB x 4 MFMA 16x16x64 blocks.  Two tiles:
 //       256 x 256: 2 x 4 wavefronts of 128 x 64 (128 int32 accumulators per lane), two
 //                  wavefronts per SIMD;
 //       256 x 192: 4 x 3 wavefronts of 64 x 64 (64 accumulators), three per SIMD: for
@@ -22,40 +22,46 @@
 //                  rounds of whole tiles for 2.25 rounds of work).
 //     The tile is large because the L2 -> CU path, not HBM, is what the operand traffic
 //     loads: bytes per multiply-add fall with the tile edge.
-//   - K is walked in stages of 128 bytes, double buffered in LDS.  A stage
-//     takes one full 128-byte cache line per row, so every L2 request is a
+//   - What bounds the large launches is power: the clock under them is 1.6 to 2.1 GHz of 2.4, and a cycle taken out of them
+//     comes back as a lower clock.  A loop of nothing but products over quantized-Gaussian operands, two waves to a SIMD,
+//     runs at 2.19 GHz with blocks of 16x16x64 and at 1.82 with 32x32x32 (half of the sums move per multiply-add); with
+//     every operand read from LDS 1.98 and 1.69, with a stage's loads beside that 1.78.  us in 32x32x32 blocks, double
+//     buffered / as it is: 32768 x 1152 -> 4608 154 to 161 / 145 to 148, -> 3456 123 / 114, -> 1152 45.3 / 41.1 to 42.2, 32768 x
+//     4608 -> 1152 164 to 169 / 147 to 149, 8192 x 1152 -> 4608 45.0 / 42.0, 8192 x 4608 -> 1152 43.7 / 40.6, with 4-bit weights
+//     32768 x 1152 -> 4608 154 / 147; fp16 operands 32768 x 4608 -> 1152 322 / 293.
+//   - K is walked in stages of 128 bytes.  A stage takes one full 128-byte cache line per row, so every L2 request is a
 //     whole line (with 64-byte stages the same bytes cost twice the requests and the
 //     CU's address path saturates).  Activations and weights go global -> LDS directly
-//     (buffer_load ... lds, 16 B per lane, no registers in between); the loads
-//     of stage i+1 are in flight while stage i is multiplied.  4-bit weights
+//     (buffer_load ... lds, 16 B per lane, no registers in between).  4-bit weights
 //     travel packed (half the bytes).
+//   - LDS holds two stages of weights and three of activations: those come from memory, a new panel for every tile, and a
+//     request that is one stage old when it is needed has not been answered by then.  32768 x 4608 -> 1152 with two of both
+//     162 us, 147.5 so; 8192 x 4608 -> 1152 39.9 and 39.8.  Packed weights, whose stages are as long and whose bytes are
+//     fewer, gain nothing (32768 x 1152 -> 4608 143 and 147): two of both.
+//   - In 256 x 256 the four older waves (one per SIMD) ask for the weights, which are needed a stage later, and the younger ones,
+//     which come to their products last, for the activations, which have two: with every wave asking for its share of both
+//     32768 x 1152 -> 4608 took 151 us, 146 so.  In 256 x 192 it is the other way round (32768 x 4608 -> 1152 148 and 152).
 //   - The direct loads are issued from inline assembly and waited for with an
 //     explicit s_waitcnt: the compiler would otherwise wait for all of them
-//     before every LDS read and undo the prefetch.  They are paced, one load per
-//     two MFMAs from the start of a stage: the CU's load path takes 64 bytes
-//     per cycle, and a wave that queues there issues no MFMA.
+//     before every LDS read and undo the prefetch.  They are paced, one load behind the products of a block of tokens: the
+//     CU's load path takes 64 bytes per cycle, and a wave that queues there issues no MFMA (all at once ahead of the
+//     products a stage of 256 x 256 takes 2600 cycles, 2180 so, of 2048 of products).
 //   - LDS tiles are [row][128 B] with the eight 16-byte chunks of a row XOR-ed
 //     by (row/2)%8, which makes the 16-lane groups of a ds_read_b128 hit 16
 //     different bank groups.
 //   - The tokens are the MFMA row operand and the weights the column operand, so a lane owns one
-//     column of each of its two blocks and, by permuting which weight row sits in which column, two
-//     neighbouring output channels, for 16 TB tokens.  The epilogue narrows them to one dword in
-//     registers and stores it: a store of a wave is two token rows x 128 bytes, whole lines,
+//     column of each of its four blocks and, by permuting which weight row sits in which column, four
+//     neighbouring output channels, for 4 XB tokens.  The epilogue narrows them to two dwords in
+//     registers and stores them: a store of a wave is four token rows x 128 bytes, whole lines,
 //     bypassing the caches' retention (nontemporal: the operands keep the L2).  Nothing is turned
-//     through LDS, a channel's scale and bias are one register each, and a token's scale is read
-//     for two outputs of every lane at once.
+//     through LDS: a lane holds its channels' scales, and a token's scale comes from another lane of its row of sixteen.
 //     What bounds the way out is vector instructions, about 15 cycles of a SIMD for an output of
-//     64 lanes (conversion 4.4, product of the scales 2.4, mixed multiply-add 8.5; nothing of it
-//     runs under MFMAs of the same SIMD): 3900 of the 29000 cycles that a 256 x 256 tile of nine
-//     stages takes, 18400 of them MFMAs.  With a lane owning 32 channels of one token, staged
-//     through LDS to be written as 16 bytes a lane, it was 33500: 20 LDS instructions of 16 bytes a
-//     lane for 32 outputs bound it.  us, then / now: 32768 x 1152 -> 4608 171 / 159, -> 3456 133 /
-//     126, 32768 x 384 -> 3456 73 / 62, 8192 x 1152 -> 3456 with 4-bit weights 37.2 / 33.7.
-//   - The kernel is persistent: one workgroup per CU walks a list of tiles.
-//     The first stage of the next tile is requested while the last stage of
-//     the current one is multiplied, its second stage in the first pieces of the epilogue (all
-//     at once ahead of it they kept every wave in the load queue for 850 cycles); the waves go
-//     from the epilogue into the next tile without meeting at a barrier.
+//     64 lanes (conversion 4.4, product of the scales 2.4, mixed multiply-add 8.5), and the stores: without them
+//     32768 x 1152 -> 4608 takes 120 us.  (A wave's own vector instructions do not run under its MFMAs; those of another
+//     wave of the SIMD do, at 6.4 cycles each instead of 4.5, and the MFMAs take no longer for it.)
+//   - The kernel is persistent: one workgroup per CU walks a list of tiles.  What is asked for runs ahead of what is
+//     multiplied from tile to tile; what a tile's first stage, which is half as long, should ask for is asked for in
+//     the first pieces of the epilogue in front; the waves go from the epilogue into the next tile without meeting at a barrier.
 //   - Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; each
 //     XCD gets a contiguous run of tiles, ordered in bands of 8 token tiles,
 //     and the workgroups of an XCD take them in turn, so that its L2 sees each
@@ -71,7 +77,7 @@
 // value of three separately rounded fp32 operations in the last fp16 place.
 //
 // W_BITS == 16 instantiates the same kernel for fp16 operands and fp32 sums
-// (v_mfma_f32_32x32x16_f16, the same 16 bytes of K per lane and operand): the FP16 layer
+// (v_mfma_f32_16x16x32_f16, the same 16 bytes of K per lane and operand): the FP16 layer
 // the paper's hardware evaluation compares against (Sec. 5.3), y = fp16(sum + bias).
 #pragma once
 #include <type_traits>
@@ -81,60 +87,43 @@
 
 namespace vq {
 
-struct GemmArgs {
-    const int8_t* xq;
-    const float* x_scale;
-    const void* w;
-    const float* w_scale;
-    const _Float16* bias;
-    _Float16* y;
-    int32_t* acc_out;
-    int M, N, K;
-    int tiles_t, tiles_c, tiles, tiles_per_xcd;
-    int slots;  // workgroups per XCD; workgroup (xcd, slot) takes tiles slot, slot + slots, ... of its XCD
-};
-
-// The 256 x 192 tile (vq_gemm_192.hip); the tile fields of `a` are filled in by the callee.
-hipError_t launch_gemm_192(const GemmArgs& a, int w_bits, int num_cus, hipStream_t stream);
-
 namespace {
 
-constexpr int kTileK = 128;                 // K bytes per stage (one cache line per row)
-constexpr int kStages = 2;
-constexpr int kScaleBytes = 3 * 1024;       // w_scale[256] fp32 | bias[256] fp16 (+pad) | x_scale[256] fp32
-constexpr int kBand = 8;                    // token tiles per band in the tile order
-constexpr int kXcds = 8;
-constexpr int kTouchRounds = 4;             // weight lines asked for up front: at most 4 x 8 KiB per wave (64 MiB per 256 CUs)
-
-// WT x WC wavefronts of (32 TB) tokens x 64 channels.
-template <int WT_, int WC_, int TB_>
+// WT x WC wavefronts of (16 XB) tokens x 64 channels.
+template <int WT_, int WC_, int XB_, bool ROLES>
 struct TileShape {
-    static constexpr int WT = WT_, WC = WC_, TB = TB_;
+    static constexpr int WT = WT_, WC = WC_, XB = XB_;
+    static constexpr bool kFourBits = XB == 8;        // packed weights too (with 64 tokens a wave: vq_gemm_192w4.hip)
     static constexpr int kWaves = WT * WC;
     static constexpr int kThreads = 64 * kWaves;
     static constexpr int kWavesPerSimd = kWaves / 4;
-    static constexpr int kTileT = WT * TB * 32;       // tokens per workgroup
+    static constexpr int kTileT = WT * XB * 16;       // tokens per workgroup
     static constexpr int kTileC = WC * 64;            // output channels per workgroup
     static constexpr int kXStage = kTileT * kTileK;   // 32 KiB
-    static constexpr int kWStage = kTileC * kTileK;   // (half of it used by packed 4-bit weights)
-    static constexpr int kLdsBytes = kStages * (kXStage + kWStage);
-    // Global -> LDS loads of 1 KiB (8 rows of int8, 16 rows of nibbles).  The X tile is 32 of them.  With
-    // eight waves each takes four of those and its share of the W tile; with more the loads of both tiles are
-    // one list (groups 0 .. 31 X, the rest W), dealt round.
-    static constexpr bool kOneList = kWaves > 8;
-    static constexpr int groups(int w_bits) { return 32 + kTileC / (w_bits == 4 ? 16 : 8); }
-    static constexpr int kStage = kXStage + kWStage;         // X tile, then W tile
-    static constexpr int kWLoaders = 8;
-    static constexpr int kWPer8 = kOneList ? 0 : kTileC / 8 / kWLoaders;    // int8 (and fp16) W loads per loading wave
-    static constexpr int kWPer4 = kOneList ? 0 : kTileC / 16 / kWLoaders;   // packed 4-bit W loads per loading wave
-    // The epilogue is 4 TB pieces of four stores; the next tile's loads go into all but the last four, so at least this
-    // many of a wave's stores are behind them.
-    static constexpr int kPieces = 4 * TB, kStoresBehind = 16;
-    static_assert(kTileT == 256, "scales are fetched by threads 0..255, one token each");
-    static_assert(kTileC <= 256 && kWaves % 4 == 0 && kWaves >= 8, "tile shape");
-    static_assert(kOneList || (kTileC / 8 % kWLoaders == 0 && kTileC / 16 % kWLoaders == 0), "W loads divide evenly");
-    static_assert(!kOneList || (kWaves % 2 == 0 && 2 * kWaves <= 32 && 3 * kWaves >= 32), "one turn of the list is mixed, and a wave's groups have its parity");
-    static_assert(kLdsBytes + kScaleBytes <= 160 * 1024, "LDS of one CU");
+    static constexpr int w_stage(int w_bits) { return kTileC * kTileK / (w_bits == 4 ? 2 : 1); }
+    // Two stages of weights in LDS, and, but for 4-bit weights, three of activations.
+    static constexpr int kWRing = 2;
+    static constexpr int x_ring(int w_bits) { return w_bits == 4 ? 2 : 3; }
+    // Global -> LDS loads of 1 KiB (8 rows of int8, 16 rows of nibbles), dealt round to the waves; or (roles) the first four
+    // waves, one per SIMD, load the weights and the others the activations.  (Where the X tile's 32 do not divide evenly, the
+    // last turn is some waves' only.)
+    static constexpr bool roles(int w_bits) { return ROLES && w_bits != 4; }
+    static constexpr int x_loaders(int w_bits) { return roles(w_bits) ? kWaves - 4 : kWaves; }
+    static constexpr int w_loaders(int w_bits) { return roles(w_bits) ? 4 : kWaves; }
+    static constexpr int x_loads(int w_bits) { return (kTileT / 8 + x_loaders(w_bits) - 1) / x_loaders(w_bits); }
+    static constexpr int w_loads(int w_bits) { return kTileC / (w_bits == 4 ? 16 : 8) / w_loaders(w_bits); }
+    static constexpr int x_last_turn(int w_bits) { return kTileT / 8 - (x_loads(w_bits) - 1) * x_loaders(w_bits); }   // waves of it
+    static constexpr int unread(int w_bits) { return x_last_turn(w_bits) < x_loaders(w_bits) ? 1024 : 0; }   // where the others' goes, a line for all rows
+    static constexpr int lds_bytes(int w_bits) { return x_ring(w_bits) * kXStage + kWRing * w_stage(w_bits) + unread(w_bits); }
+    // The epilogue is 4 XB stores; the loads that it carries go in front of all but the last eight.
+    static constexpr int kStores = 4 * XB;
+    static constexpr int load_slot(int load, int loads) { return load * (kStores - 8) / loads; }   // the store that it goes ahead of
+    static constexpr bool fits(int w_bits) {   // (and a wave's groups have its parity)
+        return lds_bytes(w_bits) <= 160 * 1024 && w_loads(w_bits) * w_loaders(w_bits) * (w_bits == 4 ? 16 : 8) == kTileC &&
+               x_loaders(w_bits) % 2 == 0 && (!roles(w_bits) || (x_loads(w_bits) == w_loads(w_bits) && !unread(w_bits)));
+    }
+    static_assert(kTileT == 256 && fits(8) && fits(16) && (!kFourBits || fits(4)), "loads divide evenly, LDS of one CU");
+    static_assert(kWaves % 4 == 0 && kWaves >= 8 && XB % 4 == 0, "tile shape");
 };
 
 // Where a tile sits in the output (wave-uniform).
@@ -142,27 +131,50 @@ struct TilePos {
     long tok0, ch0;
     int rows_x, rows_w;  // rows of the tile that exist (the rest is clamped on load, masked on store)
 };
-// What this wave's share of a tile's loads needs: buffer descriptors and per-lane offsets.
-struct TileLoads {
-    v4i rsrc_x, rsrc_w;
-    int voff_x[4], voff_w[6];   // (one list: voff_w alone, by turn)
-    int k_end_x, k_end_w;   // (used with a K tail only: see load_stage_to_lds_16)
+// Which tile: band and place in it (wave-uniform).
+struct TileIndex { int band, in_band; };
+// What a wave asks for next of an operand: a stage of a tile and its place in the ring, the operand's rows of the tile, and
+// per-lane offsets.
+template <int LOADS>
+struct Cursor {
+    TileIndex at;
+    int idx, k0;     // tile; byte of the rows
+    unsigned to;     // LDS
+    v4i rsrc;
+    int voff[LOADS];
+    int k_end;       // (used with a K tail only: see load_stage_to_lds_16)
+    bool full;       // the tile had all its rows: its per-lane offsets hold for any such tile
 };
 
-// One 32 x 32 block: int8 operands (32 values of K per lane pair) into int32 sums, or,
-// for the fp16 comparison layer, fp16 operands (16 values of K) into fp32 sums.  Both take
-// 16 bytes of each operand per lane and as long to issue.
-typedef float v16f __attribute__((ext_vector_type(16)));
+// One 16 x 16 block: int8 operands (64 values of K over four lanes) into int32 sums, or, for the fp16 comparison
+// layer, fp16 operands (32 values of K) into fp32 sums.  Both take 16 bytes of each operand per lane and as long to issue.
 template <int W_BITS>
-struct AccOf { typedef v16i type; };
+struct AccOf { typedef v4i type; };
 template <>
-struct AccOf<16> { typedef v16f type; };
-__device__ __forceinline__ v16i mfma_block(v4i x, v4i w, v16i c) {
-    return __builtin_amdgcn_mfma_i32_32x32x32_i8(x, w, c, 0, 0, 0);
+struct AccOf<16> { typedef v4f type; };
+__device__ __forceinline__ v4i mfma_block(v4i x, v4i w, v4i c) {
+    return __builtin_amdgcn_mfma_i32_16x16x64_i8(x, w, c, 0, 0, 0);
 }
-__device__ __forceinline__ v16f mfma_block(v4i x, v4i w, v16f c) {
+__device__ __forceinline__ v4f mfma_block(v4i x, v4i w, v4f c) {
     // (a cast between vector types of one size reinterprets the bits)
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16((half8)x, (half8)w, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16((half8)x, (half8)w, c, 0, 0, 0);
+}
+// LDS row r of the weight tile holds which output channel of the tile.  Rows are kept in MFMA order: r = slab*64 + b*16 + c,
+// with c the column of block b and the lane (of each quarter) that holds its sums.  Sending channel slab*64 + 4c + b
+// there gives a lane four neighbouring channels.
+__device__ __forceinline__ int w_row_to_channel16(int r) { return (r & ~63) + 4 * (r & 15) + ((r >> 4) & 3); }
+
+// Lane `from` of every row of sixteen lanes, for the whole row.
+__device__ __forceinline__ float spread_in_row(float v, int from) {
+    const int i = __builtin_bit_cast(int, v);
+    int o = i;
+    switch (from) {   // (a constant wherever this is called; the instruction holds it)
+#define VQ_LANE(n) case n: o = __builtin_amdgcn_mov_dpp(i, 0x150 + n, 0xf, 0xf, false); break
+        VQ_LANE(0); VQ_LANE(1); VQ_LANE(2); VQ_LANE(3); VQ_LANE(4); VQ_LANE(5); VQ_LANE(6); VQ_LANE(7);
+        VQ_LANE(8); VQ_LANE(9); VQ_LANE(10); VQ_LANE(11); VQ_LANE(12); VQ_LANE(13); VQ_LANE(14); VQ_LANE(15);
+#undef VQ_LANE
+    }
+    return __builtin_bit_cast(float, o);
 }
 
 // K_TAIL:  K is a multiple of 16 but not of 128 (the last stage is partly past K).
@@ -170,17 +182,11 @@ __device__ __forceinline__ v16f mfma_block(v4i x, v4i w, v16f c) {
 template <class S, int W_BITS, bool K_TAIL, Out OUT>
 __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant(const GemmArgs a) {
     constexpr bool GENERIC = OUT == kAnyRow;
-    constexpr int TB = S::TB;
-    constexpr int kXStage = S::kXStage, kLdsBytes = S::kLdsBytes;
-    __shared__ __attribute__((aligned(1024))) int8_t lds[kLdsBytes + kScaleBytes];
-    // layout: [X buffer 0][W buffer 0][X buffer 1][W buffer 1][scales]; a W
-    // buffer is [rows][128 B] of int8 or, for 4-bit weights, [rows][64 B] of nibbles.
-    int8_t* const lds_x = lds;
-    int8_t* const lds_w = lds + kXStage;
-    constexpr int kStage = S::kStage;
-    const unsigned lds_x_addr = (unsigned)(uintptr_t)(lds_ptr)lds_x;
-    const unsigned lds_w_addr = (unsigned)(uintptr_t)(lds_ptr)lds_w;
-    int8_t* const lds_sc = lds + kLdsBytes;  // w_scale | bias | x_scale of the current tile
+    constexpr int XB = S::XB, WB = 4;   // blocks of 16 tokens and of 16 channels
+    constexpr int kXStage = S::kXStage, kWStage = S::w_stage(W_BITS), kXRing = S::x_ring(W_BITS), kXArea = kXRing * kXStage, kWArea = S::kWRing * kWStage;
+    __shared__ __attribute__((aligned(1024))) int8_t lds[S::lds_bytes(W_BITS)];
+    // layout: the ring of X stages, then the ring of W stages; a stage is [rows][128 B] or, for 4-bit weights, [rows][64 B].
+    const unsigned lds_addr = (unsigned)(uintptr_t)(lds_ptr)lds;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -188,7 +194,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // Waves w, w+4 (and w+8) share a SIMD: they get the same token part and different
     // channel slabs, so a tile that is only partly full of channels still
     // leaves a working wave on every SIMD.
-    const int wave_t = wave % S::WT;   // which 32 TB tokens
+    const int wave_t = wave % S::WT;   // which 16 XB tokens
     const int wave_c = wave / S::WT;   // which 64 channels
     // (W_BITS == 16: fp16 operands, the comparison layer; rows are 2 K bytes and everything up
     // to the MFMA itself treats them like int8 rows of that many bytes)
@@ -196,12 +202,20 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     constexpr int kWDiv = (W_BITS == 4) ? 2 : 1;        // activation bytes per weight byte
     const int nk = (K + kTileK - 1) / kTileK;
 
-    // What this wave loads per stage.
-    constexpr int kWPer = (W_BITS != 4) ? S::kWPer8 : S::kWPer4;
-    constexpr int kGroups = S::groups(W_BITS), kTurns = (kGroups + S::kWaves - 1) / S::kWaves;   // (one list)
-    constexpr int kMixed = 32 / S::kWaves;   // the turn in which some waves load X and some W
-    const bool mixed_x = wave + kMixed * S::kWaves < 32;
-    const int w_loader = wave;
+    // What this wave loads per stage.  Weights are asked for one stage before they are multiplied, activations kXRing - 1.
+    constexpr bool kRoles = S::roles(W_BITS), kXFar = kXRing == 3;
+    constexpr int kXLoads = S::x_loads(W_BITS), kWLoads = S::w_loads(W_BITS), kLoads = kRoles ? kXLoads : kXLoads + kWLoads;
+    const bool loads_w = kRoles && wave < 4;
+    const bool far = kXFar && !loads_w;    // (of roles: asks two stages ahead)
+    // A quantity of the weights' or the activations' cursor or, of roles, of this wave's.  (By arithmetic: the compiler makes
+    // selects between constants in vector registers, and these go where only scalar ones can.)
+    enum Operand { kX, kW, kMine };
+    const int w_mask = (wave - 4) >> 31;
+    auto of = [&](auto op, auto w, auto x) __attribute__((always_inline)) {
+        if constexpr (decltype(op)::value == kW) return w;
+        else if constexpr (decltype(op)::value == kX) return x;
+        else return x + ((w - x) & (decltype(x))w_mask);
+    };
 
     // ---- global -> LDS mapping ---------------------------------------------
     // One direct load fills 1 KiB; lane l writes bytes [16 l, 16 l + 16).
@@ -215,480 +229,499 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // within a band, token tile by token tile within a column.  A workgroup's tiles lie
     // a.slots apart: the first one is located by division, the later ones by stepping.
     const int band_tiles = kBand * a.tiles_c;
-    int dec_band, dec_in_band;   // where the tile decoded last sits (wave-uniform)
-    bool ld_full = false;        // that tile was a full one: its per-lane offsets hold for any full tile
-    auto locate_tile = [&](int idx) {
-        const int logical = (blockIdx.x % kXcds) * a.tiles_per_xcd + idx;
-        dec_band = logical / band_tiles;
-        dec_in_band = logical - dec_band * band_tiles;
-    };
-    auto step_tile = [&]() {
-        dec_in_band += a.slots;
-        while (dec_in_band >= band_tiles) {
-            dec_in_band -= band_tiles;
-            ++dec_band;
+    auto step_tile = [&](TileIndex& t) {
+        t.in_band += a.slots;
+        while (t.in_band >= band_tiles) {
+            t.in_band -= band_tiles;
+            ++t.band;
         }
     };
-    auto decode_tile = [&](TilePos& t, TileLoads& ld) {
-        const int band_first = dec_band * kBand;
+    auto decode_tile = [&](const TileIndex& at, TilePos& t) {
+        const int band_first = at.band * kBand;
         const int band_rows = min(a.tiles_t - band_first, kBand);
         int row, col;
         if (band_rows == kBand) {
-            row = dec_in_band % kBand;
-            col = dec_in_band / kBand;
+            row = at.in_band % kBand;
+            col = at.in_band / kBand;
         } else {  // the last band of a matrix whose token tiles are not a multiple of kBand
-            row = dec_in_band % band_rows;
-            col = dec_in_band / band_rows;
+            row = at.in_band % band_rows;
+            col = at.in_band / band_rows;
         }
         t.tok0 = (long)(band_first + row) * S::kTileT;
         t.ch0 = (long)col * S::kTileC;
         t.rows_x = (int)min((long)S::kTileT, a.M - t.tok0);
         t.rows_w = (int)min((long)S::kTileC, a.N - t.ch0);
-        // (with a K tail the buffers end with the tile's last row: see load_stage_to_lds_16)
-        ld.rsrc_x = make_rsrc(a.xq + t.tok0 * K, K_TAIL ? (unsigned)(t.rows_x * K) : clamp_u32((a.M - t.tok0) * (long)K));
-        ld.rsrc_w = make_rsrc((const int8_t*)a.w + t.ch0 * (K / kWDiv),
-                              K_TAIL ? (unsigned)(t.rows_w * (K / kWDiv)) : clamp_u32((a.N - t.ch0) * (long)(K / kWDiv)));
-        // The per-lane offsets are relative to the tile and clamp rows past the matrix: between
-        // two full tiles they do not change.  (Rows < 256 and row lengths < 2^24: 24-bit products.)
-        const bool full = t.rows_x == S::kTileT && t.rows_w == S::kTileC;
-        if (full && ld_full) return;
-        ld_full = full;
-        const int l = opaque(lane);
-        const int ld_chunk16 = ((l & 7) ^ ((4 * (wave & 1) + (l >> 4)) & 7)) << 4;
-        const int ld_chunk16_w4 = ((l & 3) ^ (l >> 4)) << 4;
-        ld.k_end_x = K - ld_chunk16;
-        ld.k_end_w = W_BITS != 4 ? K - ld_chunk16 : K / 2 - ld_chunk16_w4;
-        auto x_offset = [&](int g) {
-            return __mul24(min(g * 8 + (l >> 3), t.rows_x - 1), K) + ld_chunk16;
-        };
-        auto w_offset = [&](int g) {
-            if (W_BITS != 4) return __mul24(min(w_row_to_channel(g * 8 + (l >> 3)), t.rows_w - 1), K) + ld_chunk16;
-            return __mul24(min(w_row_to_channel(g * 16 + (l >> 2)), t.rows_w - 1), K / 2) + ld_chunk16_w4;
-        };
-        if constexpr (S::kOneList) {
-#pragma unroll
-            for (int j = 0; j < kTurns; ++j) {
-                const int g = wave + j * S::kWaves;
-                if (j < kMixed || (j == kMixed && mixed_x)) ld.voff_w[j] = x_offset(g);
-                else ld.voff_w[j] = w_offset(g - 32);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) ld.voff_x[j] = x_offset(wave + 8 * j);
-#pragma unroll
-            for (int j = 0; j < kWPer; ++j) ld.voff_w[j] = w_offset(w_loader + S::kWLoaders * j);
-        }
     };
     auto tile_exists = [&](int idx) {
         return idx < a.tiles_per_xcd && (int)(blockIdx.x % kXcds) * a.tiles_per_xcd + idx < a.tiles;
     };
 
-    // One load of a wave's share of a stage.  A wave with both kinds alternates them (X, W, X,
-    // W, ...) as long as it has W loads left.
-    auto issue_x = [&](const TileLoads& ld, int buf, int k0, int j) {
-        load_stage_to_lds_16<K_TAIL>(ld.rsrc_x, lds_x_addr + buf * kStage + (wave + 8 * j) * 1024, ld.voff_x[j], k0,
-                                     ld.k_end_x);
-    };
-    auto issue_w = [&](const TileLoads& ld, int buf, int k0, int j) {
-        load_stage_to_lds_16<K_TAIL>(ld.rsrc_w, lds_w_addr + buf * kStage + (w_loader + S::kWLoaders * j) * 1024,
-                                     ld.voff_w[j], W_BITS != 4 ? k0 : k0 / 2, ld.k_end_w);
-    };
-    constexpr int kMaxSingles = S::kOneList ? kTurns : 4 + kWPer;
-    static_assert(kMaxSingles <= 3 * TB, "three K steps carry a stage's loads");
-    const int n_singles = S::kOneList ? (wave < kGroups - (kTurns - 1) * S::kWaves ? kTurns : kTurns - 1) : 4 + kWPer;
-    auto issue_single = [&](const TileLoads& ld, int buf, int k0, int s) {
-        if constexpr (S::kOneList) {
-            // (s is a compile-time constant at every call; a mixed turn's kind is wave-uniform)
-            const unsigned at = lds_x_addr + buf * kStage + (wave + s * S::kWaves) * 1024;
-            if (s < kMixed || (s == kMixed && mixed_x))
-                load_stage_to_lds_16<K_TAIL>(ld.rsrc_x, at, ld.voff_w[s], k0, ld.k_end_x);
-            else
-                load_stage_to_lds_16<K_TAIL>(ld.rsrc_w, at, ld.voff_w[s], W_BITS != 4 ? k0 : k0 / 2, ld.k_end_w);
-        } else if (s < 2 * kWPer) {
-            if (s & 1) issue_w(ld, buf, k0, s >> 1); else issue_x(ld, buf, k0, s >> 1);
-        } else {
-            issue_x(ld, buf, k0, s - kWPer);
-        }
-    };
-    // With three wavefronts to a SIMD the youngest one comes to its products last, and loads dealt out among them arrived
-    // late: it waited 240 of a stage's 2200 cycles for its own.  It asks for them ahead of its products.  us, then / now,
-    // with 8-bit weights: 8192 x 1152 -> 1152 14.7 / 14.3, 8192 x 4096 -> 2304 75.4 / 72.6, 32768 x 4608 -> 1152 162 / 158.6,
-    // 32768 x 1152 -> 1152 44.3 / 43.5.  The same for the middle one gives the gain back (75.8, 166, 44.2), as for the younger
-    // one of two in 256 x 256 (32768 x 1152 -> 4608 160, 171 so); 4-bit weights, half of the bytes, are in time as it is.
-    constexpr bool kYoungestFirst = S::kWavesPerSimd == 3 && W_BITS != 4;
-    const int n_paced = kYoungestFirst && wave >= S::kWaves - 4 ? 0 : n_singles;
-    auto issue_all = [&](const TileLoads& ld, int buf, int k0) {
+    // The per-lane offsets are relative to the tile and clamp rows past the tile: between
+    // two full tiles they do not change.  (Rows < 256 and row lengths < 2^24: 24-bit products.)
+    // (With a K tail the buffers end with the tile's last row: see load_stage_to_lds_16.)
+    auto decode_loads = [&](auto op, const TilePos& t, auto& c) __attribute__((always_inline)) {
+        constexpr int LOADS = sizeof(c.voff) / sizeof(int);
+        constexpr bool kNibbles = W_BITS == 4 && decltype(op)::value == kW;
+        const int rows = of(op, t.rows_w, t.rows_x), row_bytes = of(op, K / kWDiv, K);
+        const long first = of(op, t.ch0, t.tok0);
+        c.rsrc = make_rsrc((const int8_t*)of(op, (long)a.w, (long)a.xq) + first * row_bytes,
+                           K_TAIL ? (unsigned)(rows * row_bytes) : clamp_u32((of(op, a.N, a.M) - first) * (long)row_bytes));
+        const bool full = rows == of(op, S::kTileC, S::kTileT);
+        if (full && c.full) return;
+        c.full = full;
+        const int l = opaque(lane), loader = kRoles ? wave - of(op, 0, 4) : wave;
+        const int chunk = kNibbles ? ((l & 3) ^ (l >> 4)) << 4 : ((l & 7) ^ ((4 * (wave & 1) + (l >> 4)) & 7)) << 4;
+        c.k_end = row_bytes - chunk;
 #pragma unroll
-        for (int s = 0; s < kMaxSingles; ++s)
-            if (s < n_singles) issue_single(ld, buf, k0, s);
+        for (int j = 0; j < LOADS; ++j) {
+            const int g = loader + of(op, S::w_loaders(W_BITS), S::x_loaders(W_BITS)) * j;
+            int r = kNibbles ? g * 16 + (l >> 2) : g * 8 + (l >> 3);
+            if (decltype(op)::value == kW || (decltype(op)::value == kMine && loads_w)) r = w_row_to_channel16(r);
+            c.voff[j] = __mul24(min(r, rows - 1), row_bytes) + chunk;
+        }
     };
 
     // ---- LDS -> MFMA operand mapping -----------------------------------------
-    // Operand rows of a 32x32x32 block: lane l supplies row l%32, 16 bytes of K
-    // chosen by l/32; a stage holds four such K steps (chunks 2ks and 2ks+1).
-    // The chunk index of K step ks is (2 ks + l/32) ^ swizzle = ((l/32) ^ swizzle) ^ 2 ks, so the
-    // byte offset of step ks is that of step 0 with 32 ks XOR-ed in.
-    // 4-bit weights: two K steps 2j and 2j + 1 share one read of 16 bytes of nibbles, chunk 2j + l/32 of the row, whose
-    // first half the lane widens for the one and second half for the other.  The activations follow: chunk 4j + 2 (l/32)
-    // for the first, the one behind it for the second.  (Which 32 bytes of K a step takes does not change the sums.)
-    // With a read of 8 bytes per step the 32 lanes served together took every other 8 bytes of their rows, half of the
-    // banks, and the widening waited for LDS between the products.  us, then / now, in 256 x 192: 32768 x 4608 -> 1152 158 /
-    // 152, 32768 x 1152 -> 1152 45.9 / 44.5, 8192 x 4096 -> 2304 76.4 / 73.8; in 256 x 256 32768 x 1152 -> 4608 161 / 159,
-    // 8192 x 1152 -> 3456 33.3 / 32.9.
-    const int fr_row = lane & 31;
-    const int x_off0 = (wave_t * 32 * TB + fr_row) * kTileK + (((W_BITS != 4 ? lane >> 5 : lane >> 5 << 1) ^ ((fr_row >> 1) & 7)) << 4);
+    // Operand rows of a 16x16x64 block: lane l supplies row l%16, 16 bytes of K chosen by l/16; a stage holds two such
+    // K steps (chunks 4ks .. 4ks + 3).  The chunk index of K step ks is (4 ks + l/16) ^ swizzle = ((l/16) ^ swizzle) ^ 4 ks,
+    // so the byte offset of step ks is that of step 0 with 64 ks XOR-ed in.
+    // 4-bit weights: the two K steps share one read of 16 bytes of nibbles, chunk l/16 of the row, whose first half the lane
+    // widens for the one and second half for the other.  The activations follow: chunk 2 (l/16) for the first, the one behind
+    // it for the second.  (Which 64 bytes of K a step takes does not change the sums.)
+    const int fr_row = lane & 15;
+    const int x_off0 = (wave_t * 16 * XB + fr_row) * kTileK + (((W_BITS != 4 ? lane >> 4 : lane >> 4 << 1) ^ ((fr_row >> 1) & 7)) << 4);
     const int w_off0 = (W_BITS != 4)
-                           ? (wave_c * 64 + fr_row) * kTileK + (((lane >> 5) ^ ((fr_row >> 1) & 7)) << 4)
-                           : (wave_c * 64 + fr_row) * (kTileK / 2) + (((lane >> 5) ^ ((fr_row >> 2) & 3)) << 4);
-    auto x_off = [&](int ks) { return x_off0 ^ (W_BITS != 4 ? ks << 5 : (ks >> 1 << 6) + ((ks & 1) << 4)); };
-    auto w_off = [&](int ks) { return w_off0 ^ (W_BITS != 4 ? ks << 5 : ks >> 1 << 5); };
+                           ? (wave_c * 64 + fr_row) * kTileK + (((lane >> 4) ^ ((fr_row >> 1) & 7)) << 4)
+                           : (wave_c * 64 + fr_row) * (kTileK / 2) + (((lane >> 4) ^ ((fr_row >> 2) & 3)) << 4);
+    auto x_off = [&](int ks) { return x_off0 ^ (W_BITS != 4 ? ks << 6 : ks << 4); };
 
     // ---- the tiles of this workgroup -------------------------------------------
     int idx = blockIdx.x / kXcds;
     if (!tile_exists(idx)) return;  // uniform per workgroup
-    TilePos cur;   // the tile being multiplied
-    TileLoads ld;  // the tile whose stages are being requested (the next one during the last stage)
-    locate_tile(idx);
-    decode_tile(cur, ld);
-    int buf = 0;  // LDS buffer of the stage about to be multiplied
-    bool requested1 = false;        // the current tile's second stage was requested in the previous epilogue
-    bool stores_in_flight = false;  // this wave wrote outputs in the previous epilogue, kStoresBehind or more behind its loads
-    issue_all(ld, 0, 0);
+    TileIndex at;   // of the tile being multiplied
+    TilePos cur;
+    {
+        const int logical = (blockIdx.x % kXcds) * a.tiles_per_xcd + idx;
+        at.band = logical / band_tiles;
+        at.in_band = logical - at.band * band_tiles;
+    }
+    decode_tile(at, cur);
+    // Behind the last tile's last stage a cursor's buffer is empty: loads that move nothing, into stages that are not read.
+    auto cursor_end = [&](auto op) { return lds_addr + of(op, kXArea + kWArea, kXArea) + (kRoles ? wave - of(op, 0, 4) : wave) * 1024; };
+    auto start = [&](auto op, auto& c) {
+        c.at = at;
+        c.idx = idx;
+        c.k0 = 0;
+        c.to = cursor_end(op) - of(op, kWArea, kXArea);
+        c.full = false;
+        decode_loads(op, cur, c);
+    };
+    const unsigned unread = lds_addr + kXArea + kWArea, last_mask = (unsigned)((wave - S::x_last_turn(W_BITS)) >> 31);
+    auto load_one = [&](auto op, const auto& c, int j) __attribute__((always_inline)) {
+        constexpr int LOADS = sizeof(c.voff) / sizeof(int);
+        unsigned to = c.to + j * of(op, S::w_loaders(W_BITS), S::x_loaders(W_BITS)) * 1024;
+        if (decltype(op)::value == kX && S::unread(W_BITS) && j == LOADS - 1) to = unread + ((to - unread) & last_mask);
+        load_stage_to_lds_16<K_TAIL>(c.rsrc, to, c.voff[j], c.k0, c.k_end);
+    };
+    auto next_stage = [&](auto op, auto& c) __attribute__((always_inline)) {
+        const int stage_bytes = of(op, kTileK / kWDiv, kTileK);
+        c.to += of(op, kWStage, kXStage);
+        if (c.to == cursor_end(op)) c.to -= of(op, kWArea, kXArea);
+        c.k0 += stage_bytes;
+        if (c.k0 == nk * stage_bytes) {
+            c.k0 = 0;
+            c.idx += a.slots;
+            if (tile_exists(c.idx)) {
+                TilePos t;
+                step_tile(c.at);
+                decode_tile(c.at, t);
+                decode_loads(op, t, c);
+            } else {
+                c.rsrc[2] = 0;
+            }
+        }
+        asm volatile("" : "+s"(c.k0), "+s"(c.to));
+    };
+    // (roles: cx is this wave's, cw is not used)
+    typedef std::integral_constant<int, kRoles ? kMine : kX> OpX;
+    typedef std::integral_constant<int, kW> OpW;
+    Cursor<kXLoads> cx;
+    Cursor<kWLoads> cw;
+    start(OpX{}, cx);
+    if constexpr (!kRoles) start(OpW{}, cw);
+    // Load l of the ones that a stage of a tile asks for: weights first.
+    auto load = [&](int l) __attribute__((always_inline)) {
+        if (!kRoles && l < kWLoads) load_one(OpW{}, cw, l);
+        else load_one(OpX{}, cx, kRoles ? l : l - kWLoads);
+    };
+    auto load_x = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int l = kLoads - kXLoads; l < kLoads; ++l) load(l);
+    };
+    auto load_w = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int l = 0; l < kLoads - kXLoads; ++l) load(l);
+    };
+    auto next_loads = [&]() __attribute__((always_inline)) {
+        if constexpr (!kRoles) next_stage(OpW{}, cw);
+        next_stage(OpX{}, cx);
+    };
+    load_w();
+    load_x();
+    next_loads();
     // Every line of the weight matrix is asked for once, here, by the whole grid (one dword per
     // 128-byte line and lane, 8 KiB per wave and round): the weights are a few MB that every XCD
     // walks through completely, and a column's panel is otherwise first asked for by the eight
     // CUs that need it at that moment, which then wait out the memory latency at every stage of
     // their tile.  Fetched up front the lines are in the memory-side cache when their column's
-    // turn comes.  (Range-checked loads: lanes past the end of the matrix fetch nothing.)
-    int touched[kTouchRounds];
+    // turn comes.  (Range-checked loads: lanes past the end of the matrix fetch nothing.  They go where the ring's last stage of
+    // activations will, which is asked for when they have arrived.)
     {
         const long w_bytes = (long)a.N * (K / kWDiv);
-        const __amdgpu_buffer_rsrc_t rsrc_all = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<void*>(a.w), 0, (int)clamp_u32(w_bytes), kRsrcFlags);
+        const v4i rsrc_all = make_rsrc(a.w, clamp_u32(w_bytes));
         const unsigned per_round = gridDim.x * (unsigned)S::kWaves * 8192u;
         const unsigned off = (blockIdx.x * (unsigned)S::kWaves + (unsigned)wave) * 8192u + (unsigned)lane * 128u;
 #pragma unroll
-        for (int i = 0; i < kTouchRounds; ++i) {
-            touched[i] = 0;
+        for (int i = 0; i < kTouchRounds; ++i)
             if ((long)i * per_round < w_bytes)  // (uniform; all rounds are in flight together)
-                touched[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc_all, (int)(off + i * per_round), 0, 0);
-        }
+                load_to_lds_4(rsrc_all, lds_addr + (kXRing - 1) * kXStage + wave * 256, (int)(off + i * per_round));
     }
-    wait_loads_and_barrier();  // the first tile's first stage (later ones arrive behind an epilogue)
-#pragma unroll
-    for (int i = 0; i < kTouchRounds; ++i) asm volatile("" : : "v"(touched[i]));  // (not used; they have arrived by now)
+    // The first tile's first stage (later ones arrive behind an epilogue), and what it should ask for (later: in the epilogue
+    // in front): the next stage of weights, of activations two with a ring of three.
+    if constexpr (kRoles) {
+        if (far) {
+            load_x();
+            next_loads();
+            wait_loads_before_and_barrier<kLoads>();
+        } else {
+            wait_loads_before_and_barrier<0>();
+        }
+    } else if constexpr (kXFar) {
+        load_x();
+        next_stage(OpX{}, cx);
+        wait_loads_before_and_barrier<kXLoads>();
+    } else {
+        wait_loads_before_and_barrier<0>();
+    }
+    load_w();
+    load_x();
+    next_loads();
+    unsigned x_stage = 0, w_stage = 0;   // the stage about to be multiplied: its place in the rings
+    bool stores_in_flight = false;       // this wave wrote outputs in the previous epilogue
 
-    // Invariant at the top of a stage: its operands have landed in buffer `buf` for every
-    // wave, and nobody reads or writes the other buffer any more.
+    // Invariant at the top of a stage: its operands have landed for every wave, nobody reads the stage before any more, and
+    // this wave has asked for one or two stages behind it.
     while (true) {
         const int next_idx = idx + a.slots;
         const bool has_next = tile_exists(next_idx);
-        TilePos nxt = cur;
 
         // a wave whose 64 channels (or tokens) lie wholly past the matrix has nothing to multiply
-        const bool wave_live = (wave_c * 64 < cur.rows_w) && (wave_t * 32 * TB < cur.rows_x);
-
-        // Scales and bias of the tile: threads 0..255 fetch one channel and one token each
-        // here and park them in LDS behind the last stage, where every lane of the epilogue
-        // finds them.  Entries past N or M, and a missing bias, are zero.
-        float pre_ws = 0.0f, pre_xs = 0.0f;
-        _Float16 pre_b = (_Float16)0.0f;
-        if (wave < 4) {
-            const int i = wave * 64 + opaque(lane);
-            if (i < S::kTileC && cur.ch0 + i < a.N) {
-                if (W_BITS != 16) pre_ws = a.w_scale[cur.ch0 + i];
-                if (a.bias) pre_b = a.bias[cur.ch0 + i];
-            }
-            if (W_BITS != 16 && cur.tok0 + i < a.M) pre_xs = a.x_scale[cur.tok0 + i];
-        }
-
-        auto park_scales = [&]() {
-            if (wave < 4) {
-                const int i = wave * 64 + opaque(lane);
-                *(float*)(lds_sc + i * 4) = pre_ws;
-                *(_Float16*)(lds_sc + 1024 + i * 2) = pre_b;
-                // the 4-bit path accumulates 16 * w: the exact 1/16 rides on the token scale
-                *(float*)(lds_sc + 2048 + i * 4) = pre_xs * (W_BITS == 4 ? 0.0625f : 1.0f);
-            }
-            // (They have arrived for every wave, which the compiler is told here, ahead of a wait for all loads: it
-            // would otherwise wait for the next tile's second stage where it takes their registers for something else.)
-            asm volatile("" : : "v"(pre_ws), "v"(pre_xs), "v"((int)__builtin_bit_cast(unsigned short, pre_b)));
-        };
+        const bool wave_live = (wave_c * 64 < cur.rows_w) && (wave_t * 16 * XB < cur.rows_x);
 
         typedef typename AccOf<W_BITS>::type acc_t;
-        acc_t acc[2][TB];
-        v4i xf[2][TB], wf[2][2];  // operand registers, double buffered; [1] carries K step 3 across stages
-        v4i nibbles[2];           // (4-bit weights: of the two K steps that are read together)
-        const acc_t kZero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        acc_t acc[XB][WB];
+        v4i xf[2][XB], wf[2][WB];  // operand registers; [1] carries K step 1 across stages
+        v4i nibbles[WB];           // (4-bit weights: of both K steps)
+        const acc_t kZero4 = {0, 0, 0, 0};
 
-        // One stage = four K steps of 2 TB MFMAs per wave.  The schedule is skewed by one K step:
-        // the MFMAs of a stage's last K step are issued at the start of the next stage, behind
+        // One stage = two K steps of 4 XB MFMAs per wave.  The schedule is skewed by one K step:
+        // the MFMAs of a stage's second K step are issued at the start of the next stage, behind
         // the barrier, where they cover the latency of that stage's first LDS reads (otherwise
-        // every wave of the CU would sit idle there).  Compile-time flags: FIRST = the tile's
-        // first stage (nothing deferred to run; its first K step starts the accumulators from
-        // a constant zero), LAST = its last one (nothing is deferred past the epilogue).
-        // `requested`: the loads this stage would issue are already in flight.
-        auto stage = [&](const int it, auto first_tag, auto last_tag, const bool requested) __attribute__((always_inline)) {
-            constexpr bool FIRST = decltype(first_tag)::value;
-            constexpr bool LAST = decltype(last_tag)::value;
-            // what to request while this stage is multiplied: the next stage of this tile,
-            // or the first stage of the next tile
-            const bool fetch = (!LAST || has_next) && !requested;
-            // (In a stage of its own the next tile is located behind the first products: ahead of them every wave
-            // of the CU would be at it at once and the matrix cores idle.)
-            constexpr bool kLate = LAST && !FIRST;
-            auto next_tile = [&]() __attribute__((always_inline)) {
-                if (LAST && has_next) {
-                    step_tile();
-                    decode_tile(nxt, ld);
+        // every wave of the CU would sit idle there).
+        //
+        // The LDS reads of K step ks+1 are issued among the MFMAs of step ks, which cover their latency.
+        // A K step = XB pieces of four MFMAs, one block of tokens each.  A piece carries at most one global load
+        // (so that a wave never sits in the load queue while the matrix pipe waits for it)
+        // and its share of the LDS reads of the step after; sched_barrier(0) keeps the pieces apart.
+        constexpr int kReads = XB + WB;
+        constexpr int kReadsPerPiece = (kReads + XB - 2) / (XB - 1);   // spread over all pieces but the last
+        // in the order w0 x0 w1 x1 ..
+        auto read_one = [&](int ks, int r, v4i(&xo)[XB], v4i(&wo)[WB]) __attribute__((always_inline)) {
+            const int8_t* const xs = lds + x_stage;
+            const int8_t* const ws = lds + kXArea + w_stage;
+            const bool is_w = r < 2 * WB && r % 2 == 0;
+            const int b = r < 2 * WB ? r / 2 : r - WB;
+            if (!is_w)
+                xo[b] = *(const v4i*)(xs + x_off(ks) + b * 16 * kTileK);
+            else if (W_BITS != 4)
+                wo[b] = *(const v4i*)(ws + (w_off0 ^ (ks << 6)) + b * 16 * kTileK);
+            else if (ks == 0)
+                nibbles[b] = *(const v4i*)(ws + w_off0 + b * 16 * (kTileK / 2));
+        };
+        auto widen = [&](int ks, int b, v4i(&wo)[WB]) __attribute__((always_inline)) {
+            wo[b] = widen_nibbles(ks ? v2i{nibbles[b][2], nibbles[b][3]} : v2i{nibbles[b][0], nibbles[b][1]});
+            asm volatile("" : "+v"(wo[b]));   // (here, not where it is used)
+        };
+        // A K step.  read_ks < 0: nothing left to read (the tile's last K step).  It carries this wave's loads from .. to - 1,
+        // behind a piece's products each.  (Known where it is compiled: a branch in front of each load costs the wave more than
+        // the product it should run beside.)
+        auto k_step = [&](const v4i(&xi)[XB], const v4i(&wi)[WB], auto zero_tag, int read_ks, v4i(&xo)[XB], v4i(&wo)[WB],
+                          int from, int to) __attribute__((always_inline)) {
+#pragma unroll
+            for (int p = 0; p < XB; ++p) {
+#pragma unroll
+                for (int m = 0; m < WB; ++m) {
+                    const int b = p & 1 ? WB - 1 - m : m;   // (there and back: the weight operand of two MFMAs in a row is the same)
+                    if constexpr (decltype(zero_tag)::value)
+                        acc[p][b] = mfma_block(xi[p], wi[b], kZero4);
+                    else
+                        acc[p][b] = mfma_block(xi[p], wi[b], acc[p][b]);
                 }
-            };
-            if (!kLate) next_tile();
-            const int fk0 = LAST ? 0 : (it + 1) * kTileK;
-
-            const int8_t* xs = lds_x + buf * kStage;
-            const int8_t* ws = lds_w + buf * kStage;
-            // Operand registers are double buffered: the LDS reads of K step ks+1 are issued
-            // among the MFMAs of step ks, which cover their latency.
-            // A K step = 2 TB MFMAs in TB pieces of two.  A piece carries at most one global load
-            // (so that a wave never sits in the load queue while the matrix pipe waits for it)
-            // and its share of the LDS reads of the step after; sched_barrier(0) keeps the pieces
-            // apart.  Reads of the next step in the order of their first use: w0 x0 x1 .. w1
-            // (128-token waves: w0 x0 | x1 x2 | x3 w1; 64-token waves: w0 x0 x1 w1 in the first piece).
-            constexpr int kReads = TB + 2;
-            constexpr int kReadsPerPiece = (kReads + TB - 2) / (TB - 1);   // spread over all pieces but the last
-            auto read_one = [&](int ks, int r, v4i(&xo)[TB], v4i(&wo)[2]) __attribute__((always_inline)) {
-                if (r == 0 || r == kReads - 1) {
-                    const int cb = (r == 0) ? 0 : 1;
-                    if (W_BITS != 4)
-                        wo[cb] = *(const v4i*)(ws + w_off(ks) + cb * 32 * kTileK);
-                    else if (!(ks & 1))
-                        nibbles[cb] = *(const v4i*)(ws + w_off(ks) + cb * 32 * (kTileK / 2));
-                } else {
-                    const int tb = r - 1;
-                    xo[tb] = *(const v4i*)(xs + x_off(ks) + tb * 32 * kTileK);
-                }
-            };
-            auto widen = [&](int ks, v4i(&wo)[2]) __attribute__((always_inline)) {
+                if (from + p < to) load(from + p);
+                if (read_ks >= 0) {
 #pragma unroll
-                for (int cb = 0; cb < 2; ++cb)
-                    wo[cb] = widen_nibbles((ks & 1) ? v2i{nibbles[cb][2], nibbles[cb][3]} : v2i{nibbles[cb][0], nibbles[cb][1]});
-            };
-            auto mfma_one = [&](int i, const v4i(&xi)[TB], const v4i(&wi)[2], auto zero_tag) __attribute__((always_inline)) {
-                const int cb = i / TB, tb = i % TB;
-                if constexpr (decltype(zero_tag)::value)
-                    acc[cb][tb] = mfma_block(xi[tb], wi[cb], kZero16);
-                else
-                    acc[cb][tb] = mfma_block(xi[tb], wi[cb], acc[cb][tb]);
-            };
-            // read_ks < 0: nothing left to read (the tile's last K step); first_load < 0: no loads
-            auto k_step = [&](const v4i(&xi)[TB], const v4i(&wi)[2], auto zero_tag, int read_ks, v4i(&xo)[TB],
-                              v4i(&wo)[2], int first_load) __attribute__((always_inline)) {
+                    for (int r = p * kReadsPerPiece; r < (p + 1) * kReadsPerPiece && r < kReads; ++r) read_one(read_ks, r, xo, wo);
+                    if (W_BITS != 4 && p * kReadsPerPiece < kReads) {
 #pragma unroll
-                for (int p = 0; p < TB; ++p) {
-                    if (fetch && first_load >= 0 && first_load + p < kMaxSingles && first_load + p < n_paced)
-                        issue_single(ld, buf ^ 1, fk0, first_load + p);
-                    mfma_one(2 * p, xi, wi, zero_tag);
-                    mfma_one(2 * p + 1, xi, wi, zero_tag);
-                    if (read_ks >= 0) {
-#pragma unroll
-                        for (int r = p * kReadsPerPiece; r < (p + 1) * kReadsPerPiece && r < kReads; ++r)
-                            read_one(read_ks, r, xo, wo);
-                        if (W_BITS != 4 && p * kReadsPerPiece < kReads) {
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                   // one MFMA
-                            __builtin_amdgcn_sched_group_barrier(0x100, kReadsPerPiece / 2, 0);  // LDS reads
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x100, kReadsPerPiece / 2, 0);
+                        for (int r = 0; r < kReadsPerPiece; ++r) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+                            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
                         }
                     }
-                    // (in the last piece, which reads nothing: the nibbles have arrived behind the products before it)
-                    if (W_BITS == 4 && read_ks >= 0 && p == TB - 1) widen(read_ks, wo);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            };
-            constexpr std::false_type kAccumulate{};
-            // K steps in the order they are issued; the e-th one of a stage carries the loads
-            // e TB .. e TB + TB - 1 of this wave's share.
-            if (FIRST) {
-                // nothing deferred to cover them: the first K step's operands are read up front
+                    // (in the second half of the step: the nibbles have arrived behind the products before it)
+                    if (W_BITS == 4) {
+                        // (the first step's in its last pieces: the nibbles have arrived behind the products before; the second's
+                        // in all of them)
+                        const int from = read_ks ? p * WB / XB : p < XB / 2 ? 0 : (p - XB / 2) * WB / (XB / 2);
+                        const int to = read_ks ? (p + 1) * WB / XB : p < XB / 2 ? 0 : (p + 1 - XB / 2) * WB / (XB / 2);
 #pragma unroll
-                for (int r = 0; r < kReads; ++r) read_one(0, r, xf[0], wf[0]);
-                if (kYoungestFirst && fetch && n_paced == 0) issue_all(ld, buf ^ 1, fk0);
-                if (W_BITS == 4) widen(0, wf[0]);
-                __builtin_amdgcn_sched_barrier(0);
-                k_step(xf[0], wf[0], first_tag, 1, xf[1], wf[1], 0);          // K step 0
-                k_step(xf[1], wf[1], kAccumulate, 2, xf[0], wf[0], TB);      // K step 1
-                k_step(xf[0], wf[0], kAccumulate, 3, xf[1], wf[1], 2 * TB);  // K step 2
-            } else {
-                constexpr int kAt = kLate ? -TB : 0;
-                if (kYoungestFirst && !kLate && fetch && n_paced == 0) issue_all(ld, buf ^ 1, fk0);
-                k_step(xf[1], wf[1], kAccumulate, 0, xf[0], wf[0], kAt);           // K step 3 of the previous stage
-                if (kLate) {
-                    next_tile();
-                    if (kYoungestFirst && fetch && n_paced == 0) issue_all(ld, buf ^ 1, fk0);
-                    __builtin_amdgcn_sched_barrier(0);
+                        for (int b = 0; b < WB; ++b)
+                            if (b >= from && b < to) widen(read_ks, b, wo);
+                        if (to > from) {
+#pragma unroll
+                            for (int r = 0; r < WB; ++r) {
+                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                                if (r < kReadsPerPiece) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                                if (to - from == 1) __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);   // vector instructions
+                                else __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+                            }
+                        }
+                    }
                 }
-                k_step(xf[0], wf[0], kAccumulate, 1, xf[1], wf[1], kAt + TB);      // K step 0
-                k_step(xf[1], wf[1], kAccumulate, 2, xf[0], wf[0], kAt + 2 * TB);  // K step 1
-                k_step(xf[0], wf[0], kAccumulate, 3, xf[1], wf[1], kAt + 3 * TB);  // K step 2
+                __builtin_amdgcn_sched_barrier(0);
             }
-            // K step 3 (otherwise at the start of the next stage)
-            if (LAST) {
-                k_step(xf[1], wf[1], kAccumulate, -1, xf[0], wf[0], -1);
-                park_scales();
-            }
-            // The stage requested above has landed for every wave and every wave is done
-            // reading this one.  After the last stage this also says: the scales are in LDS,
-            // the next tile's first stage is in, and only stores can be outstanding later.
-            // (A stage whose loads were requested in the previous tile's epilogue has stores of this
-            // wave behind them: those may stay in flight.  Vector memory operations complete in the
-            // order they were issued.)
-            if (requested && stores_in_flight)
-                wait_loads_before_and_barrier<S::kStoresBehind>();
-            else
-                wait_loads_and_barrier();
-            buf ^= 1;
         };
-        constexpr std::true_type kYes{};
-        constexpr std::false_type kNo{};
-        // (the next tile's second stage is requested before this tile ends)
-        const bool request1 = has_next && nk >= 2;
-        if (wave_live) {
-            if (nk == 1) {
-                stage(0, kYes, kYes, false);
+        // Ends a stage: the next one has landed for every wave and every wave is done reading this one.  Vector memory
+        // operations complete in the order they were issued: `behind` of this wave's are behind the loads that have to have
+        // landed, beside those of a stage that is asked for two stages ahead.  (Roles: of a wave that asks two stages ahead, or one.)
+        auto end_stage = [&](auto behind_far, auto behind) __attribute__((always_inline)) {
+            if constexpr (kRoles) {
+                if (far) wait_loads_before_and_barrier<kLoads + decltype(behind_far)::value>();
+                else wait_loads_before_and_barrier<decltype(behind)::value>();
             } else {
-                stage(0, kYes, kNo, requested1);
-#pragma unroll 1
-                for (int it = 1; it < nk - 1; ++it) stage(it, kNo, kNo, false);
-                stage(nk - 1, kNo, kYes, false);
+                wait_loads_before_and_barrier<(kXFar ? kXLoads : 0) + decltype(behind)::value>();
             }
+            x_stage = x_stage == (kXRing - 1) * kXStage ? 0 : x_stage + kXStage;
+            w_stage = w_stage == kWStage ? 0 : w_stage + kWStage;
+        };
+        typedef std::integral_constant<int, 0> None;
+        // Stores of an epilogue behind the loads in it that its tile's first stage has to wait for (all of them; with a ring of
+        // three for the activations the weights).
+        constexpr int kLastNeeded = !kRoles && kXFar ? kWLoads - 1 : kLoads - 1;
+        typedef std::integral_constant<int, S::kStores - S::load_slot(kLastNeeded, kLoads)> StoresBehind;
+        typedef std::integral_constant<int, S::kStores - S::load_slot(kLoads - 1, kLoads)> StoresBehindAll;
+        typedef std::integral_constant<int, S::kStores> Stores;
+        // Which of a stage's loads its first K step carries (K step 1 of the stage before), the rest its second.
+        constexpr int kFirst = !kRoles && kXFar ? kWLoads : kLoads < XB ? kLoads : XB;
+        static_assert(kFirst <= XB && kLoads - kFirst <= XB, "a load in a piece");
+        if (wave_live) {
+            constexpr std::true_type kYes{};
+            constexpr std::false_type kNo{};
+            // The tile's first stage: nothing deferred to cover its first reads, and its first K step starts the accumulators
+            // from a constant zero.  What it should ask for was asked for in the epilogue in front.
+#pragma unroll
+            for (int r = 0; r < kReads; ++r) read_one(0, r, xf[0], wf[0]);
+            if (W_BITS == 4)
+#pragma unroll
+                for (int b = 0; b < WB; ++b) widen(0, b, wf[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            k_step(xf[0], wf[0], kYes, 1, xf[1], wf[1], 0, 0);
+            if (nk > 1) {
+                if (stores_in_flight) end_stage(Stores{}, StoresBehind{});
+                else end_stage(None{}, None{});
+#pragma unroll 1
+                for (int it = 1;; ++it) {
+                    k_step(xf[1], wf[1], kNo, 0, xf[0], wf[0], 0, kFirst);        // K step 1 of the previous stage
+                    k_step(xf[0], wf[0], kNo, 1, xf[1], wf[1], kFirst, kLoads);   // K step 0
+                    next_loads();
+                    if (it == nk - 1) break;
+                    if (kRoles && it == 1 && stores_in_flight) end_stage(StoresBehindAll{}, None{});
+                    else end_stage(None{}, None{});
+                }
+            }
+            // Scales and bias: a channel's four, and a token's in lane 4 (block % 4) + i of its row of sixteen lanes, which the
+            // epilogue spreads over the row.  Entries past N or M, and a missing bias, are zero.
+            constexpr int kXsRegs = XB / 4;
+            const int el = opaque(lane);
+            const int g = el >> 4, quad = wave_c * 64 + 4 * (el & 15);   // the lane's first channel within the tile
+            const int row0 = wave_t * 16 * XB;                           // the wave's first token within the tile
+            v4f ws4 = {0.0f, 0.0f, 0.0f, 0.0f};
+            float xs_row[kXsRegs];
+            if constexpr (W_BITS != 16) {
+                const __amdgpu_buffer_rsrc_t rs_ws = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.w_scale) + cur.ch0, 0, cur.rows_w * 4, kRsrcFlags);
+                const __amdgpu_buffer_rsrc_t rs_xs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.x_scale) + cur.tok0, 0, cur.rows_x * 4, kRsrcFlags);
+                ws4 = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs_ws, quad * 4, 0, 0));
+#pragma unroll
+                for (int r = 0; r < kXsRegs; ++r)
+                    xs_row[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                        rs_xs, (row0 + 64 * r + 16 * ((el & 15) >> 2) + 4 * g + (el & 3)) * 4, 0, 0));
+            }
+            const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<_Float16*>(a.bias) + cur.ch0, 0, a.bias ? cur.rows_w * 2 : 0, kRsrcFlags);
+            v2i bias4 = __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(rs_b, quad * 2, 0, 0));
+            if (GENERIC && (cur.rows_w & 1) && cur.rows_w - quad < 4) {
+                // (the last of an odd number is half of a dword that reaches behind the buffer)
+                const int last = (int)__builtin_amdgcn_raw_buffer_load_b16(rs_b, (cur.rows_w - 1) * 2, 0, 0) & 0xFFFF;
+                if (cur.rows_w - quad == 1) bias4[0] = last;
+                if (cur.rows_w - quad == 3) bias4[1] = last;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int kScaleLoads = W_BITS == 16 ? 1 : 2 + kXsRegs;
+            k_step(xf[1], wf[1], kNo, -1, xf[0], wf[0], 0, 0);   // K step 1 of the last stage
+            end_stage(std::integral_constant<int, kScaleLoads>{}, std::integral_constant<int, kScaleLoads>{});
 
             // ---- epilogue ------------------------------------------------------------
-            // Lane (h = lane/32, c = lane%32) holds channels 2c and 2c + 1 of the wavefront's 64 (accumulator blocks 0 and
-            // 1) for the tokens 8j + 4h + i of each of its TB token blocks (register 4j + i).  Two neighbouring outputs are
-            // one dword, and a store of one dword per lane is a whole 128-byte line of two token rows.
-            const int el = opaque(lane);  // (the epilogue's per-lane values are not kept across the mainloop)
-            const int h = el >> 5, pair = wave_c * 64 + 2 * (el & 31);   // the lane's first channel within the tile
-            const int left = cur.rows_w - pair;                          // channels from there on that exist
-            const int row0 = wave_t * 32 * TB;                           // the wave's first token within the tile
-            const float ws0 = *(const float*)(lds_sc + pair * 4), ws1 = *(const float*)(lds_sc + pair * 4 + 4);
-            const unsigned bias2 = *(const unsigned*)(lds_sc + 1024 + pair * 2);
-            const int8_t* const sc_x = lds_sc + 2048 + (row0 + 4 * h) * 4;
-            // Stores are range-checked, relative to the first of eight token rows: rows past M fall behind the end of
+            // Lane (g = lane/16, c = lane%16) holds channels 4c .. 4c + 3 of the wavefront's 64 (accumulator blocks 0 .. 3) for
+            // the tokens 4g + i of each of its blocks of 16 (register i).  Its four outputs of a token are two dwords, and a
+            // store of both per lane is a whole 128-byte line of four token rows.
+            const int left = cur.rows_w - quad;                          // channels from there on that exist
+            // (all sums are converted first, which covers the way of the scales)
+            typedef v4f sums_t;
+            sums_t sum[XB][WB];
+#pragma unroll
+            for (int xb = 0; xb < XB; ++xb)
+#pragma unroll
+                for (int b = 0; b < WB; ++b)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sum[xb][b][i] = (float)acc[xb][b][i];
+            // Stores are range-checked, relative to the first of sixteen token rows: rows past M fall behind the end of
             // the buffer, lanes whose channels lie past N get an offset behind it (N < 2^21 on this path, so nothing
-            // wraps).
-            const unsigned y_place = left > 0 ? (unsigned)(__mul24(4 * h, GENERIC ? 0 : a.N) + (int)cur.ch0 + pair) * 2u : 0x80000000u;
+            // wraps).  Of an even N two of a lane's four channels may exist: they are a dword of their own.
+            const unsigned y_place = (unsigned)(__mul24(4 * g, GENERIC ? 0 : a.N) + (int)cur.ch0 + quad) * 2u;
             unsigned y_off[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) y_off[i] = y_place + (unsigned)checked_bytes<OUT>(i, a.N);
+            for (int i = 0; i < 4; ++i) y_off[i] = left >= 4 ? y_place + (unsigned)checked_bytes<OUT>(i, a.N) : 0x80000000u;
             const _Float16* y_row = a.y + (cur.tok0 + row0) * a.N;
             int y_bytes = checked_bytes<OUT>(cur.rows_x - row0, a.N);   // from there to the end of the tile's rows
-            // (any row: token rows of the wave below which the lane has two channels to write, or one; its place in them)
-            const int rows_live = cur.rows_x - row0 - 4 * h;
-            const int rows_pair = left > 1 ? rows_live : 0, rows_single = left == 1 ? rows_live : 0;
+            // (any row: token rows of the wave below which the lane has channels to write; its place in them)
+            const int rows_live = left > 0 ? cur.rows_x - row0 - 4 * g : 0;
             long y_any[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) y_any[i] = (4 * h + i) * (long)a.N + cur.ch0 + pair;
+            for (int i = 0; i < 4; ++i) y_any[i] = (4 * g + i) * (long)a.N + cur.ch0 + quad;
             if (GENERIC && a.acc_out) {
+                typedef v4i v4i_any4 __attribute__((aligned(4)));
                 int32_t* acc_row = a.acc_out + (cur.tok0 + row0) * a.N;
 #pragma unroll
-                for (int tb = 0; tb < TB; ++tb)
+                for (int xb = 0; xb < XB; ++xb) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
+                    for (int i = 0; i < 4; ++i)
+                        if (xb * 16 + i < rows_live) {
+                            constexpr int kShift = (W_BITS == 4) ? 4 : 0;
+                            const v4i sums = v4i{(int)acc[xb][0][i], (int)acc[xb][1][i], (int)acc[xb][2][i], (int)acc[xb][3][i]} >> kShift;
+                            if (left >= 4) {
+                                *(v4i_any4*)(acc_row + y_any[i]) = sums;
+                            } else {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (tb * 32 + 8 * j + i < rows_live && left > 0) {
-                                constexpr int kShift = (W_BITS == 4) ? 4 : 0;
-                                acc_row[y_any[i]] = (int)acc[0][tb][4 * j + i] >> kShift;
-                                if (left > 1) acc_row[y_any[i] + 1] = (int)acc[1][tb][4 * j + i] >> kShift;
+                                for (int e = 0; e < 3; ++e)
+                                    if (e < left) acc_row[y_any[i] + e] = sums[e];
                             }
-                        acc_row += 8 * (long)a.N;
-                        asm volatile("" : "+s"(acc_row));
-                    }
-            }
-            v4f xs = *(const v4f*)sc_x;
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    // the next tile's second stage, a few loads at a time
-#pragma unroll
-                    for (int l = 0; l < kMaxSingles; ++l)
-                        if (l * (S::kPieces - 4) / kMaxSingles == 4 * tb + j && l < n_singles && request1) issue_single(ld, buf ^ 1, kTileK, l);
-                    v4f xs_next = xs;
-                    if (tb < TB - 1 || j < 3) xs_next = *(const v4f*)(sc_x + (tb * 32 + 8 * (j + 1)) * 4);
-                    const __amdgpu_buffer_rsrc_t rsrc_y =
-                        __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(y_row), 0, max(y_bytes, 0), kRsrcFlags);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int r = 4 * j + i;
-                        unsigned out;
-                        // y = fp16(float(acc) * (x_scale * w_scale) + bias): the product of the two scales rounded to
-                        // fp32, the rest exact and rounded once (dequant_pair)
-                        if constexpr (W_BITS == 16)  // the fp32 sum of the fp16 products, plus the bias
-                            out = add_bias_pair(acc[0][tb][r], acc[1][tb][r], bias2);
-                        else
-                            out = dequant_pair((float)acc[0][tb][r], xs[i] * ws0, (float)acc[1][tb][r], xs[i] * ws1, bias2);
-                        if (!GENERIC) {
-                            __builtin_amdgcn_raw_buffer_store_b32((int)out, rsrc_y, y_off[i], 0, OUT == kHalfLines ? 2 /* nontemporal */ : 0);
-                            continue;
                         }
-                        // Rows of Y that start at any even address; the last channel of an odd N alone.
-                        typedef unsigned u_any __attribute__((aligned(2)));
-                        if (tb * 32 + 8 * j + i < rows_pair) *(u_any*)(y_row + y_any[i]) = out;
-                        if ((cur.rows_w & 1) && tb * 32 + 8 * j + i < rows_single)
-                            *(unsigned short*)(y_row + y_any[i]) = (unsigned short)out;
-                    }
-                    xs = xs_next;
-                    y_row += 8 * (long)a.N;
-                    y_bytes -= checked_bytes<OUT>(8, a.N);
-                    if (GENERIC) asm volatile("" : "+s"(y_row), "+v"(xs));   // (nothing is made up ahead of its use)
-                    __builtin_amdgcn_sched_barrier(0);
+                    acc_row += 16 * (long)a.N;
+                    asm volatile("" : "+s"(acc_row));
                 }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // (here the compiler waits for them, ahead of the next loads)
+            asm volatile("" : "+v"(ws4), "+v"(bias4));
+            if constexpr (W_BITS != 16) {
+#pragma unroll
+                for (int r = 0; r < kXsRegs; ++r) {
+                    xs_row[r] *= W_BITS == 4 ? 0.0625f : 1.0f;   // the 4-bit path accumulates 16 * w: the exact 1/16 rides on the token scale
+                    asm volatile("" : "+v"(xs_row[r]));
+                }
+            }
+#pragma unroll
+            for (int xb = 0; xb < XB; ++xb) {
+                const __amdgpu_buffer_rsrc_t rsrc_y =
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(y_row), 0, max(y_bytes, 0), kRsrcFlags);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    // what the next tile's first stage should ask for, a load at a time
+#pragma unroll
+                    for (int l = 0; l < kLoads; ++l)
+                        if (S::load_slot(l, kLoads) == 4 * xb + i && has_next) load(l);
+                    float xs = 0.0f;
+                    if constexpr (W_BITS != 16) {
+                        xs = spread_in_row(xs_row[xb / 4], 4 * (xb % 4) + i);
+                        asm volatile("" : "+v"(xs));   // (one instruction, not part of four)
+                    }
+                    v2i out;
+                    // y = fp16(float(acc) * (x_scale * w_scale) + bias): the product of the two scales rounded to
+                    // fp32, the rest exact and rounded once (dequant_pair)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const float a0 = sum[xb][2 * e][i], a1 = sum[xb][2 * e + 1][i];
+                        if constexpr (W_BITS == 16)  // the fp32 sum of the fp16 products, plus the bias
+                            out[e] = (int)add_bias_pair(a0, a1, (unsigned)bias4[e]);
+                        else
+                            out[e] = (int)dequant_pair(a0, xs * ws4[2 * e], a1, xs * ws4[2 * e + 1], (unsigned)bias4[e]);
+                    }
+                    if (!GENERIC) {
+                        __builtin_amdgcn_raw_buffer_store_b64(out, rsrc_y, y_off[i], 0, OUT == kHalfLines ? 2 /* nontemporal */ : 0);
+                        if (OUT == kDwords && (cur.rows_w & 2))   // (uniform)
+                            __builtin_amdgcn_raw_buffer_store_b32(out[0], rsrc_y, left == 2 ? y_place + (unsigned)checked_bytes<OUT>(i, a.N) : 0x80000000u, 0, 0);
+                    } else if (xb * 16 + i < rows_live) {
+                        // Rows of Y that start at any even address; a lane's last channels one by one.
+                        typedef v2i v2i_any __attribute__((aligned(2)));
+                        _Float16* const at = const_cast<_Float16*>(y_row) + y_any[i];
+                        if (left >= 4) {
+                            *(v2i_any*)at = out;
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 3; ++e)
+                                if (e < left) ((unsigned short*)at)[e] = (unsigned short)((unsigned)out[e / 2] >> (e % 2 * 16));
+                        }
+                    }
+                    if (i % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+                }
+                y_row += 16 * (long)a.N;
+                y_bytes -= checked_bytes<OUT>(16, a.N);
+                if (GENERIC) asm volatile("" : "+s"(y_row));   // (nothing is made up ahead of its use)
+                __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             // nothing to multiply in this tile, but this wave's share of the loads is needed
 #pragma unroll 1
             for (int it = 0; it < nk; ++it) {
-                const bool more = it + 1 < nk;
-                if (!more && has_next) {
-                    step_tile();
-                    decode_tile(nxt, ld);
+                if (it > 0) {
+                    load_w();
+                    load_x();
+                    next_loads();
                 }
-                if ((more || has_next) && !(it == 0 && requested1)) issue_all(ld, buf ^ 1, more ? (it + 1) * kTileK : 0);
-                if (!more) park_scales();
-                wait_loads_and_barrier();
-                buf ^= 1;
+                end_stage(None{}, None{});
             }
-            if (request1) issue_all(ld, buf ^ 1, kTileK);
+            if (has_next) {
+                load_w();
+                load_x();
+            }
         }
-        requested1 = request1;
         stores_in_flight = wave_live && !GENERIC;
         if (!has_next) break;
-        // Of LDS the epilogue reads the scales alone, and its loads go to the stage buffer that was free
-        // from the last stage's barrier on.  With two stages and more the barrier that ends the next
-        // tile's first one comes before that tile's scales are parked, so the waves go on without
-        // meeting; a one-stage tile parks them before its only barrier: nobody may still be reading.
-        if (nk == 1) wait_lds_and_barrier();
-        cur = nxt;
+        next_loads();
+        step_tile(at);
+        decode_tile(at, cur);
         idx = next_idx;
     }
+    // (nothing may be on its way to LDS when the workgroup ends)
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
 }
 
 // Enqueues the kernel for tile shape S; `a` holds the operands and sizes.
 template <class S>
 hipError_t launch_gemm_shape(GemmArgs a, int w_bits, int num_cus, hipStream_t stream) {
-    if (a.M > 0x7FFFFF00 || a.N > 0x7FFFFF00) return hipErrorInvalidValue;  // (rows and channels of a last tile fit an int)
-    a.tiles_t = (a.M + S::kTileT - 1) / S::kTileT;
-    a.tiles_c = (a.N + S::kTileC - 1) / S::kTileC;
-    const long tiles = (long)a.tiles_t * a.tiles_c;
-    if (tiles > 0x7FFFFFF0l) return hipErrorInvalidValue;
-    a.tiles = (int)tiles;
-    a.tiles_per_xcd = (a.tiles + kXcds - 1) / kXcds;
-    // one workgroup per CU (the kernel needs most of a CU's LDS), fewer if there are fewer tiles
-    const int cus_per_xcd = num_cus >= kXcds ? num_cus / kXcds : 1;
-    a.slots = a.tiles_per_xcd < cus_per_xcd ? a.tiles_per_xcd : cus_per_xcd;
-    const dim3 grid((unsigned)(a.slots * kXcds)), block(S::kThreads);
+    dim3 grid;
+    if (!persistent_grid(a, grid, S::kTileT, S::kTileC, num_cus)) return hipErrorInvalidValue;
+    const dim3 block(S::kThreads);
     const bool tail = ((w_bits == 16 ? 2 * a.K : a.K) % kTileK) != 0;  // (in bytes of an activation row)
     const Out out = rows_out(a.N, a.y, a.acc_out);
 #define VQ_LAUNCH_GEMM(BITS, TAIL, OUT) \
@@ -706,7 +739,7 @@ hipError_t launch_gemm_shape(GemmArgs a, int w_bits, int num_cus, hipStream_t st
     } while (0)
     if (w_bits == 8) VQ_LAUNCH_BITS(8);
     else if (w_bits == 16) VQ_LAUNCH_BITS(16);
-    else VQ_LAUNCH_BITS(4);
+    else if constexpr (S::kFourBits) VQ_LAUNCH_BITS(4);
 #undef VQ_LAUNCH_BITS
 #undef VQ_LAUNCH_OUT
 #undef VQ_LAUNCH_GEMM
