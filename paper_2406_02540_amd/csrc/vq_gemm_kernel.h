@@ -177,6 +177,44 @@ __device__ __forceinline__ float spread_in_row(float v, int from) {
     return __builtin_bit_cast(float, o);
 }
 
+// Ends a stage like wait_loads_before_and_barrier, with as many operations in flight as the mode (uniform) allows.  One statement:
+// as branches of the program the choice was a dozen scalar instructions and four taken branches between a wave's last product
+// and the barrier.
+enum StageEnd { kNear = 0, kFarther = 1, kFartherSecond = 2, kFartherFirst = 3, kNearFirst = 4 };
+template <int NEAR, int FAR, int FAR_SECOND, int FAR_FIRST, int NEAR_FIRST>
+__device__ __forceinline__ void wait_by_mode_and_barrier(int mode) {
+    static_assert(NEAR <= FAR && FAR < 64 && FAR_SECOND < 64 && FAR_FIRST < 64 && NEAR_FIRST < 64, "vmcnt is a 6-bit counter");
+    asm volatile(
+        "s_cmp_gt_u32 %0, 1\n\t"
+        "s_cbranch_scc1 .Lvq_rare%=\n\t"
+        "s_cmp_lg_u32 %0, 0\n\t"
+        "s_cbranch_scc1 .Lvq_far%=\n\t"
+        "s_waitcnt vmcnt(%1)\n"
+        ".Lvq_far%=:\n\t"
+        "s_waitcnt vmcnt(%2)\n"
+        ".Lvq_end%=:\n\t"
+        "s_waitcnt lgkmcnt(0)\n\t"
+        "s_barrier\n\t"
+        "s_branch .Lvq_out%=\n"
+        ".Lvq_rare%=:\n\t"
+        "s_cmp_lg_u32 %0, 2\n\t"
+        "s_cbranch_scc1 .Lvq_first%=\n\t"
+        "s_waitcnt vmcnt(%3)\n\t"
+        "s_branch .Lvq_end%=\n"
+        ".Lvq_first%=:\n\t"
+        "s_cmp_lg_u32 %0, 3\n\t"
+        "s_cbranch_scc1 .Lvq_near%=\n\t"
+        "s_waitcnt vmcnt(%4)\n\t"
+        "s_branch .Lvq_end%=\n"
+        ".Lvq_near%=:\n\t"
+        "s_waitcnt vmcnt(%5)\n\t"
+        "s_branch .Lvq_end%=\n"
+        ".Lvq_out%=:"
+        :
+        : "s"(mode), "n"(NEAR), "n"(FAR), "n"(FAR_SECOND), "n"(FAR_FIRST), "n"(NEAR_FIRST)
+        : "memory", "scc");
+}
+
 // K_TAIL:  K is a multiple of 16 but not of 128 (the last stage is partly past K).
 // OUT:     how rows of Y are written (vq_gemm_common.h).
 template <class S, int W_BITS, bool K_TAIL, Out OUT>
@@ -206,7 +244,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     constexpr bool kRoles = S::roles(W_BITS), kXFar = kXRing == 3;
     constexpr int kXLoads = S::x_loads(W_BITS), kWLoads = S::w_loads(W_BITS), kLoads = kRoles ? kXLoads : kXLoads + kWLoads;
     const bool loads_w = kRoles && wave < 4;
-    const bool far = kXFar && !loads_w;    // (of roles: asks two stages ahead)
+    const bool far = kXFar && !loads_w;    // asks two stages ahead
     // A quantity of the weights' or the activations' cursor or, of roles, of this wave's.  (By arithmetic: the compiler makes
     // selects between constants in vector registers, and these go where only scalar ones can.)
     enum Operand { kX, kW, kMine };
@@ -323,10 +361,15 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         if (decltype(op)::value == kX && S::unread(W_BITS) && j == LOADS - 1) to = unread + ((to - unread) & last_mask);
         load_stage_to_lds_16<K_TAIL>(c.rsrc, to, c.voff[j], c.k0, c.k_end);
     };
-    auto next_stage = [&](auto op, auto& c) __attribute__((always_inline)) {
+    // One stage on.  (Two cursors that are at the same stage, those of rings of two, go as one: `with` is the weights'.)
+    auto next_stage = [&](auto op, auto& c, auto&... with) __attribute__((always_inline)) {
         const int stage_bytes = of(op, kTileK / kWDiv, kTileK);
-        c.to += of(op, kWStage, kXStage);
-        if (c.to == cursor_end(op)) c.to -= of(op, kWArea, kXArea);
+        auto place = [&](auto op, auto& c) __attribute__((always_inline)) {
+            c.to += of(op, kWStage, kXStage);
+            if (c.to == cursor_end(op)) c.to -= of(op, kWArea, kXArea);
+        };
+        place(op, c);
+        (place(std::integral_constant<int, kW>{}, with), ...);
         c.k0 += stage_bytes;
         if (c.k0 == nk * stage_bytes) {
             c.k0 = 0;
@@ -336,10 +379,13 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 step_tile(c.at);
                 decode_tile(c.at, t);
                 decode_loads(op, t, c);
+                (decode_loads(std::integral_constant<int, kW>{}, t, with), ...);
             } else {
                 c.rsrc[2] = 0;
+                ((with.rsrc[2] = 0), ...);
             }
         }
+        ((with.k0 = c.k0 / kWDiv), ...);
         asm volatile("" : "+s"(c.k0), "+s"(c.to));
     };
     // (roles: cx is this wave's, cw is not used)
@@ -363,8 +409,14 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
         for (int l = 0; l < kLoads - kXLoads; ++l) load(l);
     };
     auto next_loads = [&]() __attribute__((always_inline)) {
-        if constexpr (!kRoles) next_stage(OpW{}, cw);
-        next_stage(OpX{}, cx);
+        if constexpr (kRoles) {
+            next_stage(OpX{}, cx);
+        } else if constexpr (kXFar) {
+            next_stage(OpW{}, cw);
+            next_stage(OpX{}, cx);
+        } else {
+            next_stage(OpX{}, cx, cw);
+        }
     };
     load_w();
     load_x();
@@ -478,49 +530,44 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
                         }
                     }
-                    // (in the second half of the step: the nibbles have arrived behind the products before it)
                     if (W_BITS == 4) {
-                        // (the first step's in its last pieces: the nibbles have arrived behind the products before; the second's
-                        // in all of them)
+                        // (The first step's in its last pieces, when the nibbles have arrived behind the products before; the second's
+                        // in all of them.  Left to where they are used, 32768 x 1152 -> 4608 takes 308000 cycles, 292000 so.)
                         const int from = read_ks ? p * WB / XB : p < XB / 2 ? 0 : (p - XB / 2) * WB / (XB / 2);
                         const int to = read_ks ? (p + 1) * WB / XB : p < XB / 2 ? 0 : (p + 1 - XB / 2) * WB / (XB / 2);
 #pragma unroll
                         for (int b = 0; b < WB; ++b)
                             if (b >= from && b < to) widen(read_ks, b, wo);
-                        if (to > from) {
-#pragma unroll
-                            for (int r = 0; r < WB; ++r) {
-                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                                if (r < kReadsPerPiece) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                                if (to - from == 1) __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);   // vector instructions
-                                else __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
-                            }
-                        }
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
         // Ends a stage: the next one has landed for every wave and every wave is done reading this one.  Vector memory
-        // operations complete in the order they were issued: `behind` of this wave's are behind the loads that have to have
-        // landed, beside those of a stage that is asked for two stages ahead.  (Roles: of a wave that asks two stages ahead, or one.)
-        auto end_stage = [&](auto behind_far, auto behind) __attribute__((always_inline)) {
-            if constexpr (kRoles) {
-                if (far) wait_loads_before_and_barrier<kLoads + decltype(behind_far)::value>();
-                else wait_loads_before_and_barrier<decltype(behind)::value>();
-            } else {
-                wait_loads_before_and_barrier<(kXFar ? kXLoads : 0) + decltype(behind)::value>();
-            }
+        // operations complete in the order they were issued: how many of this wave's are behind the loads that have to have landed?
+        // Steadily, what is asked for two stages ahead.  Behind an epilogue whose stores are in flight also those behind the
+        // last load that is needed: of a ring of two all loads, of three those of weights; a wave that asks for nothing but
+        // activations, two stages ahead, waits for that epilogue's at the end of the tile's second stage.
+        constexpr int kAhead = kRoles ? kLoads : kXFar ? kXLoads : 0, kNearNeeds = !kRoles && kXFar ? kWLoads - 1 : kLoads - 1;
+        constexpr int kStoresBehind = S::kStores - S::load_slot(kNearNeeds, kLoads), kStoresBehindAll = S::kStores - S::load_slot(kLoads - 1, kLoads);
+        const int far_mask = kRoles ? ~w_mask : kXFar ? -1 : 0;
+        auto next_place = [&]() __attribute__((always_inline)) {
             x_stage = x_stage == (kXRing - 1) * kXStage ? 0 : x_stage + kXStage;
             w_stage = w_stage == kWStage ? 0 : w_stage + kWStage;
         };
-        typedef std::integral_constant<int, 0> None;
-        // Stores of an epilogue behind the loads in it that its tile's first stage has to wait for (all of them; with a ring of
-        // three for the activations the weights).
-        constexpr int kLastNeeded = !kRoles && kXFar ? kWLoads - 1 : kLoads - 1;
-        typedef std::integral_constant<int, S::kStores - S::load_slot(kLastNeeded, kLoads)> StoresBehind;
-        typedef std::integral_constant<int, S::kStores - S::load_slot(kLoads - 1, kLoads)> StoresBehindAll;
-        typedef std::integral_constant<int, S::kStores> Stores;
+        auto end_stage = [&](int& mode) __attribute__((always_inline)) {
+            if constexpr (kRoles) {   // (ahead of the barrier)
+                next_place();
+                asm volatile("" : "+s"(x_stage), "+s"(w_stage));
+            }
+            if constexpr (kRoles) wait_by_mode_and_barrier<0, kAhead, kAhead + kStoresBehindAll, kAhead + S::kStores, kStoresBehind>(mode);
+            else wait_by_mode_and_barrier<0, kAhead, kAhead, kAhead + kStoresBehind, kStoresBehind>(mode);
+            mode = far_mask & max(mode - 1, (int)kFarther);
+            asm volatile("" : "+s"(mode));
+            if constexpr (!kRoles) next_place();
+        };
+        int mode = (stores_in_flight ? kNearFirst : kNear) + (far_mask & (stores_in_flight ? kFartherFirst - kNearFirst : kFarther - kNear));
+        asm volatile("" : "+s"(mode));
         // Which of a stage's loads its first K step carries (K step 1 of the stage before), the rest its second.
         constexpr int kFirst = !kRoles && kXFar ? kWLoads : kLoads < XB ? kLoads : XB;
         static_assert(kFirst <= XB && kLoads - kFirst <= XB, "a load in a piece");
@@ -536,17 +583,26 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 for (int b = 0; b < WB; ++b) widen(0, b, wf[0]);
             __builtin_amdgcn_sched_barrier(0);
             k_step(xf[0], wf[0], kYes, 1, xf[1], wf[1], 0, 0);
-            if (nk > 1) {
-                if (stores_in_flight) end_stage(Stores{}, StoresBehind{});
-                else end_stage(None{}, None{});
+            auto stage = [&]() __attribute__((always_inline)) {
+                k_step(xf[1], wf[1], kNo, 0, xf[0], wf[0], 0, kFirst);        // K step 1 of the previous stage
+                k_step(xf[0], wf[0], kNo, 1, xf[1], wf[1], kFirst, kLoads);   // K step 0
+                next_loads();
+            };
+            if constexpr (kRoles) {
+#pragma unroll 1
+                for (int n = nk - 1; n != 0; --n) {
+                    end_stage(mode);
+                    stage();
+                    asm volatile("" : "+s"(n));
+                }
+            } else if (nk > 1) {
+                end_stage(mode);
 #pragma unroll 1
                 for (int it = 1;; ++it) {
-                    k_step(xf[1], wf[1], kNo, 0, xf[0], wf[0], 0, kFirst);        // K step 1 of the previous stage
-                    k_step(xf[0], wf[0], kNo, 1, xf[1], wf[1], kFirst, kLoads);   // K step 0
-                    next_loads();
+                    stage();
                     if (it == nk - 1) break;
-                    if (kRoles && it == 1 && stores_in_flight) end_stage(StoresBehindAll{}, None{});
-                    else end_stage(None{}, None{});
+                    wait_loads_before_and_barrier<kAhead>();
+                    next_place();
                 }
             }
             // Scales and bias: a channel's four, and a token's in lane 4 (block % 4) + i of its row of sixteen lanes, which the
@@ -578,7 +634,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             __builtin_amdgcn_sched_barrier(0);
             constexpr int kScaleLoads = W_BITS == 16 ? 1 : 2 + kXsRegs;
             k_step(xf[1], wf[1], kNo, -1, xf[0], wf[0], 0, 0);   // K step 1 of the last stage
-            end_stage(std::integral_constant<int, kScaleLoads>{}, std::integral_constant<int, kScaleLoads>{});
+            if constexpr (kRoles) wait_by_mode_and_barrier<kScaleLoads, kAhead + kScaleLoads, 0, 0, 0>(far_mask & kFarther);
+            else wait_loads_before_and_barrier<kAhead + kScaleLoads>();
+            next_place();
 
             // ---- epilogue ------------------------------------------------------------
             // Lane (g = lane/16, c = lane%16) holds channels 4c .. 4c + 3 of the wavefront's 64 (accumulator blocks 0 .. 3) for
@@ -698,7 +756,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                     load_x();
                     next_loads();
                 }
-                end_stage(None{}, None{});
+                mode = far_mask & kFarther;
+                end_stage(mode);
             }
             if (has_next) {
                 load_w();
