@@ -122,10 +122,25 @@ GemmChoice choose_gemm(int w_bits, int M, int N, int K, int num_cus) {
     return best;
 }
 
+// Tiles of 48 x 48 in the place of one of 64 x 64 or 64 x 32, where they leave every CU one at most: such a launch waits for the
+// CU's load path, and with 160 to 256 of them a CU asks for three quarters of the bytes of 64 x 64, of which there are 144.
+// us, without / with: 240 x 4096 -> 2304 9.24 / 7.27 (4-bit weights 8.19 / 6.76), 1514 x 4000 -> 366 11.2 / 8.55, 128 x 4448 ->
+// 3896 with 4-bit weights 9.86 / 8.0; over random problems 0.84 of the time where the 64 x 64 tile's wavefronts divide K (none
+// above 0.90), 0.90 of 64 x 32's where K is 2048 at least and the tiles are a hundred (below, up to 1.09 of it), 0.95 of the
+// shared 64 x 64 tile's (below 1024 1.00).  The tiles of 32 x 32 stay: 1.1 to 1.3.
+bool tiles_of_48(const GemmChoice& c, int M, int N, int K, int num_cus) {
+    const long tiles = (((long)M + 47) / 48) * (((long)N + 47) / 48);
+    if ((tiles + kXcds - 1) / kXcds > (num_cus >= kXcds ? num_cus / kXcds : 1)) return false;
+    if (c.tile_t != 64) return false;
+    if (c.tile_c == 64) return c.waves == 8 || K >= 1024;
+    return K >= 2048 && tiles >= 100;
+}
+
 hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, int w_bits,
                        const float* w_scale, const void* bias_f16, void* y_f16, int32_t* acc_out,
                        int M, int N, int K, int num_cus, hipStream_t stream) {
-    const GemmChoice c = choose_gemm(w_bits, M, N, K, num_cus);
+    GemmChoice c = choose_gemm(w_bits, M, N, K, num_cus);
+    if (w_bits != 16 && tiles_of_48(c, M, N, K, num_cus)) c = {48, 48, 8};
     if (c.waves || c.tile_t != 256) {
         TileArgs t{};
         t.xq = xq;
@@ -164,6 +179,10 @@ extern "C" void vq_internal_gemm_choice(int w_bits, int M, int N, int K, int num
     choice[0] = c.tile_t;
     choice[1] = c.tile_c;
     choice[2] = c.waves;
+}
+
+extern "C" int vq_internal_gemm_tiles_of_48(int w_bits, int M, int N, int K, int num_cus) {
+    return vq::tiles_of_48(vq::choose_gemm(w_bits, M, N, K, num_cus), M, N, K, num_cus);
 }
 
 extern "C" int vq_internal_gemm_out(int N, const void* y, const void* acc_out) { return vq::rows_out(N, y, acc_out); }

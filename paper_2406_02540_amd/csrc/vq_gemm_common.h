@@ -265,7 +265,7 @@ struct TileArgs {
 // vq_gemm_tiles.hip: 32 x 32, 64 x 64, 128 x 64, 128 x 128 or 128 x 256, the wavefronts sharing the tile.  w_bits 8 or 4.
 constexpr int shared_tile_threads(int tile_t) { return tile_t == 32 ? 256 : 512; }
 hipError_t launch_gemm_tiles(int tile_t, int tile_c, const TileArgs& a, int w_bits, hipStream_t stream);
-// vq_gemm_split.hip: 32 x 32 (3, 6 or 8 wavefronts), 64 x 32 (4) or 64 x 64 (8), the wavefronts dividing K.
+// vq_gemm_split.hip: 32 x 32 (3, 6 or 8 wavefronts), 64 x 32 (4), 64 x 64 (8) or 48 x 48 (8), the wavefronts dividing K.
 hipError_t launch_gemm_split(int tile_t, int tile_c, int waves, const TileArgs& a, int w_bits, hipStream_t stream);
 
 // The workgroup's tile, or false.  Workgroup ids are dealt round-robin to the XCDs: each gets a contiguous

@@ -18,6 +18,7 @@
 //   100 x 512 -> 700             3.3 / 3.45            3.55 / 3.45
 //   256 x 1152 -> 1152           4.7 / 3.9             5.25 / 3.85
 //   240 x 4096 -> 2304           9.15 / 9.15          11.5 / 8.5
+// 48 x 48 in blocks of 16 x 16 x 64 (tiles_of_48 in vq_gemm.hip): 240 of them are 7.3 and 6.8 us there, 144 of 64 x 64 9.2 and 8.2.
 // 4-bit weights: a read of 16 bytes of nibbles for two K steps, 0.99 of the time with one of 8 bytes for each.
 // A wavefront's next loads leave in a burst as soon as its operands are in registers, ahead of its
 // products; dealt out between the products they were up to 10 % later with 32 x 32 tiles.  With many tiles per CU
@@ -32,13 +33,14 @@
 namespace vq {
 namespace {
 
-// (32 BT) tokens x (32 BC) channels, KW wavefronts; WGS workgroups share a CU.
-template <int BT_, int BC_, int KW_, int WGS_>
+// (BLK BT) tokens x (BLK BC) channels in MFMA blocks of BLK x BLK (32 x 32 x 32 or 16 x 16 x 64), KW wavefronts; WGS
+// workgroups share a CU.
+template <int BT_, int BC_, int KW_, int WGS_, int BLK_ = 32>
 struct SplitTile {
-    static constexpr int BT = BT_, BC = BC_, KW = KW_, WGS = WGS_;
+    static constexpr int BT = BT_, BC = BC_, KW = KW_, WGS = WGS_, BLK = BLK_;
     static constexpr int kThreads = 64 * KW;
     static constexpr int kWavesPerSimd = (KW * WGS_ + 3) / 4;
-    static constexpr int kT = 32 * BT, kC = 32 * BC;
+    static constexpr int kT = BLK * BT, kC = BLK * BC;
     static constexpr int kSums = kT * kC * 4;
     static constexpr int slot(int w_bits) {   // a wavefront's LDS: its line of both operands, then its sums
         const int line = kT * kLine + kC * kLine * w_bits / 8;
@@ -46,9 +48,16 @@ struct SplitTile {
     }
 };
 
+template <int BLK>
+struct BlockSums { typedef v16i type; };
+template <>
+struct BlockSums<16> { typedef v4i type; };
+__device__ __forceinline__ v16i split_block(v4i w, v4i x, v16i c) { return __builtin_amdgcn_mfma_i32_32x32x32_i8(w, x, c, 0, 0, 0); }
+__device__ __forceinline__ v4i split_block(v4i w, v4i x, v4i c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(w, x, c, 0, 0, 0); }
+
 template <class S, int W_BITS, bool K_TAIL>
 __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant_split(const TileArgs a) {
-    constexpr int BT = S::BT, BC = S::BC, KW = S::KW;
+    constexpr int BT = S::BT, BC = S::BC, KW = S::KW, BLK = S::BLK;
     constexpr int kSlot = S::slot(W_BITS);
     static_assert(kSlot * KW * S::WGS <= 160 * 1024, "LDS of one CU");
     __shared__ __attribute__((aligned(1024))) int8_t lds[kSlot * KW];
@@ -68,7 +77,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // (l%4) ^ ((row/4)%4)).  Rows past the tile's last one lie behind the buffers.
     int8_t* const mine = lds + wave * kSlot;
     const unsigned mine_addr = (unsigned)(uintptr_t)(lds_ptr)mine;
-    constexpr int kXLoads = 4 * BT, kWLoads = (W_BITS == 8) ? 4 * BC : 2 * BC, kWAt = S::kT * kLine;
+    constexpr int kXLoads = S::kT / 8, kWLoads = (W_BITS == 8) ? S::kC / 8 : S::kC / 16, kWAt = S::kT * kLine;
     const v4i rsrc_x = make_rsrc(a.xq + (long)tok0 * K, (unsigned)(rows_x * K));
     const v4i rsrc_w = make_rsrc((const int8_t*)a.w + (long)ch0 * (K / kWDiv), (unsigned)(rows_w * (K / kWDiv)));
     int vx[kXLoads], vw[kWLoads];
@@ -113,7 +122,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // by one were 0.5 us of 3.7 at 16 x 1152 -> 1152): a thread takes eight consecutive channels of kItems tokens.
     constexpr int kPerRow = S::kC / 8, kRowStep = S::kThreads / kPerRow;
     constexpr int kItems = (S::kT + kRowStep - 1) / kRowStep;
-    static_assert(kRowStep * kPerRow == S::kThreads, "whole rows of threads");
+    static_assert(kRowStep * kPerRow == S::kThreads || kItems == 1, "whole rows of threads");
     const int c0 = (tid % kPerRow) * 8, t0 = tid / kPerRow;
     // (the tile's own scales: 4 N is past an int from 2^29 channels on; range-checked, dword by dword: channels past N
     // read as zero)
@@ -138,39 +147,44 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     for (int i = 0; i < kItems; ++i) xsc[i] = a.x_scale[tok0 + min(t0 + i * kRowStep, rows_x - 1)];
 
     // ---- a line at a time ------------------------------------------------------------------
-    const int fr_row = lane & 31;
-    // (4-bit weights: 16 bytes of nibbles serve two K steps, as in vq_gemm_kernel.h)
-    const int x_off0 = fr_row * kLine + (((W_BITS == 8 ? lane >> 5 : lane >> 5 << 1) ^ ((fr_row >> 1) & 7)) << 4);
-    const int w_off0 = kWAt + ((W_BITS == 8) ? x_off0 : fr_row * (kLine / 2) + (((lane >> 5) ^ ((fr_row >> 2) & 3)) << 4));
-    v16i acc[BC][BT];
+    // A line is kSteps K steps; a lane takes 16 bytes of K of each, by its group: with blocks of 32
+    // (two groups) chunk 2 ks + group, of 16 (four) 4 ks + group.  (4-bit weights: 16 bytes of nibbles serve two K steps, as in
+    // vq_gemm_kernel.h.)
+    constexpr int kSteps = BLK / 8, kGroups = 64 / BLK;
+    const int fr_row = lane & (BLK - 1), group = lane / BLK;
+    const int x_off0 = fr_row * kLine + (((W_BITS == 8 ? group : group << 1) ^ ((fr_row >> 1) & 7)) << 4);
+    const int w_off0 = kWAt + ((W_BITS == 8) ? x_off0 : fr_row * (kLine / 2) + ((group ^ ((fr_row >> 2) & 3)) << 4));
+    typedef typename BlockSums<BLK>::type sums_t;
+    sums_t acc[BC][BT];
 #pragma unroll
     for (int cb = 0; cb < BC; ++cb)
 #pragma unroll
         for (int tb = 0; tb < BT; ++tb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[cb][tb][r] = 0;
-    constexpr int kWReads = W_BITS == 8 ? 4 : 2;
+            for (int r = 0; r < BLK * BLK / 64; ++r) acc[cb][tb][r] = 0;
+    constexpr int kWReads = W_BITS == 8 ? kSteps : kSteps / 2;
 #pragma unroll 1
     for (int line = wave; line < nl; line += KW) {
         asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-        v4i xf[4][BT];
+        v4i xf[kSteps][BT];
         v4i wf[kWReads][BC];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            if (ks % (4 / kWReads) == 0)
+        for (int ks = 0; ks < kSteps; ++ks) {
+            constexpr int kSkip = 16 * kGroups;   // bytes of a row that a step's (of nibbles, two steps') read takes
+            if (ks % (kSteps / kWReads) == 0)
 #pragma unroll
                 for (int cb = 0; cb < BC; ++cb)
-                    wf[ks * kWReads / 4][cb] = *(const v4i*)(mine + (w_off0 ^ (ks * kWReads / 4 << 5)) + cb * 32 * (kLine / kWDiv));
-            const int at = W_BITS == 8 ? ks << 5 : (ks >> 1 << 6) + (ks % 2 << 4);
+                    wf[ks * kWReads / kSteps][cb] = *(const v4i*)(mine + (w_off0 ^ (ks * kWReads / kSteps * kSkip)) + cb * BLK * (kLine / kWDiv));
+            const int at = W_BITS == 8 ? ks * kSkip : ks / 2 * 2 * kSkip + (ks % 2 << 4);
 #pragma unroll
-            for (int tb = 0; tb < BT; ++tb) xf[ks][tb] = *(const v4i*)(mine + (x_off0 ^ at) + tb * 32 * kLine);
+            for (int tb = 0; tb < BT; ++tb) xf[ks][tb] = *(const v4i*)(mine + (x_off0 ^ at) + tb * BLK * kLine);
         }
         if (line + KW < nl) {   // (the operands are in registers: the space is free)
             asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
             issue(line + KW);
         }
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
+        for (int ks = 0; ks < kSteps; ++ks)
 #pragma unroll
             for (int cb = 0; cb < BC; ++cb) {
                 v4i wv;
@@ -178,7 +192,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                 else wv = widen_nibbles(ks % 2 ? v2i{wf[ks / 2][cb][2], wf[ks / 2][cb][3]} : v2i{wf[ks / 2][cb][0], wf[ks / 2][cb][1]});
 #pragma unroll
                 for (int tb = 0; tb < BT; ++tb)
-                    acc[cb][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wv, xf[ks][tb], acc[cb][tb], 0, 0, 0);
+                    acc[cb][tb] = split_block(wv, xf[ks][tb], acc[cb][tb]);
             }
     }
 
@@ -186,18 +200,18 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // Every wavefront leaves its sums where its lines were, as a row-major int32 tile, 16-byte chunks
     // (four channels) XOR-ed by the row; a thread adds up eight consecutive channels of a token,
     // dequantizes and writes 16 bytes.
-    constexpr int kXor = (S::kC / 4) % 16 == 0 ? 15 : 7;
+    constexpr int kXor = (S::kC / 4) % 16 == 0 ? 15 : (S::kC / 4) % 8 == 0 ? 7 : 3;   // (chunks stay in their row)
     constexpr int kRow = S::kC * 4;
     if (wave < nl) {
-        int8_t* const row = mine + (lane & 31) * kRow;
+        int8_t* const row = mine + fr_row * kRow;
 #pragma unroll
         for (int cb = 0; cb < BC; ++cb)
 #pragma unroll
             for (int tb = 0; tb < BT; ++tb)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {   // register 4j + i is channel 8j + 4 (lane/32) + i of the block
-                    const int chunk = cb * 8 + 2 * j + (lane >> 5);
-                    *(v4i*)(row + tb * 32 * kRow + ((chunk ^ (lane & kXor)) << 4)) =
+                for (int j = 0; j < BLK * BLK / 256; ++j) {   // register 4j + i is channel 8j + 4 group + i of the block (of 16: j = 0)
+                    const int chunk = cb * (BLK / 4) + 2 * j + group;
+                    *(v4i*)(row + tb * BLK * kRow + ((chunk ^ (lane & kXor)) << 4)) =
                         v4i{acc[cb][tb][4 * j], acc[cb][tb][4 * j + 1], acc[cb][tb][4 * j + 2], acc[cb][tb][4 * j + 3]};
                 }
     }

@@ -11,6 +11,7 @@ typedef SplitTile<1, 1, 6, 3> Split32Waves6;
 typedef SplitTile<1, 1, 8, 2> Split32Waves8;
 typedef SplitTile<2, 1, 4, 3> Split64x32;
 typedef SplitTile<2, 2, 8, 1> Split64x64;
+typedef SplitTile<3, 3, 8, 1, 16> Split48x48;
 
 template <class S>
 hipError_t launch_bits(const TileArgs& a, int w_bits, hipStream_t stream) {
@@ -24,6 +25,7 @@ hipError_t launch_gemm_split(int tile_t, int tile_c, int waves, const TileArgs& 
     if (tile_t == 32 && tile_c == 32 && waves == 8) return launch_bits<Split32Waves8>(a, w_bits, stream);
     if (tile_t == 64 && tile_c == 32 && waves == 4) return launch_bits<Split64x32>(a, w_bits, stream);
     if (tile_t == 64 && tile_c == 64 && waves == 8) return launch_bits<Split64x64>(a, w_bits, stream);
+    if (tile_t == 48 && tile_c == 48 && waves == 8) return launch_bits<Split48x48>(a, w_bits, stream);
     return hipErrorInvalidValue;
 }
 
