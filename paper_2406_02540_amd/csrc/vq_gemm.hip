@@ -20,7 +20,7 @@ typedef TileShape<2, 4, 8, true> Tile256;  // 2 x 4 wavefronts of 128 tokens x 6
 // 4608; 8- and 4-bit weights), each timed with every tile in captured graphs: by least squares where a tile was within 25 % of
 // the best, then by descent on what the tile chosen costs over the best one.  The kernels were those before outputs left from
 // the registers, which made 128 x 256 15 % faster on average, 128 x 128 8 %, 128 x 64 with 8-bit weights 4 %, the persistent tiles
-// 4 to 8 %, the others 1 % at most.  19580 other problems with the kernels as they are, the chosen one timed in each: over the best one on average
+// 4 to 8 % (and 3 to 10 % again since, in blocks of 16x16x64), the others 1 % at most.  19580 other problems between those two changes, the chosen one timed in each: over the best one on average
 // (98th percentile) 0.7 % (6 %) below 1e8 multiply-adds, 0.8 % (8 %) to 1e9, 0.9 % (8 %) to 6e9 and 0.1 % (3 %) above; with many
 // tokens and few channels (8 to 400) 1.4 % (11 %).  With 8-bit weights 256 x 256 is taken in 13 of 378 where 256 x 192 is more
 // than 5 % faster (13415 x 352 -> 4608 43.7 us and 39.2).

@@ -26,9 +26,9 @@
 //     comes back as a lower clock.  A loop of nothing but products over quantized-Gaussian operands, two waves to a SIMD,
 //     runs at 2.19 GHz with blocks of 16x16x64 and at 1.82 with 32x32x32 (half of the sums move per multiply-add); with
 //     every operand read from LDS 1.98 and 1.69, with a stage's loads beside that 1.78.  us in 32x32x32 blocks, double
-//     buffered / as it is: 32768 x 1152 -> 4608 154 to 161 / 145 to 148, -> 3456 123 / 114, -> 1152 45.3 / 41.1 to 42.2, 32768 x
-//     4608 -> 1152 164 to 169 / 147 to 149, 8192 x 1152 -> 4608 45.0 / 42.0, 8192 x 4608 -> 1152 43.7 / 40.6, with 4-bit weights
-//     32768 x 1152 -> 4608 154 / 147; fp16 operands 32768 x 4608 -> 1152 322 / 293.
+//     buffered / as it is: 32768 x 1152 -> 4608 154 to 161 / 144 to 148, -> 3456 123 / 113, -> 1152 45.3 / 41 to 42, 32768 x
+//     4608 -> 1152 164 to 169 / 147 to 150, 8192 x 1152 -> 4608 45.0 / 41.5, 8192 x 4608 -> 1152 43.7 / 40.0, with 4-bit weights
+//     32768 x 1152 -> 4608 154 / 145; fp16 operands 32768 x 4608 -> 1152 322 / 293.
 //   - K is walked in stages of 128 bytes.  A stage takes one full 128-byte cache line per row, so every L2 request is a
 //     whole line (with 64-byte stages the same bytes cost twice the requests and the
 //     CU's address path saturates).  Activations and weights go global -> LDS directly
