@@ -129,9 +129,9 @@ GemmChoice choose_gemm(int w_bits, int M, int N, int K, int num_cus) {
 // above 0.90), 0.90 of 64 x 32's where K is 2048 at least and the tiles are a hundred (below, up to 1.09 of it), 0.95 of the
 // shared 64 x 64 tile's (below 1024 1.00).  The tiles of 32 x 32 stay: 1.1 to 1.3.
 bool tiles_of_48(const GemmChoice& c, int M, int N, int K, int num_cus) {
+    if (c.tile_t != 64) return false;
     const long tiles = (((long)M + 47) / 48) * (((long)N + 47) / 48);
     if ((tiles + kXcds - 1) / kXcds > (num_cus >= kXcds ? num_cus / kXcds : 1)) return false;
-    if (c.tile_t != 64) return false;
     if (c.tile_c == 64) return c.waves == 8 || K >= 1024;
     return K >= 2048 && tiles >= 100;
 }

@@ -175,6 +175,13 @@ __host__ __device__ constexpr int checked_bytes(int rows, int N) {
 }
 static_assert(checked_bytes<kDwords>(256, (1 << 21) - 1) > 0 && checked_bytes<kAnyRow>(256, 0x7FFFFFFF) == 0, "nothing overflows");
 
+// Blocks of 16x16x64, 4-bit weights: which 16 bytes of nibbles of a row (0 .. 3: 0, 3, 1, 2) the lanes of group l/16 read for two K
+// steps, and so which two 16-byte chunks of the activations.  The LDS serves sixteen lanes of a ds_read_b128 at a time, rows 0 to 3
+// and 12 to 15 of one group with rows 4 to 11 of its neighbour (and the other way round), and the XOR by the row keeps those
+// apart only where the two groups' chunks differ by 1, 6 or 7 of the activations and by 3 of the nibbles.  With group l/16 at chunk
+// l/16 every read took four cycles more: 640 a stage of 256 x 256, 15 % of a launch's cycles (SQ_LDS_BANK_CONFLICT), none so.
+__device__ __forceinline__ int nibble_chunk(int group) { return (group << 1 & 2) | (group >> 1 ^ (group & 1)); }
+
 // ---- persistent kernels: tiles of 256 tokens ---------------------------------------------------
 constexpr int kTileK = 128;                 // K bytes per stage (one cache line per row)
 constexpr int kBand = 8;                    // token tiles per band in the tile order

@@ -323,14 +323,14 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // Operand rows of a 16x16x64 block: lane l supplies row l%16, 16 bytes of K chosen by l/16; a stage holds two such
     // K steps (chunks 4ks .. 4ks + 3).  The chunk index of K step ks is (4 ks + l/16) ^ swizzle = ((l/16) ^ swizzle) ^ 4 ks,
     // so the byte offset of step ks is that of step 0 with 64 ks XOR-ed in.
-    // 4-bit weights: the two K steps share one read of 16 bytes of nibbles, chunk l/16 of the row, whose first half the lane
-    // widens for the one and second half for the other.  The activations follow: chunk 2 (l/16) for the first, the one behind
+    // 4-bit weights: the two K steps share one read of 16 bytes of nibbles, chunk c = nibble_chunk(l/16) of the row, whose first half the
+    // lane widens for the one and second half for the other.  The activations follow: chunk 2 c for the first, the one behind
     // it for the second.  (Which 64 bytes of K a step takes does not change the sums.)
     const int fr_row = lane & 15;
-    const int x_off0 = (wave_t * 16 * XB + fr_row) * kTileK + (((W_BITS != 4 ? lane >> 4 : lane >> 4 << 1) ^ ((fr_row >> 1) & 7)) << 4);
+    const int x_off0 = (wave_t * 16 * XB + fr_row) * kTileK + (((W_BITS != 4 ? lane >> 4 : nibble_chunk(lane >> 4) << 1) ^ ((fr_row >> 1) & 7)) << 4);
     const int w_off0 = (W_BITS != 4)
                            ? (wave_c * 64 + fr_row) * kTileK + (((lane >> 4) ^ ((fr_row >> 1) & 7)) << 4)
-                           : (wave_c * 64 + fr_row) * (kTileK / 2) + (((lane >> 4) ^ ((fr_row >> 2) & 3)) << 4);
+                           : (wave_c * 64 + fr_row) * (kTileK / 2) + ((nibble_chunk(lane >> 4) ^ ((fr_row >> 2) & 3)) << 4);
     auto x_off = [&](int ks) { return x_off0 ^ (W_BITS != 4 ? ks << 6 : ks << 4); };
 
     // ---- the tiles of this workgroup -------------------------------------------

@@ -152,8 +152,9 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
     // vq_gemm_kernel.h.)
     constexpr int kSteps = BLK / 8, kGroups = 64 / BLK;
     const int fr_row = lane & (BLK - 1), group = lane / BLK;
-    const int x_off0 = fr_row * kLine + (((W_BITS == 8 ? group : group << 1) ^ ((fr_row >> 1) & 7)) << 4);
-    const int w_off0 = kWAt + ((W_BITS == 8) ? x_off0 : fr_row * (kLine / 2) + ((group ^ ((fr_row >> 2) & 3)) << 4));
+    const int part = W_BITS == 4 && BLK == 16 ? nibble_chunk(group) : group;   // of the row
+    const int x_off0 = fr_row * kLine + (((W_BITS == 8 ? part : part << 1) ^ ((fr_row >> 1) & 7)) << 4);
+    const int w_off0 = kWAt + ((W_BITS == 8) ? x_off0 : fr_row * (kLine / 2) + ((part ^ ((fr_row >> 2) & 3)) << 4));
     typedef typename BlockSums<BLK>::type sums_t;
     sums_t acc[BC][BT];
 #pragma unroll
