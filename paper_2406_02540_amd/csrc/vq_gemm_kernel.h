@@ -661,11 +661,17 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             for (int i = 0; i < 4; ++i) y_off[i] = left >= 4 ? y_place + (unsigned)checked_bytes<OUT>(i, a.N) : 0x80000000u;
             const _Float16* y_row = a.y + (cur.tok0 + row0) * a.N;
             int y_bytes = checked_bytes<OUT>(cur.rows_x - row0, a.N);   // from there to the end of the tile's rows
-            // (any row: token rows of the wave below which the lane has channels to write; its place in them)
+            // (Any row: token rows of the wave below which the lane has channels to write; its place in the four rows of a block.  Of
+            // 128 tokens a wave it is one place, which the rows step on from by N, and `quad` has an upper half of its own: three
+            // more of them, and a zero that is kept for it, were registers held across the stages, where 4-bit weights leave none.
+            // With their operands' places reloaded from scratch in every stage 32768 x 1152 -> 4607 took 230 us, 193 so.)
             const int rows_live = left > 0 ? cur.rows_x - row0 - 4 * g : 0;
-            long y_any[4];
+            constexpr bool kStepped = GENERIC && XB == 8;
+            constexpr int kPlaces = kStepped ? 1 : 4;
+            long y_any[kPlaces];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) y_any[i] = (4 * g + i) * (long)a.N + cur.ch0 + quad;
+            for (int i = 0; i < kPlaces; ++i) y_any[i] = (4 * g + i) * (long)a.N + cur.ch0 + (kStepped ? opaque(quad) : quad);
+            auto any_place = [&](int i) __attribute__((always_inline)) { return kStepped ? i * (long)a.N + y_any[0] : y_any[i % kPlaces]; };
             if (GENERIC && a.acc_out) {
                 typedef v4i v4i_any4 __attribute__((aligned(4)));
                 int32_t* acc_row = a.acc_out + (cur.tok0 + row0) * a.N;
@@ -677,11 +683,11 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                             constexpr int kShift = (W_BITS == 4) ? 4 : 0;
                             const v4i sums = v4i{(int)acc[xb][0][i], (int)acc[xb][1][i], (int)acc[xb][2][i], (int)acc[xb][3][i]} >> kShift;
                             if (left >= 4) {
-                                *(v4i_any4*)(acc_row + y_any[i]) = sums;
+                                *(v4i_any4*)(acc_row + any_place(i)) = sums;
                             } else {
 #pragma unroll
                                 for (int e = 0; e < 3; ++e)
-                                    if (e < left) acc_row[y_any[i] + e] = sums[e];
+                                    if (e < left) acc_row[any_place(i) + e] = sums[e];
                             }
                         }
                     acc_row += 16 * (long)a.N;
@@ -690,7 +696,8 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
             }
             __builtin_amdgcn_sched_barrier(0);
             // (here the compiler waits for them, ahead of the next loads)
-            asm volatile("" : "+v"(ws4), "+v"(bias4));
+            if constexpr (W_BITS != 16) asm volatile("" : "+v"(ws4));
+            asm volatile("" : "+v"(bias4));
             if constexpr (W_BITS != 16) {
 #pragma unroll
                 for (int r = 0; r < kXsRegs; ++r) {
@@ -731,7 +738,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_i8_dequant
                     } else if (xb * 16 + i < rows_live) {
                         // Rows of Y that start at any even address; a lane's last channels one by one.
                         typedef v2i v2i_any __attribute__((aligned(2)));
-                        _Float16* const at = const_cast<_Float16*>(y_row) + y_any[i];
+                        _Float16* const at = const_cast<_Float16*>(y_row) + any_place(i);
                         if (left >= 4) {
                             *(v2i_any*)at = out;
                         } else {

@@ -54,6 +54,15 @@ def test_unaligned_output_rows(vq, bits, M, N, K):
     check_gemm(vq, bits, M, N, K)
 
 
+# ... over stages enough for the persistent kernel's steady loop, in tiles of 256 x 256, with an odd last channel in lanes of one
+# and of three channels
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N,K", [(5003, 4999, 1152), (5003, 4993, 1184)])
+def test_unaligned_output_rows_over_many_stages(vq, bits, M, N, K):
+    assert tile_picked(bits, M, N, K) == (256, 256, 0)
+    check_gemm(vq, bits, M, N, K)
+
+
 # rows of whole 16-byte chunks that do not start on 64-byte boundaries, by N or by Y's address: tiles of 256 x 192
 # and of 256 x 256 in one round and in several, full and ragged
 @pytest.mark.parametrize("bits", [8, 4])
