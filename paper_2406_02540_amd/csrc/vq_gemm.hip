@@ -89,10 +89,9 @@ double launch_cost(const SplitCost& c, const Problem& p) {
            (double)((rounds + c.per_cu - 1) / c.per_cu) * (c.fill + c.turn * (double)((p.lines + c.waves - 1) / c.waves)) +
            p.traffic(c.mb, tiles, rows);
 }
-}  // namespace
 
 // The cheapest of the tiles that one launch takes.  (The persistent kernel's grid does not grow with the problem.)
-GemmChoice choose_gemm(int w_bits, int M, int N, int K, int num_cus) {
+GemmChoice cheapest_tile(int w_bits, int M, int N, int K, int num_cus) {
     const Problem p(w_bits, M, N, K, num_cus);
     GemmChoice best{0, 0, 0};
     double best_cost = 0.0;
@@ -128,19 +127,24 @@ GemmChoice choose_gemm(int w_bits, int M, int N, int K, int num_cus) {
 // 3896 with 4-bit weights 9.86 / 8.0; over random problems 0.84 of the time where the 64 x 64 tile's wavefronts divide K (none
 // above 0.90), 0.90 of 64 x 32's where K is 2048 at least and the tiles are a hundred (below, up to 1.09 of it), 0.95 of the
 // shared 64 x 64 tile's (below 1024 1.00).  The tiles of 32 x 32 stay: 1.1 to 1.3.
-bool tiles_of_48(const GemmChoice& c, int M, int N, int K, int num_cus) {
+inline bool tiles_of_48(const GemmChoice& c, int M, int N, int K, int num_cus) {
     if (c.tile_t != 64) return false;
     const long tiles = (((long)M + 47) / 48) * (((long)N + 47) / 48);
     if ((tiles + kXcds - 1) / kXcds > (num_cus >= kXcds ? num_cus / kXcds : 1)) return false;
     if (c.tile_c == 64) return c.waves == 8 || K >= 1024;
     return K >= 2048 && tiles >= 100;
 }
+}  // namespace
+
+GemmChoice choose_gemm(int w_bits, int M, int N, int K, int num_cus) {
+    const GemmChoice c = cheapest_tile(w_bits, M, N, K, num_cus);
+    return w_bits != 16 && tiles_of_48(c, M, N, K, num_cus) ? GemmChoice{48, 48, 8} : c;
+}
 
 hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, int w_bits,
                        const float* w_scale, const void* bias_f16, void* y_f16, int32_t* acc_out,
                        int M, int N, int K, int num_cus, hipStream_t stream) {
-    GemmChoice c = choose_gemm(w_bits, M, N, K, num_cus);
-    if (w_bits != 16 && tiles_of_48(c, M, N, K, num_cus)) c = {48, 48, 8};
+    const GemmChoice c = choose_gemm(w_bits, M, N, K, num_cus);
     if (c.waves || c.tile_t != 256) {
         TileArgs t{};
         t.xq = xq;
@@ -179,10 +183,6 @@ extern "C" void vq_internal_gemm_choice(int w_bits, int M, int N, int K, int num
     choice[0] = c.tile_t;
     choice[1] = c.tile_c;
     choice[2] = c.waves;
-}
-
-extern "C" int vq_internal_gemm_tiles_of_48(int w_bits, int M, int N, int K, int num_cus) {
-    return vq::tiles_of_48(vq::choose_gemm(w_bits, M, N, K, num_cus), M, N, K, num_cus);
 }
 
 extern "C" int vq_internal_gemm_out(int N, const void* y, const void* acc_out) { return vq::rows_out(N, y, acc_out); }

@@ -63,11 +63,10 @@ hipError_t launch_gemm(const int8_t* xq, const float* x_scale, const void* w, in
                        const float* w_scale, const void* bias_f16, void* y_f16, int32_t* acc_out,
                        int M, int N, int K, int num_cus, hipStream_t stream);
 
-// The kernel that launch_gemm takes (or, of 64 tokens, the one with tiles of 48 x 48 in its place: tiles_of_48): tiles of tokens x channels, and the number of wavefronts that divide K (0:
+// The kernel that launch_gemm takes: tiles of tokens x channels, and the number of wavefronts that divide K (0:
 // the workgroup shares the tile; with 256 tokens it is the persistent kernel).
 struct GemmChoice { int tile_t, tile_c, waves; };
 GemmChoice choose_gemm(int w_bits, int M, int N, int K, int num_cus);
-bool tiles_of_48(const GemmChoice& c, int M, int N, int K, int num_cus);
 
 // A layer of few tokens in one launch (vq_linear_small.hip): quantizer, with its producer, and GEMM.
 // small_layer: whether it is the faster way for these sizes.
@@ -80,5 +79,4 @@ hipError_t launch_linear_small(const ProducerArgs& p, const void* w, int w_bits,
 // For the tests, which name the kernels that they mean to reach: choose_gemm, and how the persistent kernel
 // writes its rows (Out, vq_gemm_common.h).  Not a part of vq.h.
 extern "C" void vq_internal_gemm_choice(int w_bits, int M, int N, int K, int num_cus, int choice[3]);
-extern "C" int vq_internal_gemm_tiles_of_48(int w_bits, int M, int N, int K, int num_cus);
 extern "C" int vq_internal_gemm_out(int N, const void* y, const void* acc_out);

@@ -1,5 +1,6 @@
 """The GEMM's tiles of 48 x 48, which take the place of some of 64 tokens: which problems reach them (decided on the host), and
 every output and sum exactly."""
+import ctypes
 import os
 
 import pytest
@@ -18,7 +19,9 @@ NOT_TAKEN = [(310, 2001, 4096), (769, 769, 4096), (16, 1152, 4608), (256, 1152, 
 def taken(bits, M, N, K):
     if not os.path.exists(binding.LIB_PATH):
         build.build(verbose=False)
-    return bool(binding.lib().vq_internal_gemm_tiles_of_48(bits, M, N, K, 256))
+    choice = (ctypes.c_int * 3)()
+    binding.lib().vq_internal_gemm_choice(bits, M, N, K, 256, choice)
+    return tuple(choice) == (48, 48, 8)
 
 
 def test_which_problems_take_them():

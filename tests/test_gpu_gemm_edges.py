@@ -176,8 +176,8 @@ def test_one_tile_per_workgroup(vq, bits, M, N, K):
     check_gemm(vq, bits, M, N, K)
 
 
-# wavefronts that divide K (32 x 32 with three, six and eight of them, 64 x 32, 64 x 64; a few of the shapes run in shared
-# tiles): fewer lines of K than wavefronts, a line more than they share evenly, tails of a line, ragged last tiles
+# wavefronts that divide K (32 x 32 with three, six and eight of them, 48 x 48; a few of the shapes run in shared tiles, and 64 x 32
+# and 64 x 64 have theirs in EVERY_TILE): fewer lines of K than wavefronts, a line more than they share evenly, tails of a line, ragged last tiles
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K", [(100, 1000, 160), (100, 1001, 512), (1000, 200, 800), (999, 31, 4608), (16, 1152, 4608),
                                    (61, 1001, 1184), (500, 4607, 512), (300, 1152, 4096), (257, 1149, 4128),
