@@ -22,8 +22,9 @@ typedef TileShape<2, 4, 8, true> Tile256;  // 2 x 4 wavefronts of 128 tokens x 6
 // the registers, which made 128 x 256 15 % faster on average, 128 x 128 8 %, 128 x 64 with 8-bit weights 4 %, the persistent tiles
 // 4 to 8 % (and 3 to 10 % again since, in blocks of 16x16x64), the others 1 % at most.  19580 other problems between those two changes, the chosen one timed in each: over the best one on average
 // (98th percentile) 0.7 % (6 %) below 1e8 multiply-adds, 0.8 % (8 %) to 1e9, 0.9 % (8 %) to 6e9 and 0.1 % (3 %) above; with many
-// tokens and few channels (8 to 400) 1.4 % (11 %).  With 8-bit weights 256 x 256 is taken in 13 of 378 where 256 x 192 is more
-// than 5 % faster (13415 x 352 -> 4608 43.7 us and 39.2).
+// tokens and few channels (8 to 400) 1.4 % (11 %).  With the kernels as they are, 1300 problems that take 128 x 128 or larger: 0.2 %
+// (4 %) with 8-bit weights, 0.1 % (2 %) with 4-bit, nothing with fp16 operands; 256 x 256 is taken in 3 of 162 where 256 x 192 is 3 to
+// 5 % faster (29853 x 1120 -> 1160 68.7 us and 65.5).
 // Without the bytes, and fitted to problems few of which had few channels, the rule took 2.2 % (17 %) there: 17964 x 3744 -> 88
 // 29.8 us in tiles of 32 x 32, 20.3 in 128 x 128.
 struct Traffic { double x, y, w, l2; };
@@ -124,14 +125,17 @@ GemmChoice cheapest_tile(int w_bits, int M, int N, int K, int num_cus) {
 // Tiles of 48 x 48 in the place of one of 64 x 64 or 64 x 32, where they leave every CU one at most: such a launch waits for the
 // CU's load path, and with 160 to 256 of them a CU asks for three quarters of the bytes of 64 x 64, of which there are 144.
 // us, without / with: 240 x 4096 -> 2304 9.24 / 7.27 (4-bit weights 8.19 / 6.76), 1514 x 4000 -> 366 11.2 / 8.55, 128 x 4448 ->
-// 3896 with 4-bit weights 9.86 / 8.0; over random problems 0.84 of the time where the 64 x 64 tile's wavefronts divide K (none
-// above 0.90), 0.90 of 64 x 32's where K is 2048 at least and the tiles are a hundred (below, up to 1.09 of it), 0.95 of the
-// shared 64 x 64 tile's (below 1024 1.00).  The tiles of 32 x 32 stay: 1.1 to 1.3.
+// 3896 with 4-bit weights 9.86 / 8.0.  Over 1160 random problems, time with over time without: 0.83 where the 64 x 64 tile's
+// wavefronts divide K (none above 0.95), 0.87 of 64 x 32's where K is 2048 at least and the tiles are a hundred (none above 0.97;
+// below, up to 1.04 of it), 0.94 of the shared 64 x 64 tile's from twelve lines of K on (up to 1.13; 1.01 at ten and eleven, 1.07
+// at nine, where the second turn is one wavefront's, 1.06 below).  The tiles of 32 x 32 stay: 1.11, 1.19 and 1.17 of three, six
+// and eight wavefronts', 1.26 of the shared one's (0.91 in the 18 of 360 with three or eight where K is 1600 at least and the tiles
+// of 48 x 48 are 170).
 inline bool tiles_of_48(const GemmChoice& c, int M, int N, int K, int num_cus) {
     if (c.tile_t != 64) return false;
     const long tiles = (((long)M + 47) / 48) * (((long)N + 47) / 48);
     if ((tiles + kXcds - 1) / kXcds > (num_cus >= kXcds ? num_cus / kXcds : 1)) return false;
-    if (c.tile_c == 64) return c.waves == 8 || K >= 1024;
+    if (c.tile_c == 64) return c.waves == 8 || K > 11 * kLine;
     return K >= 2048 && tiles >= 100;
 }
 }  // namespace
