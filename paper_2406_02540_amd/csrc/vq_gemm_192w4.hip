@@ -2,10 +2,14 @@
 // walk through the tiles; ViDiT-Q appendices "Hardware implementation of quantized linear layers" and "Performance under
 // lower bitwidth") in 32 x 32 x 32 blocks instead of 16 x 16 x 64.
 //
-// Where every wavefront has 64 tokens for its 64 channels, the widening of the weights is two and a half vector instructions
-// for each 16 x 16 x 64 product, and those leave a wavefront no time for them; a product of twice the length does, though its
-// matrix work draws more power.  us, 16 x 16 x 64 / 32 x 32 x 32: 32768 x 4608 -> 1152 159 to 164 / 156 to 160, 8192 x 4608 ->
-// 1152 44.1 / 42.4 (94400 cycles and 79400).  With 128 tokens for 64 channels (256 x 256) it is the other way round.
+// The template in that shape, 4-bit weights read without bank conflicts, over 70 random problems of this tile takes 1.05 of this
+// kernel's time (1.00 to 1.10).  us, 16 x 16 x 64 / 32 x 32 x 32: 8192 x 4608 -> 1152 43.2 / 41.4,
+// 32768 x 4608 -> 1152 165.8 / 155.8, 32768 x 1152 -> 1152 47.3 / 44.9, 8192 x 1152 -> 4608 47.4 / 44.6.  Its clock is higher (2.26
+// GHz and 2.15 in the first, 2.07 and 1.90 in the second) and its cycles are a tenth more (117400 and 104300, 326000 and 296000): the matrix
+// cores' are the same, the vector instructions a tenth more (64 tokens for 64 channels are two and a half of widening for each 16 x
+// 16 x 64 product), and wavefronts wait as often.  With three stages of activations 160.0 in the second, 1.05 over the 70; shorter than
+// here in 11, long K and few columns of tiles (31465 x 4608 -> 558 93 us, 101 here).  With 128 tokens for 64 channels (256 x 256)
+// 16 x 16 x 64 is the faster one.
 //
 //   - 4 x 3 wavefronts of 64 tokens x 64 channels, 2 x 2 blocks each, three to a SIMD; K in stages of 128 bytes, double
 //     buffered in LDS.  4-bit weights travel packed and are widened to 16 * w on their way from LDS into the operand registers.
