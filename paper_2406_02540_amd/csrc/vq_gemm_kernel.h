@@ -89,8 +89,8 @@ namespace vq {
 
 namespace {
 
-// WT x WC wavefronts of (16 XB) tokens x 64 channels.
-template <int WT_, int WC_, int XB_, bool ROLES>
+// WT x WC wavefronts of (16 XB) tokens x 64 channels; XRING stages of activations in LDS.
+template <int WT_, int WC_, int XB_, bool ROLES, int XRING = 3>
 struct TileShape {
     static constexpr int WT = WT_, WC = WC_, XB = XB_;
     static constexpr bool kFourBits = XB == 8;        // packed weights too (with 64 tokens a wave: vq_gemm_192w4.hip)
@@ -101,9 +101,9 @@ struct TileShape {
     static constexpr int kTileC = WC * 64;            // output channels per workgroup
     static constexpr int kXStage = kTileT * kTileK;   // 32 KiB
     static constexpr int w_stage(int w_bits) { return kTileC * kTileK / (w_bits == 4 ? 2 : 1); }
-    // Two stages of weights in LDS, and, but for 4-bit weights, three of activations.
+    // Two stages of weights in LDS; of activations XRING, with 4-bit weights two.
     static constexpr int kWRing = 2;
-    static constexpr int x_ring(int w_bits) { return w_bits == 4 ? 2 : 3; }
+    static constexpr int x_ring(int w_bits) { return w_bits == 4 ? 2 : XRING; }
     // Global -> LDS loads of 1 KiB (8 rows of int8, 16 rows of nibbles), dealt round to the waves; or (roles) the first four
     // waves, one per SIMD, load the weights and the others the activations.  (Where the X tile's 32 do not divide evenly, the
     // last turn is some waves' only.)

@@ -98,6 +98,14 @@ def test_gemm_f16_rows_of_whole_dwords(vq, M, N, K, at):
     check_gemm_f16_rows(vq, M, N, K, at)
 
 
+# ... around four stages of K (of 64 values), where 256 x 192 goes from two stages of activations in LDS to three: one tile, and
+# several rounds of them
+@pytest.mark.parametrize("M,N,K,at", [(12, 164, 256, 0), (12, 163, 264, 0), (9001, 2304, 256, 0), (9001, 2304, 320, 0),
+                                      (9001, 2306, 264, 0), (9001, 2303, 256, 0), (9001, 2303, 328, 0), (9001, 2304, 64, 0)])
+def test_gemm_f16_stages_of_activations(vq, M, N, K, at):
+    check_gemm_f16_rows(vq, M, N, K, at)
+
+
 def check_gemm_f16_rows(vq, M, N, K, at):
     say(f"gemm_f16 rows M={M} N={N} K={K} at={at}")
     g = torch.Generator(device="cuda").manual_seed(83 + M + N)

@@ -88,6 +88,16 @@ def test_every_tile(vq, bits, tile, M, N, K):
     check_gemm(vq, bits, M, N, K)
 
 
+# 256 x 192 keeps two stages of activations in LDS to four stages of K and three from there on: both sides of the line, several
+# rounds of tiles, rows of each kind
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N,K", [(9001, 2304, 512), (9001, 2304, 544), (9001, 2306, 480), (9001, 2306, 640), (9001, 2303, 512),
+                                   (9001, 2303, 544), (9001, 2304, 128), (9001, 2304, 256)])
+def test_stages_of_activations(vq, bits, M, N, K):
+    assert tile_picked(bits, M, N, K) == (256, 192, 0)
+    check_gemm(vq, bits, M, N, K)
+
+
 # the tiles whose outputs leave from the registers, by how they write rows (0: on 64-byte boundaries, 1: whole dwords, 2: any
 # row): whole and ragged tiles of tokens and channels, with a tail of K and without.  (128 x 64 with 4-bit weights goes through
 # LDS and knows one way only: its rows below are stores that end inside a row of eight channels, or don't.)
