@@ -20,11 +20,12 @@ typedef TileShape<2, 4, 8, true> Tile256;  // 2 x 4 wavefronts of 128 tokens x 6
 // 4608; 8- and 4-bit weights), each timed with every tile in captured graphs: by least squares where a tile was within 25 % of
 // the best, then by descent on what the tile chosen costs over the best one.  The kernels were those before outputs left from
 // the registers, which made 128 x 256 15 % faster on average, 128 x 128 8 %, 128 x 64 with 8-bit weights 4 %, the persistent tiles
-// 4 to 8 % (and 3 to 10 % again since, in blocks of 16x16x64), the others 1 % at most.  19580 other problems between those two changes, the chosen one timed in each: over the best one on average
-// (98th percentile) 0.7 % (6 %) below 1e8 multiply-adds, 0.8 % (8 %) to 1e9, 0.9 % (8 %) to 6e9 and 0.1 % (3 %) above; with many
-// tokens and few channels (8 to 400) 1.4 % (11 %).  With the kernels as they are, 1300 problems that take 128 x 128 or larger: 0.2 %
-// (4 %) with 8-bit weights, 0.1 % (2 %) with 4-bit, nothing with fp16 operands; 256 x 256 is taken in 3 of 162 where 256 x 192 is 3 to
-// 5 % faster (29853 x 1120 -> 1160 68.7 us and 65.5).
+// 4 to 8 % (and 3 to 10 % again since, in blocks of 16x16x64), the others 1 % at most.  19580 other problems between those two
+// changes, the chosen one timed in each: over the best one on average (98th percentile) 0.7 % (6 %) below 1e8 multiply-adds, 0.8 %
+// (8 %) to 1e9, 0.9 % (8 %) to 6e9 and 0.1 % (3 %) above; with many tokens and few channels (8 to 400) 1.4 % (11 %).  With the
+// kernels as they are, 1300 problems that take 128 x 128 or larger: 0.2 % (4 %) with 8-bit weights, 0.1 % (2 %) with 4-bit,
+// nothing with fp16 operands; 256 x 256 is taken in 3 of 162 where 256 x 192 is 3 to 5 % faster (29853 x 1120 -> 1160 68.7 us and
+// 65.5).
 // Without the bytes, and fitted to problems few of which had few channels, the rule took 2.2 % (17 %) there: 17964 x 3744 -> 88
 // 29.8 us in tiles of 32 x 32, 20.3 in 128 x 128.
 struct Traffic { double x, y, w, l2; };

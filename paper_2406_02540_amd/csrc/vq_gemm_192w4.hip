@@ -3,11 +3,11 @@
 // lower bitwidth") in 32 x 32 x 32 blocks instead of 16 x 16 x 64.
 //
 // The template in that shape, 4-bit weights read without bank conflicts, over 70 random problems of this tile takes 1.05 of this
-// kernel's time (1.00 to 1.10).  us, 16 x 16 x 64 / 32 x 32 x 32: 8192 x 4608 -> 1152 43.2 / 41.4,
-// 32768 x 4608 -> 1152 165.8 / 155.8, 32768 x 1152 -> 1152 47.3 / 44.9, 8192 x 1152 -> 4608 47.4 / 44.6.  Its clock is higher (2.26
-// GHz and 2.15 in the first, 2.07 and 1.90 in the second) and its cycles are a tenth more (117400 and 104300, 326000 and 296000): the matrix
-// cores' are the same, the vector instructions a tenth more (64 tokens for 64 channels are two and a half of widening for each 16 x
-// 16 x 64 product), and wavefronts wait as often.  With three stages of activations 160.0 in the second, 1.05 over the 70; shorter than
+// kernel's time (1.00 to 1.10).  us, 16 x 16 x 64 / 32 x 32 x 32: 8192 x 4608 -> 1152 43.2 / 41.4, 32768 x 4608 -> 1152 165.8 /
+// 155.8, 32768 x 1152 -> 1152 47.3 / 44.9, 8192 x 1152 -> 4608 47.4 / 44.6.  Its clock is higher (2.26 GHz and 2.15 in the first,
+// 2.07 and 1.90 in the second) and its cycles are a tenth more (117400 and 104300, 326000 and 296000): the matrix cores' are the
+// same, the vector instructions a tenth more (64 tokens for 64 channels are two and a half of widening for each 16 x 16 x 64
+// product), and wavefronts wait as often.  With three stages of activations 160.0 in the second, 1.05 over the 70; shorter than
 // here in 11, long K and few columns of tiles (31465 x 4608 -> 558 93 us, 101 here).  With 128 tokens for 64 channels (256 x 256)
 // 16 x 16 x 64 is the faster one.
 //

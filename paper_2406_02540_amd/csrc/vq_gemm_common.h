@@ -148,18 +148,20 @@ __device__ __forceinline__ int opaque(int v) {
 }
 
 // ---- how rows of Y are written by the kernels that store them from the registers -------------------------
-// A store is two token rows x 128 bytes, a dword (two channels) per lane.
+// A store is two dwords (four channels) per lane over four token rows x 128 bytes in the persistent kernel, a dword over two of them
+// in 256 x 192 with 4-bit weights and the tiles of one per workgroup.
 //   kHalfLines: rows start on 64-byte boundaries (N % 32 == 0): range-checked, past the caches (nontemporal).  Through them
-//               over random problems 4 to 6 % longer in the persistent kernel, 7 % in 128 x 256, 4 % in 128 x 128, 2 % in 128 x
-//               64: 32768 x 1152 -> 4608 with 4-bit weights 172 us and 160, 1001 x 1152 -> 4608 12.6 and 11.7.  Nor does a
-//               quantizer that reads Y right behind it want them there: both together 1 % shorter to 3 % longer through them.
+//               over random problems 4 to 6 % longer in the persistent tiles (fp16 operands 2 to 3 %), 7 % in 128 x 256, 4 % in
+//               128 x 128, 2 % in 128 x 64: 32768 x 1152 -> 4608 169 us and 161 (4-bit weights 168 and 160), 1001 x 1152 -> 4608
+//               12.6 and 11.7.  Nor does a quantizer that reads Y right behind it want them there: both together 1 % shorter to 3 %
+//               longer through them.
 //   kDwords:    rows start on dwords (N even): range-checked, through the caches.  A piece of 128 bytes that begins elsewhere
 //               than a memory sector does is two part-written sectors, which the L2 puts together with those of the
 //               neighbouring pieces and memory does not.  us past the caches / through them / as any row: 20120 x 352 -> 3464
-//               101 / 62 / 64, 8192 x 1152 -> 3472 50 / 43 / 44, 8192 x 1152 -> 1154 24.9 / 19.8 / 20.0, 1001 x 1152 -> 4610
-//               13.5 / 12.9 / 14.4; fp16 operands 20120 x 352 -> 3464 108 / 83 / 84.  Over random problems past them 1.21 to
-//               1.30 of the time through them in the persistent kernel (fp16 operands 1.08), 1.01 in 128 x 128, 1.04 in 128 x 64
-//               and 128 x 256; as any row 1.02 to 1.05 and 1.03 to 1.09.
+//               103 / 65 / 66, 8192 x 1152 -> 3472 46.0 / 37.7 / 38.3, 8192 x 1152 -> 1156 22.2 / 17.4 / 17.6, 1001 x 1152 -> 4610
+//               13.5 / 12.9 / 14.4; fp16 operands 20120 x 352 -> 3464 109 / 81 / 82.  Over random problems past them 1.21 to
+//               1.26 of the time through them in the persistent tiles (fp16 operands 1.03 to 1.12), 1.01 in 128 x 128, 1.04 in 128 x
+//               64 and 128 x 256; as any row 1.00 to 1.03 and 1.03 to 1.09.
 //   kAnyRow:    odd N, whose every other row starts between dwords, N from 2^21, and an optional copy of the integer sums:
 //               64-bit addresses, and a comparison for every row.
 enum Out { kHalfLines, kDwords, kAnyRow };

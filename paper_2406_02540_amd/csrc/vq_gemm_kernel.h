@@ -22,13 +22,15 @@
 //                  rounds of whole tiles for 2.25 rounds of work).
 //     The tile is large because the L2 -> CU path, not HBM, is what the operand traffic
 //     loads: bytes per multiply-add fall with the tile edge.
-//   - What bounds the large launches is power: the clock under them is 1.6 to 2.1 GHz of 2.4, and a cycle taken out of them
-//     comes back as a lower clock.  A loop of nothing but products over quantized-Gaussian operands, two waves to a SIMD,
-//     runs at 2.19 GHz with blocks of 16x16x64 and at 1.82 with 32x32x32 (half of the sums move per multiply-add); with
-//     every operand read from LDS 1.98 and 1.69, with a stage's loads beside that 1.78.  us in 32x32x32 blocks, double
-//     buffered / as it is: 32768 x 1152 -> 4608 154 to 161 / 144 to 148, -> 3456 123 / 113, -> 1152 45.3 / 41 to 42, 32768 x
-//     4608 -> 1152 164 to 169 / 147 to 150, 8192 x 1152 -> 4608 45.0 / 41.5, 8192 x 4608 -> 1152 43.7 / 40.0, with 4-bit weights
-//     32768 x 1152 -> 4608 154 / 145; fp16 operands 32768 x 4608 -> 1152 322 / 293.
+//   - What bounds the large launches back to back is power: a cycle taken out of them comes back as a lower clock.  Between the
+//     quantizers of a step it is waiting: 2.2 to 2.5 GHz, the matrix cores 38 to 57 % busy, 28 to 38 % of the wavefronts' cycles
+//     waiting for something and 38 to 42 % for their turn to issue.  A loop of nothing but products over quantized-Gaussian
+//     operands, two waves to a SIMD, runs at 2.19 GHz with blocks of 16x16x64 and at 1.82 with 32x32x32 (half of the sums move
+//     per multiply-add); with every operand read from LDS 1.98 and 1.69, with a stage's loads beside that 1.78.  us in 32x32x32
+//     blocks, double buffered / as it is: 32768 x 1152 -> 4608 154 to 161 / 144 to 148, -> 3456 123 / 113, -> 1152 45.3 / 41 to 42,
+//     32768 x 4608 -> 1152 164 to 169 / 147 to 150, 8192 x 1152 -> 4608 45.0 / 41.5, 8192 x 4608 -> 1152 43.7 / 40.0, with 4-bit
+//     weights 32768 x 1152 -> 4608 154 / 145; fp16 operands 32768 x 4608 -> 1152 322 / 293.  Where power is no bound the shorter
+//     products are the slower ones: one or two stages of K 1 to 3 % longer in 256 x 256, fp16 operands of few tokens 3 to 5 %.
 //   - K is walked in stages of 128 bytes.  A stage takes one full 128-byte cache line per row, so every L2 request is a
 //     whole line (with 64-byte stages the same bytes cost twice the requests and the
 //     CU's address path saturates).  Activations and weights go global -> LDS directly
@@ -37,7 +39,7 @@
 //   - LDS holds two stages of weights and three of activations: those come from memory, a new panel for every tile, and a
 //     request that is one stage old when it is needed has not been answered by then.  32768 x 4608 -> 1152 with two of both
 //     162 us, 147.5 so; 8192 x 4608 -> 1152 39.9 and 39.8.  Packed weights, whose stages are as long and whose bytes are
-//     fewer, gain nothing (32768 x 1152 -> 4608 143 and 147): two of both.
+//     fewer, gain nothing (32768 x 1152 -> 4608 143 and 147): two of both, as in 256 x 192 with few stages of K.
 //   - In 256 x 256 the four older waves (one per SIMD) ask for the weights, which are needed a stage later, and the younger ones,
 //     which come to their products last, for the activations, which have two: with every wave asking for its share of both
 //     32768 x 1152 -> 4608 took 151 us, 146 so.  In 256 x 192 it is the other way round (32768 x 4608 -> 1152 148 and 152).

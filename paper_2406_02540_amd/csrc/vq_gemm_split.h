@@ -18,7 +18,7 @@
 //   100 x 512 -> 700             3.3 / 3.45            3.55 / 3.45
 //   256 x 1152 -> 1152           4.7 / 3.9             5.25 / 3.85
 //   240 x 4096 -> 2304           9.15 / 9.15          11.5 / 8.5
-// 48 x 48 in blocks of 16 x 16 x 64 (tiles_of_48 in vq_gemm.hip): 240 of them are 7.3 and 6.8 us there, 144 of 64 x 64 9.2 and 8.2.
+// 48 x 48 in blocks of 16 x 16 x 64 (where: choose_gemm in vq_gemm.hip): 240 of them are 7.3 and 6.8 us there, 144 of 64 x 64 9.2 and 8.2.
 // 4-bit weights: a read of 16 bytes of nibbles for two K steps, 0.99 of the time with one of 8 bytes for each.
 // A wavefront's next loads leave in a burst as soon as its operands are in registers, ahead of its
 // products; dealt out between the products they were up to 10 % later with 32 x 32 tiles.  With many tiles per CU

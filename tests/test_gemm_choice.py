@@ -42,7 +42,7 @@ def test_rows_of_whole_chunks_go_out_in_chunks(N, at, sums, want):
     assert binding.lib().vq_internal_gemm_out(N, ctypes.c_void_p(4096 + at), ctypes.c_void_p(4096 if sums else None)) == want
 
 
-# ... and a store is a dword per lane, so that rows of whole dwords (Y itself is 16-byte aligned) are none either
+# ... and stores are of dwords, so that rows of whole dwords (Y itself is 16-byte aligned) are none either
 @pytest.mark.parametrize("N,at,sums,want", [(1156, 0, 0, 1), (1154, 16, 0, 1), (2, 0, 0, 1), ((1 << 21) - 2, 0, 0, 1), (1, 0, 0, 2),
                                             (1154, 0, 1, 2)])
 def test_rows_of_whole_dwords_go_out_in_dwords(N, at, sums, want):
